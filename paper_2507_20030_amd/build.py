@@ -8,11 +8,12 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libiwdft.so")
-SOURCES = ["api.hip", "append.hip", "prefill.hip", "prefill_fft.hip", "reconstruct.hip", "attn.hip", "ablate.hip"]
+SOURCES = ["api.hip", "append.hip", "prefill.hip", "prefill_fft.hip", "reconstruct.hip", "attn.hip", "ablate.hip", "fft_tab.hip"]
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-fgpu-rdc" if False else "-fno-gpu-rdc",
     # packed-FP32 instruction selection is switched off for every device translation unit
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-fconstexpr-steps=200000000",  # the twiddle tables are evaluated by the compiler
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
 ]
 

@@ -13,6 +13,7 @@
 
 #include "../../include/iwdft.h"
 #include "common.h"
+#include "fft_tab.h"
 
 using namespace iwdft;
 
@@ -473,6 +474,8 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       e = hipMemcpy(c->state + pl.off_tw, tw.data(), sizeof(float2) * tw.size(), hipMemcpyHostToDevice);
     }
+    const float2* tab = nullptr;
+    if (e == hipSuccess) e = fft_table(&tab);
     if (e != hipSuccess) {
       return fail(IWDFT_ERR_HIP, "initialising the state buffer: %s", hipGetErrorString(e));
     }
@@ -501,6 +504,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.chirp_logN = pl.chirp_logN;
     P.chirp_Q = (uint32_t)pl.chirp_Q;
     P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;
+    P.tab = tab;
     P.FK = (float2*)(c->state + pl.off_FK);
     P.FV = (float2*)(c->state + pl.off_FV);
     P.gain = 1.0f;

@@ -54,6 +54,7 @@ struct Params {
   // Twiddle octant of the in-LDS power-of-two transforms: tw8[m] = exp(+j 2 pi m / Q), m = 0 .. Q/8, with
   // Q = min(M, 8192); made on the host in double precision (null unless M = 2^m >= 256).
   const float2* tw8;
+  const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
   float2* FK;
   float2* FV;
   // Exact tokens (Sec. 4.2.1): S sink tokens and a ring of R recent tokens per slice, kv_dtype,
@@ -69,6 +70,17 @@ struct Params {
   void* ringK;
   void* ringV;
 };
+
+// Geometry of a layer (wave-uniform index) through scalar loads: the constant address space says that no store of the
+// kernel changes it, which the compiler cannot see.
+__device__ __forceinline__ LayerInfo layer_info(const Params& P, int layer) {
+  typedef const __attribute__((address_space(4))) LayerInfo* cptr;
+  const cptr p = (cptr)(uintptr_t)(P.layers + __builtin_amdgcn_readfirstlane(layer));
+  LayerInfo L;
+  L.bin_off = p->bin_off, L.nb = p->nb, L.Bp = p->Bp, L.fold_rounds = p->fold_rounds, L.coef_off = p->coef_off,
+  L.ws_off = p->ws_off;
+  return L;
+}
 
 // (a * b) mod M, exact.
 __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, uint32_t M, uint32_t Mmask) {

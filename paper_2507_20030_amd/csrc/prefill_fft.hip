@@ -13,7 +13,7 @@
 // workgroups of one (slice, tensor) are placed on one XCD next to each other in time and share the rows
 // in that XCD's L2: HBM delivers every row once.
 #include "common.h"
-#include "fft_lds.h"
+#include "fft_core.h"
 
 namespace iwdft {
 
@@ -56,173 +56,274 @@ __device__ __forceinline__ void raw_pop(Raw<NW>& r) {
 }
 
 // hardware block id -> (xcd = id & 7, idx = id >> 3); XCD x owns the (slice, tensor) pairs
-// x * per_xcd .. (x + 1) * per_xcd - 1, 64 / NP consecutive idx each.
-// NP = channel pairs per workgroup: every thread fetches its samples of NP adjacent pairs with one load
-// (4 NP bytes of a token row for bf16) and the pairs are then transformed one after the other from
-// registers, so that a 128-byte line of a token row is requested by 32 / NP workgroups instead of 32.
-// NBT = kept bins per thread; 0: any number of kept bins -- the threads walk the bin list in strides of the workgroup
-// and, in the decimated form, keep the running sums over the residues in the output rows themselves (every bin
-// belongs to one thread, which reads back its own earlier store).
-template <int LOGQ, bool BF16, bool MULTI, int NBT, int NP>
-__global__ __launch_bounds__(kFftThreads, (MULTI && NBT > 4 && NP > 1) ? 2 : 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
-                                                                    const void* __restrict__ V, int per_xcd,
-                                                                    int n_st) {
+// x * per_xcd .. (x + 1) * per_xcd - 1, 64 / (NS NP) consecutive idx each.
+// A workgroup of 512 threads runs NS = 8192 / Q transforms side by side, each on NP channel pairs one after the other.  The
+// transforms are interleaved over the lanes (thread = t NS + g), so that NS lanes fetch 4 NP NS adjacent bytes of a token
+// row (bf16) with one load each: a token row is two 128-byte lines, and what bounds the loads is the number of lines that
+// are asked for, not their bytes (measured on 1.07 GB: 16 bytes of every line per load 0.37 ms, 32 0.28, 64 0.19, 128 0.18).
+// A thread's 16 samples are the 16 consecutive positions that the first radix-16 pass combines: that pass runs on the
+// loaded words and the samples go to LDS once, behind it; the last radix-2 stage (M >= 8192, M = 512) is formed at the kept
+// bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
+// MULTI (M > 8192): the running sums over the residues live in the output rows (every bin belongs to one thread, which
+// reads back its own earlier store).
+__host__ __device__ constexpr int prefill_ns(int logQ) { return 1 << (13 - logQ); }
+// Distance of two transforms' buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses fall into distinct banks.
+__host__ __device__ constexpr int prefill_bs(int logQ) {
+  return fft_lds(logQ) + (prefill_ns(logQ) == 1 ? 0 : prefill_ns(logQ) >= 8 ? 2 : 16 / prefill_ns(logQ));
+}
+template <int LOGQ, bool BF16, bool MULTI, int NP>
+__global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
+                                                            const void* __restrict__ V, int per_xcd, int n_st) {
   extern __shared__ float2 smem[];
-  constexpr int Q = 1 << LOGQ;
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = prefill_ns(LOGQ), BS = prefill_bs(LOGQ);
+  static_assert(T * NS == 512 && NS * NP <= kPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;  // bytes per token row
   constexpr int NW = NP * (BF16 ? 1 : 2);
-  constexpr int kGroups = kPairs / NP;    // workgroups per (slice, tensor)
-  float2* buf = smem;
-  float2* tab = smem + Q + (Q >> 5);
+  constexpr int kGroups = kPairs / (NP * NS);  // workgroups per (slice, tensor)
+  const TabMem tab{P.tab + tab_base(LOGQ)};
   const int tid = threadIdx.x;
   const uint32_t idx = blockIdx.x >> 3;
   const uint32_t st = (blockIdx.x & 7u) * (uint32_t)per_xcd + idx / kGroups;
   if (st >= (uint32_t)n_st) return;
-  const int pair0 = (idx % kGroups) * NP;
+  const int pair0 = (idx % kGroups) * (NS * NP);
   const int tensor = st & 1;
   const int slice = st >> 1;
   const int spl = P.batch * P.n_kv;
   const int layer = slice / spl;
   const int s = slice - layer * spl;
-  const LayerInfo L = P.layers[layer];
+  const LayerInfo L = layer_info(P, layer);
   const int32_t* bins = P.bins + L.bin_off;
   const int64_t N = (int64_t)P.S + P.M + P.R;  // tokens per slice in the caller's tensor
-  const char* X = (const char*)(tensor ? V : K) + ((int64_t)slice * N + P.S) * kRow + pair0 * 2 * kElem;
+  const int t = tid / NS;                      // thread of transform tid % NS
+  float2* buf = smem + (tid % NS) * BS;
+  const char* X = (const char*)(tensor ? V : K) + ((int64_t)slice * N + P.S) * kRow + (pair0 + (tid % NS) * NP) * 2 * kElem;
   const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
-  float2* F = (tensor ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + pair0 * 2) * L.Bp;
+  // the pruning goes through the transforms one after the other: consecutive threads, consecutive bins
+  const int tp = tid % T;
+  const float2* spec = smem + (tid / T) * BS;
+  float2* F = (tensor ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + (pair0 + (tid / T) * NP) * 2) * L.Bp;
 
-  for (int m = tid; m <= (Q >> 3); m += kFftThreads) tab[m] = P.tw8[m];  // exp(+j 2 pi m / Q), host-made
-
-  // MULTI: running sums over the residues, per pair, channel and kept bin of this thread
-  constexpr int NBR = NBT ? NBT : 1;  // register-held bins per thread
-  float2 acc[MULTI ? NP : 1][2][NBR];
-  uint32_t kk[NBR];
-#pragma unroll
-  for (int j = 0; j < NBT; ++j) {
-#pragma unroll
-    for (int p = 0; p < (MULTI ? NP : 1); ++p) acc[p][0][j] = acc[p][1][j] = make_float2(0.f, 0.f);
-    const int i = j * kFftThreads + tid;
-    kk[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
-  }
-
-  // samples per thread: IT sample pairs (a, a + Q/2) when the first radix-2 stage is taken here (odd LOGQ),
-  // IT single samples otherwise
-  constexpr bool kOdd = (LOGQ & 1) != 0;
-  constexpr int H = kOdd ? Q / 2 : Q;
-  constexpr int IT = (H + kFftThreads - 1) / kFftThreads;
-
+  const int64_t step = (int64_t)Pb * kRow;  // bytes between consecutive samples of one residue
   for (uint32_t b = 0; b < Pb; ++b) {
     // The thread index is made opaque per iteration so that the address arithmetic of the transform
     // passes is recomputed (a few instructions) instead of being hoisted out of the residue loop into
     // long-lived registers that would spill.
-    int lt = tid;
+    int lt = t;
     if (MULTI) asm volatile("" : "+v"(lt));
-    const char* Xb = X + (int64_t)b * kRow;
-    const int64_t step = (int64_t)Pb * kRow;  // bytes between consecutive samples of this residue
-    // Thread -> sample assignment: consecutive threads own consecutive LDS positions of the digit-reversed
-    // order (their stores fall into distinct banks) and fetch the samples that belong there; every sample is
-    // a token row of its own, so the order of the loads is free.
-    Raw<NW> za[IT], zc[kOdd ? IT : 1];
+    Raw<NW> z[16];
+    const char* Xb = X + (int64_t)b * kRow + (int64_t)sample_at<LOGQ>(16 * lt) * step;
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int i = it * kFftThreads + lt;
-      if (H % kFftThreads == 0 || i < H) {
-        const int a = digit_pos<kOdd ? LOGQ - 1 : LOGQ>(i);  // digit reversal is its own inverse
-        za[it] = load_raw<NW>(Xb + (int64_t)a * step);
-        if constexpr (kOdd) zc[it] = load_raw<NW>(Xb + (int64_t)(a + H) * step);
-      }
-    }
-    // One pair after the other: scatter into the digit-reversed order of the decimation-in-time passes,
-    // transform, separate the two channels' spectra at the kept bins.
-    auto one_pair = [&](int p, auto& accp) {
+    for (int m = 0; m < 16; ++m)  // position 16 t + m holds sample_at(16 t) + (digits of m reversed) Q / 16
+      z[m] = load_raw<NW>(Xb + (int64_t)((((m & 3) << 2) | (m >> 2)) * (Q / 16)) * step);
 #pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        const int i = it * kFftThreads + lt;
-        if (H % kFftThreads == 0 || i < H) {
-          const int pos = kOdd ? 2 * i : i;
-          const float2 u = raw_front<BF16, NW>(za[it]);
-          raw_pop<BF16, NW>(za[it]);
-          if constexpr (kOdd) {  // first radix-2 stage
-            const float2 v = raw_front<BF16, NW>(zc[it]);
-            raw_pop<BF16, NW>(zc[it]);
-            buf[pad(pos)] = cadd(u, v);
-            buf[pad(pos + 1)] = csub(u, v);
-          } else {
-            buf[pad(pos)] = u;
-          }
-        }
+    for (int p = 0; p < NP; ++p) {
+      float2 x[16];
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        x[m] = raw_front<BF16, NW>(z[m]);
+        raw_pop<BF16, NW>(z[m]);
       }
-      __syncthreads();  // (the first time also publishes tab)
-      fft_dit<LOGQ>(buf, tab, lt);
       float2* F0 = F + (int64_t)(2 * p) * L.Bp;
-      if constexpr (NBT == 0) {
-        for (int i = tid; i < L.nb; i += kFftThreads) {
-          const uint32_t kj = (uint32_t)bins[i];
-          const int r = kj & (Q - 1), rm = (Q - r) & (Q - 1);
-          const float2 w1 = buf[pad(r)], w2 = buf[pad(rm)];
-          float2 d0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-          float2 d1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
-          if constexpr (MULTI) {
-            const float2 tw = conjf2(cis_poly2((kj * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
-            d0 = cmul(tw, d0);
-            d1 = cmul(tw, d1);
-            if (b) {
-              d0 = cadd(F0[i], d0);
-              d1 = cadd(F0[L.Bp + i], d1);
-            }
-          }
-          F0[i] = d0;
-          F0[L.Bp + i] = d1;
-        }
-      }
+      // kept bins of this thread, four at a time; the first four are fetched while the transform runs
+      constexpr int U = 4;
+      uint32_t kj[U];
+      float2 wj[U];
+      auto fetch_bins = [&](int i0) {
 #pragma unroll
-      for (int j = 0; j < NBT; ++j) {
-        const int i = j * kFftThreads + tid;
-        if (i < L.nb) {
-          // decimated form with several pairs: the bin index is fetched again (an L1 / L2 hit) instead of being kept --
-          // the registers it frees are what the kernel would otherwise spill
-          const uint32_t kj = (MULTI && NP > 1) ? (uint32_t)bins[i] : kk[j];
-          const int r = kj & (Q - 1), rm = (Q - r) & (Q - 1);
-          const float2 w1 = buf[pad(r)], w2 = buf[pad(rm)];
-          const float2 d0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-          const float2 d1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
-          if constexpr (MULTI) {
-            const float2 tw = conjf2(cis_poly2((kj * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
-            accp[0][j] = cadd(accp[0][j], cmul(tw, d0));
-            accp[1][j] = cadd(accp[1][j], cmul(tw, d1));
-          } else {
+        for (int j = 0; j < U; ++j) {
+          const int i = i0 + j * T;
+          kj[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
+        }
+      };
+      auto fetch_tw = [&](int k) {
+        if (k != fft_np(LOGQ) - 1) return;
+#pragma unroll
+        for (int j = 0; j < U; ++j) wj[j] = pair_twiddle<LOGQ>(tab.tab, kj[j] & (Q - 1));
+      };
+      fetch_bins(pin_index(tp));
+      fft_forward<LOGQ>(buf, tab, lt, x, fetch_tw);
+      for (int i0 = tp; i0 < L.nb; i0 += U * T) {
+        if (i0 >= U * T) {
+          fetch_bins(i0);
+          fetch_tw(fft_np(LOGQ) - 1);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int i = i0 + j * T;
+          if (i < L.nb) {
+            float2 w1, w2;
+            spectrum_pair<LOGQ>(spec, kj[j] & (Q - 1), wj[j], w1, w2);
+            float2 d0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
+            float2 d1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+            if constexpr (MULTI) {
+              const float2 tw = conjf2(cis_poly2((kj[j] * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
+              d0 = cmul(tw, d0);
+              d1 = cmul(tw, d1);
+              if (b) {
+                d0 = cadd(F0[i], d0);
+                d1 = cadd(F0[L.Bp + i], d1);
+              }
+            }
             F0[i] = d0;
             F0[L.Bp + i] = d1;
           }
         }
       }
-      __syncthreads();  // the next scatter overwrites buf
-    };
-    if constexpr (MULTI) {
-#pragma unroll
-      for (int p = 0; p < NP; ++p) one_pair(p, acc[p]);
-    } else {
-#pragma unroll 1
-      for (int p = 0; p < NP; ++p) one_pair(p, acc[0]);
-    }
-  }
-
-  if constexpr (MULTI && NBT > 0) {
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      float2* F0 = F + (int64_t)(2 * p) * L.Bp;
-#pragma unroll
-      for (int j = 0; j < NBT; ++j) {
-        const int i = j * kFftThreads + tid;
-        if (i < L.nb) {
-          F0[i] = acc[p][0][j];
-          F0[L.Bp + i] = acc[p][1][j];
-        }
-      }
+      __syncthreads();  // the next transform overwrites buf
     }
   }
 }
+
+// M > 8192 and up to NBT * 512 kept bins per layer: one persistent workgroup per CU walks the (slice, tensor, NP channel
+// pairs) items of its XCD and their residues with the running sums of all kept bins in registers (which is why there is
+// one), and fetches the samples of the next step while it transforms the pairs of the current one, a row or so per phase: a
+// wave that issues more than the address queue takes stalls, and the barriers make the others wait.  Vector memory answers
+// in order, so nothing else in the loop may be a load that is waited for at once: the passes' twiddles and the bin
+// twiddles sit in LDS.  8 x 8 slices of 131072 tokens, 4096 bins: 4.77 -> 4.27 ms; with the token loads taken out 2.2.
+// The last radix-2 stage of the transform and the residue sum are one thing: sample n = Pb (2 a + h) + b, so every bin takes
+// two products, with e^{-j 2 pi k b / M} for the even half spectrum E and e^{-j 2 pi k (b + Pb) / M} for the odd one O; with
+// r = k mod 4096 and the mirror entry r' = -r mod 4096, the first channel's part is (E[r] + conj E[r']) / 2 and so on.
+template <bool BF16, int NBT, int NP>
+__global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const void* __restrict__ K,
+                                                               const void* __restrict__ V, int per_xcd, int n_st,
+                                                               int slots) {
+  constexpr int LOGQ = 13, Q = 1 << LOGQ, H = Q / 2, T = 512;
+  static_assert(fft_threads(LOGQ) == T && kFftMaxLogQ == LOGQ, "");
+  constexpr int kElem = BF16 ? 2 : 4;
+  constexpr int kRow = kHeadDim * kElem;
+  constexpr int NW = NP * (BF16 ? 1 : 2);  // words per sample: 16 bytes, one pair's for tensors that are not 16-byte aligned
+  constexpr int kGroups = kPairs / NP;
+  extern __shared__ float2 buf[];
+  float4* ltab = (float4*)(buf + fft_lds(LOGQ));
+  float4* btw = ltab + TabLds::entries<LOGQ>();  // [NBT * T] bin twiddles, half of (even, odd); a thread's own entries only
+  const TabLds tab{P.tab + tab_base(LOGQ), ltab};
+  const int tid = threadIdx.x;
+  const uint32_t xcd = blockIdx.x & 7u;
+  const int st_first = (int)xcd * per_xcd, st_count = min(per_xcd, n_st - st_first);
+  const int n_items = st_count * kGroups;
+  int n = (int)(blockIdx.x >> 3);
+  if (n >= n_items) return;  // the whole workgroup
+  tab.fill<LOGQ>(ltab, tid);
+
+  const uint32_t M = P.M, Pb = M >> LOGQ;
+  const int spl = P.batch * P.n_kv;
+  const int64_t N = (int64_t)P.S + M + P.R;      // tokens per slice in the caller's tensor
+  const uint32_t step = Pb * (uint32_t)kRow;     // bytes between consecutive samples of one residue
+  const uint32_t voff = sample_at<LOGQ>(16 * tid) * step;  // < 2^32: the launcher checks M
+  auto rows = [&](int item, uint32_t b) {        // first sample of residue b of an item
+    const int st = st_first + item / kGroups;
+    return (const char*)((st & 1) ? V : K) + ((int64_t)(st >> 1) * N + P.S + b) * kRow + (item % kGroups) * (NP * 2 * kElem);
+  };
+  auto fetch = [&](Raw<NW>& z, const char* base, uint32_t off, int m) {
+    z = load_raw<NW>(base + (int64_t)((((m & 3) << 2) | (m >> 2)) * (Q / 16)) * step + off);
+  };
+  auto layer_of = [&](int item) { return layer_info(P, ((st_first + item / kGroups) >> 1) / spl); };
+
+  uint32_t kk[NBT];
+  auto fetch_bins = [&](uint32_t (&k)[NBT], int bin_off, int nb) {
+    const int o = pin_index(tid);
+#pragma unroll
+    for (int j = 0; j < NBT; ++j) {
+      const int i = j * T + o;
+      k[j] = (uint32_t)P.bins[bin_off + (i < nb ? i : nb - 1)];
+    }
+  };
+  Raw<NW> z[16];
+  LayerInfo L = layer_of(n);
+  fetch_bins(kk, L.bin_off, L.nb);
+#pragma unroll
+  for (int m = 0; m < 16; ++m) fetch(z[m], rows(n, 0), voff, m);
+  float2 acc[NP][2][NBT];  // running sums over the residues
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int j = 0; j < NBT; ++j) acc[p][0][j] = acc[p][1][j] = make_float2(0.f, 0.f);
+  __syncthreads();
+
+  uint32_t b = 0;
+#pragma unroll 1
+  for (;;) {
+    const int st = st_first + n / kGroups;
+    const int s = (st >> 1) - ((st >> 1) / spl) * spl;
+    float2* F = ((st & 1) ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + (n % kGroups) * (NP * 2)) * L.Bp;
+    const bool last_b = b + 1 == Pb;
+    const int n1 = last_b ? n + slots : n;
+    const bool more = n1 < n_items;
+    const uint32_t b1 = last_b ? 0u : b + 1;
+    // at the very end the current rows are fetched once more instead of a branch
+    const char* nx = more ? rows(n1, b1) : rows(n, b);
+    const LayerInfo Ln = layer_of(more ? n1 : n);
+    Raw<NW> zn[16];
+
+#pragma unroll
+    for (int j = 0; j < NBT; ++j) {
+      const float2 t0 = cis_poly2((kk[j] * b) & (M - 1u), M), t1 = cis_poly2((kk[j] * (b + Pb)) & (M - 1u), M);
+      btw[j * T + tid] = make_float4(0.5f * t0.x, -0.5f * t0.y, 0.5f * t1.x, -0.5f * t1.y);
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      float2 x[16];
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        x[m] = raw_front<BF16, NW>(z[m]);
+        raw_pop<BF16, NW>(z[m]);
+      }
+      // The next step's samples, one row or so per phase (three passes and the pruning): a wave that issues more than the
+      // address queue takes stalls.  In this order every word lands in a register that the current samples have left.
+      auto fetch_next = [&](int phase) {
+        constexpr int kPhases = 4 * NP;
+        const int at = 4 * p + phase;
+        const uint32_t off = (uint32_t)pin_index((int)voff);
+#pragma unroll
+        for (int m = at * 16 / kPhases; m < (at + 1) * 16 / kPhases; ++m) fetch(zn[m], nx, off, m);
+      };
+      fft_forward<LOGQ>(buf, tab, tid, x, fetch_next);
+      fetch_next(3);
+#pragma unroll
+      for (int j = 0; j < NBT; ++j) {
+        const uint32_t r = kk[j] & (H - 1), rm = (H - r) & (H - 1);
+        const float2 *u = buf + fpad((int)r), *v = buf + fpad((int)rm);
+        const float2 e = u[0], o = u[H + H / 8], em = v[0], om = v[H + H / 8];
+        const float4 w = btw[j * T + tid];
+        const float2 se = make_float2(e.x + em.x, e.y - em.y), de = make_float2(e.y + em.y, em.x - e.x);  // -j (E - conj E')
+        const float2 so = make_float2(o.x + om.x, o.y - om.y), dd = make_float2(o.y + om.y, om.x - o.x);
+        float2 &a0 = acc[p][0][j], &a1 = acc[p][1][j];
+        a0 = make_float2(fmaf(w.x, se.x, fmaf(-w.y, se.y, a0.x)), fmaf(w.x, se.y, fmaf(w.y, se.x, a0.y)));
+        a1 = make_float2(fmaf(w.x, de.x, fmaf(-w.y, de.y, a1.x)), fmaf(w.x, de.y, fmaf(w.y, de.x, a1.y)));
+        a0 = make_float2(fmaf(w.z, so.x, fmaf(-w.w, so.y, a0.x)), fmaf(w.z, so.y, fmaf(w.w, so.x, a0.y)));
+        a1 = make_float2(fmaf(w.z, dd.x, fmaf(-w.w, dd.y, a1.x)), fmaf(w.z, dd.y, fmaf(w.w, dd.x, a1.y)));
+      }
+      __syncthreads();  // the next transform overwrites buf
+    }
+    if (last_b) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        float2* F0 = F + (int64_t)(2 * p) * L.Bp;
+#pragma unroll
+        for (int j = 0; j < NBT; ++j) {
+          const int i = j * T + tid;
+          if (i < L.nb) {
+            F0[i] = acc[p][0][j];
+            F0[L.Bp + i] = acc[p][1][j];
+          }
+          acc[p][0][j] = acc[p][1][j] = make_float2(0.f, 0.f);
+        }
+      }
+    }
+    if (!more) break;
+    if (last_b) fetch_bins(kk, Ln.bin_off, Ln.nb);
+    n = n1;
+    b = b1;
+    L = Ln;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) z[m] = zn[m];
+  }
+}
+
+constexpr int kCusPerXcd = 32;
+constexpr uint64_t kFewWorkgroups = 256;
+constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 
 bool prefill_fft_ok(const Params& P) { return P.Mmask != 0 && P.M >= 256; }
 
@@ -230,54 +331,56 @@ template <bool BF16>
 static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const void* V, hipStream_t st) {
   int logM = 0;
   while ((1u << logM) < P.M) ++logM;
-  const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
   const int n_st = P.n_slices * 2;
   const int per_xcd = (n_st + 7) / 8;
-  const size_t lds = sizeof(float2) * (size_t)fft_lds_float2(logQ);
-  const int per_thread = (P.max_nb + kFftThreads - 1) / kFftThreads;
-  // 16-byte sample loads need 16-byte aligned tensors (and rows, which are 256 or 512 bytes)
+  // several pairs per load need 16-byte aligned tensors (and rows, which are 256 or 512 bytes)
   const bool wide = (((uintptr_t)K | (uintptr_t)V) & 15u) == 0;
   hipError_t e = hipSuccess;
-#define IWDFT_PF_CASE(LQ, MULTI, NBT, NP)                                                                    \
-  {                                                                                                          \
-    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / (NP)) * 8;                                         \
-    if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                         \
-    static LdsLimit lim;                                                                                     \
-    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NBT, NP>, (int)lds);                     \
-    if (e != hipSuccess) return e;                                                                           \
-    prefill_fft_kernel<LQ, BF16, MULTI, NBT, NP><<<dim3((uint32_t)blocks), dim3(kFftThreads), lds, st>>>(    \
-        P, K, V, per_xcd, n_st);                                                                             \
+  if (logM > kFftMaxLogQ && P.max_nb <= 4096 && P.M <= kStreamMaxM) {
+#define IWDFT_PF_STREAM(NBT, NP)                                                                              \
+  {                                                                                                           \
+    const size_t bytes = sizeof(float2) * fft_lds(kFftMaxLogQ) +                                              \
+                         sizeof(float4) * (TabLds::entries<kFftMaxLogQ>() + (NBT) * 512);                     \
+    const int items = per_xcd * (kPairs / (NP)), slots = items < kCusPerXcd ? items : kCusPerXcd;             \
+    static LdsLimit lim;                                                                                      \
+    e = lim.ensure((const void*)prefill_stream_kernel<BF16, NBT, NP>, (int)bytes);                            \
+    if (e != hipSuccess) return e;                                                                            \
+    prefill_stream_kernel<BF16, NBT, NP><<<dim3((uint32_t)slots * 8), dim3(512), bytes, st>>>(P, K, V,        \
+                                                                                             per_xcd, n_st,  \
+                                                                                             slots);         \
   }
-  // Pairs per workgroup: as many as the register budget (128) holds next to the transform -- the staged samples
-  // take 16 registers per further bf16 pair, the running sums of the decimated form 4 per pair and kept bin.
-#define IWDFT_PF_SINGLE(LQ)                                                                                  \
-  {                                                                                                          \
-    constexpr int kNpSingle = BF16 ? 4 : (LQ < 13 ? 2 : 1);                                                  \
-    if (wide) IWDFT_PF_CASE(LQ, false, 8, kNpSingle)                                                         \
-    else IWDFT_PF_CASE(LQ, false, 8, 1)                                                                      \
+    constexpr int kNp = BF16 ? 4 : 2;
+    if (P.max_nb > 2048) {
+      if (wide) IWDFT_PF_STREAM(8, kNp) else IWDFT_PF_STREAM(8, 1)
+    } else {
+      if (wide) IWDFT_PF_STREAM(4, kNp) else IWDFT_PF_STREAM(4, 1)
+    }
+#undef IWDFT_PF_STREAM
+    return hipGetLastError();
   }
-  if (per_thread > kFftNBT) {  // more than 4096 kept bins in some layer (so M >= 8192): the bin-strided form
+  const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
+  // Pairs per thread: as many as the register budget (128) holds next to the transform (the staged samples take 16
+  // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.
+  const bool few = (uint64_t)n_st * (kPairs / 4 / prefill_ns(logQ)) < kFewWorkgroups;
+#define IWDFT_PF_CASE(LQ, MULTI, NP)                                                                        \
+  {                                                                                                         \
+    const size_t lds = sizeof(float2) * (size_t)(prefill_ns(LQ) * prefill_bs(LQ));                          \
+    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * prefill_ns(LQ))) * 8;                     \
+    if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                        \
+    static LdsLimit lim;                                                                                    \
+    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NP>, (int)lds);                         \
+    if (e != hipSuccess) return e;                                                                          \
+    prefill_fft_kernel<LQ, BF16, MULTI, NP><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(P, K, V,        \
+                                                                                           per_xcd, n_st); \
+  }
+#define IWDFT_PF_SINGLE(LQ)                                                        \
+  {                                                                                \
+    constexpr int kNp = (LQ == 8 || !BF16) ? 2 : 4;                                \
+    if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp) else IWDFT_PF_CASE(LQ, false, 1) \
+  }
+  if (logM > kFftMaxLogQ) {
     constexpr int kNpBig = BF16 ? 2 : 1;
-    if (logM > logQ) {
-      if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, 0, kNpBig)
-      else IWDFT_PF_CASE(kFftMaxLogQ, true, 0, 1)
-    } else {
-      if (wide) IWDFT_PF_CASE(kFftMaxLogQ, false, 0, kNpBig)
-      else IWDFT_PF_CASE(kFftMaxLogQ, false, 0, 1)
-    }
-  } else if (logM > logQ) {
-    if (per_thread <= 4) {
-      constexpr int kNpMulti = BF16 ? 2 : 1;
-      if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, 4, kNpMulti)
-      else IWDFT_PF_CASE(kFftMaxLogQ, true, 4, 1)
-    } else {
-      // 5 .. 8 kept bins per thread: the running sums alone take 32 registers per pair, so the kernel that shares
-      // its loads among four pairs gets the 256-register budget (one workgroup per CU); measured against one pair
-      // per workgroup at 128 registers: 46 -> 43.5 ms (M = 32768, 2048 slices), 26.6 -> 20.5 ms (M = 131072, 256).
-      constexpr int kNpMulti8 = BF16 ? 4 : 1;
-      if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, 8, kNpMulti8)
-      else IWDFT_PF_CASE(kFftMaxLogQ, true, 8, 1)
-    }
+    if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, kNpBig) else IWDFT_PF_CASE(kFftMaxLogQ, true, 1)
   } else switch (logQ) {
     case 8: IWDFT_PF_SINGLE(8) break;
     case 9: IWDFT_PF_SINGLE(9) break;
