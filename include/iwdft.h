@@ -79,7 +79,7 @@ enum {
                                        with more than 4096 kept bins take a form that
                                        keeps nothing per bin in registers).  With neither flag
                                        the library picks: FFT when it applies and some
-                                       layer keeps >= 384 bins                     */
+                                       layer keeps >= 128 bins or >= M / 32        */
   IWDFT_FLAG_SHORTCUT = 8u,         /* the variant of the update that Sec. 4.1 mentions for long
                                        contexts, the factor (N-1)/N of Eq. infi-dft taken as 1:
                                        S_{T+1}[k] = W_k ( S_T[k] + x_T / (T+1) ).  Tokens no longer

@@ -64,7 +64,8 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
 // Most kept bins per layer the FFT kernels keep in registers (prefill, reconstruction, the deferred write-back);
 // decode attention itself takes any number through its bin-strided kernel.
 constexpr int kFftMaxBins = 4096;
-constexpr int kFftPrefillMinBins = 384;  // fewer kept bins per layer: the dense contraction is faster
+// Prefill without a flag, M = 2^m: FFTs from this many kept bins in some layer, or from 1 / kFftPrefillMinShare of all bins.
+constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32;
 constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit in LDS)
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
@@ -143,15 +144,18 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
 
   const bool pow2 = (d->M & (d->M - 1)) == 0;
   pl->use_fft = pow2 && (uint64_t)d->M >= kFftMinM && !(d->flags & IWDFT_FLAG_DIRECT_SYNTHESIS);
-  // Prefill: the FFT costs the same whatever the number of kept bins, the dense contraction grows
-  // with it; measured break-even on MI355X: about 300 kept bins per layer at M = 8192, 430 at M = 131072.
+  // Prefill: the FFT costs about the same whatever the number of kept bins, the dense contraction grows with it in steps of
+  // 128.  Measured (16 layers x 8 heads, bf16, dense / FFT): M = 1024, 64 bins 52 / 30 us; M = 4096, 256 bins 235 / 134;
+  // M = 8192, 128 bins 336 / 282; one layer, M = 1024, 64 bins, fp32: 78 / 7.5.  The FFT is ahead below the line too (M = 4096,
+  // 64 bins: 177 / 116), but there iwdft_prefill_kind has always answered "dense", with that path's documented input range.
   const bool fft_pf_ok = pow2 && (uint64_t)d->M >= kFftMinM;
   if (d->flags & IWDFT_FLAG_FFT_PREFILL) {
     if (!fft_pf_ok)
       return fail(IWDFT_ERR_UNSUPPORTED, "FFT prefill needs M = 2^m >= %d", (int)kFftMinM);
     pl->use_fft_prefill = true;
   } else {
-    pl->use_fft_prefill = fft_pf_ok && !(d->flags & IWDFT_FLAG_DENSE_PREFILL) && pl->max_nb >= kFftPrefillMinBins;
+    pl->use_fft_prefill = fft_pf_ok && !(d->flags & IWDFT_FLAG_DENSE_PREFILL) &&
+                          (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M);
   }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
   // of M / Pb points, Pb the smallest divisor of M that brings the block down to 8192 (none: the direct sums).
