@@ -149,11 +149,11 @@ int iwdft_prefill_kind(const iwdft_ctx* ctx);
  * weights through in-LDS FFTs (M = 2^m >= 256: O(M log M) per query head, the HBM-bound path; layers with more than
  * 4096 kept bins run a form of it that keeps nothing per bin in registers); 2 = through chirp-z transforms (any
  * other M >= 32 that is at most 8192 or has a divisor Pb <= 256 with 32 <= M / Pb <= 8192, e.g. M = context - sink -
- * recent = 16384 - 60 = 2 * 8162: O(M log M) as well, about 8 times the arithmetic of 1); 0 = the direct O(M |B|)
+ * recent = 16384 - 60 = 2 * 8162: O(M log M) as well, 2 to 4 times the arithmetic of 1); 0 = the direct O(M |B|)
  * sums (arithmetic-bound; chosen by IWDFT_FLAG_DIRECT_SYNTHESIS, for M < 32, and for M > 8192 without such a divisor,
  * e.g. a prime -- there only while M * (most kept bins of a layer) <= 2^30, beyond that iwdft_query_bytes /
  * iwdft_create return IWDFT_ERR_UNSUPPORTED unless the flag insists); -1 if ctx is NULL.
- * With 0 or 2, or when some layer keeps more than 4096 bins, desc.write_every is taken as 1. */
+ * With 0, with 2 and M < 256, or with 1 when some layer keeps more than 4096 bins, desc.write_every is taken as 1. */
 int iwdft_attn_kind(const iwdft_ctx* ctx);
 
 /* Whether decode attention on this context (Sec. 4.2.2 "Calculating Attention") walks the slices in groups, with
@@ -221,8 +221,8 @@ int compressed_decode_attn_static(iwdft_ctx* ctx, const void* d_q, void* d_out, 
  * coefficients are written once per J steps.  Every other call on the context (append, attention,
  * reconstruct, export) first writes the deferred tokens back, so results never depend on J beyond
  * rounding order; only a caller that copies the state buffer itself (checkpoint) must call iwdft_flush
- * first.  Deferral needs the FFT attention path and at most 8 query heads per KV head; without them
- * J is taken as 1. */
+ * first.  Deferral needs the FFT or the chirp-z attention path (see iwdft_attn_kind) and at most 8 query heads
+ * per KV head; without them J is taken as 1. */
 int iwdft_append_attn(iwdft_ctx* ctx, const void* d_tok_k, const void* d_tok_v, const void* d_q,
                       void* d_out, float scale, void* hip_stream);
 

@@ -50,8 +50,9 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   bool use_fft = false;          // decode attention through power-of-two FFTs
   bool use_chirp = false;        // ... through chirp-z transforms (any M up to kChirpMaxM when use_fft is false)
   int chirp_logN = 0;            // length of its circular convolutions
+  int chirp_logS = 0;            // length of the table in the state buffer (kept for copies of it; nothing reads it)
   int64_t chirp_Q = 0;           // points per chirp-z transform: M / Pb (M itself up to 8192)
-  size_t off_chirp = 0, off_chirpH = 0;
+  size_t off_chirp = 0, off_chirpS = 0, off_chirpW = 0;
   int64_t tw_Q = 0;              // length of the power-of-two in-LDS transforms (0: none), table at off_tw
   size_t off_tw = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
@@ -170,8 +171,9 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     }
   }
   if (pl->use_chirp) {
-    pl->chirp_logN = 8;
-    while (((int64_t)1 << pl->chirp_logN) < 2 * pl->chirp_Q - 1) pl->chirp_logN += 2;  // even lengths only
+    pl->chirp_logN = pl->chirp_logS = 8;
+    while (((int64_t)1 << pl->chirp_logN) < 2 * pl->chirp_Q - 1) ++pl->chirp_logN;
+    while (((int64_t)1 << pl->chirp_logS) < 2 * pl->chirp_Q - 1) pl->chirp_logS += 2;
   }
   pl->fold.assign((size_t)pl->n_bins_total, 0);
   if (pl->use_fft || pl->use_chirp) {
@@ -217,7 +219,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_weights = o; o = align256(o + sizeof(float) * (size_t)pl->n_bins_total);
   pl->off_fold = o;    o = align256(o + sizeof(uint16_t) * (size_t)pl->n_bins_total);
   pl->off_chirp = o;   o = align256(o + (pl->use_chirp ? sizeof(float2) * (size_t)pl->chirp_Q : 0));
-  pl->off_chirpH = o;  o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
+  pl->off_chirpS = o;  o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logS) : 0));
   pl->tw_Q = (pow2 && (uint64_t)d->M >= kFftMinM) ? (d->M < kFftMaxQ ? d->M : kFftMaxQ) : 0;
   pl->off_tw = o;      o = align256(o + (pl->tw_Q ? sizeof(float2) * (size_t)(pl->tw_Q / 8 + 1) : 0));
   pl->off_FK = o;      o = align256(o + sizeof(float2) * (size_t)coef);
@@ -234,16 +236,19 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_qc = o; o = align256(o + sizeof(float2) * (size_t)ws);
   pl->off_Pn = o; o = align256(o + sizeof(float2) * (size_t)ws);
   pl->off_pe = o; o = align256(o + sizeof(float) * n_sl * (size_t)pl->G * (size_t)(d->n_sink + d->n_recent));
-  // Deferred write-back needs the FFT attention kernels (they weigh the pending tokens) and all
-  // query heads of a KV head in one pass; otherwise every step writes back.
-  pl->write_every = (d->write_every > 1 && pl->use_fft && pl->max_nb <= kFftMaxBins && heads_fit_one_pass(pl->G) &&
-                     !(d->flags & IWDFT_FLAG_SHORTCUT))
+  // Deferred write-back needs the FFT or chirp-z attention kernels (they weigh the pending tokens; the bin-strided FFT form
+  // does not, and below 256 slots a layer's coefficients are no traffic worth deferring) and all query heads of a KV head in
+  // one pass; otherwise every step writes back.  32 layers x 8 heads, M = 8132, 2033 bins: a step reads 1.06 GB instead of
+  // moving 2.1.
+  const bool weighs = (pl->use_fft && pl->max_nb <= kFftMaxBins) || (pl->use_chirp && (uint64_t)d->M >= kFftMinM);
+  pl->write_every = (d->write_every > 1 && weighs && heads_fit_one_pass(pl->G) && !(d->flags & IWDFT_FLAG_SHORTCUT))
                         ? (int)d->write_every
                         : 1;
   const size_t pend_rows = (d->n_recent || pl->write_every > 1) ? (size_t)pl->write_every : 0;
   pl->off_pendK = o; o = align256(o + esz * n_sl * pend_rows * kHeadDim);
   pl->off_pendV = o; o = align256(o + esz * n_sl * pend_rows * kHeadDim);
   pl->off_ps = o;    o = align256(o + (pl->write_every > 1 ? sizeof(float) * n_sl * (size_t)pl->G * kMaxPend : 0));
+  pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
   pl->off_direct = o;
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
@@ -252,21 +257,27 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   return IWDFT_OK;
 }
 
-// Tables of the chirp-z attention kernel, in double precision: c[a] = exp(+j pi a^2 / M) and the length-N
-// transform (sign +) of h[n] = exp(-j pi n^2 / M), |n| < M, wrapped modulo N, divided by N and stored where the
-// kernel's first in-LDS transform leaves entry m: base-4 digit-reversed position.
-void make_chirp_tables(int64_t M, int logN, std::vector<float2>* chirp, std::vector<float2>* H) {
+// Tables of the chirp-z transforms, in double precision: c[a] = exp(+j pi a^2 / M) and the length-N transform (sign +) of
+// h[n] = exp(-j pi n^2 / M), |n| < M, wrapped modulo N, divided by N.
+void make_chirp(int64_t M, std::vector<float2>* chirp) {
   const double kPi = 3.14159265358979323846;
-  const int64_t N = (int64_t)1 << logN;
   chirp->resize((size_t)M);
-  std::vector<std::complex<double>> h((size_t)N, 0.0);
   for (int64_t n = 0; n < M; ++n) {
     const double ph = kPi * (double)((n * n) % (2 * M)) / (double)M;  // exact phase reduction
     (*chirp)[(size_t)n] = make_float2((float)std::cos(ph), (float)std::sin(ph));
+  }
+}
+void make_chirp_transform(int64_t M, int logN, std::vector<float2>* H) {
+  const double kPi = 3.14159265358979323846;
+  const int64_t N = (int64_t)1 << logN;
+  std::vector<std::complex<double>> h((size_t)N, 0.0), w((size_t)(N / 2));
+  for (int64_t n = 0; n < M; ++n) {
+    const double ph = kPi * (double)((n * n) % (2 * M)) / (double)M;
     const std::complex<double> v(std::cos(ph), -std::sin(ph));
     h[(size_t)n] = v;
     if (n) h[(size_t)(N - n)] = v;
   }
+  for (int64_t j = 0; j < N / 2; ++j) w[(size_t)j] = std::polar(1.0, 2.0 * kPi * (double)j / (double)N);
   // iterative radix-2 transform, sign +
   for (int64_t i = 1, j = 0; i < N; ++i) {
     int64_t bit = N >> 1;
@@ -277,19 +288,23 @@ void make_chirp_tables(int64_t M, int logN, std::vector<float2>* chirp, std::vec
   for (int64_t len = 2; len <= N; len <<= 1) {
     for (int64_t i = 0; i < N; i += len)
       for (int64_t j = 0; j < len / 2; ++j) {
-        const double a = 2.0 * kPi * (double)j / (double)len;
-        const std::complex<double> w(std::cos(a), std::sin(a));
-        const std::complex<double> u = h[(size_t)(i + j)], v = h[(size_t)(i + j + len / 2)] * w;
+        const std::complex<double> u = h[(size_t)(i + j)], z = h[(size_t)(i + j + len / 2)], t = w[(size_t)(j * (N / len))];
+        const std::complex<double> v(z.real() * t.real() - z.imag() * t.imag(), z.real() * t.imag() + z.imag() * t.real());
         h[(size_t)(i + j)] = u + v;
         h[(size_t)(i + j + len / 2)] = u - v;
       }
   }
   H->resize((size_t)N);
-  for (int64_t m = 0; m < N; ++m) {
-    int64_t p = 0;
-    for (int t = 0; t < logN / 2; ++t) p |= ((m >> (2 * t)) & 3) << (logN - 2 * t - 2);
-    (*H)[(size_t)p] = make_float2((float)(h[(size_t)m].real() / (double)N), (float)(h[(size_t)m].imag() / (double)N));
-  }
+  for (int64_t m = 0; m < N; ++m)
+    (*H)[(size_t)m] = make_float2((float)(h[(size_t)m].real() / (double)N), (float)(h[(size_t)m].imag() / (double)N));
+}
+// Entry m of the transform sits at position digit_position(m) of the order that the in-LDS transforms of 2^logN points leave
+// (fft_core.h, sample_at): the base-4 digits reversed, for odd logN behind the low bit, which moves to the top.
+int64_t digit_position(int64_t m, int logN) {
+  int64_t p = 0;
+  const int odd = logN & 1, even = logN - odd;
+  for (int t = 0; t < even / 2; ++t) p |= ((m >> (odd + 2 * t)) & 3) << (even - 2 * t - 2);
+  return odd ? p | ((m & 1) << even) : p;
 }
 
 }  // namespace
@@ -463,11 +478,23 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       e = hipMemcpy(c->state + pl.off_fold, pl.fold.data(), sizeof(uint16_t) * pl.fold.size(),
                     hipMemcpyHostToDevice);
     if (e == hipSuccess && pl.use_chirp) {
-      std::vector<float2> chirp, H;
-      make_chirp_tables(pl.chirp_Q, pl.chirp_logN, &chirp, &H);
+      std::vector<float2> chirp, H, out;
+      make_chirp(pl.chirp_Q, &chirp);
       e = hipMemcpy(c->state + pl.off_chirp, chirp.data(), sizeof(float2) * chirp.size(), hipMemcpyHostToDevice);
+      make_chirp_transform(pl.chirp_Q, pl.chirp_logN, &H);
+      out.resize(H.size());
+      const int64_t T = (int64_t)H.size() / 16;
+      for (int64_t m = 0; m < (int64_t)H.size(); ++m) {  // chirp.h: thread t owns the positions 16 t .. 16 t + 15, two per load
+        const int64_t p = digit_position(m, pl.chirp_logN), t = p >> 4, j = (p & 15) >> 1;
+        out[(size_t)((j * T + t) * 2 + (p & 1))] = H[(size_t)m];
+      }
       if (e == hipSuccess)
-        e = hipMemcpy(c->state + pl.off_chirpH, H.data(), sizeof(float2) * H.size(), hipMemcpyHostToDevice);
+        e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
+      if (pl.chirp_logS != pl.chirp_logN) make_chirp_transform(pl.chirp_Q, pl.chirp_logS, &H);
+      out.resize(H.size());
+      for (int64_t m = 0; m < (int64_t)H.size(); ++m) out[(size_t)digit_position(m, pl.chirp_logS)] = H[(size_t)m];
+      if (e == hipSuccess)
+        e = hipMemcpy(c->state + pl.off_chirpS, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && pl.tw_Q) {
       const double kTwoPi = 6.28318530717958647692;
@@ -504,7 +531,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.weights = (const float*)(c->state + pl.off_weights);
     P.fold = (const uint16_t*)(c->state + pl.off_fold);
     P.chirp = pl.use_chirp ? (const float2*)(c->state + pl.off_chirp) : nullptr;
-    P.chirpH = pl.use_chirp ? (const float2*)(c->state + pl.off_chirpH) : nullptr;
+    P.chirpW = pl.use_chirp ? (const float4*)(c->ws + pl.off_chirpW) : nullptr;
     P.chirp_logN = pl.chirp_logN;
     P.chirp_Q = (uint32_t)pl.chirp_Q;
     P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;

@@ -1,0 +1,305 @@
+// Kernel B of the decode attention (see attn.hip) for M that is not a power of two (e.g. M = context - sink - recent,
+// Sec. 4.2.1, which is a power of two only by arrangement): scores, softmax and weights through chirp-z transforms (chirp.h).
+#include "chirp.h"
+
+namespace iwdft {
+
+// One workgroup of N / 16 threads per (slice, pair of query heads: real and imaginary part of one signal).  Q = M up to 8192.
+// Longer M run Pb = M / Q blocks (Pb the smallest divisor of M that brings Q down to 8192): time index a = Pb a' + b, block b
+// comes from the spectrum folded modulo Q with twiddle e^{j 2 pi k b / M}, softmax runs online across the blocks and the
+// running sums of the weights live in the output rows (every bin belongs to one thread, which reads back its own earlier
+// store).
+// What bounds it is vector arithmetic and the barriers of four N-point transforms per block: half of every input is zero and
+// half of every output is not wanted, so the wide stages run on registers, and scores, softmax and weights never leave them.
+// 32 x 8 slices, 4 query heads each, M = 8132, 2033 bins: 75 us (134 with one transform of 16384 points by 512 threads, every
+// pass through LDS); with the write-back deferred a decode step takes 286 us instead of 510.
+// Pending tokens of the deferred write-back enter as in attn_fft_kernel (np, ptsh, ps).
+template <int LOGN>
+__global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params P, const float2* __restrict__ qc,
+                                                                      float2* __restrict__ Pn, float* __restrict__ pe,
+                                                                      float scale, int pairs, int np, uint32_t ptsh,
+                                                                      float* __restrict__ ps) {
+  constexpr int T = fft_threads(LOGN), NWV = T < 64 ? 1 : T / 64;
+  constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
+  extern __shared__ float2 buf[];
+  __shared__ float2 smax[NWV], ssum[NWV];
+  __shared__ float pscr[NWV][2 * kMaxPend];
+  const TabMem tab{P.tab + tab_base(LOGN)};
+  const float4* __restrict__ H = P.chirpW;
+  const int t = threadIdx.x;
+  const int pair = blockIdx.x % pairs;
+  const int slice = blockIdx.x / pairs;
+  const int spl = P.batch * P.n_kv;
+  const int layer = slice / spl;
+  const int s = slice - layer * spl;
+  const LayerInfo L = layer_info(P, layer);
+  const int g0 = pair * 2;
+  const bool has1 = (g0 + 1) < P.G;
+  const uint32_t M = P.M, Q = P.chirp_Q, Pb = M / Q;
+  const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
+  const float2* q1 = has1 ? q0 + L.Bp : q0;
+  float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
+  float2* o1 = o0 + L.Bp;  // written only if has1
+  const int32_t* bins = P.bins + L.bin_off;
+  const float* wts = P.weights + L.bin_off;
+  const uint16_t* fold = P.fold + L.bin_off;
+  const float gain = 0.5f * 1.44269504088896341f * scale * P.gain / (float)M;  // log2 units; 0.5: bin + mirror
+  const float inv_Mf = 1.0f / (float)M, inv_Q = 1.0f / (float)Q;
+  float2* own = buf + fpad(t);  // this thread's entries t + T i at i * SP
+
+  auto wave_op = [&](float v, auto op) {
+#pragma unroll
+    for (int o = (T < 64 ? T : 64) / 2; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
+    return v;
+  };
+  auto max2 = [](float a, float b) { return fmaxf(a, b); };
+  auto add2 = [](float a, float b) { return a + b; };
+  // Over the workgroup; the barrier of the one separates the reads of the other from its next writes.
+  auto block_max = [&](float2 v) {
+    v = make_float2(wave_op(v.x, max2), wave_op(v.y, max2));
+    if ((t & 63) == 0) smax[t >> 6] = v;
+    __syncthreads();
+    v = smax[0];
+    for (int w = 1; w < NWV; ++w) v = make_float2(fmaxf(v.x, smax[w].x), fmaxf(v.y, smax[w].y));
+    return v;
+  };
+  auto block_sum = [&](float2 v) {
+    v = make_float2(wave_op(v.x, add2), wave_op(v.y, add2));
+    if ((t & 63) == 0) ssum[t >> 6] = v;
+    __syncthreads();
+    v = ssum[0];
+    for (int w = 1; w < NWV; ++w) v = cadd(v, ssum[w]);
+    return v;
+  };
+
+  float2 c[8];  // chirp of the thread's entries, 0 from Q on
+#pragma unroll
+  for (int i = 0; i < 8; ++i) c[i] = (uint32_t)(t + T * i) < Q ? P.chirp[t + T * i] : make_float2(0.f, 0.f);
+
+  // Exact tokens open the softmax (raw scores q . k_e from kernel A).
+  float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);
+  const int E = P.S + P.R;
+  float* pe0 = pe + ((int64_t)slice * P.G + g0) * E;
+  float* pe1 = pe0 + E;
+  const float escale = 1.44269504088896341f * scale;
+  if (E > 0) {
+    float2 lm = mx;
+    for (int e = t; e < E; e += T) {
+      lm.x = fmaxf(lm.x, pe0[e] * escale);
+      if (has1) lm.y = fmaxf(lm.y, pe1[e] * escale);
+    }
+    mx = block_max(lm);
+    float2 ls = make_float2(0.f, 0.f);
+    for (int e = t; e < E; e += T) {
+      ls.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
+      if (has1) ls.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
+    }
+    Z = block_sum(ls);
+  }
+
+  constexpr int U = 4;  // bins whose inputs are fetched together
+  for (uint32_t b = 0; b < Pb; ++b) {
+    auto block_tw = [&](uint32_t k) {  // e^{j 2 pi k b / M}
+      return Pb == 1 ? make_float2(1.f, 0.f) : cis_rev((float)mod_small(k * b, M, inv_Mf) * inv_Mf);
+    };
+    auto slot_of = [&](uint32_t k) { return Pb == 1 ? k : mod_small(k, Q, inv_Q); };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) own[i * SP] = make_float2(0.f, 0.f);
+    __syncthreads();
+    // Hermitian spectrum of both heads (head g0 real, head g0 + 1 imaginary in time), folded modulo Q.  A slot can receive
+    // several terms: successive rounds (host-made schedule).
+    for (int round = 0; round < L.fold_rounds; ++round) {
+      for (int i0 = t; i0 < L.nb; i0 += U * T) {
+        uint32_t k[U], fr[U];
+        float w[U];
+        float2 y0[U], y1[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int i = i0 + j * T, ic = i < L.nb ? i : L.nb - 1;
+          k[j] = (uint32_t)bins[ic];
+          fr[j] = i < L.nb ? (uint32_t)fold[ic] : 0xffffu;  // 0xff: no round matches
+          w[j] = wts[ic] * gain;
+          y0[j] = q0[ic];
+          y1[j] = q1[ic];
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const bool direct = (fr[j] & 0xffu) == (uint32_t)round, mirror = (fr[j] >> 8) == (uint32_t)round;
+          if (!direct && !mirror) continue;
+          const float2 tw = block_tw(k[j]);
+          const float2 z0 = cmul(make_float2(y0[j].x * w[j], y0[j].y * w[j]), tw);
+          const float2 z1 = has1 ? cmul(make_float2(y1[j].x * w[j], y1[j].y * w[j]), tw) : make_float2(0.f, 0.f);
+          const uint32_t r = slot_of(k[j]), rm = r ? Q - r : 0u;
+          if (direct) {  //      z0  + j z1
+            float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
+            if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
+            if (round) v = cadd(v, buf[fpad((int)r)]);
+            buf[fpad((int)r)] = v;
+          }
+          if (mirror) {  // conj z0  + j conj z1
+            float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
+            if (round) v = cadd(v, buf[fpad((int)rm)]);
+            buf[fpad((int)rm)] = v;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    float2 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = cmul(own[i * SP], c[i]);
+    chirp_convolve<LOGN, false>(buf, tab, H, t, v);
+
+    // scores of slot a < Q of this block: real part head g0, imaginary part head g0 + 1
+    float2 lm = make_float2(-INFINITY, -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[i] = cmul(v[i], c[i]);
+      if ((uint32_t)(t + T * i) < Q) {
+        lm.x = fmaxf(lm.x, v[i].x);
+        lm.y = fmaxf(lm.y, v[i].y);
+      }
+    }
+    const float2 bm = block_max(lm);
+    const float2 mn = make_float2(fmaxf(mx.x, bm.x), fmaxf(mx.y, bm.y));
+    // exp2(-inf) = 0 the first time
+    const float2 f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
+    mx = mn;
+    float2 ls = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float2 p = make_float2(0.f, 0.f);
+      if ((uint32_t)(t + T * i) < Q)
+        p = make_float2(__builtin_amdgcn_exp2f(v[i].x - mn.x), has1 ? __builtin_amdgcn_exp2f(v[i].y - mn.y) : 0.f);
+      ls = cadd(ls, p);
+      v[i] = cmul(p, conjf2(c[i]));
+    }
+    const float2 bs = block_sum(ls);
+    Z = make_float2(Z.x * f.x + bs.x, Z.y * f.y + bs.y);
+    chirp_convolve<LOGN, true>(buf, tab, H, t, v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) own[i * SP] = cmul(v[i], conjf2(c[i]));
+    __syncthreads();
+
+    for (int i0 = t; i0 < L.nb; i0 += U * T) {
+      uint32_t k[U];
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = i0 + j * T;
+        k[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = i0 + j * T;
+        if (i >= L.nb) continue;
+        const uint32_t r = slot_of(k[j]), rm = r ? Q - r : 0u;
+        const float2 w1 = buf[fpad((int)r)], w2 = buf[fpad((int)rm)];
+        float2 p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
+        float2 p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+        if (Pb > 1) {
+          const float2 twc = conjf2(block_tw(k[j]));
+          p0 = cmul(twc, p0);
+          p1 = cmul(twc, p1);
+          if (b) {  // this thread's own running sums, scaled to the new maximum
+            const float2 a0 = o0[i];
+            p0 = make_float2(a0.x * f.x + p0.x, a0.y * f.x + p0.y);
+            if (has1) {
+              const float2 a1 = o1[i];
+              p1 = make_float2(a1.x * f.y + p1.x, a1.y * f.y + p1.y);
+            }
+          }
+        }
+        o0[i] = p0;
+        if (has1) o1[i] = p1;
+      }
+    }
+    __syncthreads();
+  }
+
+  const float inv_M = P.gain / (float)M;
+  const float iz0 = inv_M / Z.x, iz1 = has1 ? inv_M / Z.y : 0.f;
+  const double inv_Md = 1.0 / (double)M;
+  float sp[2 * kMaxPend];  // [token][head g0, head g0 + 1]: Re sum_k e^{j theta_jk} Pn[k] of the pending tokens
+#pragma unroll
+  for (int j = 0; j < 2 * kMaxPend; ++j) sp[j] = 0.f;
+  for (int i = t; i < L.Bp; i += T) {  // padding entries are written as zeros: kernel C reads whole rows
+    float2 r0 = make_float2(0.f, 0.f), r1 = r0;
+    if (i < L.nb) {
+      const float w = wts[i];
+      const float2 a0 = o0[i];
+      r0 = make_float2(a0.x * (w * iz0), -a0.y * (w * iz0));
+      if (has1) {
+        const float2 a1 = o1[i];
+        r1 = make_float2(a1.x * (w * iz1), -a1.y * (w * iz1));
+      }
+      if (np > 0) {  // block-uniform; u_n = Re(tw step^n r) obeys u_{n+1} = 2 cos(step) u_n - u_{n-1}
+        const uint32_t k = (uint32_t)bins[i];
+        const float2 tw = cis_rev(phase_of(k, ptsh, M, inv_Md)), step = cis_rev((float)k * inv_Mf), t1 = cmul(tw, step);
+        const float c2 = 2.f * step.x;
+        float u0 = tw.x * r0.x - tw.y * r0.y, u1 = t1.x * r0.x - t1.y * r0.y;
+        float v0 = tw.x * r1.x - tw.y * r1.y, v1 = t1.x * r1.x - t1.y * r1.y;
+#pragma unroll
+        for (int j = 0; j < kMaxPend; ++j) {
+          if (j < np) {
+            sp[2 * j] += u0;
+            sp[2 * j + 1] += v0;
+            const float u2 = c2 * u1 - u0, v2 = c2 * v1 - v0;
+            u0 = u1, u1 = u2;
+            v0 = v1, v1 = v2;
+          }
+        }
+      }
+    }
+    o0[i] = r0;
+    if (has1) o1[i] = r1;
+  }
+  if (np > 0) {
+#pragma unroll
+    for (int j = 0; j < 2 * kMaxPend; ++j) {
+      if (j < 2 * np) {
+        const float tot = wave_op(sp[j], add2);
+        if ((t & 63) == 0) pscr[t >> 6][j] = tot;
+      }
+    }
+    __syncthreads();
+    for (int e = t; e < 2 * np; e += T) {
+      float sum = 0.f;
+      for (int w = 0; w < NWV; ++w) sum += pscr[w][e];
+      if ((e & 1) == 0 || has1) ps[((int64_t)slice * P.G + g0 + (e & 1)) * kMaxPend + (e >> 1)] = sum;
+    }
+  }
+  for (int e = t; e < E; e += T) {  // raw scores -> weights p_e / Z
+    pe0[e] = __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x) / Z.x;
+    if (has1) pe1[e] = __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y) / Z.y;
+  }
+}
+
+hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, float* pe, float scale, int np, uint32_t ptsh,
+                             float* ps, hipStream_t st) {
+  const int pairs = (P.G + 1) / 2;
+  const uint64_t grid = (uint64_t)P.n_slices * pairs;
+  if (grid > 0x7fffffffull || np > kMaxPend) return hipErrorInvalidConfiguration;
+#define IWDFT_CHIRP_CASE(LN)                                                                                            \
+  case LN: {                                                                                                            \
+    constexpr int bytes = (int)sizeof(float2) * fft_lds(LN);                                                            \
+    static LdsLimit lim;                                                                                                \
+    const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN>, bytes);                                         \
+    if (e != hipSuccess) return e;                                                                                      \
+    attn_chirp_kernel<LN><<<dim3((uint32_t)grid), dim3(fft_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
+                                                                                     ptsh, ps);                        \
+  } break;
+  switch (P.chirp_logN) {
+    IWDFT_CHIRP_CASE(8)
+    IWDFT_CHIRP_CASE(9)
+    IWDFT_CHIRP_CASE(10)
+    IWDFT_CHIRP_CASE(11)
+    IWDFT_CHIRP_CASE(12)
+    IWDFT_CHIRP_CASE(13)
+    IWDFT_CHIRP_CASE(14)
+    default: return hipErrorInvalidValue;
+  }
+#undef IWDFT_CHIRP_CASE
+  return hipGetLastError();
+}
+
+}  // namespace iwdft

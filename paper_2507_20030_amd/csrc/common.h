@@ -9,6 +9,7 @@
 namespace iwdft {
 
 constexpr int kHeadDim = 128;  // channels per head the kernels are written for
+constexpr int kMaxPend = 16;   // most tokens of a deferred write-back
 constexpr int kRowPad = 32;    // a coefficient row is padded to a multiple of this many bins
 
 // Per-layer geometry, one entry per layer in device memory.
@@ -43,12 +44,11 @@ struct Params {
   const float* weights;
   const uint16_t* fold;  // per kept bin: low byte = round of its direct slot, high byte = round of its mirror slot
                          // (0xff: the mirror falls on the direct slot and is added in the same write)
-  // Chirp-z attention (M that is not a power of two; null otherwise): transforms of chirp_Q = M / Pb points, Pb the
-  // smallest divisor of M with M / Pb <= 8192 (1 for M <= 8192).  chirp[a] = exp(+j pi a^2 / chirp_Q), a < chirp_Q;
-  // chirpH: 2^chirp_logN entries, the transform of the conjugate chirp divided by its length, in the digit-reversed
-  // order of the in-LDS transform.
+  // Chirp-z transforms (M that is not a power of two; null otherwise) of chirp_Q = M / Pb points, Pb the smallest divisor of
+  // M with M / Pb <= 8192 (1 for M <= 8192).  chirp[a] = exp(+j pi a^2 / chirp_Q), a < chirp_Q; chirpW: the transform of the
+  // conjugate chirp divided by its length 2^chirp_logN, laid out as chirp.h reads it.
   const float2* chirp;
-  const float2* chirpH;
+  const float4* chirpW;
   int32_t chirp_logN;
   uint32_t chirp_Q;
   // Twiddle octant of the in-LDS power-of-two transforms: tw8[m] = exp(+j 2 pi m / Q), m = 0 .. Q/8, with
@@ -185,6 +185,10 @@ hipError_t launch_attn(const Params& P, const void* q, void* out, float scale, f
                        float2* Pn, float* pe, float* direct_scratch, bool use_fft,
                        const PhaseEvents* marks, hipStream_t st);
 
+// The softmax through chirp-z transforms (Params::chirp set).
+hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, float* pe, float scale, int np, uint32_t ptsh,
+                             float* ps, hipStream_t st);
+
 // One decode step = append + attention with the update fused into the attention kernels.
 // write_every = 1: every coefficient is read once and written once per step.  write_every = J > 1: the
 // coefficients are written back only on every J-th step; in between the tokens they do not hold yet
@@ -192,7 +196,6 @@ hipError_t launch_attn(const Params& P, const void* q, void* out, float scale, f
 // attention through rank-one corrections, so every step returns the same result (up to rounding order).
 // t_shift0: slot shift of the oldest pending token (of this step's token if none is pending);
 // ps: [slice][query head][kMaxPend] floats.  step_can_fuse: all query heads fit one pass.
-constexpr int kMaxPend = 16;
 bool heads_fit_one_pass(int G);
 // Whether decode attention on this context walks the slices in groups (kernels A and B pipelined, see attn_ab_kernel).
 bool attn_pipelines(const Params& P, bool use_fft);

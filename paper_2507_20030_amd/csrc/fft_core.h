@@ -206,7 +206,8 @@ __device__ __forceinline__ void write16(float2* buf, int t, const float2 (&x)[16
 
 // One radix-16 pass of span 16^K (K >= 1) in place.  Tab::kEarly: w holds its twiddles on entry and, NEXT >= 0, those of
 // the pass of span 16^NEXT on return.  hook(k) runs between the butterflies and the stores.
-template <int LOGQ, int K, bool INV, int NEXT, typename Tab, typename Hook>
+// HALF: the upper half of the input is zero (only looked at where the radix-2 stage comes with the reads).
+template <int LOGQ, int K, bool INV, int NEXT, bool HALF = false, typename Tab, typename Hook>
 __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw16& w, Hook hook) {
   constexpr int Q = 1 << LOGQ, S = 4 * K, s2 = 1 << S;
   constexpr int SP = s2 + s2 / 8;  // distance in LDS of positions s2 apart
@@ -221,8 +222,11 @@ __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw1
     const float sg = (t >> S) ? -1.f : 1.f;  // block 0: the even samples, block 1: the odd ones
 #pragma unroll
     for (int m = 0; m < 16; ++m) {
-      const float2 u = lo[m * SP], v = hi[m * SP];
-      x[m] = make_float2(fmaf(sg, v.x, u.x), fmaf(sg, v.y, u.y));
+      x[m] = lo[m * SP];
+      if constexpr (!HALF) {
+        const float2 v = hi[m * SP];
+        x[m] = make_float2(fmaf(sg, v.x, x[m].x), fmaf(sg, v.y, x[m].y));
+      }
     }
     __syncthreads();
   } else {
@@ -333,6 +337,138 @@ __device__ __forceinline__ void fft_forward(float2* buf, const Tab& tab, int t, 
   __syncthreads();
   fft_fwd_passes<LOGQ, 1>(buf, tab, t, w, hook);
   if constexpr (fft_rem(LOGQ) >= 2 || (WIDE && fft_rem(LOGQ) == 1)) fft_wide<LOGQ, false>(buf, tab.tab, t);
+}
+
+// The two transforms between signals of at most N / 2 points, for convolutions of length N = 2^LOGN (chirp.h): thread t holds
+// entries t + T i, i < 8, T = N / 16, in registers; the upper half of the inverse transform's input is zero, that of the
+// forward transform's output is not formed.  Neither needs a barrier in front as long as buf was last touched at these and
+// the thread's other entries t + T i, i < 16, only.
+template <int LOGN>
+__device__ __forceinline__ void half_inverse(float2* buf, const TabMem& tab, int t, const float2 (&v)[8], float2 (&x)[16]) {
+  constexpr int N = 1 << LOGN, T = fft_threads(LOGN), REM = fft_rem(LOGN), NP = fft_np(LOGN);
+  constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
+  static_assert(NP >= 2 && T >= 16, "256 points at least");
+  Tw16 w;
+  float2* b = buf + fpad(t);
+  if constexpr (REM == 0) {  // the wide pass starts from the registers
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = v[m], x[m + 8] = make_float2(0.f, 0.f);
+    dft16_1<true>(x);
+    tab.load<LOGN, NP - 2, true>(w, t);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) b[m * SP] = x[m];
+    __syncthreads();
+    fft_inv_passes<LOGN, NP - 2>(buf, tab, t, w);
+  } else {
+    tab.load<LOGN, NP - 1, true>(w, t);
+    if constexpr (REM == 1) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b[i * SP] = v[i];
+      __syncthreads();
+      fft_pass<LOGN, NP - 1, true, NP - 2, true>(buf, tab, t, w, [] {});
+      fft_inv_passes<LOGN, NP - 2>(buf, tab, t, w);
+    } else {
+      if constexpr (REM == 2) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float2 u = v[i], z = v[i + 4];
+          b[i * SP] = cadd(u, z);
+          b[(i + 4) * SP] = make_float2(u.x - z.y, u.y + z.x);
+          b[(i + 8) * SP] = csub(u, z);
+          b[(i + 12) * SP] = make_float2(u.x + z.y, u.y - z.x);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float2 y[8];
+#pragma unroll
+          for (int m = 0; m < 4; ++m) y[m] = y[m + 4] = v[i + 2 * m];
+          r4_1<true>(y[0], y[1], y[2], y[3]);
+          r4_e<true>(y[4], y[5], y[6], y[7]);
+#pragma unroll
+          for (int m = 0; m < 8; ++m) b[(i + 2 * m) * SP] = y[m];
+        }
+      }
+      __syncthreads();
+      fft_inv_passes<LOGN, NP - 1>(buf, tab, t, w);
+    }
+  }
+  static_assert(N == 16 * T, "");
+  read16(buf, t, x);
+  dft16<true>(x, w);
+}
+// buf: last read by half_inverse.
+template <int LOGN>
+__device__ __forceinline__ void half_forward(float2* buf, const TabMem& tab, int t, float2 (&x)[16], float2 (&v)[8]) {
+  constexpr int N = 1 << LOGN, T = fft_threads(LOGN), REM = fft_rem(LOGN), NP = fft_np(LOGN);
+  constexpr int SP = T + T / 8;
+  const float2* b = buf + fpad(t);
+  const float2* __restrict__ tw = tab.tab + tab_off_rem(LOGN);
+  Tw16 w;
+  tab.load<LOGN, 1, false>(w, t);
+  dft16_1<false>(x);
+  write16(buf, t, x);
+  __syncthreads();
+  if constexpr (REM == 0) {
+    if constexpr (NP == 3) fft_pass<LOGN, 1, false, 2>(buf, tab, t, w, [] {});
+    static_assert(NP <= 3, "one pass between the two ends at most");
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m] = b[m * SP];
+    dft16<false>(x, w);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) v[m] = x[m];
+  } else if constexpr (REM == 1) {
+    float2 wt[8];  // fetched before the last barrier
+    fft_fwd_passes<LOGN, 1>(buf, tab, t, w, [&](int k) {
+      if (k != NP - 1) return;
+      const int i0 = pin_index(t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) wt[i] = tw[i0 + i * T];
+    });
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float2 o = b[(i + 8) * SP];
+      v[i] = b[i * SP];
+      bfly<false>(v[i], o, wt[i].x, wt[i].y);
+    }
+  } else if constexpr (REM == 2) {
+    float4 wt[4];
+    fft_fwd_passes<LOGN, 1>(buf, tab, t, w, [&](int k) {
+      if (k != NP - 1) return;
+      const int i0 = pin_index(t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wt[i] = ((const float4*)tw)[i0 + i * T];
+    });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float2 y0 = b[i * SP], y1 = b[(i + 4) * SP], y2 = b[(i + 8) * SP], y3 = b[(i + 12) * SP];
+      r4<false>(y0, y1, y2, y3, wt[i].x, wt[i].y, wt[i].z, wt[i].w);
+      v[i] = y0;
+      v[i + 4] = y1;
+    }
+  } else {
+    float4 wt[2], wu[2];
+    fft_fwd_passes<LOGN, 1>(buf, tab, t, w, [&](int k) {
+      if (k != NP - 1) return;
+      const int i0 = pin_index(t);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) wt[i] = ((const float4*)tw)[i0 + i * T], wu[i] = ((const float4*)(tw + N / 4))[i0 + i * T];
+    });
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float2 y[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) y[m] = b[(i + 2 * m) * SP];
+      r4<false>(y[0], y[1], y[2], y[3], wt[i].x, wt[i].y, wt[i].z, wt[i].w);
+      r4<false>(y[4], y[5], y[6], y[7], wt[i].x, wt[i].y, wt[i].z, wt[i].w);
+      bfly<false>(y[0], y[4], wu[i].x, wu[i].y);
+      bfly<false>(y[1], y[5], wu[i].z, wu[i].w);
+      bfly_j<false>(y[2], y[6], wu[i].x, wu[i].y);
+      bfly_j<false>(y[3], y[7], wu[i].z, wu[i].w);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) v[i + 2 * m] = y[m];
+    }
+  }
 }
 
 // Table entry that spectrum_pair needs for entry r (nothing when the spectrum is complete).

@@ -729,6 +729,33 @@ def test_any_length_attention_through_chirp_transforms(dtype, L, S, R, group, n_
     d.close()
 
 
+@pytest.mark.parametrize("L,S,R,group,n_bins,J", [
+    (255, 0, 0, 2, 60, 4),       # below 256 slots every step writes back
+    (256 + 1, 0, 3, 1, 90, 4),   # 513 -> 1024 points
+    (500, 10, 50, 4, 120, 8), (513, 0, 0, 3, 300, 16), (1025, 1, 0, 8, 200, 4), (2048 - 1, 0, 2, 2, 500, 8),
+    (4096 + 1, 0, 0, 1, 1000, 8), (2 * 4099, 10, 50, 5, 2000, 4), (3 * 8191, 0, 1, 2, 4500, 4),
+])
+def test_chirp_attention_defers_the_write_back(L, S, R, group, n_bins, J):
+    """Both sides of every convolution length (2 M - 1 against 2^m), one block and several, more bins than 4096, an odd
+    number of heads: fused steps across two write-backs against the oracle, and with every step written back."""
+    cfg = small_cfg(L=L, n_bins=n_bins, group=group, dtype="f32", steps=J + 3, n_layers=2, batch=1, n_sink=S, n_recent=R)
+    bins = random_bins(cfg, 57)
+    run_stream(cfg, bins, rec=(0, min(64, L)), fused=True, write_every=J, tag=f"chirp-defer-{L}")
+    K, V = wl.prefill_tensors(cfg, DEV)
+    a, d = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins)
+    assert B.iwdft_attn_kind(a.ctx) == "chirp"
+    a.prefill(K, V)
+    d.prefill(K, V)
+    for i in range(J + 3):
+        k, v, q = wl.decode_step(cfg, i, DEV)
+        assert rel_l2(f64(a.step(k, v, q)), f64(d.step(k, v, q))) < 2e-5
+    for layer in range(2):
+        for x, y in zip(a.export_coeffs(layer), d.export_coeffs(layer)):
+            assert rel_l2(c128(x), c128(y)) < 2e-6
+    a.close()
+    d.close()
+
+
 @pytest.mark.parametrize("L,S,R,group,n_bins,dtype", [
     (16324, 10, 50, 4, 1600, "bf16"),    # 16384 - 60 = 2 * 8162: the paper's windows cut out of a 16K context
     (32708, 10, 50, 2, 3000, "f32"),     # 32768 - 60 = 4 * 8177
