@@ -22,7 +22,7 @@
 // and write it back, or -- deferred write-back -- leave the coefficients alone and add the exact
 // contribution of the tokens they do not hold yet (see StepUpdate).
 #include "common.h"
-#include "fft_lds.h"
+#include "fft_core.h"
 
 namespace iwdft {
 
@@ -529,359 +529,51 @@ __global__ __launch_bounds__(kOutThreads) void attn_out_kernel(Params P, const f
 }
 
 // ------------------------------------------------------------------------------------- B (FFT)
-// Block-wide max / sum of two values at once (one per packed query head).  One barrier each: the two use
-// different scratch rows and always alternate, so the barrier of the one separates the reads of the other from
-// its next writes.
-__device__ __forceinline__ float2 block_max2(float2 v, float2* scratch, int tid) {
-  v.x = wave_max(v.x);
-  v.y = wave_max(v.y);
-  if ((tid & 63) == 0) scratch[tid >> 6] = v;
-  __syncthreads();
-  float2 r = scratch[0];
-  for (int w = 1; w < kFftThreads / 64; ++w) {
-    r.x = fmaxf(r.x, scratch[w].x);
-    r.y = fmaxf(r.y, scratch[w].y);
-  }
-  return r;
+// exp(+j 2 pi p / M) through the hardware sine / cosine (argument in revolutions, exact for the power-of-two M of this
+// path; ~1e-6 absolute error: block twiddles of the scores and weights, where 1e-6 is far below the output tolerance).
+__device__ __forceinline__ float2 cis_fast(uint32_t p, uint32_t M) {
+  const float f = (float)p * rcp_pow2(M);
+  return make_float2(__builtin_amdgcn_cosf(f), __builtin_amdgcn_sinf(f));
 }
-__device__ __forceinline__ float2 block_sum2(float2 v, float2* scratch, int tid) {
-  v.x = wave_sum(v.x);
-  v.y = wave_sum(v.y);
-  if ((tid & 63) == 0) scratch[kFftThreads / 64 + (tid >> 6)] = v;
-  __syncthreads();
-  float2 r = scratch[kFftThreads / 64];
-  for (int w = 1; w < kFftThreads / 64; ++w) {
-    r.x += scratch[kFftThreads / 64 + w].x;
-    r.y += scratch[kFftThreads / 64 + w].y;
-  }
-  return r;
-}
-
-__device__ __forceinline__ int64_t s_global_head(int slice, int G, int g) { return (int64_t)slice * G + g; }
-
-// Softmax over the Q time samples of one block, two heads side by side (real / imaginary part), on sample pairs held in
-// registers; the radix-2 stage that ends the inverse transform and the one that starts the forward transform (odd
-// log2 Q) are applied right here.  Online across blocks: (mx, Z) are the running maximum and sum; returns the factor
-// exp2(old max - new max) by which everything accumulated so far has to be scaled.
-template <int LOGQ>
-__device__ __forceinline__ float2 softmax_block(float2* buf, int tid, bool has1, float2* scratch, float2& mx, float2& Z) {
-  constexpr int Q = 1 << LOGQ;
-  float2 v[kFftEPT];
-  float2 lm = make_float2(-INFINITY, -INFINITY);
+// Over the lanes of a workgroup of T threads (one wave of it).
+template <int T, typename Op>
+__device__ __forceinline__ float lanes_reduce(float v, Op op) {
 #pragma unroll
-  for (int j = 0; j < kFftEPT / 2; ++j) {
-    const int bf = j * kFftThreads + tid;
-    if (2 * bf < Q) {
-      float2 a = buf[pad(2 * bf)], c = buf[pad(2 * bf + 1)];
-      if (LOGQ & 1) {
-        const float2 t = a;
-        a = cadd(t, c);
-        c = csub(t, c);
-      }
-      v[2 * j] = a;
-      v[2 * j + 1] = c;
-      lm.x = fmaxf(lm.x, fmaxf(a.x, c.x));
-      lm.y = fmaxf(lm.y, fmaxf(a.y, c.y));
-    }
-  }
-  const float2 bm = block_max2(lm, scratch, tid);
-  const float2 mn = make_float2(fmaxf(mx.x, bm.x), fmaxf(mx.y, bm.y));
-  // exp2(-inf) = 0 the first time
-  const float2 f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
-  mx = mn;
-  float2 ls = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int j = 0; j < kFftEPT / 2; ++j) {
-    const int bf = j * kFftThreads + tid;
-    if (2 * bf < Q) {
-      float2 a = make_float2(__builtin_amdgcn_exp2f(v[2 * j].x - mn.x),
-                             has1 ? __builtin_amdgcn_exp2f(v[2 * j].y - mn.y) : 0.f);
-      float2 c = make_float2(__builtin_amdgcn_exp2f(v[2 * j + 1].x - mn.x),
-                             has1 ? __builtin_amdgcn_exp2f(v[2 * j + 1].y - mn.y) : 0.f);
-      ls.x += a.x + c.x;
-      ls.y += a.y + c.y;
-      if (LOGQ & 1) {
-        const float2 t = a;
-        a = cadd(t, c);
-        c = csub(t, c);
-      }
-      buf[pad(2 * bf)] = a;
-      buf[pad(2 * bf + 1)] = c;
-    }
-  }
-  const float2 bs = block_sum2(ls, scratch, tid);  // its barrier also publishes the writes above
-  Z = make_float2(Z.x * f.x + bs.x, Z.y * f.y + bs.y);
-  return f;
+  for (int o = (T < 64 ? T : 64) / 2; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
+  return v;
 }
 
-// grid: slice * pairs + pair.  Two query heads share one complex transform: head g0 travels in
-// the real part, head g0+1 in the imaginary part (each head's spectrum is made Hermitian first,
-// so its time-domain signal is real).  Time index a = Pb * a' + b: block b of Q = M / Pb samples
-// comes from the spectrum folded modulo Q with twiddle e^{j 2 pi k b / M}; softmax runs online
-// across the Pb blocks (MULTI); with Pb == 1 nothing is carried between iterations.
-// Folding uses no atomics: entries that share a slot are added in successive rounds (host-made
-// schedule in P.fold), which also fixes the summation order.  NBT = kept bins per thread.
-// Register budget: 128 VGPRs (two workgroups per CU) except for the multi-block kernel with 8 bins
-// per thread, whose per-bin inputs and running sums (~80 registers) then spill; that one gets 256
-// VGPRs and one workgroup per CU (measured 1.5x faster than spilling at two per CU).
-// The work of logical block `bid` (wave-uniform); smem: fft_lds_float2(LOGQ) float2.
+// grid: slice * pairs + pair, Q / 16 threads.  Two query heads share one complex transform: head g0 travels in the real
+// part, head g0 + 1 in the imaginary part (each head's spectrum is made Hermitian first, so its time-domain signal is
+// real).  Time index a = Pb * a' + b: block b of Q = M / Pb samples comes from the spectrum folded modulo Q with twiddle
+// e^{j 2 pi k b / M}; softmax runs online across the Pb blocks (MULTI).
+// Folding uses no atomics: entries that share a slot are added in successive rounds (host-made schedule in P.fold), which
+// also fixes the summation order.
+// A thread's 16 scores leave the inverse transform in registers and enter the forward one from there, so that softmax costs
+// one barrier (the maximum); the sum stays a partial sum per thread until the end.
+// Weights: with one block they are normalised and written as the spectrum is gathered; MULTI keeps the running sums of the
+// thread's NBT bins in registers, or (NBT = 0, more than 4096 kept bins) in the output rows themselves -- every bin belongs
+// to one thread, which reads back its own earlier store.
+// The work of logical block `bid` (wave-uniform); buf: fft_lds(LOGQ) float2.
 template <int LOGQ, int NBT, bool MULTI>
 __device__ __forceinline__ void fft_body(const Params& P, const float2* __restrict__ qc, float2* __restrict__ Pn,
                                          float* __restrict__ pe, float scale, int pairs, int np, uint32_t ptsh,
-                                         float* __restrict__ ps, uint32_t bid, float2* smem) {
-  __shared__ float2 scratch[2 * (kFftThreads / 64)];  // row 0: block_max2, row 1: block_sum2
-  __shared__ float pscr[kFftThreads / 64][2 * kMaxPend];
-  const int tid = threadIdx.x;
-  constexpr int Q = 1 << LOGQ;
-  float2* buf = smem;                 // Q samples, padded
-  float2* tab = smem + Q + (Q >> 5);  // Q/8 + 1 twiddles
+                                         float* __restrict__ ps, uint32_t bid, float2* buf) {
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NWV = T < 64 ? 1 : T / 64;
+  constexpr bool kRegs = MULTI && NBT > 0;  // running sums in registers
+  constexpr bool kKeep = kRegs && NBT > 4;  // with the register budget of one workgroup per CU: the inputs stay as well
+  constexpr int U = kRegs ? NBT : 4;  // bins whose inputs are fetched together
+  static_assert(MULTI || NBT == 0, "one block: nothing to keep");
+  __shared__ float2 smax[NWV], ssum[NWV];
+  __shared__ float pscr[NWV][2 * kMaxPend];
+  const TabMem tab{P.tab + tab_base(LOGQ)};
+  const int t = threadIdx.x;
   const int pair = bid % pairs;
   const int slice = bid / pairs;
   const int spl = P.batch * P.n_kv;
   const int layer = slice / spl;
   const int s = slice - layer * spl;
-  const LayerInfo L = P.layers[layer];
-  const int g0 = pair * 2;
-  const bool has1 = (g0 + 1) < P.G;
-  const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
-  const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
-  const float2* q1 = has1 ? q0 + L.Bp : q0;
-  const int32_t* bins = P.bins + L.bin_off;
-  const float* wts = P.weights + L.bin_off;
-  const uint16_t* fold = P.fold + L.bin_off;
-  // log2(e) is folded into the scores so that softmax can use the bare exp2 instruction;
-  // 0.5: each bin is split into k and its mirror.
-  const float gain = 0.5f * 1.44269504088896341f * scale * P.gain / (float)P.M;
-
-  for (int m = tid; m <= (Q >> 3); m += kFftThreads) tab[m] = P.tw8[m];  // exp(+j 2 pi m / Q), host-made
-
-  float2 A0[NBT], A1[NBT];  // running sums over blocks (MULTI) / the single result
-  // The 128-register multi-block kernel fetches its bin indices again at every use (L1 / L2 hits) instead of
-  // keeping them: fewer spilled registers (12 -> 7).
-  constexpr bool kReloadK = MULTI && NBT <= 4;
-  uint32_t kkr[kReloadK ? 1 : NBT];
-#pragma unroll
-  for (int j = 0; j < NBT; ++j) {
-    A0[j] = A1[j] = make_float2(0.f, 0.f);
-    const int i = j * kFftThreads + tid;
-    if constexpr (!kReloadK) kkr[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
-  }
-  auto KK = [&](int j) -> uint32_t {
-    if constexpr (kReloadK) { const int i = j * kFftThreads + tid; return (uint32_t)bins[i < L.nb ? i : L.nb - 1]; }
-    else return kkr[j];
-  };
-  float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);
-
-  // Exact tokens open the online softmax: their raw scores q . k_e come from kernel A.
-  const int E = P.S + P.R;
-  float* pe0 = pe + ((int64_t)s_global_head(slice, P.G, g0)) * E;
-  float* pe1 = pe0 + E;
-  const float escale = 1.44269504088896341f * scale;  // scores live in log2 units (exp2 softmax)
-  if (E > 0) {
-    float2 lm = make_float2(-INFINITY, -INFINITY);
-    for (int e = tid; e < E; e += kFftThreads) {
-      lm.x = fmaxf(lm.x, pe0[e] * escale);
-      if (has1) lm.y = fmaxf(lm.y, pe1[e] * escale);
-    }
-    mx = block_max2(lm, scratch, tid);
-    float2 ls = make_float2(0.f, 0.f);
-    for (int e = tid; e < E; e += kFftThreads) {
-      ls.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
-      if (has1) ls.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
-    }
-    Z = block_sum2(ls, scratch, tid);
-  }
-
-  constexpr bool kTight = MULTI && NBT <= 4;  // 128-VGPR multi-block variant: fight hoisting
-  for (uint32_t b = 0; b < Pb; ++b) {
-    if (kTight) {
-      // Per-bin inputs are re-read every iteration (L2 hits) instead of being kept in ~50 VGPRs.
-      asm volatile("" : "+s"(q0), "+s"(q1), "+s"(wts), "+s"(fold));
-    }
-    // The thread index is made opaque per iteration so that the address arithmetic of the six
-    // transform passes is recomputed (a few instructions) instead of being hoisted out of the
-    // block loop into ~40 long-lived registers.
-    int lt = tid;
-    if (kTight) asm volatile("" : "+v"(lt));
-    for (int e = tid; e < Q + (Q >> 5); e += kFftThreads) buf[e] = make_float2(0.f, 0.f);
-    __syncthreads();
-    // Folded entry of bin j of this thread: (z0, z1) for the two heads, from inputs loaded as a group (all
-    // loads are issued before the first use: one latency, not one per bin).
-    auto place = [&](int j, uint32_t frj, float2 z0, float2 z1, int round) {
-      const int r = KK(j) & (Q - 1), rm = (Q - r) & (Q - 1);
-      if ((frj & 0xffu) == (uint32_t)round) {  //      z0  + j z1
-        float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
-        if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
-        if (round) v = cadd(v, buf[pad(r)]);
-        buf[pad(r)] = v;
-      }
-      if ((frj >> 8) == (uint32_t)round) {     // conj z0  + j conj z1
-        float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
-        if (round) v = cadd(v, buf[pad(rm)]);
-        buf[pad(rm)] = v;
-      }
-    };
-    // The entries are formed once and the rounds only place them, except in the 8-bins-per-thread kernel with
-    // the 128-register budget, which has no room to keep them and forms them again in every round.
-    constexpr bool kKeep = MULTI || NBT <= 4;
-    // The block twiddles e^{j 2 pi k b / M} serve the folding and, conjugated, the pruning below; the kernel with
-    // the 256-register budget keeps them, the others form them twice.
-    constexpr bool kKeepTw = MULTI && NBT > 4;
-    float2 twk[kKeepTw ? NBT : 1];
-    float2 z0[kKeep ? NBT : 1], z1[kKeep ? NBT : 1];
-    uint32_t fr[NBT];
-    for (int round = 0; round < L.fold_rounds; ++round) {
-      if (!kKeep || round == 0) {
-        float ww[NBT];
-        float2 y0[NBT], y1[NBT];
-#pragma unroll
-        for (int j = 0; j < NBT; ++j) {
-          const int i = j * kFftThreads + tid;
-          const int ic = i < L.nb ? i : L.nb - 1;
-          ww[j] = wts[ic] * gain;
-          y0[j] = q0[ic];
-          y1[j] = q1[ic];
-          fr[j] = i < L.nb ? (uint32_t)fold[ic] : 0xffffu;  // 0xff: no round matches
-        }
-#pragma unroll
-        for (int j = 0; j < NBT; ++j) {
-          float2 twj = make_float2(1.f, 0.f);
-          if (MULTI) twj = cis_fast((KK(j) * b) & (P.M - 1u), P.M);
-          if constexpr (kKeepTw) twk[j] = twj;
-          const float w = ww[j];
-          const float2 a0 = cmul(make_float2(y0[j].x * w, y0[j].y * w), twj);
-          const float2 a1 = has1 ? cmul(make_float2(y1[j].x * w, y1[j].y * w), twj) : make_float2(0.f, 0.f);
-          if constexpr (kKeep) {
-            z0[j] = a0;
-            z1[j] = a1;
-          } else {
-            place(j, fr[j], a0, a1, round);
-          }
-        }
-      }
-      if constexpr (kKeep) {
-#pragma unroll
-        for (int j = 0; j < NBT; ++j) place(j, fr[j], z0[j], z1[j], round);
-      }
-      __syncthreads();
-    }
-    ifft_dif<LOGQ>(buf, tab, lt);
-
-    const float2 f = softmax_block<LOGQ>(buf, tid, has1, scratch, mx, Z);
-    fft_dit<LOGQ>(buf, tab, lt);
-#pragma unroll
-    for (int j = 0; j < NBT; ++j) {
-      const int r = KK(j) & (Q - 1), rm = (Q - r) & (Q - 1);
-      const float2 w1 = buf[pad(r)], w2 = buf[pad(rm)];
-      const float2 p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-      const float2 p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
-      if (MULTI) {
-        const float2 twc = conjf2(kKeepTw ? twk[j] : cis_fast((KK(j) * b) & (P.M - 1u), P.M));
-        A0[j] = cadd(make_float2(A0[j].x * f.x, A0[j].y * f.x), cmul(twc, p0));
-        A1[j] = cadd(make_float2(A1[j].x * f.y, A1[j].y * f.y), cmul(twc, p1));
-      } else {
-        A0[j] = p0;
-        A1[j] = p1;
-      }
-    }
-    __syncthreads();
-  }
-
-  float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
-  float2* o1 = o0 + L.Bp;
-  const float inv_M = P.gain / (float)P.M;
-  const float iz0 = inv_M / Z.x, iz1 = has1 ? inv_M / Z.y : 0.f;
-  // Pending tokens of the fused decode step (not yet inside F_V): token j adds
-  // v_j * Re sum_k e^{j theta_jk} Pn[k] to the output; the sums are formed here, where Pn is at hand.
-  float sp[2 * kMaxPend];  // [token][head g0, head g0 + 1]
-#pragma unroll
-  for (int v = 0; v < 2 * kMaxPend; ++v) sp[v] = 0.f;
-#pragma unroll
-  for (int j = 0; j < NBT; ++j) {
-    const int i = j * kFftThreads + tid;
-    if (i < L.Bp) {  // padding entries are written as zeros: kernel C reads whole rows
-      float2 r0 = make_float2(0.f, 0.f), r1 = r0;
-      if (i < L.nb) {
-        const float w = wts[i];
-        r0 = make_float2(A0[j].x * (w * iz0), -A0[j].y * (w * iz0));
-        r1 = make_float2(A1[j].x * (w * iz1), -A1[j].y * (w * iz1));
-        if (np > 0) {  // block-uniform
-          // hardware sine / cosine (~1e-6 absolute): these are weights of value rows, far inside the tolerance
-          // u_n = Re(t step^n r) for n = 0 .. np - 1 obeys u_{n+1} = 2 cos(phi) u_n - u_{n-1} (phi = the step's angle):
-          // one multiply-add per token and head instead of a complex rotation (at most 15 steps: no error growth
-          // that matters next to the 1e-6 of the hardware sine)
-          const float2 t = cis_fast((KK(j) * ptsh) & (P.M - 1u), P.M);
-          const float2 step = cis_fast(KK(j), P.M);
-          const float2 t1 = cmul(t, step);
-          const float c2 = 2.f * step.x;
-          float a0 = t.x * r0.x - t.y * r0.y, a1 = t1.x * r0.x - t1.y * r0.y;  // head g0: u_0, u_1
-          float b0 = t.x * r1.x - t.y * r1.y, b1 = t1.x * r1.x - t1.y * r1.y;  // head g0 + 1
-#pragma unroll
-          for (int jp = 0; jp < kMaxPend; ++jp) {
-            if (jp < np) {
-              sp[2 * jp] += a0;
-              sp[2 * jp + 1] += b0;
-              const float a2 = c2 * a1 - a0, b2 = c2 * b1 - b0;
-              a0 = a1, a1 = a2;
-              b0 = b1, b1 = b2;
-            }
-          }
-        }
-      }
-      o0[i] = r0;
-      if (has1) o1[i] = r1;
-    }
-  }
-  if (np > 0) {
-    // all 2 * kMaxPend sums over the wave at once: afterwards lane l holds the total of entry l / rep
-    const float tot = wave_reduce_scatter<2 * kMaxPend>(sp, tid & 63);
-    constexpr int rep = 64 / (2 * kMaxPend);  // lanes that end up with the same total
-    if ((tid & 63) % rep == 0) pscr[tid >> 6][(tid & 63) / rep] = tot;
-    __syncthreads();
-    if (tid < 2 * np) {
-      float sum = 0.f;
-      for (int w = 0; w < kFftThreads / 64; ++w) sum += pscr[w][tid];
-      const int jp = tid >> 1, head = tid & 1;
-      if (head == 0 || has1) ps[((int64_t)s_global_head(slice, P.G, g0) + head) * kMaxPend + jp] = sum;
-    }
-  }
-  for (int e = tid; e < E; e += kFftThreads) {  // raw scores -> weights p_e / Z (same thread, same entry)
-    pe0[e] = __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x) / Z.x;
-    if (has1) pe1[e] = __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y) / Z.y;
-  }
-}
-
-template <int LOGQ, int NBT, bool MULTI>
-__global__ __launch_bounds__(kFftThreads, (MULTI && NBT > 4) ? 2 : 4) void attn_fft_kernel(Params P, const float2* __restrict__ qc,
-                                                                 float2* __restrict__ Pn, float* __restrict__ pe,
-                                                                 float scale, int pairs, int np, uint32_t ptsh,
-                                                                 float* __restrict__ ps) {
-  extern __shared__ float2 smem[];
-  fft_body<LOGQ, NBT, MULTI>(P, qc, Pn, pe, scale, pairs, np, ptsh, ps, blockIdx.x, smem);
-}
-
-// ------------------------------------------------------------------------- B (FFT, > 4096 kept bins)
-// The same computation for layers that keep more bins than the kernel above holds in registers (8 per thread): the
-// threads walk the bin list in strides of the workgroup, nothing per bin stays in registers.  Folding re-reads the
-// inputs in every round and block; the running sums over blocks (MULTI) live in the output rows themselves -- every bin
-// belongs to one thread, which reads back its own earlier store, scales it by the online-softmax factor and adds the
-// block's term -- and a last sweep turns them into the normalised weights.  No pending tokens (write_every is 1).
-template <int LOGQ, bool MULTI>
-__global__ __launch_bounds__(kFftThreads, 4) void attn_fft_big_kernel(Params P, const float2* __restrict__ qc,
-                                                                     float2* __restrict__ Pn, float* __restrict__ pe,
-                                                                     float scale, int pairs) {
-  extern __shared__ float2 smem[];
-  __shared__ float2 scratch[2 * (kFftThreads / 64)];
-  const int tid = threadIdx.x;
-  constexpr int Q = 1 << LOGQ;
-  float2* buf = smem;
-  float2* tab = smem + Q + (Q >> 5);
-  const int pair = blockIdx.x % pairs;
-  const int slice = blockIdx.x / pairs;
-  const int spl = P.batch * P.n_kv;
-  const int layer = slice / spl;
-  const int s = slice - layer * spl;
-  const LayerInfo L = P.layers[layer];
+  const LayerInfo L = layer_info(P, layer);
   const int g0 = pair * 2;
   const bool has1 = (g0 + 1) < P.G;
   const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
@@ -892,107 +584,321 @@ __global__ __launch_bounds__(kFftThreads, 4) void attn_fft_big_kernel(Params P, 
   const int32_t* bins = P.bins + L.bin_off;
   const float* wts = P.weights + L.bin_off;
   const uint16_t* fold = P.fold + L.bin_off;
-  const float gain = 0.5f * 1.44269504088896341f * scale * P.gain / (float)P.M;  // log2 units; 0.5: bin + mirror
+  // log2(e) is folded into the scores so that softmax can use the bare exp2 instruction;
+  // 0.5: each bin is split into k and its mirror.
+  const float gain = 0.5f * 1.44269504088896341f * scale * P.gain / (float)P.M;
+  auto max2 = [](float a, float b) { return fmaxf(a, b); };
+  auto add2 = [](float a, float b) { return a + b; };
+  auto block_max = [&](float2 v) {  // other barriers separate its reads from its next writes
+    v = make_float2(lanes_reduce<T>(v.x, max2), lanes_reduce<T>(v.y, max2));
+    if constexpr (NWV > 1) {
+      if ((t & 63) == 0) smax[t >> 6] = v;
+      __syncthreads();
+      v = smax[0];
+#pragma unroll
+      for (int w = 1; w < NWV; ++w) v = make_float2(fmaxf(v.x, smax[w].x), fmaxf(v.y, smax[w].y));
+    }
+    return v;
+  };
 
-  for (int m = tid; m <= (Q >> 3); m += kFftThreads) tab[m] = P.tw8[m];
-
-  float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);
+  // Exact tokens open the online softmax: their raw scores q . k_e come from kernel A.
+  float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);  // Z: this thread's share
   const int E = P.S + P.R;
-  float* pe0 = pe + ((int64_t)s_global_head(slice, P.G, g0)) * E;
+  float* pe0 = pe + ((int64_t)slice * P.G + g0) * E;
   float* pe1 = pe0 + E;
-  const float escale = 1.44269504088896341f * scale;
-  if (E > 0) {  // exact tokens open the online softmax (raw scores from kernel A)
-    float2 lm = make_float2(-INFINITY, -INFINITY);
-    for (int e = tid; e < E; e += kFftThreads) {
+  const float escale = 1.44269504088896341f * scale;  // scores live in log2 units (exp2 softmax)
+  if (E > 0) {
+    float2 lm = mx;
+    for (int e = t; e < E; e += T) {
       lm.x = fmaxf(lm.x, pe0[e] * escale);
       if (has1) lm.y = fmaxf(lm.y, pe1[e] * escale);
     }
-    mx = block_max2(lm, scratch, tid);
-    float2 ls = make_float2(0.f, 0.f);
-    for (int e = tid; e < E; e += kFftThreads) {
-      ls.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
-      if (has1) ls.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
+    mx = block_max(lm);
+    for (int e = t; e < E; e += T) {
+      Z.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
+      if (has1) Z.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
     }
-    Z = block_sum2(ls, scratch, tid);
   }
 
-  for (uint32_t b = 0; b < Pb; ++b) {
-    for (int e = tid; e < Q + (Q >> 5); e += kFftThreads) buf[e] = make_float2(0.f, 0.f);
-    __syncthreads();
-    for (int round = 0; round < L.fold_rounds; ++round) {
-      for (int i = tid; i < L.nb; i += kFftThreads) {
-        const uint32_t fr = fold[i];
-        const bool direct = (fr & 0xffu) == (uint32_t)round, mirror = (fr >> 8) == (uint32_t)round;
-        if (!direct && !mirror) continue;
-        const uint32_t k = (uint32_t)bins[i];
-        const float w = wts[i] * gain;
-        const float2 y0 = q0[i], y1 = q1[i];
-        const float2 tw = MULTI ? cis_fast((k * b) & (P.M - 1u), P.M) : make_float2(1.f, 0.f);
-        const float2 z0 = cmul(make_float2(y0.x * w, y0.y * w), tw);
-        const float2 z1 = has1 ? cmul(make_float2(y1.x * w, y1.y * w), tw) : make_float2(0.f, 0.f);
-        const int r = k & (Q - 1), rm = (Q - r) & (Q - 1);
-        if (direct) {  //      z0  + j z1
-          float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
-          if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
-          if (round) v = cadd(v, buf[pad(r)]);
-          buf[pad(r)] = v;
-        }
-        if (mirror) {  // conj z0  + j conj z1
-          float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
-          if (round) v = cadd(v, buf[pad(rm)]);
-          buf[pad(rm)] = v;
-        }
-      }
-      __syncthreads();
-    }
-    ifft_dif<LOGQ>(buf, tab, tid);
-    const float2 f = softmax_block<LOGQ>(buf, tid, has1, scratch, mx, Z);
-    fft_dit<LOGQ>(buf, tab, tid);
-    for (int i = tid; i < L.nb; i += kFftThreads) {
-      const uint32_t k = (uint32_t)bins[i];
-      const int r = k & (Q - 1), rm = (Q - r) & (Q - 1);
-      const float2 w1 = buf[pad(r)], w2 = buf[pad(rm)];
-      float2 p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-      float2 p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
-      if (MULTI) {
-        const float2 twc = conjf2(cis_fast((k * b) & (P.M - 1u), P.M));
-        p0 = cmul(twc, p0);
-        p1 = cmul(twc, p1);
-        if (b) {  // this thread's own running sums, scaled to the new maximum
-          const float2 a0 = o0[i];
-          p0 = make_float2(a0.x * f.x + p0.x, a0.y * f.x + p0.y);
-          if (has1) {
-            const float2 a1 = o1[i];
-            p1 = make_float2(a1.x * f.y + p1.x, a1.y * f.y + p1.y);
-          }
-        }
-      }
-      o0[i] = p0;
-      if (has1) o1[i] = p1;
-    }
-    __syncthreads();
-  }
-
-  const float inv_M = P.gain / (float)P.M;
-  const float iz0 = inv_M / Z.x, iz1 = has1 ? inv_M / Z.y : 0.f;
-  for (int i = tid; i < L.Bp; i += kFftThreads) {  // padding entries are written as zeros: kernel C reads whole rows
-    float2 r0 = make_float2(0.f, 0.f), r1 = r0;
+  // Weights of the output: normalised and with the bin weight; the share of the pending tokens of the fused decode step (not
+  // yet inside F_V): token j adds v_j * Re sum_k e^{j theta_jk} Pn[k], summed here, where Pn is at hand.
+  float iz0 = 0.f, iz1 = 0.f;
+  float sp[2 * kMaxPend];  // [token][head g0, head g0 + 1]
+  auto finish = [&](int i, uint32_t k, float2 a0, float2 a1) {
+    float2 r0 = make_float2(0.f, 0.f), r1 = r0;  // padding entries are written as zeros: kernel C reads whole rows
     if (i < L.nb) {
       const float w = wts[i];
-      const float2 a0 = o0[i];
       r0 = make_float2(a0.x * (w * iz0), -a0.y * (w * iz0));
-      if (has1) {
-        const float2 a1 = o1[i];
-        r1 = make_float2(a1.x * (w * iz1), -a1.y * (w * iz1));
+      r1 = make_float2(a1.x * (w * iz1), -a1.y * (w * iz1));
+    }
+    if (np > 0) {  // block-uniform
+      // hardware sine / cosine (~1e-6 absolute): these are weights of value rows, far inside the tolerance.
+      // u_n = Re(tw step^n r) for n = 0 .. np - 1 obeys u_{n+1} = 2 cos(phi) u_n - u_{n-1} (phi = the step's angle):
+      // one multiply-add per token and head instead of a complex rotation (at most 15 steps: no error growth
+      // that matters next to the 1e-6 of the hardware sine)
+      const float2 tw = cis_fast((k * ptsh) & (P.M - 1u), P.M), step = cis_fast(k, P.M), t1 = cmul(tw, step);
+      const float c2 = 2.f * step.x;
+      float u0 = tw.x * r0.x - tw.y * r0.y, u1 = t1.x * r0.x - t1.y * r0.y;
+      float v0 = tw.x * r1.x - tw.y * r1.y, v1 = t1.x * r1.x - t1.y * r1.y;
+#pragma unroll
+      for (int j = 0; j < kMaxPend; ++j) {
+        if (j < np) {
+          sp[2 * j] += u0;
+          sp[2 * j + 1] += v0;
+          const float u2 = c2 * u1 - u0, v2 = c2 * v1 - v0;
+          u0 = u1, u1 = u2;
+          v0 = v1, v1 = v2;
+        }
       }
     }
     o0[i] = r0;
     if (has1) o1[i] = r1;
+  };
+  auto normalise = [&] {  // behind a barrier that publishes ssum
+    float2 z = ssum[0];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) z = cadd(z, ssum[w]);
+    Z = z;
+    const float inv_M = P.gain / (float)P.M;
+    iz0 = inv_M / Z.x;
+    iz1 = has1 ? inv_M / Z.y : 0.f;
+#pragma unroll
+    for (int v = 0; v < 2 * kMaxPend; ++v) sp[v] = 0.f;
+  };
+  auto publish_sum = [&] {
+    const float2 z = make_float2(lanes_reduce<T>(Z.x, add2), lanes_reduce<T>(Z.y, add2));
+    if ((t & 63) == 0) ssum[t >> 6] = z;
+  };
+
+  float2 A0[kRegs ? NBT : 1], A1[kRegs ? NBT : 1];  // running sums over the blocks
+  if constexpr (kRegs) {
+#pragma unroll
+    for (int j = 0; j < NBT; ++j) A0[j] = A1[j] = make_float2(0.f, 0.f);
   }
-  for (int e = tid; e < E; e += kFftThreads) {  // raw scores -> weights p_e / Z (same thread, same entry)
+
+  uint32_t fr[U], kj[U];
+  float2 y0[U], y1[U], wj[U];
+  // Inputs of the bins i0 + T j of this thread: fold schedule (0xff: no round matches), then spectrum entries of the heads.
+  auto load_fold = [&](int i0) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int i = i0 + j * T;
+      fr[j] = i < L.nb ? (uint32_t)fold[i] : 0xffffu;
+    }
+  };
+  auto load_in = [&](int i0) {
+    float w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int i = i0 + j * T, ic = i < L.nb ? i : L.nb - 1;
+      kj[j] = (uint32_t)bins[ic];
+      w[j] = wts[ic] * gain;
+      y0[j] = q0[ic];
+      y1[j] = q1[ic];
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      y0[j] = make_float2(y0[j].x * w[j], y0[j].y * w[j]);
+      y1[j] = has1 ? make_float2(y1[j].x * w[j], y1[j].y * w[j]) : make_float2(0.f, 0.f);
+    }
+  };
+  auto load_tw = [&] {
+#pragma unroll
+    for (int j = 0; j < U; ++j) wj[j] = pair_twiddle<LOGQ>(tab.tab, kj[j] & (Q - 1));
+  };
+  if constexpr (kKeep) {
+    load_fold(t);
+    load_in(t);
+    load_tw();
+  }
+
+  for (uint32_t b = 0; b < Pb; ++b) {
+    // The thread index is made opaque per iteration so that the address arithmetic of the transforms is recomputed (a few
+    // instructions) instead of being hoisted out of the block loop into long-lived registers.
+    int lt = t;
+    if (MULTI) asm volatile("" : "+v"(lt));
+    float2 x[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m] = make_float2(0.f, 0.f);
+    write16(buf, lt, x);
+    __syncthreads();
+    auto fold_group = [&](int i0, int round) {
+      if constexpr (!kKeep) {
+        load_fold(i0);
+        bool any = round == 0;
+#pragma unroll
+        for (int j = 0; j < U; ++j) any |= (fr[j] & 0xffu) == (uint32_t)round || (fr[j] >> 8) == (uint32_t)round;
+        if (!any) return;  // few bins share a slot
+        load_in(i0);
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        float2 z0 = y0[j], z1 = y1[j];
+        if (MULTI) {
+          const float2 tw = cis_fast((kj[j] * b) & (P.M - 1u), P.M);
+          z0 = cmul(z0, tw);
+          z1 = cmul(z1, tw);
+        }
+        const int r = kj[j] & (Q - 1), rm = (Q - r) & (Q - 1);
+        if ((fr[j] & 0xffu) == (uint32_t)round) {  //      z0  + j z1
+          float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
+          if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
+          if (round) v = cadd(v, buf[fpad(r)]);
+          buf[fpad(r)] = v;
+        }
+        if ((fr[j] >> 8) == (uint32_t)round) {     // conj z0  + j conj z1
+          float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
+          if (round) v = cadd(v, buf[fpad(rm)]);
+          buf[fpad(rm)] = v;
+        }
+      }
+    };
+    for (int round = 0; round < L.fold_rounds; ++round) {
+      if constexpr (kRegs) {
+        fold_group(lt, round);
+      } else {
+        for (int i0 = lt; i0 < L.nb; i0 += U * T) fold_group(i0, round);
+      }
+      __syncthreads();
+    }
+    fft_inverse<LOGQ>(buf, tab.tab, lt, x);
+
+    // softmax: real part head g0, imaginary part head g0 + 1
+    float2 lm = x[0];
+#pragma unroll
+    for (int m = 1; m < 16; ++m) lm = make_float2(fmaxf(lm.x, x[m].x), fmaxf(lm.y, x[m].y));
+    const float2 bm = block_max(lm);
+    const float2 mn = make_float2(fmaxf(mx.x, bm.x), fmaxf(mx.y, bm.y));
+    // exp2(-inf) = 0 the first time
+    const float2 f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
+    mx = mn;
+    float2 ls = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      x[m] = make_float2(__builtin_amdgcn_exp2f(x[m].x - mn.x), has1 ? __builtin_amdgcn_exp2f(x[m].y - mn.y) : 0.f);
+      ls = cadd(ls, x[m]);
+    }
+    Z = make_float2(Z.x * f.x + ls.x, Z.y * f.y + ls.y);
+    if constexpr (!MULTI) publish_sum();  // read behind the barriers of the transform
+
+    auto fetch_bins = [&](int i0) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = i0 + j * T;
+        kj[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
+      }
+    };
+    if constexpr (!kKeep) fetch_bins(pin_index(lt));
+    fft_forward<LOGQ>(buf, tab, lt, x, [&](int pass) {  // the first bins' twiddles are fetched while the transform runs
+      if constexpr (!kKeep) {
+        if (pass == fft_np(LOGQ) - 1) load_tw();
+      }
+    });
+    auto gather = [&](int j, float2& p0, float2& p1) {
+      float2 w1, w2;
+      spectrum_pair<LOGQ>(buf, kj[j] & (Q - 1), wj[j], w1, w2);
+      p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
+      p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+      if constexpr (MULTI) {
+        const float2 twc = conjf2(cis_fast((kj[j] * b) & (P.M - 1u), P.M));
+        p0 = cmul(twc, p0);
+        p1 = cmul(twc, p1);
+      }
+    };
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int j = 0; j < NBT; ++j) {
+        float2 p0, p1;
+        gather(j, p0, p1);
+        A0[j] = make_float2(fmaf(A0[j].x, f.x, p0.x), fmaf(A0[j].y, f.x, p0.y));
+        A1[j] = make_float2(fmaf(A1[j].x, f.y, p1.x), fmaf(A1[j].y, f.y, p1.y));
+      }
+    } else {
+      if constexpr (!MULTI) normalise();
+      const int n = MULTI ? L.nb : L.Bp;
+      for (int i0 = lt; i0 < n; i0 += U * T) {
+        if (i0 >= U * T) {
+          fetch_bins(i0);
+          load_tw();
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int i = i0 + j * T;
+          if (i >= n) continue;
+          float2 p0, p1;
+          gather(j, p0, p1);
+          if constexpr (!MULTI) {
+            finish(i, kj[j], p0, p1);
+          } else {
+            if (b) {  // this thread's own running sums, scaled to the new maximum
+              const float2 a0 = o0[i];
+              p0 = make_float2(a0.x * f.x + p0.x, a0.y * f.x + p0.y);
+              if (has1) {
+                const float2 a1 = o1[i];
+                p1 = make_float2(a1.x * f.y + p1.x, a1.y * f.y + p1.y);
+              }
+            }
+            o0[i] = p0;
+            if (has1) o1[i] = p1;
+          }
+        }
+      }
+    }
+    if (MULTI) __syncthreads();
+  }
+
+  if constexpr (MULTI) {
+    publish_sum();
+    __syncthreads();
+    normalise();
+    const float2 none = make_float2(0.f, 0.f);
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int j = 0; j < NBT; ++j) {
+        const int i = j * T + t;
+        if (i < L.Bp) finish(i, kj[j], A0[j], A1[j]);
+      }
+    } else {
+      for (int i = t; i < L.Bp; i += T) {
+        const bool live = i < L.nb;
+        finish(i, live ? (uint32_t)bins[i] : 0u, live ? o0[i] : none, live && has1 ? o1[i] : none);
+      }
+    }
+  }
+  if (np > 0) {
+    if constexpr (T >= 64) {
+      // all 2 * kMaxPend sums over the wave at once: afterwards lane l holds the total of entry l / rep
+      const float tot = wave_reduce_scatter<2 * kMaxPend>(sp, t & 63);
+      constexpr int rep = 64 / (2 * kMaxPend);  // lanes that end up with the same total
+      if ((t & 63) % rep == 0) pscr[t >> 6][(t & 63) / rep] = tot;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 2 * kMaxPend; ++v) {
+        const float tot = lanes_reduce<T>(sp[v], add2);
+        if (t == 0) pscr[0][v] = tot;
+      }
+    }
+    __syncthreads();
+    for (int v = t; v < 2 * np; v += T) {
+      float sum = 0.f;
+      for (int w = 0; w < NWV; ++w) sum += pscr[w][v];
+      const int jp = v >> 1, head = v & 1;
+      if (head == 0 || has1) ps[((int64_t)slice * P.G + g0 + head) * kMaxPend + jp] = sum;
+    }
+  }
+  for (int e = t; e < E; e += T) {  // raw scores -> weights p_e / Z (same thread, same entry)
     pe0[e] = __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x) / Z.x;
     if (has1) pe1[e] = __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y) / Z.y;
   }
+}
+
+template <int LOGQ, int NBT, bool MULTI>
+__global__ __launch_bounds__(fft_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_kernel(Params P, const float2* __restrict__ qc,
+                                                                       float2* __restrict__ Pn, float* __restrict__ pe,
+                                                                       float scale, int pairs, int np, uint32_t ptsh,
+                                                                       float* __restrict__ ps) {
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
+  fft_body<LOGQ, NBT, MULTI>(P, qc, Pn, pe, scale, pairs, np, ptsh, ps, blockIdx.x, smem);
 }
 
 // ----------------------------------------------------------------------------------- A + B
@@ -1003,20 +909,21 @@ __global__ __launch_bounds__(kFftThreads, 4) void attn_fft_big_kernel(Params P, 
 // Hardware block ids go round-robin to the 8 XCDs; the role is a function of the per-XCD sequence number, so
 // every XCD sees the same even mix (nA8 / nB8 = blocks of either role per XCD, rounded up).
 // A runs in its read-only form with 512 threads (1024 bins per block).
-template <bool BF16, int GT, int LOGQ, int NBT, bool MULTI>
-__global__ __launch_bounds__(kFftThreads, (MULTI && NBT > 4) ? 2 : 4) void attn_ab_kernel(
+constexpr int kAbThreads = fft_threads(kFftMaxLogQ);
+template <bool BF16, int GT, int NBT>
+__global__ __launch_bounds__(kAbThreads, NBT > 4 ? 2 : 4) void attn_ab_kernel(
     Params P, const void* __restrict__ q, float2* __restrict__ qc, float* __restrict__ pe, int chunks, StepUpdate up,
     float2* __restrict__ Pn, float scale, int pairs, int np, float* __restrict__ ps, uint32_t baseA, uint32_t nA,
     uint32_t nA8, uint32_t baseB, uint32_t nB, uint32_t nB8) {
-  extern __shared__ float2 smem[];
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
   const uint32_t seq = blockIdx.x >> 3, xcd = blockIdx.x & 7u, tot = nA8 + nB8;
   const uint32_t cb = (uint32_t)(((uint64_t)seq * nB8) / tot), cb1 = (uint32_t)(((uint64_t)(seq + 1) * nB8) / tot);
   if (cb1 > cb) {
     const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)(cb * 8 + xcd));
-    if (id < nB) fft_body<LOGQ, NBT, MULTI>(P, qc, Pn, pe, scale, pairs, np, up.tsh, ps, baseB + id, smem);
+    if (id < nB) fft_body<kFftMaxLogQ, NBT, true>(P, qc, Pn, pe, scale, pairs, np, up.tsh, ps, baseB + id, smem);
   } else {
     const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)((seq - cb) * 8 + xcd));
-    if (id < nA) qc_body<BF16, GT, kPlain, kFftThreads>(P, q, qc, pe, chunks, 1, up, baseA + id, (float*)smem);
+    if (id < nA) qc_body<BF16, GT, kPlain, kAbThreads>(P, q, qc, pe, chunks, 1, up, baseA + id, (float*)smem);
   }
 }
 
@@ -1115,8 +1022,8 @@ constexpr uint32_t kAbMinB = 1024, kAbMaxGroups = 8;  // fewest B blocks per gro
 static int heads_per_pass(int G);
 bool attn_pipelines(const Params& P, bool use_fft) {
   const int GT = heads_per_pass(P.G);
-  const int per_thread = (P.max_Bp + kFftThreads - 1) / kFftThreads;
-  return use_fft && P.G <= GT && (GT == 4 || GT == 8) && P.M >= 16384u && per_thread > 2 && per_thread <= kFftNBT &&
+  const int per_thread = (P.max_Bp + kAbThreads - 1) / kAbThreads;
+  return use_fft && P.G <= GT && (GT == 4 || GT == 8) && P.M >= 16384u && per_thread > 2 && per_thread <= 8 &&
          (uint64_t)P.n_slices * ((P.G + 1) / 2) >= 2 * kAbMinB && !P.serial_phases;
 }
 static int heads_per_pass(int G) { return G <= 2 ? G : (G <= 4 ? 4 : 8); }  // 1, 2, 4 or 8; heads beyond G are masked
@@ -1164,13 +1071,13 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
   // measured (A + B, all slices, ms): 2048 slices x 4096 bins, M = 32768: 2.36 -> 1.9; 10240 x 1638, M = 16384:
   // 6.3 -> 5.5; no gain at M = 8192 (B is 30 us) or with 512 B blocks in all (M = 131072, 256 slices).
   const int pairsB = (P.G + 1) / 2;
-  const int per_thread_ab = (P.max_Bp + kFftThreads - 1) / kFftThreads;
+  const int per_thread_ab = (P.max_Bp + kAbThreads - 1) / kAbThreads;
   const uint64_t nB_all = (uint64_t)P.n_slices * pairsB;
   const bool pipeline_ab = mode == kPlain && attn_pipelines(P, use_fft);
   if (pipeline_ab) {
     IWDFT_MARK(0)
-    const size_t lds = sizeof(float2) * (size_t)fft_lds_float2(kFftMaxLogQ);
-    const int chunksA = (P.max_Bp + 2 * kFftThreads - 1) / (2 * kFftThreads);
+    const size_t lds = sizeof(float2) * (size_t)fft_lds(kFftMaxLogQ);
+    const int chunksA = (P.max_Bp + 2 * kAbThreads - 1) / (2 * kAbThreads);
     uint32_t groups = (uint32_t)(nB_all / kAbMinB);
     if (groups > kAbMaxGroups) groups = kAbMaxGroups;
     const uint32_t spg = ((uint32_t)P.n_slices + groups - 1) / groups;  // slices per group
@@ -1183,19 +1090,19 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
       if (nA + nB == 0) continue;
       const uint32_t nA8 = (nA + 7) / 8, nB8 = (nB + 7) / 8;
       const uint32_t grid = (nA8 + nB8) * 8;
-#define IWDFT_AB_CASE(GTV, NBT, MULTI)                                                                          \
+#define IWDFT_AB_CASE(GTV, NBT)                                                                          \
   {                                                                                                             \
     static LdsLimit lim;                                                                                        \
-    e = lim.ensure((const void*)attn_ab_kernel<BF16, GTV, kFftMaxLogQ, NBT, MULTI>, (int)lds);                  \
+    e = lim.ensure((const void*)attn_ab_kernel<BF16, GTV, NBT>, (int)lds);                  \
     if (e != hipSuccess) return e;                                                                              \
-    attn_ab_kernel<BF16, GTV, kFftMaxLogQ, NBT, MULTI><<<dim3(grid), dim3(kFftThreads), lds, st>>>(             \
+    attn_ab_kernel<BF16, GTV, NBT><<<dim3(grid), dim3(kAbThreads), lds, st>>>(             \
         P, q, qc, pe, chunksA, u, Pn, scale, pairsB, np_plain, u.ps, a0 * chunksA, nA, nA8, b0 * pairsB, nB,    \
         nB8);                                                                                                   \
   }
       if (GT == 4) {
-        if (per_thread_ab <= 4) IWDFT_AB_CASE(4, 4, true) else IWDFT_AB_CASE(4, 8, true)
+        if (per_thread_ab <= 4) IWDFT_AB_CASE(4, 4) else IWDFT_AB_CASE(4, 8)
       } else {
-        if (per_thread_ab <= 4) IWDFT_AB_CASE(8, 4, true) else IWDFT_AB_CASE(8, 8, true)
+        if (per_thread_ab <= 4) IWDFT_AB_CASE(8, 4) else IWDFT_AB_CASE(8, 8)
       }
 #undef IWDFT_AB_CASE
       e = hipGetLastError();
@@ -1217,46 +1124,30 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     while ((1u << logM) < P.M) ++logM;
     const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
     const int pairs = (P.G + 1) / 2;
-    const size_t lds = sizeof(float2) * (size_t)fft_lds_float2(logQ);
     const uint32_t gridB = (uint32_t)((uint64_t)P.n_slices * pairs);
-    const int per_thread = (P.max_Bp + kFftThreads - 1) / kFftThreads;  // <= 8 (checked at create)
-#define IWDFT_FFT_CASE(LQ, NBT, MULTI)                                                                   \
-  {                                                                                                      \
-    static LdsLimit lim;                                                                                 \
-    e = lim.ensure((const void*)attn_fft_kernel<LQ, NBT, MULTI>, (int)lds);                              \
-    if (e != hipSuccess) return e;                                                                       \
-    attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(kFftThreads), lds, st>>>(P, qc, Pn, pe, scale,   \
-                                                                                pairs, np_plain, u.tsh,  \
-                                                                                u.ps);                   \
+#define IWDFT_FFT_CASE(LQ, NBT, MULTI)                                                                    \
+  {                                                                                                       \
+    constexpr int lds = (int)sizeof(float2) * fft_lds(LQ);                                                \
+    static LdsLimit lim;                                                                                  \
+    e = lim.ensure((const void*)attn_fft_kernel<LQ, NBT, MULTI>, lds);                                    \
+    if (e != hipSuccess) return e;                                                                        \
+    attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(fft_threads(LQ)), lds, st>>>(                     \
+        P, qc, Pn, pe, scale, pairs, np_plain, u.tsh, u.ps);                                              \
   }
-#define IWDFT_FFT_NBT(LQ, MULTI)                                                                         \
-  {                                                                                                      \
-    if (per_thread <= 2) IWDFT_FFT_CASE(LQ, 2, MULTI)                                                    \
-    else if (per_thread <= 4) IWDFT_FFT_CASE(LQ, 4, MULTI)                                               \
-    else IWDFT_FFT_CASE(LQ, 8, MULTI)                                                                    \
-  }
-    if (per_thread > kFftNBT) {  // more than 4096 kept bins in some layer (so M > 4096): nothing per bin in registers
-      if (np_plain > 0) return hipErrorInvalidValue;  // no pending tokens on this path (the plan takes write_every as 1)
-#define IWDFT_FFT_BIG(MULTI)                                                                             \
-  {                                                                                                      \
-    static LdsLimit lim;                                                                                 \
-    e = lim.ensure((const void*)attn_fft_big_kernel<kFftMaxLogQ, MULTI>, (int)lds);                      \
-    if (e != hipSuccess) return e;                                                                       \
-    attn_fft_big_kernel<kFftMaxLogQ, MULTI><<<dim3(gridB), dim3(kFftThreads), lds, st>>>(P, qc, Pn, pe,  \
-                                                                                        scale, pairs);  \
-  }
-      if (logM > logQ) IWDFT_FFT_BIG(true) else IWDFT_FFT_BIG(false)
-#undef IWDFT_FFT_BIG
-    } else if (logM > logQ) IWDFT_FFT_NBT(kFftMaxLogQ, true)
-    else switch (logQ) {
-      case 8: IWDFT_FFT_CASE(8, 8, false) break;
-      case 9: IWDFT_FFT_CASE(9, 8, false) break;
-      case 10: IWDFT_FFT_CASE(10, 8, false) break;
-      case 11: IWDFT_FFT_CASE(11, 8, false) break;
-      case 12: IWDFT_FFT_CASE(12, 8, false) break;
-      default: IWDFT_FFT_NBT(13, false) break;
+    if (logM > logQ) {
+      const int per_thread = (P.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
+      if (per_thread <= 2) IWDFT_FFT_CASE(kFftMaxLogQ, 2, true)
+      else if (per_thread <= 4) IWDFT_FFT_CASE(kFftMaxLogQ, 4, true)
+      else if (per_thread <= 8) IWDFT_FFT_CASE(kFftMaxLogQ, 8, true)
+      else IWDFT_FFT_CASE(kFftMaxLogQ, 0, true)
+    } else switch (logQ) {
+      case 8: IWDFT_FFT_CASE(8, 0, false) break;
+      case 9: IWDFT_FFT_CASE(9, 0, false) break;
+      case 10: IWDFT_FFT_CASE(10, 0, false) break;
+      case 11: IWDFT_FFT_CASE(11, 0, false) break;
+      case 12: IWDFT_FFT_CASE(12, 0, false) break;
+      default: IWDFT_FFT_CASE(13, 0, false) break;
     }
-#undef IWDFT_FFT_NBT
 #undef IWDFT_FFT_CASE
   } else if (P.chirp) {
     e = launch_attn_chirp(P, qc, Pn, pe, scale, np_plain, u.tsh, u.ps, st);
