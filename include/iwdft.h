@@ -73,13 +73,16 @@ enum {
                                        bf16 inputs below 2^-14 in magnitude lose bits
                                        (below 2^-24 they count as 0), fp32 inputs keep
                                        ~21 bits down to 2^-14 and an absolute 2^-25
-                                       below.  The FFT prefill has no such limits.   */
+                                       below.  The FFT and chirp-z prefills have no such
+                                       limits.                                       */
   IWDFT_FLAG_FFT_PREFILL = 4u,      /* iwdft_prefill always runs FFTs + pruning; needs
                                        M = 2^m >= 256, else IWDFT_ERR_UNSUPPORTED (layers
                                        with more than 4096 kept bins take a form that
                                        keeps nothing per bin in registers).  With neither flag
                                        the library picks: FFT when it applies and some
-                                       layer keeps >= 128 bins or >= M / 32        */
+                                       layer keeps >= 128 bins or >= M / 32; other M: chirp-z
+                                       transforms where the attention has them (see
+                                       iwdft_attn_kind) and they are faster        */
   IWDFT_FLAG_SHORTCUT = 8u,         /* the variant of the update that Sec. 4.1 mentions for long
                                        contexts, the factor (N-1)/N of Eq. infi-dft taken as 1:
                                        S_{T+1}[k] = W_k ( S_T[k] + x_T / (T+1) ).  Tokens no longer
@@ -134,15 +137,15 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
 int iwdft_destroy(iwdft_ctx* ctx); /* frees host memory only; NULL is accepted */
 
 /* Prefill transform (Eq. dft-full at the kept bins, Eq. prefill-dft, Eq. freq-zero), either as a
- * dense contraction with an on-chip basis or as FFTs followed by pruning (see desc.flags).
+ * dense contraction with an on-chip basis or as transforms followed by pruning (see desc.flags).
  * d_K, d_V: [n_layers][batch][n_kv_heads][S + M + R][head_dim] contiguous, kv_dtype.
  * Per slice the first S tokens are copied to the sink store, the last R to the recent
  * window, and the middle M tokens are transformed (Sec. 4.2.1).  Overwrites the state;
  * T becomes M. */
 int iwdft_prefill(iwdft_ctx* ctx, const void* d_K, const void* d_V, void* hip_stream);
 
-/* Which transform iwdft_prefill runs for this context: 0 = dense contraction, 1 = FFTs + pruning;
- * -1 if ctx is NULL. */
+/* Which transform iwdft_prefill runs for this context: 0 = dense contraction or, for M that is
+ * not a power of two, chirp-z transforms + pruning; 1 = FFTs + pruning; -1 if ctx is NULL. */
 int iwdft_prefill_kind(const iwdft_ctx* ctx);
 
 /* Which synthesis compressed_decode_attn / iwdft_append_attn run for this context: 1 = scores and softmax

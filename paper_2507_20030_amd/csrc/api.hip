@@ -48,6 +48,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int64_t ws_total = 0;    // float2 per workspace array
   int32_t G = 1, max_nb = 0, max_Bp = 0;
   bool use_fft = false;          // decode attention through power-of-two FFTs
+  bool use_chirp_prefill = false;  // prefill through chirp-z transforms
   bool use_chirp = false;        // ... through chirp-z transforms (any M up to kChirpMaxM when use_fft is false)
   int chirp_logN = 0;            // length of its circular convolutions
   int chirp_logS = 0;            // length of the table in the state buffer (kept for copies of it; nothing reads it)
@@ -71,6 +72,7 @@ constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit 
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
+constexpr int64_t kChirpPrefillPoints = 80;  // points of convolution that take as long as one token of the contraction
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
@@ -201,6 +203,20 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
       }
       L.fold_rounds = rounds;
     }
+  }
+
+  // Prefill through chirp-z transforms where they are faster than the dense contraction.  Measured: the transforms take one
+  // slice's 128 pairs of channels at 1900 points of convolution per us, and 1.5 points per kept bin where blocks are summed
+  // in the output rows; the contraction walks the M tokens at 23 per us with 256 workgroups (slices x tiles of 128 bins) at
+  // a time, whether or not the last round is full.  S slices, dense / chirp in us: S = 8, M = 8132, 512 bins 361 / 75; S = 64:
+  // 482 / 573, with 640 bins 818 / 578; S = 256, 2033 bins 7400 / 2300; S = 64, M = 1988, 256 bins 111 / 111, 640 bins
+  // 224 / 113; S = 64, M = 9000, 640 bins 898 / 965; S = 32, M = 32708, 4096 bins 7300 / 1500.
+  // Longer M with blocks of a few points only stay with the contraction.
+  if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
+    const int64_t S = slices_per_layer * d->n_layers, Pb = d->M / pl->chirp_Q;
+    const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
+    const int64_t rounds = (S * ((pl->max_nb + 127) / 128) + 255) / 256;
+    pl->use_chirp_prefill = S * points <= kChirpPrefillPoints * d->M * rounds;
   }
 
   // What is left takes the direct O(M |B|) sums: fine for short or sparse states, useless beyond -- refuse instead of
@@ -624,7 +640,9 @@ int iwdft_prefill(iwdft_ctx* ctx, const void* d_K, const void* d_V, void* hip_st
   }
   ctx->pend = 0;  // the prefill overwrites the whole state
   rc = launched(ctx->plan.use_fft_prefill ? launch_prefill_fft(ctx->P, d_K, d_V, (hipStream_t)hip_stream)
-                                          : launch_prefill(ctx->P, d_K, d_V, (hipStream_t)hip_stream),
+                : ctx->plan.use_chirp_prefill
+                    ? launch_prefill_chirp(ctx->P, d_K, d_V, (hipStream_t)hip_stream)
+                    : launch_prefill(ctx->P, d_K, d_V, (hipStream_t)hip_stream),
                 "prefill launch");
   if (rc != IWDFT_OK) return rc;
   ctx->T = ctx->desc.M;

@@ -163,6 +163,8 @@ hipError_t launch_prefill(const Params& P, const void* K, const void* V, hipStre
 // keeps more than 4096 bins.  launch_prefill_edges copies the sink / recent tokens (both prefills).
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
+// ... and through chirp-z transforms (Params::chirp set).
+hipError_t launch_prefill_chirp(const Params& P, const void* K, const void* V, hipStream_t st);
 hipError_t launch_prefill_edges(const Params& P, const void* K, const void* V, hipStream_t st);
 // ring_pos: slot of the recent ring that holds the oldest token (ignored when R == 0).
 hipError_t launch_append(const Params& P, const void* tok_k, const void* tok_v, uint32_t t_shift,

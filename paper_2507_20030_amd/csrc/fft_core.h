@@ -16,6 +16,17 @@ __host__ __device__ constexpr int fft_threads(int logQ) { return 1 << (logQ - 4)
 __device__ __forceinline__ int fpad(int i) { return i + ((i >> 4) << 1); }
 __host__ __device__ constexpr int fft_lds(int logQ) { return (1 << logQ) + (1 << logQ) / 8; }
 
+// Transforms of 2^logQ points that a workgroup of 512 threads runs side by side, interleaved over the lanes (thread = t NS + g
+// for thread t of transform g), and the distance of their buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses
+// fall into distinct banks.
+__host__ __device__ constexpr int side_ns(int logQ) { return 1 << (13 - logQ); }
+__host__ __device__ constexpr int side_bs(int logQ) {
+  return fft_lds(logQ) + (side_ns(logQ) == 1 ? 0 : side_ns(logQ) >= 8 ? 2 : 16 / side_ns(logQ));
+}
+// Time index of position 16 t + m relative to that of position 16 t: the digits of m reversed, times Q / 16.
+template <int LOGQ>
+__device__ __forceinline__ constexpr int sample_step(int m) { return (((m & 3) << 2) | (m >> 2)) << (LOGQ - 4); }
+
 // Base-4 digit reversal of an even number of bits.
 template <int BITS>
 __device__ __forceinline__ uint32_t digit_reverse4(uint32_t i) {

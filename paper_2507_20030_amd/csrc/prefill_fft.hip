@@ -14,46 +14,11 @@
 // in that XCD's L2: HBM delivers every row once.
 #include "common.h"
 #include "fft_core.h"
+#include "pair_io.h"
 
 namespace iwdft {
 
 constexpr int kPairs = kHeadDim / 2;  // channel pairs per (slice, tensor)
-
-// One token sample of NP adjacent channel pairs as NW 32-bit words (NW = NP for bf16, 2 NP for fp32), fetched
-// with one load of 4 NW bytes.
-template <int NW>
-struct Raw {
-  uint32_t w[NW];
-};
-template <int NW>
-__device__ __forceinline__ Raw<NW> load_raw(const char* p) {
-  Raw<NW> r;
-  if constexpr (NW == 1) {
-    r.w[0] = *(const uint32_t*)p;
-  } else if constexpr (NW == 2) {
-    const uint2 u = *(const uint2*)p;
-    r.w[0] = u.x, r.w[1] = u.y;
-  } else {
-    static_assert(NW == 4, "1, 2 or 4 words per sample");
-    const uint4 u = *(const uint4*)p;
-    r.w[0] = u.x, r.w[1] = u.y, r.w[2] = u.z, r.w[3] = u.w;
-  }
-  return r;
-}
-// The first channel pair of a sample as a complex number (first channel real, second imaginary), and the
-// sample with that pair dropped and the next one moved to the front: the pairs are taken in turn inside a
-// run-time loop while the words stay in registers (no run-time index).
-template <bool BF16, int NW>
-__device__ __forceinline__ float2 raw_front(const Raw<NW>& r) {
-  if constexpr (BF16) return make_float2(__uint_as_float(r.w[0] << 16), __uint_as_float(r.w[0] & 0xffff0000u));
-  else return make_float2(__uint_as_float(r.w[0]), __uint_as_float(r.w[1]));
-}
-template <bool BF16, int NW>
-__device__ __forceinline__ void raw_pop(Raw<NW>& r) {
-  constexpr int W = BF16 ? 1 : 2;
-#pragma unroll
-  for (int n = 0; n + W < NW; ++n) r.w[n] = r.w[n + W];
-}
 
 // hardware block id -> (xcd = id & 7, idx = id >> 3); XCD x owns the (slice, tensor) pairs
 // x * per_xcd .. (x + 1) * per_xcd - 1, 64 / (NS NP) consecutive idx each.
@@ -66,16 +31,11 @@ __device__ __forceinline__ void raw_pop(Raw<NW>& r) {
 // bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
 // MULTI (M > 8192): the running sums over the residues live in the output rows (every bin belongs to one thread, which
 // reads back its own earlier store).
-__host__ __device__ constexpr int prefill_ns(int logQ) { return 1 << (13 - logQ); }
-// Distance of two transforms' buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses fall into distinct banks.
-__host__ __device__ constexpr int prefill_bs(int logQ) {
-  return fft_lds(logQ) + (prefill_ns(logQ) == 1 ? 0 : prefill_ns(logQ) >= 8 ? 2 : 16 / prefill_ns(logQ));
-}
 template <int LOGQ, bool BF16, bool MULTI, int NP>
 __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
                                                             const void* __restrict__ V, int per_xcd, int n_st) {
   extern __shared__ float2 smem[];
-  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = prefill_ns(LOGQ), BS = prefill_bs(LOGQ);
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
   static_assert(T * NS == 512 && NS * NP <= kPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;  // bytes per token row
@@ -361,11 +321,11 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
   // Pairs per thread: as many as the register budget (128) holds next to the transform (the staged samples take 16
   // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.
-  const bool few = (uint64_t)n_st * (kPairs / 4 / prefill_ns(logQ)) < kFewWorkgroups;
+  const bool few = (uint64_t)n_st * (kPairs / 4 / side_ns(logQ)) < kFewWorkgroups;
 #define IWDFT_PF_CASE(LQ, MULTI, NP)                                                                        \
   {                                                                                                         \
-    const size_t lds = sizeof(float2) * (size_t)(prefill_ns(LQ) * prefill_bs(LQ));                          \
-    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * prefill_ns(LQ))) * 8;                     \
+    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                          \
+    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LQ))) * 8;                     \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                        \
     static LdsLimit lim;                                                                                    \
     e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NP>, (int)lds);                         \

@@ -922,3 +922,49 @@ def test_misaligned_tensors_are_refused_before_any_launch():
         torch.cuda.synchronize()
         assert bool(torch.isfinite(out.float()).all())
         c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,S,R,n_bins,n_layers", [
+    (257, 0, 0, 257, 2),      # prime, every bin kept: convolutions of 1024 points
+    (1000, 3, 5, 333, 2),     # 2048
+    (1001, 0, 0, 1001, 4),    # ... enough slices for several channel pairs per load
+    (2047, 0, 0, 700, 2),     # 4096, one point short of the limit
+    (2047, 2, 2, 1100, 3),
+    (4095, 0, 3, 1500, 2),    # 8192
+    (4095, 0, 0, 1500, 3),
+    (8191, 0, 0, 2100, 3),    # 16384
+    (8191, 1, 0, 900, 1),
+    (16324, 10, 50, 1500, 1),  # two blocks of 8162 points, the paper's windows
+    (12003, 0, 0, 1500, 3),    # three blocks of 4001 points
+])
+def test_chirp_prefill_all_convolution_lengths(dtype, L, S, R, n_bins, n_layers):
+    cfg = small_cfg(L=L, dtype=dtype, n_bins=n_bins, n_sink=S, n_recent=R, steps=1, n_layers=n_layers,
+                    batch=2 if n_layers > 1 else 1, n_kv_heads=8 if n_layers > 2 else 2)
+    st = run_stream(cfg, random_bins(cfg, 53), rec=(3, 20), tag=f"chirppf-{dtype}-L{L}")
+    assert st["coef0"] < 2e-5
+
+
+def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one():
+    # neighbouring channels share a transform; every channel has to be as accurate as alone (fp32 rounding, 2^-24, times
+    # ~log2 of the 16384 points of each of two transforms and the tables: below 1e-5)
+    cfg = small_cfg(L=8132, n_bins=2033, dtype="f32", n_layers=1, batch=1, n_kv_heads=1)
+    bins = [np.arange(cfg.n_bins, dtype=np.int32)]
+    K, V = wl.prefill_tensors(cfg, DEV)
+    K[..., 0::4] *= 2.0 ** 20
+    K[..., 3::4] *= 2.0 ** -20
+    V[..., 1] = 0.0
+    V[..., 100, 6] = float("inf")
+    c = make_cache(cfg, bins)
+    c.prefill(K, V)
+    for name, X, got in zip("KV", (K, V), c.export_coeffs(0)):
+        X = X.nan_to_num(0.0, 0.0, 0.0)
+        ref = orc.prefill(f64(X[0, 0, 0]), bins[0])
+        got = c128(got[0, 0]).reshape(ref.shape)
+        for ch in range(128):
+            g, r = np.take(got, ch, axis=ref.shape.index(128)), np.take(ref, ch, axis=ref.shape.index(128))
+            if name == "V" and ch == 6:  # its transform partner, channel 7, is as it would be without it
+                assert not np.isfinite(g).any()
+            else:
+                assert np.linalg.norm(g - r) <= 1e-5 * np.linalg.norm(r), ch
+    c.close()
