@@ -4,19 +4,16 @@
 // forward transform) and the FFT prefill (forward transform).
 #pragma once
 #include "common.h"
+#include "fft_core.h"
 
 namespace iwdft {
 
 constexpr int kFftThreads = 512;
 constexpr int kFftNBT = 8;   // most kept bins per thread                (|B| <= 4096)
 constexpr int kFftEPT = 16;  // time samples per thread                  (Q   <= 8192)
-constexpr int kFftMaxLogQ = 13;
 
 __device__ __forceinline__ float2 mul_i(float2 a) { return make_float2(-a.y, a.x); }    // * (+j)
 __device__ __forceinline__ float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }   // * (-j)
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
 
 // exp(+j 2 pi p / M) through the hardware sine / cosine (argument in revolutions, exact for the
 // power-of-two M this path requires; ~1e-6 absolute error, used only for the block twiddles of the

@@ -114,3 +114,32 @@ def test_ablate_chunk_matches_the_oracle(dtype, M, C, chunks):
             pieces = -(-(M // 2 + 1) // 4096) if M > 8192 else 1
             bar = 1e-3 if (dtype == torch.float32 or pieces == 1) else pieces * 2.0 ** -8
             assert float(out.float().abs().max()) < bar * float(x.float().abs().max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
+def test_ablate_chunk_several_channel_pairs_per_load(dtype, M):
+    """Enough slices (one more than a multiple of 8) for the form that fetches several channel pairs at once, all transform
+    lengths: against the oracle, and bit for bit against the one-pair form that a tensor 8 bytes off alignment takes."""
+    n = 16 * (8192 // M) + 1
+    C = 5
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn((n, M, 128), generator=g, device="cuda").to(dtype)
+    flat = torch.empty(x.numel() + 16, dtype=dtype, device="cuda")
+    off = 8 // x.element_size()
+    y = flat[off:off + x.numel()].view(x.shape)
+    y.copy_(x)
+    out, out_y = torch.empty_like(x), torch.empty_like(x)
+    for c in (0, 2, 4):
+        out.fill_(float("nan"))
+        out_y.fill_(float("nan"))
+        B.iwdft_ablate_chunk(x, out, C, c)
+        B.iwdft_ablate_chunk(y, out_y, C, c)
+        torch.cuda.synchronize()
+        assert torch.equal(out, out_y)
+        for s in (0, n // 2, n - 1):
+            ref = orc.ablate_chunk(x[s].cpu().to(torch.float64).numpy(), C, c)
+            err = np.linalg.norm(out[s].cpu().to(torch.float64).numpy() - ref) / np.linalg.norm(ref)
+            # fp32: 2^-24 times ~log2 M roundings of two transforms; bf16: output rounding, at most 2^-9 per element
+            assert err < (3e-6 if dtype == torch.float32 else 2.0 ** -9), (M, c, s, err)
