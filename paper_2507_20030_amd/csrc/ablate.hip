@@ -193,15 +193,13 @@ __global__ __launch_bounds__(kFftThreads, 2) void ablate_long_kernel(const char*
   }
 }
 
-constexpr uint64_t kFewWorkgroups = 256;
-
 template <bool BF16>
 static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int logQ, int lo, int hi, hipStream_t st) {
   const int per_xcd = (n_slices + 7) / 8;
-  // several pairs per load need 16-byte aligned tensors; not where the device would not be full: the pairs spread over more
+  // several pairs per load need 16-byte aligned tensors; not where the device would not be full (pair_io.h): the pairs spread over more
   // workgroups then
   const bool wide = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0 &&
-                    (uint64_t)n_slices * (kAbPairs / 4) >= kFewWorkgroups * (uint64_t)side_ns(logQ);
+                    (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
   const float2* tab = nullptr;
   hipError_t e = fft_table(&tab);
   if (e != hipSuccess) return e;
@@ -218,7 +216,7 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
   }
 #define IWDFT_AB_CASE(LQ)                                                             \
   {                                                                                   \
-    constexpr int kNp = (LQ == 8 || !BF16) ? 2 : 4;                                   \
+    constexpr int kNp = side_pairs(LQ, BF16);                                   \
     if (wide) IWDFT_AB_LAUNCH(LQ, kNp) else IWDFT_AB_LAUNCH(LQ, 1)                    \
   }
   switch (logQ) {

@@ -51,9 +51,6 @@ struct Params {
   const float4* chirpW;
   int32_t chirp_logN;
   uint32_t chirp_Q;
-  // Twiddle octant of the in-LDS power-of-two transforms: tw8[m] = exp(+j 2 pi m / Q), m = 0 .. Q/8, with
-  // Q = min(M, 8192); made on the host in double precision (null unless M = 2^m >= 256).
-  const float2* tw8;
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
   float2* FK;
   float2* FV;

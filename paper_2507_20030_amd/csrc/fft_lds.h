@@ -1,7 +1,6 @@
-// In-LDS complex FFT of 2^LOGQ points (256 .. 8192) for one workgroup of 512 threads: radix-16
-// register passes (two radix-4 stages per LDS round trip), twiddles from an octant table in LDS,
-// data padded by one element per 32.  Shared by the decode-attention softmax kernel (inverse, then
-// forward transform) and the FFT prefill (forward transform).
+// In-LDS complex FFT of 2^LOGQ points for one workgroup of 512 threads: radix-16 register passes (two radix-4 stages per LDS
+// round trip), twiddles from an octant table in LDS, data padded by one element per 32.  Used by the ablation of contexts
+// longer than 8192 tokens only; everything else runs on fft_core.h.
 #pragma once
 #include "common.h"
 #include "fft_core.h"
@@ -9,19 +8,10 @@
 namespace iwdft {
 
 constexpr int kFftThreads = 512;
-constexpr int kFftNBT = 8;   // most kept bins per thread                (|B| <= 4096)
-constexpr int kFftEPT = 16;  // time samples per thread                  (Q   <= 8192)
+constexpr int kFftNBT = 8;   // bins per thread and piece
 
 __device__ __forceinline__ float2 mul_i(float2 a) { return make_float2(-a.y, a.x); }    // * (+j)
 __device__ __forceinline__ float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }   // * (-j)
-
-// exp(+j 2 pi p / M) through the hardware sine / cosine (argument in revolutions, exact for the
-// power-of-two M this path requires; ~1e-6 absolute error, used only for the block twiddles of the
-// score synthesis where 1e-6 of a score is far below the output tolerance).
-__device__ __forceinline__ float2 cis_fast(uint32_t p, uint32_t M) {
-  const float f = (float)p * rcp_pow2(M);
-  return make_float2(__builtin_amdgcn_cosf(f), __builtin_amdgcn_sinf(f));
-}
 
 // LDS index of logical sample i: one float2 of padding after every 32 keeps the strided
 // accesses of the late passes spread over all banks.

@@ -40,6 +40,14 @@ __device__ __forceinline__ void raw_pop(Raw<NW>& r) {
   for (int n = 0; n + W < NW; ++n) r.w[n] = r.w[n + W];
 }
 
+// Channel pairs per load and store of the kernels that run 8192 / 2^logQ transforms side by side and write samples back
+// (ablation, reconstruction), and the workgroups (of four pairs) from which on more than one is faster.  Measured, several
+// pairs / one, us: ablation of 64 x 8192 tokens bf16 173 / 294, fp32 253 / 404, 16 x 8192 tokens 55 / 83, 61 / 86; where the
+// lanes of one pair already cover 32 bytes of a row (bf16) the longer serial chain costs more: 512 x 1024 tokens 95 / 85;
+// fp32 there 512 x 1024 134 / 147, 256 x 1024 61 / 56.
+constexpr int side_pairs(int logQ, bool bf16) { return bf16 ? (logQ >= 11 ? 4 : 1) : (logQ >= 10 ? 2 : 1); }
+constexpr uint64_t side_pairs_min(int logQ) { return logQ == 10 ? 768 : 256; }
+
 // f32_to_bf16 of both (the hardware conversion rounds to nearest even and keeps NaN, bit for bit the same).
 __device__ __forceinline__ uint32_t pack_bf16(float2 v) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -8,12 +8,14 @@
 // Two kernels: the tiled direct contraction (any M, any slot range) and, for power-of-two M and long
 // ranges, in-LDS inverse FFTs (reconstruct_fft_kernel below).
 #include "common.h"
-#include "fft_lds.h"
+#include "fft_core.h"
+#include "pair_io.h"
 
 namespace iwdft {
 
 constexpr int kRecSlots = 64;  // slots per block
 constexpr int kRecBins = 32;   // bins per LDS tile
+constexpr int kRecPairs = kHeadDim / 2;
 
 // grid: ((s * atiles) + atile) * 2 + tensor ; 256 threads, each 4 channels x 8 slots.
 template <bool BF16>
@@ -88,111 +90,115 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(Params P, int layer, u
   }
 }
 
-// All M slots of two adjacent channels of one slice per workgroup: the kept coefficients (times w_k / (2M))
+// All M slots of two adjacent channels of one slice at a time: the kept coefficients (times w_k / (2M))
 // go to bin k and, conjugated, to bin M - k of an LDS spectrum -- channel c0 as it is, channel c1 times j,
 // so that after the inverse transform the real part is channel c0 and the imaginary part channel c1 --
 // folded modulo Q = min(M, 8192) with the collision rounds the attention kernel uses (Params::fold).
 // M > Q: block b of the token axis, slots Pb a + b, comes from the spectrum with bin k turned by
 // e^{j 2 pi k b / M}.  Rows go out rotated by the slot shift (T - M) mod M; slots outside [a0, a0 + n_slots)
-// are skipped.  Block ids are dealt so that the 64 workgroups of a (slice, tensor) share one XCD's L2 and
-// their 4-byte pieces of each 256-byte output row merge there.
-template <int LOGQ, bool BF16, bool MULTI>
-__global__ __launch_bounds__(kFftThreads, 4) void reconstruct_fft_kernel(Params P, int layer, uint32_t a0,
-                                                                        uint32_t n_slots, void* __restrict__ Kt,
-                                                                        void* __restrict__ Vt, uint32_t tsh,
-                                                                        int per_xcd, int n_st) {
-  extern __shared__ float2 smem[];
-  constexpr int Q = 1 << LOGQ;
+// are skipped.  Block ids are dealt so that the workgroups of a (slice, tensor) share one XCD's L2.
+// A workgroup runs NS = 8192 / Q transforms side by side, interleaved over the lanes, on NP channel pairs one after the other
+// (as the FFT prefill does), so that a lane stores 16 bytes and NS lanes 16 NS adjacent bytes of an output row at a time: with
+// one pair per workgroup every 128-byte line was written in 32 pieces.  K and V of 64 slices, 8192 slots, 2048 bins, bf16:
+// 408 -> 232 us (0.54 GB, 2.3 TB/s); what is left is vector arithmetic, the coefficients are read once per pair.
+template <int LOGQ, bool BF16, bool MULTI, int NP>
+__global__ __launch_bounds__(512, 4) void reconstruct_fft_kernel(Params P, int layer, uint32_t a0, uint32_t n_slots,
+                                                                void* __restrict__ Kt, void* __restrict__ Vt,
+                                                                uint32_t tsh, int per_xcd, int n_st) {
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
+  static_assert(T * NS == 512 && NS * NP <= kRecPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;
-  constexpr int kPairs = kHeadDim / 2;
-  float2* buf = smem;
-  float2* tab = smem + Q + (Q >> 5);
+  constexpr int NW = NP * (BF16 ? 1 : 2);
+  constexpr int kGroups = kRecPairs / (NP * NS);  // workgroups per (slice, tensor)
+  const float2* tab = P.tab + tab_base(LOGQ);
   const int tid = threadIdx.x;
   const uint32_t idx = blockIdx.x >> 3;
-  const uint32_t stn = (blockIdx.x & 7u) * (uint32_t)per_xcd + idx / kPairs;
+  const uint32_t stn = (blockIdx.x & 7u) * (uint32_t)per_xcd + idx / kGroups;
   if (stn >= (uint32_t)n_st) return;
-  const int pair = idx % kPairs;
+  const int pair0 = (idx % kGroups) * (NS * NP);
   const int tensor = stn & 1;
   const int s = stn >> 1;  // slice within the layer
   char* out = (char*)(tensor ? Vt : Kt);
   if (!out) return;
-  const LayerInfo L = P.layers[layer];
-  const float2* F0 = (tensor ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + pair * 2) * L.Bp;
-  const float2* F1 = F0 + L.Bp;
+  const LayerInfo L = layer_info(P, layer);
   const int32_t* bins = P.bins + L.bin_off;
   const float* wts = P.weights + L.bin_off;
   const uint16_t* fold = P.fold + L.bin_off;
   const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
   const float gain = 0.5f * P.gain / (float)P.M;
-  char* orow = out + (int64_t)s * n_slots * kRow + pair * 2 * kElem;
+  const int t = tid / NS;  // thread of transform tid % NS
+  float2* buf = smem + (tid % NS) * BS;
+  char* orow = out + (int64_t)s * n_slots * kRow + (pair0 + (tid % NS) * NP) * 2 * kElem;
+  // the coefficients go through the transforms one after the other: consecutive threads, consecutive bins
+  const int tp = tid % T;
+  float2* spec = smem + (tid / T) * BS;
+  const float2* F = (tensor ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + (pair0 + (tid / T) * NP) * 2) * L.Bp;
 
-  for (int m = tid; m <= (Q >> 3); m += kFftThreads) tab[m] = P.tw8[m];  // exp(+j 2 pi m / Q), host-made
-
+#pragma unroll 1
   for (uint32_t b = 0; b < Pb; ++b) {
-    int lt = tid;
-    if (MULTI) asm volatile("" : "+v"(lt));  // keeps the passes' address arithmetic out of long-lived registers
-    for (int e = tid; e < Q + (Q >> 5); e += kFftThreads) buf[e] = make_float2(0.f, 0.f);
-    __syncthreads();
-    for (int round = 0; round < L.fold_rounds; ++round) {
-#pragma unroll
-      for (int j = 0; j < kFftNBT; ++j) {
-        const int i = j * kFftThreads + tid;
-        if (i < L.nb) {
-          const uint32_t k = (uint32_t)bins[i];
-          const uint32_t fr = fold[i];
-          const float w = wts[i] * gain;
-          float2 tw = make_float2(1.f, 0.f);
-          if (MULTI) tw = cis_poly2((k * b) & (P.M - 1u), P.M);
-          const float2 f0 = F0[i], f1 = F1[i];
-          const float2 z0 = cmul(make_float2(f0.x * w, f0.y * w), tw);
-          const float2 z1 = cmul(make_float2(f1.x * w, f1.y * w), tw);
-          const int r = k & (Q - 1), rm = (Q - r) & (Q - 1);
-          if ((fr & 0xffu) == (uint32_t)round) {  //      z0  + j z1
-            float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
-            if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
-            if (round) v = cadd(v, buf[pad(r)]);
-            buf[pad(r)] = v;
-          }
-          if ((fr >> 8) == (uint32_t)round) {     // conj z0  + j conj z1
-            float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
-            if (round) v = cadd(v, buf[pad(rm)]);
-            buf[pad(rm)] = v;
-          }
-        }
-      }
+    Raw<NW> z[16] = {};
+#pragma unroll 1
+    for (int p = 0; p < NP; ++p) {
+      float2 x[16] = {};
+      write16(buf, t, x);  // this thread read these positions last
       __syncthreads();
-    }
-    ifft_dif<LOGQ>(buf, tab, lt);
-    constexpr int H = (LOGQ & 1) ? Q / 2 : Q;
-    constexpr int IT = (H + kFftThreads - 1) / kFftThreads;
+      const float2 *F0 = F + (int64_t)(2 * p) * L.Bp, *F1 = F0 + L.Bp;
+      for (int round = 0; round < L.fold_rounds; ++round) {
+        constexpr int U = 4;  // bins whose loads are in flight together
+        for (int i0 = tp; i0 < L.nb; i0 += U * T) {
+          uint32_t k[U], fr[U];
+          float w[U];
+          float2 f0[U], f1[U];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int a = it * kFftThreads + tid;
-      if (H % kFftThreads == 0 || a < H) {
-        const int p = digit_pos<LOGQ>(a);
-        float2 y0 = buf[pad(p)], y1 = y0;
-        if (LOGQ & 1) {
-          const float2 c = buf[pad(p + 1)];
-          y1 = csub(y0, c);
-          y0 = cadd(y0, c);
-        }
+          for (int j = 0; j < U; ++j) {
+            const int i = i0 + j * T < L.nb ? i0 + j * T : L.nb - 1;
+            k[j] = (uint32_t)bins[i], fr[j] = fold[i], w[j] = wts[i], f0[j] = F0[i], f1[j] = F1[i];
+          }
 #pragma unroll
-        for (int h = 0; h < ((LOGQ & 1) ? 2 : 1); ++h) {
-          const uint32_t ap = (uint32_t)(a + h * H) * Pb + b;      // index of the un-shifted transform
-          const uint32_t slot = (ap + tsh) & (P.M - 1u);          // where it sits after T - M appends
-          const uint32_t rel = slot - a0;                          // wraps for slot < a0
-          if (rel < n_slots) store_pair<BF16>(orow + (int64_t)rel * kRow, h ? y1 : y0);
+          for (int j = 0; j < U; ++j) {
+            if (i0 + j * T >= L.nb) continue;
+            const float wg = w[j] * gain;
+            float2 z0 = make_float2(f0[j].x * wg, f0[j].y * wg), z1 = make_float2(f1[j].x * wg, f1[j].y * wg);
+            if constexpr (MULTI) {
+              const float2 tw = cis_poly2((k[j] * b) & (P.M - 1u), P.M);
+              z0 = cmul(z0, tw);
+              z1 = cmul(z1, tw);
+            }
+            const int r = k[j] & (Q - 1), rm = (Q - r) & (Q - 1);
+            if ((fr[j] & 0xffu) == (uint32_t)round) {  //      z0  + j z1
+              float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
+              if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
+              if (round) v = cadd(v, spec[fpad(r)]);
+              spec[fpad(r)] = v;
+            }
+            if ((fr[j] >> 8) == (uint32_t)round) {     // conj z0  + j conj z1
+              float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
+              if (round) v = cadd(v, spec[fpad(rm)]);
+              spec[fpad(rm)] = v;
+            }
+          }
         }
+        __syncthreads();
       }
+      fft_inverse<LOGQ>(buf, tab, t, x);
+#pragma unroll
+      for (int m = 0; m < 16; ++m) raw_push<BF16, NW>(z[m], x[m]);
     }
-    if (MULTI) __syncthreads();
+    const uint32_t first = sample_at<LOGQ>(16 * t);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const uint32_t ap = (first + sample_step<LOGQ>(m)) * Pb + b;  // index of the un-shifted transform
+      const uint32_t slot = (ap + tsh) & (P.M - 1u);                // where it sits after T - M appends
+      const uint32_t rel = slot - a0;                                // wraps for slot < a0
+      if (rel < n_slots) store_raw<NW>(orow + (int64_t)rel * kRow, z[m]);
+    }
   }
 }
 
-bool reconstruct_fft_ok(const Params& P) {
-  return P.Mmask != 0 && P.M >= 256 && P.max_nb <= kFftNBT * kFftThreads;
-}
+constexpr int kRecMaxBins = 4096;
+bool reconstruct_fft_ok(const Params& P) { return P.Mmask != 0 && P.M >= 256 && P.max_nb <= kRecMaxBins; }
 
 template <bool BF16>
 static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t a0, uint32_t n_slots, void* Kt,
@@ -202,17 +208,26 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
   const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
   const int n_st = P.batch * P.n_kv * 2;
   const int per_xcd = (n_st + 7) / 8;
-  const uint64_t blocks = (uint64_t)per_xcd * (kHeadDim / 2) * 8;
-  if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-  const size_t lds = sizeof(float2) * (size_t)fft_lds_float2(logQ);
+  // several pairs per store need 16-byte aligned outputs (a null one is skipped); not where the device would not be full (pair_io.h):
+  // the pairs spread over more workgroups then
+  const bool wide = (((uintptr_t)Kt | (uintptr_t)Vt) & 15u) == 0 &&
+                    (uint64_t)n_st * (kRecPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
   hipError_t e = hipSuccess;
-#define IWDFT_RC_CASE(LQ, MULTI)                                                                        \
+#define IWDFT_RC_LAUNCH(LQ, MULTI, NP)                                                                  \
   {                                                                                                     \
+    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                            \
+    const uint64_t blocks = (uint64_t)per_xcd * (kRecPairs / ((NP) * side_ns(LQ))) * 8;                 \
+    if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                    \
     static LdsLimit lim;                                                                                \
-    e = lim.ensure((const void*)reconstruct_fft_kernel<LQ, BF16, MULTI>, (int)lds);                     \
+    e = lim.ensure((const void*)reconstruct_fft_kernel<LQ, BF16, MULTI, NP>, (int)lds);                 \
     if (e != hipSuccess) return e;                                                                      \
-    reconstruct_fft_kernel<LQ, BF16, MULTI><<<dim3((uint32_t)blocks), dim3(kFftThreads), lds, st>>>(    \
+    reconstruct_fft_kernel<LQ, BF16, MULTI, NP><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(        \
         P, layer, a0, n_slots, Kt, Vt, tsh, per_xcd, n_st);                                             \
+  }
+#define IWDFT_RC_CASE(LQ, MULTI)                                                      \
+  {                                                                                   \
+    constexpr int kNp = side_pairs(LQ, BF16);                                   \
+    if (wide) IWDFT_RC_LAUNCH(LQ, MULTI, kNp) else IWDFT_RC_LAUNCH(LQ, MULTI, 1)      \
   }
   if (logM > logQ) IWDFT_RC_CASE(kFftMaxLogQ, true)
   else switch (logQ) {
@@ -224,6 +239,7 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
     default: IWDFT_RC_CASE(13, false) break;
   }
 #undef IWDFT_RC_CASE
+#undef IWDFT_RC_LAUNCH
   return hipGetLastError();
 }
 

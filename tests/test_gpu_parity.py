@@ -968,3 +968,32 @@ def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_on
             else:
                 assert np.linalg.norm(g - r) <= 1e-5 * np.linalg.norm(r), ch
     c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,batch", [(256, 100, 34), (512, 300, 17), (1024, 600, 25), (2048, 700, 5), (4096, 2100, 3),
+                                            (8192, 900, 2), (16384, 2000, 2)])
+def test_reconstruct_several_channel_pairs_per_store(dtype, L, n_bins, batch):
+    """Enough slices for the form that stores several channel pairs at once, a range that starts and ends inside the rows and
+    wraps: against the oracle on three slices, and bit for bit against the one-pair form that outputs 8 bytes off take."""
+    cfg = small_cfg(L=L, dtype=dtype, n_bins=n_bins, steps=3, group=1, n_layers=1, batch=batch, n_kv_heads=8)
+    bins = random_bins(cfg, 79)
+    K, V = wl.prefill_tensors(cfg, DEV)
+    cache = make_cache(cfg, bins)
+    cache.prefill(K, V)
+    ora = SliceOracle(cfg, bins, None, K, V, wl.sample_slices(cfg, 3))
+    for i in range(3):
+        tk, tv, _ = wl.decode_step(cfg, i, DEV)
+        cache.append(tk, tv)
+        ora.append(tk, tv)
+    a0, n = L // 4 + 3, L // 2 + 1
+    check_reconstruct(cfg, cache, ora, a0, n, f"rec-wide-{dtype}-L{L}")
+    Ka, Va = cache.reconstruct(0, a0, n)
+    flat = torch.empty(2 * Ka.numel() + 64, dtype=Ka.dtype, device=DEV)
+    off = 8 // Ka.element_size()
+    Kb = flat[off:off + Ka.numel()].view(Ka.shape)
+    Vb = flat[off + Ka.numel():off + 2 * Ka.numel()].view(Va.shape)
+    B.iwdft_reconstruct(cache.ctx, 0, a0, n, Kb, Vb)
+    torch.cuda.synchronize()
+    assert torch.equal(Ka, Kb) and torch.equal(Va, Vb)
+    cache.close()
