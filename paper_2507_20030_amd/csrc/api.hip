@@ -158,7 +158,9 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     pl->use_fft_prefill = true;
   } else {
     pl->use_fft_prefill = fft_pf_ok && !(d->flags & IWDFT_FLAG_DENSE_PREFILL) &&
-                          (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M);
+                          (pl->max_nb >= kFftAloneBins ||
+                           (d->M <= (int64_t)kStreamMaxM &&
+                            (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M)));
   }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
   // of M / Pb points, Pb the smallest divisor of M that brings the block down to 8192 (none: the direct sums).

@@ -156,8 +156,12 @@ __device__ __forceinline__ void store_kv(void* p, int64_t i, float v) {
 // Host-side launchers (defined next to their kernels).  Each validates nothing: the C ABI
 // layer has already checked every shape.  They return the hipError_t of the launch.
 hipError_t launch_prefill(const Params& P, const void* K, const void* V, hipStream_t st);
-// The same transform through in-LDS FFTs; prefill_fft_ok: M is a power of two >= 256 and no layer
-// keeps more than 4096 bins.  launch_prefill_edges copies the sink / recent tokens (both prefills).
+// The same transform through in-LDS FFTs; prefill_fft_ok: M is a power of two >= 256.  Layers that all keep fewer than
+// kFftAloneBins bins (and M <= kStreamMaxM) get every channel as exact as alone, as the contraction computes it; otherwise two
+// neighbouring channels share the rounding of the larger one.  launch_prefill_edges copies the sink / recent tokens (all
+// prefills).
+constexpr int kFftAloneBins = 384;
+constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
 // ... and through chirp-z transforms (Params::chirp set).

@@ -40,6 +40,72 @@ __device__ __forceinline__ void raw_pop(Raw<NW>& r) {
   for (int n = 0; n + W < NW; ++n) r.w[n] = r.w[n + W];
 }
 
+// Two channels that travel as real and imaginary part of one transform may differ by orders of magnitude, and its rounding
+// error goes with the larger one.  The second channel is therefore scaled by a power of two (exact) to the size of the first
+// one's largest value, and its spectrum back; a channel that is not finite stays out of the transform (its spectrum is NaN,
+// its partner's is not), one that is zero stays exactly zero.  Magnitudes are compared as bits: infinities and NaN come out on
+// top.
+struct PairScale {
+  float up;      // factor of the second channel on the way in
+  float h0, h1;  // factors of the sums and differences of mirror entries (1/2 of them each) on the way out
+};
+__device__ __forceinline__ bool not_finite(uint32_t magnitude) { return magnitude >= 0x7f800000u; }
+__device__ __forceinline__ PairScale pair_scale(uint32_t m0, uint32_t m1) {  // largest magnitudes, as float bits
+  // 2^(exponent of the first one's maximum - that of the second's); 1 where either is zero, subnormal or not finite
+  const int e0 = (int)(m0 >> 23), e1 = (int)(m1 >> 23);
+  const int de = (e0 > 0 && e0 < 255 && e1 > 0 && e1 < 255) ? min(max(e0 - e1, -60), 60) : 0;
+  PairScale s;
+  s.up = __uint_as_float((uint32_t)(127 + de) << 23);
+  s.h0 = not_finite(m0) ? NAN : m0 ? 0.5f : 0.f;
+  s.h1 = not_finite(m1) ? NAN : m1 ? 0.5f * __uint_as_float((uint32_t)(127 - de) << 23) : 0.f;
+  return s;
+}
+// The same for all pairs of the raw words of a thread's 16 samples, in a workgroup of 512 threads with NS transforms interleaved
+// over the lanes (this thread's: tid % NS): channels that are not finite are cleared in the words.  red is free again behind the
+// next barrier.  One lane reduction and one barrier serve all pairs of a load; the maxima of a bf16 pair are one packed word.
+template <bool BF16>
+__device__ __forceinline__ uint32_t word_max(uint32_t a, uint32_t b) {  // of magnitudes; per half for bf16
+  if constexpr (BF16) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+  } else {
+    return max(a, b);
+  }
+}
+template <bool BF16, int NS, int NW, int NP>
+__device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[16], int tid, uint32_t (&red)[8][NS][NW], PairScale (&sc)[NP]) {
+  static_assert(NW == NP * (BF16 ? 1 : 2) && NS <= 32, "");
+  uint32_t m[NW];
+#pragma unroll
+  for (int n = 0; n < NW; ++n) {
+    m[n] = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m[n] = word_max<BF16>(m[n], z[i].w[n] & (BF16 ? 0x7fff7fffu : 0x7fffffffu));
+#pragma unroll
+    for (int o = 32; o >= NS; o >>= 1) m[n] = word_max<BF16>(m[n], (uint32_t)__shfl_xor((int)m[n], o));
+    if ((tid & 63) < NS) red[tid >> 6][tid & (NS - 1)][n] = m[n];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < NW; ++n) {
+#pragma unroll
+    for (int w = 0; w < 8; ++w) m[n] = word_max<BF16>(m[n], red[w][tid & (NS - 1)][n]);
+    if constexpr (NS == 1) m[n] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m[n]);
+    uint32_t keep;
+    if constexpr (BF16) keep = (not_finite(m[n] << 16) ? 0u : 0xffffu) | (not_finite(m[n] & 0xffff0000u) ? 0u : 0xffff0000u);
+    else keep = not_finite(m[n]) ? 0u : ~0u;
+    if (keep != ~0u) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z[i].w[n] &= keep;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if constexpr (BF16) sc[p] = pair_scale(m[p] << 16, m[p] & 0xffff0000u);
+    else sc[p] = pair_scale(m[2 * p], m[2 * p + 1]);
+  }
+}
+
 // Channel pairs per load and store of the kernels that run 8192 / 2^logQ transforms side by side and write samples back
 // (ablation, reconstruction), and the workgroups (of four pairs) from which on more than one is faster.  Measured, several
 // pairs / one, us: ablation of 64 x 8192 tokens bf16 173 / 294, fp32 253 / 404, 16 x 8192 tokens 55 / 83, 61 / 86; where the

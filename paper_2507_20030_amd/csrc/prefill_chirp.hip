@@ -3,8 +3,7 @@
 // (chirp.h), O(M log M) per channel where the dense contraction costs O(M |B|).
 //
 // Two channels of a slice travel as real and imaginary part of one signal and are separated at the kept bins, as in the
-// power-of-two prefill.  The two may differ by orders of magnitude and a transform's rounding error goes with the larger
-// one: the second channel is scaled by a power of two (exact) to the first one's size, and back when it is stored.
+// power-of-two prefill; the second one is scaled to the first one's size on the way (pair_scale).
 // M > 8192 runs in Pb = M / Q decimated blocks (chirp.h's Q): U[k] = sum_b e^{-j 2 pi k b / M} DFT_Q(x[Pb a + b])[k mod Q],
 // the running sums live in the output rows (every bin belongs to one thread, which reads back its own earlier store).
 #include "chirp.h"
@@ -92,19 +91,15 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void prefill_chirp_kernel(Par
 #pragma unroll
         for (int w = 1; w < NWV; ++w) m = max2(m, smax[w]);
       }
-      // 2^(exponent of the first channel's maximum - that of the second's); 1 where either is zero, subnormal or not finite.
-      // A channel that is not finite stays out of the transform (its partner is not), one that is zero stays exactly zero.
-      const int e0 = (int)(m.x >> 23), e1 = (int)(m.y >> 23);
-      const bool bad0 = e0 == 255, bad1 = e1 == 255;
-      const int de = (e0 > 0 && e0 < 255 && e1 > 0 && e1 < 255) ? min(max(e0 - e1, -60), 60) : 0;
-      const float up = __uint_as_float((uint32_t)(127 + de) << 23), down = __uint_as_float((uint32_t)(127 - de) << 23);
-      const float h0 = bad0 ? NAN : m.x ? 0.5f : 0.f, h1 = bad1 ? NAN : m.y ? 0.5f * down : 0.f;
+      const PairScale sc = pair_scale(m.x, m.y);
+      const bool bad0 = not_finite(m.x), bad1 = not_finite(m.y);
+      const float h0 = sc.h0, h1 = sc.h1;
       const int o = pin_index(t);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const uint32_t a = (uint32_t)(o + T * i);
         const float2 c = a < Q ? P.chirp[a] : make_float2(0.f, 0.f);
-        v[i] = cmul(make_float2(bad0 ? 0.f : v[i].x, bad1 ? 0.f : v[i].y * up), conjf2(c));
+        v[i] = cmul(make_float2(bad0 ? 0.f : v[i].x, bad1 ? 0.f : v[i].y * sc.up), conjf2(c));
       }
       chirp_convolve<LOGN, true>(buf, tab, H, t, v);
       const int o2 = pin_index(t);

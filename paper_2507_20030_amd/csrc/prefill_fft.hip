@@ -31,15 +31,18 @@ constexpr int kPairs = kHeadDim / 2;  // channel pairs per (slice, tensor)
 // bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
 // MULTI (M > 8192): the running sums over the residues live in the output rows (every bin belongs to one thread, which
 // reads back its own earlier store).
-template <int LOGQ, bool BF16, bool MULTI, int NP>
+// EQ: the two channels of a pair are scaled to one size on the way (pair_scale), each as exact as alone; see the launcher.
+template <int LOGQ, bool BF16, bool MULTI, int NP, bool EQ>
 __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
                                                             const void* __restrict__ V, int per_xcd, int n_st) {
-  extern __shared__ float2 smem[];
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
   static_assert(T * NS == 512 && NS * NP <= kPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;  // bytes per token row
   constexpr int NW = NP * (BF16 ? 1 : 2);
+  __shared__ uint32_t maxima[EQ ? 8 : 1][EQ ? NS : 1][EQ ? NW : 1];
+  __shared__ float2 halves[EQ ? NS : 1][EQ ? NP : 1];  // (h0, h1): transforms are pruned by other threads than those that fetch
   constexpr int kGroups = kPairs / (NP * NS);  // workgroups per (slice, tensor)
   const TabMem tab{P.tab + tab_base(LOGQ)};
   const int tid = threadIdx.x;
@@ -76,12 +79,21 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
 #pragma unroll
     for (int m = 0; m < 16; ++m)  // position 16 t + m holds sample_at(16 t) + (digits of m reversed) Q / 16
       z[m] = load_raw<NW>(Xb + (int64_t)((((m & 3) << 2) | (m >> 2)) * (Q / 16)) * step);
+    PairScale sc[NP];
+    if constexpr (EQ) {
+      scale_pairs<BF16>(z, tid, maxima, sc);
+      if (NS > 1 && tid < NS) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) halves[tid][p] = make_float2(sc[p].h0, sc[p].h1);
+      }
+    }
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       float2 x[16];
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
         x[m] = raw_front<BF16, NW>(z[m]);
+        if constexpr (EQ) x[m].y *= sc[p].up;
         raw_pop<BF16, NW>(z[m]);
       }
       float2* F0 = F + (int64_t)(2 * p) * L.Bp;
@@ -103,6 +115,8 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
       };
       fetch_bins(pin_index(tp));
       fft_forward<LOGQ>(buf, tab, lt, x, fetch_tw);
+      float2 h = make_float2(0.5f, 0.5f);
+      if constexpr (EQ) h = NS > 1 ? halves[tid / T][p] : make_float2(sc[p].h0, sc[p].h1);
       for (int i0 = tp; i0 < L.nb; i0 += U * T) {
         if (i0 >= U * T) {
           fetch_bins(i0);
@@ -114,8 +128,8 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
           if (i < L.nb) {
             float2 w1, w2;
             spectrum_pair<LOGQ>(spec, kj[j] & (Q - 1), wj[j], w1, w2);
-            float2 d0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-            float2 d1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+            float2 d0 = make_float2(h.x * (w1.x + w2.x), h.x * (w1.y - w2.y));
+            float2 d1 = make_float2(h.y * (w1.y + w2.y), h.y * (w2.x - w1.x));
             if constexpr (MULTI) {
               const float2 tw = conjf2(cis_poly2((kj[j] * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
               d0 = cmul(tw, d0);
@@ -144,7 +158,7 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
 // The last radix-2 stage of the transform and the residue sum are one thing: sample n = Pb (2 a + h) + b, so every bin takes
 // two products, with e^{-j 2 pi k b / M} for the even half spectrum E and e^{-j 2 pi k (b + Pb) / M} for the odd one O; with
 // r = k mod 4096 and the mirror entry r' = -r mod 4096, the first channel's part is (E[r] + conj E[r']) / 2 and so on.
-template <bool BF16, int NBT, int NP>
+template <bool BF16, int NBT, int NP, bool EQ>
 __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const void* __restrict__ K,
                                                                const void* __restrict__ V, int per_xcd, int n_st,
                                                                int slots) {
@@ -154,9 +168,10 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
   constexpr int kRow = kHeadDim * kElem;
   constexpr int NW = NP * (BF16 ? 1 : 2);  // words per sample: 16 bytes, one pair's for tensors that are not 16-byte aligned
   constexpr int kGroups = kPairs / NP;
-  extern __shared__ float2 buf[];
+  extern __shared__ __attribute__((aligned(16))) float2 buf[];
+  __shared__ uint32_t maxima[EQ ? 8 : 1][1][EQ ? NW : 1];
   float4* ltab = (float4*)(buf + fft_lds(LOGQ));
-  float4* btw = ltab + TabLds::entries<LOGQ>();  // [NBT * T] bin twiddles, half of (even, odd); a thread's own entries only
+  float4* btw = ltab + TabLds::entries<LOGQ>();  // [NBT * T] bin twiddles (even, odd), halves of them without EQ; a thread's own entries only
   const TabLds tab{P.tab + tab_base(LOGQ), ltab};
   const int tid = threadIdx.x;
   const uint32_t xcd = blockIdx.x & 7u;
@@ -219,14 +234,18 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
 #pragma unroll
     for (int j = 0; j < NBT; ++j) {
       const float2 t0 = cis_poly2((kk[j] * b) & (M - 1u), M), t1 = cis_poly2((kk[j] * (b + Pb)) & (M - 1u), M);
-      btw[j * T + tid] = make_float4(0.5f * t0.x, -0.5f * t0.y, 0.5f * t1.x, -0.5f * t1.y);
+      constexpr float kHalf = EQ ? 1.f : 0.5f;
+      btw[j * T + tid] = make_float4(kHalf * t0.x, -kHalf * t0.y, kHalf * t1.x, -kHalf * t1.y);
     }
+    PairScale sc[NP];
+    if constexpr (EQ) scale_pairs<BF16>(z, tid, maxima, sc);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       float2 x[16];
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
         x[m] = raw_front<BF16, NW>(z[m]);
+        if constexpr (EQ) x[m].y *= sc[p].up;
         raw_pop<BF16, NW>(z[m]);
       }
       // The next step's samples, one row or so per phase (three passes and the pruning): a wave that issues more than the
@@ -240,14 +259,18 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
       };
       fft_forward<LOGQ>(buf, tab, tid, x, fetch_next);
       fetch_next(3);
+      float2 h = make_float2(1.f, 1.f);  // without EQ the bin twiddles hold the halves
+      if constexpr (EQ) h = make_float2(sc[p].h0, sc[p].h1);
 #pragma unroll
       for (int j = 0; j < NBT; ++j) {
         const uint32_t r = kk[j] & (H - 1), rm = (H - r) & (H - 1);
         const float2 *u = buf + fpad((int)r), *v = buf + fpad((int)rm);
         const float2 e = u[0], o = u[H + H / 8], em = v[0], om = v[H + H / 8];
         const float4 w = btw[j * T + tid];
-        const float2 se = make_float2(e.x + em.x, e.y - em.y), de = make_float2(e.y + em.y, em.x - e.x);  // -j (E - conj E')
-        const float2 so = make_float2(o.x + om.x, o.y - om.y), dd = make_float2(o.y + om.y, om.x - o.x);
+        const float2 se = make_float2(h.x * (e.x + em.x), h.x * (e.y - em.y));
+        const float2 de = make_float2(h.y * (e.y + em.y), h.y * (em.x - e.x));  // -j (E - conj E')
+        const float2 so = make_float2(h.x * (o.x + om.x), h.x * (o.y - om.y));
+        const float2 dd = make_float2(h.y * (o.y + om.y), h.y * (om.x - o.x));
         float2 &a0 = acc[p][0][j], &a1 = acc[p][1][j];
         a0 = make_float2(fmaf(w.x, se.x, fmaf(-w.y, se.y, a0.x)), fmaf(w.x, se.y, fmaf(w.y, se.x, a0.y)));
         a1 = make_float2(fmaf(w.x, de.x, fmaf(-w.y, de.y, a1.x)), fmaf(w.x, de.y, fmaf(w.y, de.x, a1.y)));
@@ -283,8 +306,6 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
 
 constexpr int kCusPerXcd = 32;
 constexpr uint64_t kFewWorkgroups = 256;
-constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
-
 bool prefill_fft_ok(const Params& P) { return P.Mmask != 0 && P.M >= 256; }
 
 template <bool BF16>
@@ -295,25 +316,31 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   const int per_xcd = (n_st + 7) / 8;
   // several pairs per load need 16-byte aligned tensors (and rows, which are 256 or 512 bytes)
   const bool wide = (((uintptr_t)K | (uintptr_t)V) & 15u) == 0;
+  // Below kFftAloneBins the channels of a pair are scaled to one size: without a flag these contexts take the FFT for its speed
+  // only, and the contraction it replaces keeps every channel alone (8192 points, a channel 2^11 below its partner: 1.8e-4
+  // relative error in an unscaled transform).  It costs 31 packed maxima and 16 products per pair and a barrier: 32 x 8 slices
+  // of 8192 tokens, 2048 bins, bf16 794 us against 730 without.
+  const bool eq = P.max_nb < kFftAloneBins;
   hipError_t e = hipSuccess;
   if (logM > kFftMaxLogQ && P.max_nb <= 4096 && P.M <= kStreamMaxM) {
-#define IWDFT_PF_STREAM(NBT, NP)                                                                              \
+#define IWDFT_PF_STREAM(NBT, NP, EQ)                                                                          \
   {                                                                                                           \
     const size_t bytes = sizeof(float2) * fft_lds(kFftMaxLogQ) +                                              \
                          sizeof(float4) * (TabLds::entries<kFftMaxLogQ>() + (NBT) * 512);                     \
     const int items = per_xcd * (kPairs / (NP)), slots = items < kCusPerXcd ? items : kCusPerXcd;             \
     static LdsLimit lim;                                                                                      \
-    e = lim.ensure((const void*)prefill_stream_kernel<BF16, NBT, NP>, (int)bytes);                            \
+    e = lim.ensure((const void*)prefill_stream_kernel<BF16, NBT, NP, EQ>, (int)bytes);                        \
     if (e != hipSuccess) return e;                                                                            \
-    prefill_stream_kernel<BF16, NBT, NP><<<dim3((uint32_t)slots * 8), dim3(512), bytes, st>>>(P, K, V,        \
-                                                                                             per_xcd, n_st,  \
-                                                                                             slots);         \
+    prefill_stream_kernel<BF16, NBT, NP, EQ><<<dim3((uint32_t)slots * 8), dim3(512), bytes, st>>>(            \
+        P, K, V, per_xcd, n_st, slots);                                                                       \
   }
     constexpr int kNp = BF16 ? 4 : 2;
     if (P.max_nb > 2048) {
-      if (wide) IWDFT_PF_STREAM(8, kNp) else IWDFT_PF_STREAM(8, 1)
+      if (wide) IWDFT_PF_STREAM(8, kNp, false) else IWDFT_PF_STREAM(8, 1, false)
+    } else if (!eq) {
+      if (wide) IWDFT_PF_STREAM(4, kNp, false) else IWDFT_PF_STREAM(4, 1, false)
     } else {
-      if (wide) IWDFT_PF_STREAM(4, kNp) else IWDFT_PF_STREAM(4, 1)
+      if (wide) IWDFT_PF_STREAM(4, kNp, true) else IWDFT_PF_STREAM(4, 1, true)
     }
 #undef IWDFT_PF_STREAM
     return hipGetLastError();
@@ -322,25 +349,33 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   // Pairs per thread: as many as the register budget (128) holds next to the transform (the staged samples take 16
   // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.
   const bool few = (uint64_t)n_st * (kPairs / 4 / side_ns(logQ)) < kFewWorkgroups;
-#define IWDFT_PF_CASE(LQ, MULTI, NP)                                                                        \
+#define IWDFT_PF_CASE(LQ, MULTI, NP, EQ)                                                                    \
   {                                                                                                         \
     const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                          \
     const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LQ))) * 8;                     \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                        \
     static LdsLimit lim;                                                                                    \
-    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NP>, (int)lds);                         \
+    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NP, EQ>, (int)lds);                     \
     if (e != hipSuccess) return e;                                                                          \
-    prefill_fft_kernel<LQ, BF16, MULTI, NP><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(P, K, V,        \
-                                                                                           per_xcd, n_st); \
+    prefill_fft_kernel<LQ, BF16, MULTI, NP, EQ><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(            \
+        P, K, V, per_xcd, n_st);                                                                            \
   }
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
     constexpr int kNp = (LQ == 8 || !BF16) ? 2 : 4;                                \
-    if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp) else IWDFT_PF_CASE(LQ, false, 1) \
+    constexpr bool kAll = (1 << LQ) >= kFftAloneBins; /* shorter: never as many */ \
+    if (kAll && !eq) {                                                             \
+      if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp, !kAll)                       \
+      else IWDFT_PF_CASE(LQ, false, 1, !kAll)                                      \
+    } else if (wide && !few) {                                                     \
+      IWDFT_PF_CASE(LQ, false, kNp, true)                                          \
+    } else {                                                                       \
+      IWDFT_PF_CASE(LQ, false, 1, true)                                            \
+    }                                                                              \
   }
   if (logM > kFftMaxLogQ) {
     constexpr int kNpBig = BF16 ? 2 : 1;
-    if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, kNpBig) else IWDFT_PF_CASE(kFftMaxLogQ, true, 1)
+    if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, kNpBig, false) else IWDFT_PF_CASE(kFftMaxLogQ, true, 1, false)
   } else switch (logQ) {
     case 8: IWDFT_PF_SINGLE(8) break;
     case 9: IWDFT_PF_SINGLE(9) break;

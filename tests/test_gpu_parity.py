@@ -971,6 +971,44 @@ def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_on
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,heads", [
+    (256, 40, 1), (512, 128, 1), (1024, 300, 1), (2048, 128, 1), (4096, 200, 1), (8192, 300, 1),  # one pair per load
+    (256, 256, 257), (512, 100, 129), (1024, 256, 65), (2048, 383, 33), (4096, 128, 17), (8192, 383, 9),  # several
+    (16384, 128, 2), (65536, 383, 1),  # residues
+])
+def test_fft_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one(dtype, L, n_bins, heads):
+    """Fewer than 384 kept bins: neighbouring channels share a transform, each is as accurate as alone (fp32 rounding, 2^-24, times ~log2 of the 8192
+    points and the residue sums: below 4e-6 relative per channel over the kept bins), zero stays zero, and a channel that is not
+    finite does not reach its partner -- in every residue, and where it is not finite in one of them only."""
+    cfg = small_cfg(L=L, n_bins=n_bins, dtype=dtype, n_layers=1, batch=1, n_kv_heads=heads)
+    bins = random_bins(cfg, 23)
+    K, V = wl.prefill_tensors(cfg, DEV)
+    K[..., 0::4] *= 2.0 ** 20
+    K[..., 3::4] *= 2.0 ** -20
+    K[..., L // 2:, 9] = 0.0
+    K[..., L // 2:, 8] *= 2.0 ** 10
+    V[..., 1] = 0.0
+    V[..., 64] = 0.0
+    V[..., 100, 6] = float("inf")
+    V[..., 7, 11] = float("nan")
+    V[..., 8, 20:22] = float("-inf")
+    c = make_cache(cfg, bins)
+    assert B.iwdft_prefill_kind(c.ctx) == "fft"
+    c.prefill(K, V)
+    for name, X, got in zip("KV", (K, V), c.export_coeffs(0)):
+        for h in sorted({0, heads // 2, heads - 1}):
+            ref = orc.prefill(f64(X[0, 0, h].nan_to_num(0.0, 0.0, 0.0)), bins[0])
+            g = c128(got[0, h])
+            assert g.shape == ref.shape == (n_bins, 128)
+            for ch in range(128):
+                if name == "V" and ch in (6, 11, 20, 21):
+                    assert not np.isfinite(g[:, ch]).any(), ch
+                else:
+                    assert np.linalg.norm(g[:, ch] - ref[:, ch]) <= 4e-6 * np.linalg.norm(ref[:, ch]), (name, h, ch)
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,n_bins,batch", [(256, 100, 34), (512, 300, 17), (1024, 600, 25), (2048, 700, 5), (4096, 2100, 3),
                                             (8192, 900, 2), (16384, 2000, 2)])
 def test_reconstruct_several_channel_pairs_per_store(dtype, L, n_bins, batch):
