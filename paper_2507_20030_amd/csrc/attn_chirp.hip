@@ -232,20 +232,18 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
         const float2 a1 = o1[i];
         r1 = make_float2(a1.x * (w * iz1), -a1.y * (w * iz1));
       }
-      if (np > 0) {  // block-uniform; u_n = Re(tw step^n r) obeys u_{n+1} = 2 cos(step) u_n - u_{n-1}
+      if (np > 0) {  // block-uniform
+        // exact first phase and step, one rotation per token: a token's weight is off by less than 16 roundings, as where the
+        // coefficients themselves take the tokens up (kernel A's and C's update modes)
         const uint32_t k = (uint32_t)bins[i];
-        const float2 tw = cis_rev(phase_of(k, ptsh, M, inv_Md)), step = cis_rev((float)k * inv_Mf), t1 = cmul(tw, step);
-        const float c2 = 2.f * step.x;
-        float u0 = tw.x * r0.x - tw.y * r0.y, u1 = t1.x * r0.x - t1.y * r0.y;
-        float v0 = tw.x * r1.x - tw.y * r1.y, v1 = t1.x * r1.x - t1.y * r1.y;
+        const float2 step = cis_exact(k, 1u, M, inv_Md);
+        float2 tw = cis_exact(k, ptsh, M, inv_Md);
 #pragma unroll
         for (int j = 0; j < kMaxPend; ++j) {
           if (j < np) {
-            sp[2 * j] += u0;
-            sp[2 * j + 1] += v0;
-            const float u2 = c2 * u1 - u0, v2 = c2 * v1 - v0;
-            u0 = u1, u1 = u2;
-            v0 = v1, v1 = v2;
+            sp[2 * j] += tw.x * r0.x - tw.y * r0.y;
+            sp[2 * j + 1] += tw.x * r1.x - tw.y * r1.y;
+            tw = cmul(tw, step);
           }
         }
       }

@@ -27,19 +27,21 @@ __device__ __forceinline__ void chirp_convolve(float2* buf, const TabMem& tab, c
   half_forward<LOGN>(buf, tab, t, x, v);
 }
 
-// k mod n and the phase (a b mod M) / M in revolutions for factors below 2^21 (M <= 256 * 8192), without an integer division.
+// k mod n for factors below 2^21 (M <= 256 * 8192), without an integer division.
 __device__ __forceinline__ uint32_t mod_small(uint32_t k, uint32_t n, float inv_n) {  // k < 2^29, k / n < 2^20
   int32_t r = (int32_t)(k - (uint32_t)((float)k * inv_n) * n);  // the quotient is off by one at most
   if (r < 0) r += (int32_t)n;
   if (r >= (int32_t)n) r -= (int32_t)n;
   return (uint32_t)r;
 }
-__device__ __forceinline__ float phase_of(uint32_t a, uint32_t b, uint32_t M, double inv_M) {
+// e^{+j 2 pi a b / M} to fp32 rounding: M is not a power of two, so the phase is reduced in integers and split in double.
+__device__ __forceinline__ float2 cis_exact(uint32_t a, uint32_t b, uint32_t M, double inv_M) {
   const uint64_t p = (uint64_t)a * b;
   int64_t r = (int64_t)(p - (uint64_t)((double)p * inv_M) * M);
   if (r < 0) r += M;
   if (r >= (int64_t)M) r -= M;
-  return (float)(uint32_t)r * (float)inv_M;
+  const double x = (double)r * inv_M, q = rint(8.0 * x);
+  return cis_octant((float)((x - 0.125 * q) * 6.283185307179586477), (int)q);
 }
 // e^{+j 2 pi ph} through the hardware sine / cosine (argument in revolutions, ~1e-6 absolute).
 __device__ __forceinline__ float2 cis_rev(float ph) {

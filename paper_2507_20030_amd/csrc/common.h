@@ -98,6 +98,7 @@ __device__ __forceinline__ float2 cis(uint32_t p, uint32_t M) {
 // octant reduction in exact arithmetic (p/M and q/8 are exact for power-of-two M), degree-7/8
 // Taylor polynomials on |theta| <= pi/8 (truncation < 1e-9), then a rotation by q * 45 degrees.
 __device__ __forceinline__ float2 cis_poly_x(float x);
+__device__ __forceinline__ float2 cis_octant(float th, int q);
 __device__ __forceinline__ float2 cis_poly(uint32_t p, uint32_t M) { return cis_poly_x((float)p / (float)M); }
 // 1 / M for M = 2^m, exact (exponent negated), without the division sequence.
 __device__ __forceinline__ float rcp_pow2(uint32_t M) { return __uint_as_float(0x7f000000u - __float_as_uint((float)M)); }
@@ -106,11 +107,13 @@ __device__ __forceinline__ float2 cis_poly2(uint32_t p, uint32_t M) { return cis
 // x = p / M in [0, 1).
 __device__ __forceinline__ float2 cis_poly_x(float x) {
   const float qf = rintf(x * 8.0f);               // nearest octant boundary, 0..8
-  const float th = (x - qf * 0.125f) * 6.283185307179586f;  // |th| <= pi/8
+  return cis_octant((x - qf * 0.125f) * 6.283185307179586f, (int)qf);
+}
+// th + q * 45 degrees, |th| <= pi/8.
+__device__ __forceinline__ float2 cis_octant(float th, int q) {
   const float t2 = th * th;
   float sn = th * (1.0f + t2 * (-1.0f / 6.0f + t2 * (1.0f / 120.0f + t2 * (-1.0f / 5040.0f))));
   float cs = 1.0f + t2 * (-0.5f + t2 * (1.0f / 24.0f + t2 * (-1.0f / 720.0f + t2 * (1.0f / 40320.0f))));
-  const int q = (int)qf;
   if (q & 1) {  // + 45 degrees (compiles to selects)
     const float c2 = (cs - sn) * 0.70710678118654752f, s2 = (cs + sn) * 0.70710678118654752f;
     cs = c2;

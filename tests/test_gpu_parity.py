@@ -756,6 +756,38 @@ def test_chirp_attention_defers_the_write_back(L, S, R, group, n_bins, J):
     d.close()
 
 
+@pytest.mark.parametrize("L,n_bins,heads", [(1000, 250, 260), (8132, 2033, 32), (3 * 8191, 4100, 16)])
+def test_chirp_attention_weighs_pending_tokens_as_exactly_as_absorbed_ones(L, n_bins, heads):
+    """V is zero but for the pending tokens, whose rows are unit vectors: the output holds their weights, one per channel.
+    Bins from the whole circle (high ones turn fastest) and no constant term, which would hide the others.  On top of what
+    the step that writes every token back shows: up to 15 rotations, 2 roundings of 2^-24 each, adding up at random: 5e-7."""
+    cfg = small_cfg(L=L, n_bins=n_bins, group=2, dtype="f32", steps=15, n_layers=1, batch=1, n_kv_heads=heads)
+    bins = [np.sort(np.random.default_rng(5).choice(np.arange(L // 2, L), size=n_bins, replace=False)).astype(np.int32)]
+    K, V = wl.prefill_tensors(cfg, DEV)
+    V.zero_()
+    a, d = make_cache(cfg, bins, write_every=16), make_cache(cfg, bins)
+    assert B.iwdft_attn_kind(a.ctx) == "chirp" and a.ws_bytes > d.ws_bytes
+    a.prefill(K, V)
+    d.prefill(K, V)
+    slices = [(0, 0, 0), (0, 0, heads - 1)]
+    ora = SliceOracle(cfg, bins, None, K, V, slices)
+    worst = {"deferred": 0.0, "written": 0.0}
+    for i in range(cfg.steps):
+        tk, tv, q = wl.decode_step(cfg, i, DEV)
+        tv = torch.zeros_like(tv)
+        tv[..., i] = 1.0
+        ora.append(tk, tv)
+        ref = ora.attend(q)
+        for name, c in (("deferred", a), ("written", d)):
+            out = c.step(tk, tv, q)
+            for (l, b, h), r in ref.items():
+                worst[name] = max(worst[name], rel_l2(f64(out[l, b, 2 * h:2 * h + 2]), r))
+    print(f"\n[pending-{L}] deferred {worst['deferred']:.2e} written {worst['written']:.2e}", flush=True)
+    assert worst["deferred"] < worst["written"] + 5e-7, worst
+    a.close()
+    d.close()
+
+
 @pytest.mark.parametrize("L,S,R,group,n_bins,dtype", [
     (16324, 10, 50, 4, 1600, "bf16"),    # 16384 - 60 = 2 * 8162: the paper's windows cut out of a 16K context
     (32708, 10, 50, 2, 3000, "f32"),     # 32768 - 60 = 4 * 8177
