@@ -80,7 +80,11 @@ enum {
                                        M > 2^26) the smaller one has the fp32 rounding of
                                        the larger one, and a value that is not finite
                                        reaches both.  Otherwise, and in the chirp-z
-                                       prefill, each is as exact as alone.            */
+                                       prefill, each is as exact as alone.  All transforms
+                                       of this library (attention, reconstruction and
+                                       ablation too) hold sums up to 2^97: values times
+                                       their number's square root, 6-fold at the peaks,
+                                       have to stay below.                            */
   IWDFT_FLAG_FFT_PREFILL = 4u,      /* iwdft_prefill always runs FFTs + pruning; needs
                                        M = 2^m >= 256, else IWDFT_ERR_UNSUPPORTED (layers
                                        with more than 4096 kept bins take a form that
@@ -283,6 +287,7 @@ int iwdft_select_bins(const float* delta, int32_t n_layers, int32_t n_chunks, in
  * d_x, d_out: DEVICE [n_slices][M][head_dim], kv_dtype, must not overlap.  This build: head_dim 128 and
  * M = 2^m, 256 <= M <= 2^24 (IWDFT_ERR_UNSUPPORTED otherwise).  For M > 8192 the chunk's part is taken off the
  * input 4096 bins at a time through d_out, so a bf16 result carries one more rounding per such piece.
+ * For M <= 8192 values up to 2^(93 - log2(M) / 2) in magnitude come through (see IWDFT_FLAG_DENSE_PREFILL).
  * Needs no context; enqueues on hip_stream. */
 int iwdft_ablate_chunk(const void* d_x, void* d_out, int64_t n_slices, int64_t M, int32_t head_dim,
                        int32_t kv_dtype, int32_t n_chunks, int32_t chunk, void* hip_stream);

@@ -18,14 +18,14 @@ constexpr int kAbPairs = kHeadDim / 2;
 
 // Two adjacent channels of a slice travel as one complex signal: forward transform, weights
 // h[k] = 1 - ([k in chunk] + [M-k in chunk]) / 2 (the real part of the inverse transform of a real signal's spectrum with the
-// chunk zeroed; symmetric, so both packed channels stay real), inverse transform, 1/M.  Block ids are dealt so that the
-// workgroups of a slice share one XCD's L2.
+// chunk zeroed; symmetric, so both packed channels stay real), 1/M (on the spectrum: M times the samples may be out of range), inverse transform.  Block
+// ids are dealt so that the workgroups of a slice share one XCD's L2.
 // As in the FFT prefill a workgroup runs NS = 8192 / Q transforms side by side, interleaved over the lanes, on NP channel
 // pairs one after the other: what bounded this kernel was one pair per workgroup, 4 bytes of every 128-byte line per load and
 // per store.  A thread's 16 samples are 16 consecutive positions of the digit-reversed order, where the forward transform
 // starts and the inverse one ends in registers, so samples cross LDS only inside the transforms; results take the place of
 // the inputs in the loaded words.  Only the chunk's entries and their mirrors are weighed.  64 slices of 8192 tokens, bf16:
-// 310 -> 179 us (0.27 GB read and written: 1.5 TB/s); what is left is the vector arithmetic of the two transforms.
+// 310 -> 167 us (0.27 GB read and written: 1.6 TB/s); what is left is the vector arithmetic of the two transforms.
 template <int LOGQ, bool BF16, int NP>
 __global__ __launch_bounds__(512, 4) void ablate_kernel(const char* __restrict__ x, char* __restrict__ out,
                                                        const float2* __restrict__ tabs, int n_slices, int per_xcd, int lo,
@@ -43,7 +43,6 @@ __global__ __launch_bounds__(512, 4) void ablate_kernel(const char* __restrict__
   const uint32_t slice = (blockIdx.x & 7u) * (uint32_t)per_xcd + idx / kGroups;
   if (slice >= (uint32_t)n_slices) return;  // the whole workgroup
   const int64_t base = ((int64_t)slice * Q + sample_at<LOGQ>(16 * t)) * kRow + ((idx % kGroups) * NS + g) * (NP * 2 * kElem);
-  const float inv = 1.0f / (float)Q;
   float2* buf = smem + g * BS;
 
   Raw<NW> z[16];
@@ -66,9 +65,9 @@ __global__ __launch_bounds__(512, 4) void ablate_kernel(const char* __restrict__
       }
     }
     __syncthreads();
-    fft_inverse<LOGQ>(buf, tab.tab, t, v);
+    fft_inverse<LOGQ, true>(buf, tab.tab, t, v);
 #pragma unroll
-    for (int m = 0; m < 16; ++m) raw_push<BF16, NW>(z[m], make_float2(v[m].x * inv, v[m].y * inv));
+    for (int m = 0; m < 16; ++m) raw_push<BF16, NW>(z[m], v[m]);
   }
 #pragma unroll
   for (int m = 0; m < 16; ++m) store_raw<NW>(out + base + sample_step<LOGQ>(m) * kRow, z[m]);

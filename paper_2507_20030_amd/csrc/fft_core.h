@@ -49,7 +49,9 @@ __device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.
 // complex product and two additions are eight, and no twiddle is derived at run time.  The forward transform (decimation
 // in time, narrow span first) has such butterflies by nature; the inverse one splits the spectrum block by block
 // (x^L - z  ->  x^(L/4) - z^(1/4) j^r), so that its twiddles multiply inputs too and depend on the block only.  Where c is
-// small t is large, but the rounding of t b.y is scaled by c: nothing is lost.
+// small t is large, but the rounding of t b.y is scaled by c: nothing is lost.  (It costs range: t reaches 2^30, so sums beyond
+// 2^97 overflow.)  The form is E. Linzer and E. Feig's, "Modified FFTs for fused multiply-add architectures", Mathematics of
+// Computation 60 (1993).
 // INV: w as tabled (sign +), otherwise its conjugate.
 template <bool INV>
 __device__ __forceinline__ void bfly(float2& a, float2& b, float c, float t) {
@@ -218,7 +220,8 @@ __device__ __forceinline__ void write16(float2* buf, int t, const float2 (&x)[16
 // One radix-16 pass of span 16^K (K >= 1) in place.  Tab::kEarly: w holds its twiddles on entry and, NEXT >= 0, those of
 // the pass of span 16^NEXT on return.  hook(k) runs between the butterflies and the stores.
 // HALF: the upper half of the input is zero (only looked at where the radix-2 stage comes with the reads).
-template <int LOGQ, int K, bool INV, int NEXT, bool HALF = false, typename Tab, typename Hook>
+// NORM: the input is divided by Q on the way in.
+template <int LOGQ, int K, bool INV, int NEXT, bool HALF = false, bool NORM = false, typename Tab, typename Hook>
 __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw16& w, Hook hook) {
   constexpr int Q = 1 << LOGQ, S = 4 * K, s2 = 1 << S;
   constexpr int SP = s2 + s2 / 8;  // distance in LDS of positions s2 apart
@@ -244,6 +247,10 @@ __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw1
 #pragma unroll
     for (int m = 0; m < 16; ++m) x[m] = base[m * SP];
   }
+  if constexpr (NORM) {
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m] = make_float2(x[m].x * (1.f / Q), x[m].y * (1.f / Q));
+  }
   if constexpr (kOne) dft16_1<INV>(x);
   else dft16<INV>(x, w);
   if constexpr (NEXT >= 0 && Tab::kEarly) tab.template load<LOGQ, NEXT, INV>(w, t);
@@ -253,8 +260,8 @@ __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw1
   __syncthreads();
 }
 
-// The stage of radix 2^rem at the wide end as a pass of its own.
-template <int LOGQ, bool INV>
+// The stage of radix 2^rem at the wide end as a pass of its own (NORM: as in fft_pass).
+template <int LOGQ, bool INV, bool NORM = false>
 __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__ tab, int t) {
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), REM = fft_rem(LOGQ), R = 1 << REM, NB = Q / R;
   constexpr int SP = NB + NB / 8;
@@ -265,7 +272,10 @@ __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__
     float2* b = buf + fpad(k);
     float2 x[R];
 #pragma unroll
-    for (int m = 0; m < R; ++m) x[m] = b[m * SP];
+    for (int m = 0; m < R; ++m) {
+      x[m] = b[m * SP];
+      if constexpr (NORM) x[m] = make_float2(x[m].x * (1.f / Q), x[m].y * (1.f / Q));
+    }
     if constexpr (REM == 1) {
       if constexpr (INV) bfly1(x[0], x[1]);
       else {
@@ -304,22 +314,23 @@ __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__
 
 // Inverse transform of the natural-order spectrum in buf (complete: behind a barrier); on return x holds the samples at
 // positions 16 t + m.  buf may be overwritten position by position by the same thread without a
-// barrier, otherwise only behind one.  tab: this length's block of the tables.
-template <int LOGQ, int K = fft_np(LOGQ) - 1>
+// barrier, otherwise only behind one.  tab: this length's block of the tables.  NORM: with the factor 1 / Q, applied to the
+// spectrum, so that no sum exceeds the range that the samples and their spectrum have.
+template <int LOGQ, int K = fft_np(LOGQ) - 1, bool NORM = false>
 __device__ __forceinline__ void fft_inv_passes(float2* buf, const TabMem& tab, int t, Tw16& w) {
   if constexpr (K >= 1) {
-    fft_pass<LOGQ, K, true, K - 1>(buf, tab, t, w, [] {});
+    fft_pass<LOGQ, K, true, K - 1, false, NORM>(buf, tab, t, w, [] {});
     fft_inv_passes<LOGQ, K - 1>(buf, tab, t, w);
   }
 }
-template <int LOGQ>
+template <int LOGQ, bool NORM = false>
 __device__ __forceinline__ void fft_inverse(float2* buf, const float2* __restrict__ tab, int t, float2 (&x)[16]) {
   static_assert(fft_np(LOGQ) >= 2, "256 points at least");
   Tw16 w;
-  if constexpr (fft_rem(LOGQ) >= 2) fft_wide<LOGQ, true>(buf, tab, t);
+  if constexpr (fft_rem(LOGQ) >= 2) fft_wide<LOGQ, true, NORM>(buf, tab, t);
   const TabMem tm{tab};
   tm.load<LOGQ, fft_np(LOGQ) - 1, true>(w, t);
-  fft_inv_passes<LOGQ>(buf, tm, t, w);
+  fft_inv_passes<LOGQ, fft_np(LOGQ) - 1, NORM && (fft_rem(LOGQ) < 2)>(buf, tm, t, w);
   read16(buf, t, x);
   dft16<true>(x, w);
 }

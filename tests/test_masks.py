@@ -143,3 +143,22 @@ def test_ablate_chunk_several_channel_pairs_per_load(dtype, M):
             err = np.linalg.norm(out[s].cpu().to(torch.float64).numpy() - ref) / np.linalg.norm(ref)
             # fp32: 2^-24 times ~log2 M roundings of two transforms; bf16: output rounding, at most 2^-9 per element
             assert err < (3e-6 if dtype == torch.float32 else 2.0 ** -9), (M, c, s, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
+def test_ablate_chunk_of_values_near_the_end_of_the_range(dtype, M):
+    """The butterflies multiply by tangents of up to 2^30, so sums on the way may reach 2^97.  The spectrum is about sqrt(M)
+    times as large as the values, 6 times that at its peak: values of 2^(93 - log2(M) / 2) have to come through, which
+    unnormalised samples, M times as large, would not."""
+    scale = 2.0 ** (93 - int(np.log2(M)) // 2)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = (torch.randn((2, M, 128), generator=g, device="cuda").clamp_(-4, 4) * scale).to(dtype)
+    out = torch.empty_like(x)
+    B.iwdft_ablate_chunk(x, out, 5, 2)
+    torch.cuda.synchronize()
+    for s in range(2):
+        ref = orc.ablate_chunk(x[s].cpu().to(torch.float64).numpy() / scale, 5, 2)
+        err = np.linalg.norm(out[s].cpu().to(torch.float64).numpy() / scale - ref) / np.linalg.norm(ref)
+        assert err < (3e-6 if dtype == torch.float32 else 2.0 ** -9), (M, s, err)
