@@ -154,8 +154,8 @@ int iwdft_destroy(iwdft_ctx* ctx); /* frees host memory only; NULL is accepted *
  * T becomes M. */
 int iwdft_prefill(iwdft_ctx* ctx, const void* d_K, const void* d_V, void* hip_stream);
 
-/* Which transform iwdft_prefill runs for this context: 0 = dense contraction or, for M that is
- * not a power of two, chirp-z transforms + pruning; 1 = FFTs + pruning; -1 if ctx is NULL. */
+/* Which transform iwdft_prefill runs for this context: 0 = dense contraction, 1 = FFTs + pruning
+ * (M = 2^m), 2 = chirp-z transforms + pruning (other M); -1 if ctx is NULL. */
 int iwdft_prefill_kind(const iwdft_ctx* ctx);
 
 /* Which synthesis compressed_decode_attn / iwdft_append_attn run for this context: 1 = scores and softmax

@@ -223,7 +223,7 @@ def iwdft_flush(ctx, stream=None) -> None:
 
 
 def iwdft_prefill_kind(ctx) -> str:
-    return {0: "dense", 1: "fft"}[load_library().iwdft_prefill_kind(ctx)]
+    return {0: "dense", 1: "fft", 2: "chirp"}[load_library().iwdft_prefill_kind(ctx)]
 
 
 def iwdft_attn_kind(ctx) -> str:

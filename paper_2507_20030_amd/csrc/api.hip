@@ -614,7 +614,9 @@ int iwdft_phase_times(iwdft_ctx* ctx, double* ms, int64_t* n_calls) {
 
 int64_t iwdft_num_tokens(const iwdft_ctx* ctx) { return ctx ? ctx->T : -1; }
 
-int iwdft_prefill_kind(const iwdft_ctx* ctx) { return ctx ? (ctx->plan.use_fft_prefill ? 1 : 0) : -1; }
+int iwdft_prefill_kind(const iwdft_ctx* ctx) {
+  return ctx ? (ctx->plan.use_fft_prefill ? 1 : (ctx->plan.use_chirp_prefill ? 2 : 0)) : -1;
+}
 
 int iwdft_attn_pipelined(const iwdft_ctx* ctx) { return ctx ? (attn_pipelines(ctx->P, ctx->plan.use_fft) ? 1 : 0) : -1; }
 

@@ -831,9 +831,13 @@ def test_paper_windows_on_a_context_that_is_a_power_of_two_full_size():
     assert cfg.n_prefill == 8192
     bins = wl.layer_bins(cfg)
     c = make_cache(cfg, bins)
-    assert B.iwdft_attn_kind(c.ctx) == "chirp" and B.iwdft_prefill_kind(c.ctx) == "dense"
+    assert B.iwdft_attn_kind(c.ctx) == "chirp" and B.iwdft_prefill_kind(c.ctx) == "chirp"
     c.close()
+    d = make_cache(cfg, bins, flags=B.IWDFT_FLAG_DENSE_PREFILL)
+    assert B.iwdft_attn_kind(d.ctx) == "chirp" and B.iwdft_prefill_kind(d.ctx) == "dense"
+    d.close()
     run_stream(cfg, bins, steps=3, tag="cfg2w-8132")
+    run_stream(cfg, bins, flags=B.IWDFT_FLAG_DENSE_PREFILL, steps=1, tag="cfg2w-8132-dense")
     run_stream(cfg, bins, steps=3, fused=True, tag="cfg2w-8132-fused")
 
 
@@ -973,6 +977,9 @@ def test_misaligned_tensors_are_refused_before_any_launch():
 def test_chirp_prefill_all_convolution_lengths(dtype, L, S, R, n_bins, n_layers):
     cfg = small_cfg(L=L, dtype=dtype, n_bins=n_bins, n_sink=S, n_recent=R, steps=1, n_layers=n_layers,
                     batch=2 if n_layers > 1 else 1, n_kv_heads=8 if n_layers > 2 else 2)
+    c = make_cache(cfg, random_bins(cfg, 53))
+    assert B.iwdft_prefill_kind(c.ctx) == "chirp"
+    c.close()
     st = run_stream(cfg, random_bins(cfg, 53), rec=(3, 20), tag=f"chirppf-{dtype}-L{L}")
     assert st["coef0"] < 2e-5
 
@@ -988,6 +995,7 @@ def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_on
     V[..., 1] = 0.0
     V[..., 100, 6] = float("inf")
     c = make_cache(cfg, bins)
+    assert B.iwdft_prefill_kind(c.ctx) == "chirp"
     c.prefill(K, V)
     for name, X, got in zip("KV", (K, V), c.export_coeffs(0)):
         X = X.nan_to_num(0.0, 0.0, 0.0)
