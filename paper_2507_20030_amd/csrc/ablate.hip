@@ -84,7 +84,7 @@ template <bool BF16>
 __global__ __launch_bounds__(kFftThreads, 2) void ablate_long_kernel(const char* __restrict__ x, char* __restrict__ out,
                                                                     int n_slices, int per_xcd, uint32_t M, int lo,
                                                                     int hi) {
-  extern __shared__ float2 smem[];
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
   constexpr int LOGQ = kFftMaxLogQ, Q = 1 << LOGQ, H = Q / 2, IT = H / kFftThreads;
   static_assert(LOGQ & 1, "written for the odd transform length 2^13");
   constexpr int kElem = BF16 ? 2 : 4;

@@ -21,7 +21,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
                                                                       float* __restrict__ ps) {
   constexpr int T = fft_threads(LOGN), NWV = T < 64 ? 1 : T / 64;
   constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
-  extern __shared__ float2 buf[];
+  extern __shared__ __attribute__((aligned(16))) float2 buf[];
   __shared__ float2 smax[NWV], ssum[NWV];
   __shared__ float pscr[NWV][2 * kMaxPend];
   const TabMem tab{P.tab + tab_base(LOGN)};

@@ -172,7 +172,7 @@ template <bool BF16, bool FULL>
 __global__ __launch_bounds__(kPfThreads) void prefill_mfma_kernel(Params P, const void* __restrict__ K,
                                                                  const void* __restrict__ V, int nt,
                                                                  int per_xcd, int total) {
-  extern __shared__ _Float16 lds[];
+  extern __shared__ __attribute__((aligned(16))) _Float16 lds[];
   constexpr int kParts = BF16 ? 1 : 2;
   constexpr int kBufHalves = kParts * kPfCh * kPfRS;
   constexpr int kSteps = kPfTok / 16;

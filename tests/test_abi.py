@@ -140,3 +140,15 @@ def test_plan_accepts_long_contexts_with_a_small_divisor_and_the_direct_sums_on_
     assert B.iwdft_query_bytes(desc(M=(1 << 20) - 64 * 1, bins=big))[0] > 0
     assert B.iwdft_query_bytes(desc(M=1048583, bins=big, flags=B.IWDFT_FLAG_DIRECT_SYNTHESIS))[0] > 0
     assert B.iwdft_query_bytes(desc(M=10007, bins=big))[0] > 0      # 10007 * 2048 terms: the direct sums are fine
+
+
+def test_dynamic_lds_is_declared_for_16_byte_accesses():
+    """Static arrays are placed in front of dynamic LDS: without the attribute its start is only as aligned as its element."""
+    csrc = os.path.join(ROOT, "paper_2507_20030_amd", "csrc")
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        for line in open(os.path.join(csrc, name)):
+            if "extern __shared__" in line:
+                found += 1
+                assert "__attribute__((aligned(16)))" in line, (name, line.strip())
+    assert found >= 8
