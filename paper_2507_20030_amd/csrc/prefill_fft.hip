@@ -347,8 +347,10 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   }
   const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
   // Pairs per thread: as many as the register budget (128) holds next to the transform (the staged samples take 16
-  // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.
-  const bool few = (uint64_t)n_st * (kPairs / 4 / side_ns(logQ)) < kFewWorkgroups;
+  // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.  At 256
+  // points the 32 transforms side by side cover 128 bytes of a row with one pair each (512 slices, 64 bins, two pairs / one:
+  // 30 / 25 us, fp32 40 / 33).
+  const bool few = (uint64_t)n_st * (kPairs / 4) < kFewWorkgroups * (uint64_t)side_ns(logQ);
 #define IWDFT_PF_CASE(LQ, MULTI, NP, EQ)                                                                    \
   {                                                                                                         \
     const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                          \
@@ -362,7 +364,7 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   }
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
-    constexpr int kNp = (LQ == 8 || !BF16) ? 2 : 4;                                \
+    constexpr int kNp = LQ == 8 ? 1 : BF16 ? 4 : 2;                                \
     constexpr bool kAll = (1 << LQ) >= kFftAloneBins; /* shorter: never as many */ \
     if (kAll && !eq) {                                                             \
       if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp, !kAll)                       \
