@@ -76,15 +76,15 @@ enum {
                                        below.  The FFT and chirp-z prefills have no such
                                        limits, but two neighbouring channels (2 i, 2 i + 1)
                                        share a transform: in the FFT prefill of contexts
-                                       with 384 or more kept bins in some layer (or
-                                       M > 2^26) the smaller one has the fp32 rounding of
-                                       the larger one, and a value that is not finite
-                                       reaches both.  Otherwise, and in the chirp-z
-                                       prefill, each is as exact as alone.  All transforms
-                                       of this library (attention, reconstruction and
-                                       ablation too) hold sums up to 2^97: values times
-                                       their number's square root, 6-fold at the peaks,
-                                       have to stay below.                            */
+                                       with 384 or more kept bins in some layer, or with
+                                       IWDFT_FLAG_FFT_PREFILL, the smaller one has the
+                                       fp32 rounding of the larger one, and a value that
+                                       is not finite reaches both.  Otherwise, and in the
+                                       chirp-z prefill, each is as exact as alone.  All
+                                       transforms of this library (attention,
+                                       reconstruction and ablation too) hold sums up to
+                                       2^97: values times their number's square root,
+                                       6-fold at the peaks, have to stay below.       */
   IWDFT_FLAG_FFT_PREFILL = 4u,      /* iwdft_prefill always runs FFTs + pruning; needs
                                        M = 2^m >= 256, else IWDFT_ERR_UNSUPPORTED (layers
                                        with more than 4096 kept bins take a form that

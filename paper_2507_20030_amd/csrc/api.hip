@@ -57,6 +57,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int64_t tw_Q = 0;              // length of the twiddle octant at off_tw in the state buffer (kept for copies of it; nothing reads it)
   size_t off_tw = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
+  bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
   size_t off_layers = 0, off_bins = 0, off_weights = 0, off_fold = 0, off_FK = 0, off_FV = 0, state_bytes = 0;
   size_t off_sinkK = 0, off_sinkV = 0, off_ringK = 0, off_ringV = 0;
@@ -162,6 +163,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
                            (d->M <= (int64_t)kStreamMaxM &&
                             (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M)));
   }
+  // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
+  pl->scale_pairs = pl->use_fft_prefill && !(d->flags & IWDFT_FLAG_FFT_PREFILL) && pl->max_nb < kFftAloneBins;
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
   // of M / Pb points, Pb the smallest divisor of M that brings the block down to 8192 (none: the direct sums).
   pl->use_chirp = false;
@@ -557,6 +560,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.FV = (float2*)(c->state + pl.off_FV);
     P.gain = 1.0f;
     P.x_scale = 1.0f;
+    P.scale_pairs = pl.scale_pairs ? 1 : 0;
     P.serial_phases = (desc->flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : 0;
     P.S = desc->n_sink;
     P.R = desc->n_recent;

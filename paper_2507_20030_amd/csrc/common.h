@@ -60,6 +60,7 @@ struct Params {
   // absorbed token enters scaled by x_scale = M / (T + 1), and everything that reads the coefficients as the
   // paper's S_T (reconstruction, scores, outputs) applies the extra gain = T / M.
   float gain, x_scale;
+  int32_t scale_pairs;    // FFT prefill: channels of a pair scaled to one size
   int32_t serial_phases;  // IWDFT_FLAG_SERIAL_PHASES: never pipeline kernels A and B over groups of slices
   int32_t S, R;
   void* sinkK;
@@ -159,9 +160,9 @@ __device__ __forceinline__ void store_kv(void* p, int64_t i, float v) {
 // Host-side launchers (defined next to their kernels).  Each validates nothing: the C ABI
 // layer has already checked every shape.  They return the hipError_t of the launch.
 hipError_t launch_prefill(const Params& P, const void* K, const void* V, hipStream_t st);
-// The same transform through in-LDS FFTs; prefill_fft_ok: M is a power of two >= 256.  Layers that all keep fewer than
-// kFftAloneBins bins (and M <= kStreamMaxM) get every channel as exact as alone, as the contraction computes it; otherwise two
-// neighbouring channels share the rounding of the larger one.  launch_prefill_edges copies the sink / recent tokens (all
+// The same transform through in-LDS FFTs; prefill_fft_ok: M is a power of two >= 256.  Params::scale_pairs
+// (fewer than kFftAloneBins bins, M <= kStreamMaxM): every channel as exact as alone, as the contraction computes it; otherwise
+// two neighbouring channels share the rounding of the larger one.  launch_prefill_edges copies the sink / recent tokens (all
 // prefills).
 constexpr int kFftAloneBins = 384;
 constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples

@@ -72,6 +72,10 @@ __device__ __forceinline__ uint32_t word_max(uint32_t a, uint32_t b) {  // of ma
     return max(a, b);
   }
 }
+template <int N>
+__device__ __forceinline__ uint32_t row_ror(uint32_t v) {  // the value N lanes further in the row of 16
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xf, 0xf, false);
+}
 template <bool BF16, int NS, int NW, int NP>
 __device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[16], int tid, uint32_t (&red)[8][NS][NW], PairScale (&sc)[NP]) {
   static_assert(NW == NP * (BF16 ? 1 : 2) && NS <= 32, "");
@@ -81,9 +85,21 @@ __device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[16], int tid, uint32_t 
     m[n] = 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) m[n] = word_max<BF16>(m[n], z[i].w[n] & (BF16 ? 0x7fff7fffu : 0x7fffffffu));
+    // over the lanes of the same transform: rotations inside the rows of 16 lanes, then the rows
+    if constexpr (NS <= 8) m[n] = word_max<BF16>(m[n], row_ror<8>(m[n]));
+    if constexpr (NS <= 4) m[n] = word_max<BF16>(m[n], row_ror<4>(m[n]));
+    if constexpr (NS <= 2) m[n] = word_max<BF16>(m[n], row_ror<2>(m[n]));
+    if constexpr (NS <= 1) m[n] = word_max<BF16>(m[n], row_ror<1>(m[n]));
+  }
 #pragma unroll
-    for (int o = 32; o >= NS; o >>= 1) m[n] = word_max<BF16>(m[n], (uint32_t)__shfl_xor((int)m[n], o));
-    if ((tid & 63) < NS) red[tid >> 6][tid & (NS - 1)][n] = m[n];
+  for (int o = 16; o <= 32; o *= 2) {
+#pragma unroll
+    for (int n = 0; n < NW; ++n)
+      if (o >= NS) m[n] = word_max<BF16>(m[n], (uint32_t)__shfl_xor((int)m[n], o));
+  }
+  if ((tid & 63) < NS) {
+#pragma unroll
+    for (int n = 0; n < NW; ++n) red[tid >> 6][tid & (NS - 1)][n] = m[n];
   }
   __syncthreads();
 #pragma unroll

@@ -316,11 +316,11 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   const int per_xcd = (n_st + 7) / 8;
   // several pairs per load need 16-byte aligned tensors (and rows, which are 256 or 512 bytes)
   const bool wide = (((uintptr_t)K | (uintptr_t)V) & 15u) == 0;
-  // Below kFftAloneBins the channels of a pair are scaled to one size: without a flag these contexts take the FFT for its speed
-  // only, and the contraction it replaces keeps every channel alone (8192 points, a channel 2^11 below its partner: 1.8e-4
-  // relative error in an unscaled transform).  It costs 31 packed maxima and 16 products per pair and a barrier: 32 x 8 slices
-  // of 8192 tokens, 2048 bins, bf16 794 us against 730 without.
-  const bool eq = P.max_nb < kFftAloneBins;
+  // Contexts of few bins take the FFT for its speed only, and the contraction it replaces keeps every channel alone (8192 points,
+  // a channel 2^11 below its partner: 1.8e-4 relative error in an unscaled transform): there the channels of a pair are scaled to
+  // one size.  It costs 31 packed maxima and 16 products per pair and a barrier: 256 slices of 8192 tokens, 128 bins, bf16 622 us
+  // against 547 without, fp32 876 / 861.
+  const bool eq = P.scale_pairs != 0;
   hipError_t e = hipSuccess;
   if (logM > kFftMaxLogQ && P.max_nb <= 4096 && P.M <= kStreamMaxM) {
 #define IWDFT_PF_STREAM(NBT, NP, EQ)                                                                          \
@@ -365,10 +365,9 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
     constexpr int kNp = LQ == 8 ? 1 : BF16 ? 4 : 2;                                \
-    constexpr bool kAll = (1 << LQ) >= kFftAloneBins; /* shorter: never as many */ \
-    if (kAll && !eq) {                                                             \
-      if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp, !kAll)                       \
-      else IWDFT_PF_CASE(LQ, false, 1, !kAll)                                      \
+    if (!eq) {                                                                     \
+      if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp, false)                       \
+      else IWDFT_PF_CASE(LQ, false, 1, false)                                      \
     } else if (wide && !few) {                                                     \
       IWDFT_PF_CASE(LQ, false, kNp, true)                                          \
     } else {                                                                       \
