@@ -90,7 +90,8 @@ enum {
                                        with more than 4096 kept bins take a form that
                                        keeps nothing per bin in registers).  With neither flag
                                        the library picks: FFT when it applies and some
-                                       layer keeps >= 128 bins or >= M / 32; other M: chirp-z
+                                       layer keeps >= 128 bins or >= M / 32 (with fewer
+                                       than 384 only where it is faster); other M: chirp-z
                                        transforms where the attention has them (see
                                        iwdft_attn_kind) and they are faster        */
   IWDFT_FLAG_SHORTCUT = 8u,         /* the variant of the update that Sec. 4.1 mentions for long

@@ -68,7 +68,8 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
 // decode attention itself takes any number through its bin-strided kernel.
 constexpr int kFftMaxBins = 4096;
 // Prefill without a flag, M = 2^m: FFTs from this many kept bins in some layer, or from 1 / kFftPrefillMinShare of all bins.
-constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32;
+constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32, kFftPrefillRoundM = 2048;
+constexpr int kFftPrefillRound16 = 144, kFftPrefillRound32 = 168;  // slices per round of the contraction, bf16 and fp32
 constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit in LDS)
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
@@ -148,10 +149,16 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
 
   const bool pow2 = (d->M & (d->M - 1)) == 0;
   pl->use_fft = pow2 && (uint64_t)d->M >= kFftMinM && !(d->flags & IWDFT_FLAG_DIRECT_SYNTHESIS);
-  // Prefill: the FFT costs about the same whatever the number of kept bins, the dense contraction grows with it in steps of
-  // 128.  Measured (16 layers x 8 heads, bf16, dense / FFT): M = 1024, 64 bins 52 / 30 us; M = 4096, 256 bins 235 / 134;
-  // M = 8192, 128 bins 336 / 282; one layer, M = 1024, 64 bins, fp32: 78 / 7.5.  The FFT is ahead below the line too (M = 4096,
-  // 64 bins: 177 / 116), but there iwdft_prefill_kind has always answered "dense", with that path's documented input range.
+  // Prefill: the FFT costs about the same whatever the number of kept bins and in proportion to the slices; the dense contraction
+  // grows with the bins in steps of 128 and walks the tokens once per round of 256 workgroups (slices x steps), whether or not
+  // the last round is full.  Measured (bf16, dense / FFT, us): 128 slices, M = 1024, 64 bins 52 / 30; M = 4096, 256 bins
+  // 235 / 134; M = 8192, 128 bins 336 / 282; one layer of 8, M = 1024, 64 bins, fp32: 78 / 7.3.  256 slices, 128 bins, one full
+  // round: M = 2048 127 / 131, M = 8192 471 / 622, M = 16384 930 / 1220 (fp32 838 / 876, 1664 / 2185); 160 slices 357 / 396,
+  // 713 / 761 (fp32 703 / 548, 1391 / 1326); 64 slices, M = 65536: 2594 / 1081.  So the contraction stays where a round has more
+  // than kFftPrefillRound16 / 32 slices.  Below kFftPrefillMinBins and kFftPrefillMinShare it stays as well, though not for speed
+  // (M = 4096, 64 bins, 128 slices: 177 / 116): such contexts keep its result.
+  const int64_t S = slices_per_layer * d->n_layers, rounds = (S * ((pl->max_nb + 127) / 128) + 255) / 256;
+  const int64_t round_slices = d->kv_dtype == IWDFT_BF16 ? kFftPrefillRound16 : kFftPrefillRound32;
   const bool fft_pf_ok = pow2 && (uint64_t)d->M >= kFftMinM;
   if (d->flags & IWDFT_FLAG_FFT_PREFILL) {
     if (!fft_pf_ok)
@@ -160,7 +167,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   } else {
     pl->use_fft_prefill = fft_pf_ok && !(d->flags & IWDFT_FLAG_DENSE_PREFILL) &&
                           (pl->max_nb >= kFftAloneBins ||
-                           (d->M <= (int64_t)kStreamMaxM &&
+                           (d->M <= (int64_t)kStreamMaxM && (d->M < kFftPrefillRoundM || S <= round_slices * rounds) &&
                             (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M)));
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
@@ -218,9 +225,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // 224 / 113; S = 64, M = 9000, 640 bins 898 / 965; S = 32, M = 32708, 4096 bins 7300 / 1500.
   // Longer M with blocks of a few points only stay with the contraction.
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
-    const int64_t S = slices_per_layer * d->n_layers, Pb = d->M / pl->chirp_Q;
+    const int64_t Pb = d->M / pl->chirp_Q;
     const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
-    const int64_t rounds = (S * ((pl->max_nb + 127) / 128) + 255) / 256;
     pl->use_chirp_prefill = S * points <= kChirpPrefillPoints * d->M * rounds;
   }
 

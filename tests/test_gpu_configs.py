@@ -217,6 +217,19 @@ def test_pipelined_and_serial_phases_agree_bit_for_bit(group, n_bins, shape, dty
     b.close()
 
 
+@pytest.mark.parametrize("L,slices,n_bins,kind", [
+    (16384, 144, 128, "fft"), (16384, 145, 128, "dense"), (8192, 256, 128, "dense"), (8192, 257, 128, "fft"),  # a second round
+    (8192, 256, 129, "fft"), (65536, 64, 128, "fft"), (8192, 256, 384, "fft"), (2048, 256, 128, "dense"), (1024, 256, 128, "fft"),
+    (16384, 64, 127, "dense"),
+])
+def test_prefill_takes_the_contraction_where_its_workgroups_fill_the_device(L, slices, n_bins, kind):
+    """Contexts of fewer than 384 kept bins: the FFT costs in proportion to the slices, the contraction one walk over the tokens
+    per round of 256 workgroups (slices x tiles of 128 bins)."""
+    c = B.Cache(1, 1, slices, slices, 128, torch.bfloat16, L, [np.arange(n_bins, dtype=np.int32)], device=DEV)
+    assert B.iwdft_prefill_kind(c.ctx) == kind
+    c.close()
+
+
 def test_cfg3_shape_with_8192_kept_bins_full_size():
     """A quarter of the bins of a 32768-token context (the paper's largest ratio) at cfg3's full shape: bin-strided FFT
     prefill and decode attention, two calls and the fused step, on sampled slices against the oracle."""
