@@ -54,7 +54,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int chirp_logS = 0;            // length of the table in the state buffer (kept for copies of it; nothing reads it)
   int64_t chirp_Q = 0;           // points per chirp-z transform: M / Pb (M itself up to 8192)
   size_t off_chirp = 0, off_chirpS = 0, off_chirpW = 0;
-  int64_t tw_Q = 0;              // length of the twiddle octant at off_tw in the state buffer (kept for copies of it; nothing reads it)
+  int64_t tw_Q = 0;              // length of the transforms whose twiddle octant is at off_tw
   size_t off_tw = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
   bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
@@ -562,6 +562,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.chirp_logN = pl.chirp_logN;
     P.chirp_Q = (uint32_t)pl.chirp_Q;
     P.tab = tab;
+    P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;
     P.FK = (float2*)(c->state + pl.off_FK);
     P.FV = (float2*)(c->state + pl.off_FV);
     P.gain = 1.0f;

@@ -52,6 +52,7 @@ struct Params {
   int32_t chirp_logN;
   uint32_t chirp_Q;
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
+  const float2* tw8;  // e^{j 2 pi m / Q}, m = 0 .. Q / 8, Q = min(M, 8192), for fft_lds.h (null unless M = 2^m >= 256)
   float2* FK;
   float2* FV;
   // Exact tokens (Sec. 4.2.1): S sink tokens and a ring of R recent tokens per slice, kv_dtype,

@@ -1,6 +1,6 @@
 // In-LDS complex FFT of 2^LOGQ points for one workgroup of 512 threads: radix-16 register passes (two radix-4 stages per LDS
 // round trip), twiddles from an octant table in LDS, data padded by one element per 32.  Used by the ablation of contexts
-// longer than 8192 tokens only; everything else runs on fft_core.h.
+// longer than 8192 tokens and by prefill_rows_kernel; everything else runs on fft_core.h.
 #pragma once
 #include "common.h"
 #include "fft_core.h"

@@ -8,12 +8,15 @@
 // X_c0[k] = (Z[k] + conj Z[-k]) / 2, X_c1[k] = (Z[k] - conj Z[-k]) / (2j).  M > 8192: the token axis is
 // decimated by Pb = M / 8192, n = Pb a + b, so that
 //   U[k] = sum_b e^{-j 2 pi k b / M} * DFT_8192( x[Pb a + b] )[k mod 8192],
-// one in-LDS transform per residue b, accumulated per kept bin in registers (only the kept bins are
-// ever formed).  Each thread reads a few bytes (1, 2 or 4 bf16 pairs) of a 256-byte token row, so the
-// workgroups of one (slice, tensor) are placed on one XCD next to each other in time and share the rows
-// in that XCD's L2: HBM delivers every row once.
+// one in-LDS transform per residue b (only the kept bins are ever formed).  Each lane reads 4 to 16 bytes
+// of a token row (256 or 512), so the workgroups of one (slice, tensor) are placed on one XCD next to each
+// other in time and share the rows in that XCD's L2: HBM delivers every row once.
+//
+// Three kernels: prefill_fft_kernel (M <= 8192), prefill_stream_kernel (longer M, running sums in
+// registers, 4096 bins a launch) and prefill_rows_kernel (longer M and more bins, sums in the output rows).
 #include "common.h"
 #include "fft_core.h"
+#include "fft_lds.h"
 #include "pair_io.h"
 
 namespace iwdft {
@@ -29,10 +32,8 @@ constexpr int kPairs = kHeadDim / 2;  // channel pairs per (slice, tensor)
 // A thread's 16 samples are the 16 consecutive positions that the first radix-16 pass combines: that pass runs on the
 // loaded words and the samples go to LDS once, behind it; the last radix-2 stage (M >= 8192, M = 512) is formed at the kept
 // bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
-// MULTI (M > 8192): the running sums over the residues live in the output rows (every bin belongs to one thread, which
-// reads back its own earlier store).
 // EQ: the two channels of a pair are scaled to one size on the way (pair_scale), each as exact as alone; see the launcher.
-template <int LOGQ, bool BF16, bool MULTI, int NP, bool EQ>
+template <int LOGQ, bool BF16, int NP, bool EQ>
 __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
                                                             const void* __restrict__ V, int per_xcd, int n_st) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
@@ -61,95 +62,153 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
   const int t = tid / NS;                      // thread of transform tid % NS
   float2* buf = smem + (tid % NS) * BS;
   const char* X = (const char*)(tensor ? V : K) + ((int64_t)slice * N + P.S) * kRow + (pair0 + (tid % NS) * NP) * 2 * kElem;
-  const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
   // the pruning goes through the transforms one after the other: consecutive threads, consecutive bins
   const int tp = tid % T;
   const float2* spec = smem + (tid / T) * BS;
   float2* F = (tensor ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + (pair0 + (tid / T) * NP) * 2) * L.Bp;
 
-  const int64_t step = (int64_t)Pb * kRow;  // bytes between consecutive samples of one residue
-  for (uint32_t b = 0; b < Pb; ++b) {
-    // The thread index is made opaque per iteration so that the address arithmetic of the transform
-    // passes is recomputed (a few instructions) instead of being hoisted out of the residue loop into
-    // long-lived registers that would spill.
-    int lt = t;
-    if (MULTI) asm volatile("" : "+v"(lt));
-    Raw<NW> z[16];
-    const char* Xb = X + (int64_t)b * kRow + (int64_t)sample_at<LOGQ>(16 * lt) * step;
+  Raw<NW> z[16];
+  const char* X0 = X + (int64_t)sample_at<LOGQ>(16 * t) * kRow;
 #pragma unroll
-    for (int m = 0; m < 16; ++m)  // position 16 t + m holds sample_at(16 t) + (digits of m reversed) Q / 16
-      z[m] = load_raw<NW>(Xb + (int64_t)((((m & 3) << 2) | (m >> 2)) * (Q / 16)) * step);
-    PairScale sc[NP];
-    if constexpr (EQ) {
-      scale_pairs<BF16>(z, tid, maxima, sc);
-      if (NS > 1 && tid < NS) {
+  for (int m = 0; m < 16; ++m) z[m] = load_raw<NW>(X0 + sample_step<LOGQ>(m) * kRow);
+  PairScale sc[NP];
+  if constexpr (EQ) {
+    scale_pairs<BF16>(z, tid, maxima, sc);
+    if (NS > 1 && tid < NS) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) halves[tid][p] = make_float2(sc[p].h0, sc[p].h1);
+      for (int p = 0; p < NP; ++p) halves[tid][p] = make_float2(sc[p].h0, sc[p].h1);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    float2 x[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      x[m] = raw_front<BF16, NW>(z[m]);
+      if constexpr (EQ) x[m].y *= sc[p].up;
+      raw_pop<BF16, NW>(z[m]);
+    }
+    float2* F0 = F + (int64_t)(2 * p) * L.Bp;
+    // kept bins of this thread, four at a time; the first four are fetched while the transform runs
+    constexpr int U = 4;
+    uint32_t kj[U];
+    float2 wj[U];
+    auto fetch_bins = [&](int i0) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = i0 + j * T;
+        kj[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
       }
+    };
+    auto fetch_tw = [&](int k) {
+      if (k != fft_np(LOGQ) - 1) return;
+#pragma unroll
+      for (int j = 0; j < U; ++j) wj[j] = pair_twiddle<LOGQ>(tab.tab, kj[j] & (Q - 1));
+    };
+    fetch_bins(pin_index(tp));
+    fft_forward<LOGQ>(buf, tab, t, x, fetch_tw);
+    float2 h = make_float2(0.5f, 0.5f);
+    if constexpr (EQ) h = NS > 1 ? halves[tid / T][p] : make_float2(sc[p].h0, sc[p].h1);
+    for (int i0 = tp; i0 < L.nb; i0 += U * T) {
+      if (i0 >= U * T) {
+        fetch_bins(i0);
+        fetch_tw(fft_np(LOGQ) - 1);
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = i0 + j * T;
+        if (i < L.nb) {
+          float2 w1, w2;
+          spectrum_pair<LOGQ>(spec, kj[j] & (Q - 1), wj[j], w1, w2);
+          F0[i] = make_float2(h.x * (w1.x + w2.x), h.x * (w1.y - w2.y));
+          F0[L.Bp + i] = make_float2(h.y * (w1.y + w2.y), h.y * (w2.x - w1.x));
+        }
+      }
+    }
+    __syncthreads();  // the next transform overwrites buf
+  }
+}
+
+// M > 8192 and more kept bins than registers hold (prefill_stream_kernel): the running sums over the residues live in the output
+// rows, every bin belongs to one thread, which reads back its own earlier store.  On the transforms of fft_lds.h, whose twiddles
+// sit in LDS: vector memory answers in order, and table loads between the stores of the sums and the next transform waited for
+// these (on fft_core.h, 256 slices of 16384 tokens, 4200 bins: bf16 3.03 ms, fp32 4.18; here 2.65 and 3.51).
+template <bool BF16, int NP>
+__global__ __launch_bounds__(kFftThreads, 4) void prefill_rows_kernel(Params P, const void* __restrict__ K,
+                                                                     const void* __restrict__ V, int per_xcd, int n_st) {
+  extern __shared__ __attribute__((aligned(16))) float2 buf[];
+  constexpr int LOGQ = kFftMaxLogQ, Q = 1 << LOGQ, H = Q / 2, IT = H / kFftThreads;
+  static_assert(LOGQ & 1, "written for the odd transform length 2^13");
+  constexpr int kElem = BF16 ? 2 : 4;
+  constexpr int kRow = kHeadDim * kElem;  // bytes per token row
+  constexpr int NW = NP * (BF16 ? 1 : 2);
+  constexpr int kGroups = kPairs / NP;    // workgroups per (slice, tensor)
+  float2* tab = buf + Q + (Q >> 5);
+  const int tid = threadIdx.x;
+  const uint32_t idx = blockIdx.x >> 3;
+  const uint32_t st = (blockIdx.x & 7u) * (uint32_t)per_xcd + idx / kGroups;
+  if (st >= (uint32_t)n_st) return;
+  const int pair0 = (idx % kGroups) * NP;
+  const int slice = st >> 1;
+  const int spl = P.batch * P.n_kv;
+  const int layer = slice / spl;
+  const LayerInfo L = layer_info(P, layer);
+  const int32_t* bins = P.bins + L.bin_off;
+  const int64_t N = (int64_t)P.S + P.M + P.R;  // tokens per slice in the caller's tensor
+  const char* X = (const char*)((st & 1) ? V : K) + ((int64_t)slice * N + P.S) * kRow + pair0 * 2 * kElem;
+  const uint32_t Pb = P.M >> LOGQ;
+  const int64_t step = (int64_t)Pb * kRow;  // bytes between consecutive samples of one residue
+  float2* F = ((st & 1) ? P.FV : P.FK) + L.coef_off + ((int64_t)(slice - layer * spl) * kHeadDim + pair0 * 2) * L.Bp;
+
+  for (int m = tid; m <= (Q >> 3); m += kFftThreads) tab[m] = P.tw8[m];  // e^{j 2 pi m / Q}, host-made
+
+  for (uint32_t b = 0; b < Pb; ++b) {
+    int lt = tid;
+    asm volatile("" : "+v"(lt));  // keeps the passes' address arithmetic out of long-lived registers
+    const char* Xb = X + (int64_t)b * kRow;
+    // Consecutive threads own consecutive LDS positions (their stores fall into distinct banks) and fetch the samples that
+    // belong there, a and a + Q / 2 for the first radix-2 stage.
+    Raw<NW> za[IT], zc[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int a = digit_pos<LOGQ - 1>(it * kFftThreads + lt);  // digit reversal is its own inverse
+      za[it] = load_raw<NW>(Xb + (int64_t)a * step);
+      zc[it] = load_raw<NW>(Xb + (int64_t)(a + H) * step);
     }
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      float2 x[16];
 #pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        x[m] = raw_front<BF16, NW>(z[m]);
-        if constexpr (EQ) x[m].y *= sc[p].up;
-        raw_pop<BF16, NW>(z[m]);
+      for (int it = 0; it < IT; ++it) {
+        const int pos = 2 * (it * kFftThreads + lt);
+        const float2 u = raw_front<BF16, NW>(za[it]), v = raw_front<BF16, NW>(zc[it]);
+        raw_pop<BF16, NW>(za[it]);
+        raw_pop<BF16, NW>(zc[it]);
+        buf[pad(pos)] = cadd(u, v);
+        buf[pad(pos + 1)] = csub(u, v);
       }
+      __syncthreads();  // (the first time also publishes tab)
+      fft_dit<LOGQ>(buf, tab, lt);
       float2* F0 = F + (int64_t)(2 * p) * L.Bp;
-      // kept bins of this thread, four at a time; the first four are fetched while the transform runs
-      constexpr int U = 4;
-      uint32_t kj[U];
-      float2 wj[U];
-      auto fetch_bins = [&](int i0) {
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-          const int i = i0 + j * T;
-          kj[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
+      for (int i = tid; i < L.nb; i += kFftThreads) {
+        const uint32_t kj = (uint32_t)bins[i];
+        const int r = kj & (Q - 1), rm = (Q - r) & (Q - 1);
+        const float2 w1 = buf[pad(r)], w2 = buf[pad(rm)];
+        const float2 tw = conjf2(cis_poly2((kj * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
+        float2 d0 = cmul(tw, make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y)));
+        float2 d1 = cmul(tw, make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x)));
+        if (b) {
+          d0 = cadd(F0[i], d0);
+          d1 = cadd(F0[L.Bp + i], d1);
         }
-      };
-      auto fetch_tw = [&](int k) {
-        if (k != fft_np(LOGQ) - 1) return;
-#pragma unroll
-        for (int j = 0; j < U; ++j) wj[j] = pair_twiddle<LOGQ>(tab.tab, kj[j] & (Q - 1));
-      };
-      fetch_bins(pin_index(tp));
-      fft_forward<LOGQ>(buf, tab, lt, x, fetch_tw);
-      float2 h = make_float2(0.5f, 0.5f);
-      if constexpr (EQ) h = NS > 1 ? halves[tid / T][p] : make_float2(sc[p].h0, sc[p].h1);
-      for (int i0 = tp; i0 < L.nb; i0 += U * T) {
-        if (i0 >= U * T) {
-          fetch_bins(i0);
-          fetch_tw(fft_np(LOGQ) - 1);
-        }
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-          const int i = i0 + j * T;
-          if (i < L.nb) {
-            float2 w1, w2;
-            spectrum_pair<LOGQ>(spec, kj[j] & (Q - 1), wj[j], w1, w2);
-            float2 d0 = make_float2(h.x * (w1.x + w2.x), h.x * (w1.y - w2.y));
-            float2 d1 = make_float2(h.y * (w1.y + w2.y), h.y * (w2.x - w1.x));
-            if constexpr (MULTI) {
-              const float2 tw = conjf2(cis_poly2((kj[j] * b) & (P.M - 1u), P.M));  // e^{-j 2 pi k b / M}
-              d0 = cmul(tw, d0);
-              d1 = cmul(tw, d1);
-              if (b) {
-                d0 = cadd(F0[i], d0);
-                d1 = cadd(F0[L.Bp + i], d1);
-              }
-            }
-            F0[i] = d0;
-            F0[L.Bp + i] = d1;
-          }
-        }
+        F0[i] = d0;
+        F0[L.Bp + i] = d1;
       }
-      __syncthreads();  // the next transform overwrites buf
+      __syncthreads();  // the next pair overwrites buf
     }
   }
 }
 
-// M > 8192 and up to NBT * 512 kept bins per layer: one persistent workgroup per CU walks the (slice, tensor, NP channel
+// M > 8192, NBT * 512 kept bins per layer and launch: one persistent workgroup per CU walks the (slice, tensor, NP channel
 // pairs) items of its XCD and their residues with the running sums of all kept bins in registers (which is why there is
 // one), and fetches the samples of the next step while it transforms the pairs of the current one, a row or so per phase: a
 // wave that issues more than the address queue takes stalls, and the barriers make the others wait.  Vector memory answers
@@ -161,7 +220,7 @@ __global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const voi
 template <bool BF16, int NBT, int NP, bool EQ>
 __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const void* __restrict__ K,
                                                                const void* __restrict__ V, int per_xcd, int n_st,
-                                                               int slots) {
+                                                               int slots, int bin0) {
   constexpr int LOGQ = 13, Q = 1 << LOGQ, H = Q / 2, T = 512;
   static_assert(fft_threads(LOGQ) == T && kFftMaxLogQ == LOGQ, "");
   constexpr int kElem = BF16 ? 2 : 4;
@@ -177,12 +236,23 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
   const uint32_t xcd = blockIdx.x & 7u;
   const int st_first = (int)xcd * per_xcd, st_count = min(per_xcd, n_st - st_first);
   const int n_items = st_count * kGroups;
-  int n = (int)(blockIdx.x >> 3);
+  const int spl = P.batch * P.n_kv;
+  auto layer_of = [&](int item) {  // this launch's bins of the item's layer: NBT * T from bin0 on
+    LayerInfo L = layer_info(P, ((st_first + item / kGroups) >> 1) / spl);
+    L.bin_off += bin0;
+    L.coef_off += bin0;
+    L.nb = min(L.nb - bin0, NBT * T);
+    return L;
+  };
+  auto with_bins = [&](int item) {  // the first of items item, item + slots, ... whose layer has any
+    while (item < n_items && layer_of(item).nb <= 0) item += slots;
+    return item;
+  };
+  int n = with_bins((int)(blockIdx.x >> 3));
   if (n >= n_items) return;  // the whole workgroup
   tab.fill<LOGQ>(ltab, tid);
 
   const uint32_t M = P.M, Pb = M >> LOGQ;
-  const int spl = P.batch * P.n_kv;
   const int64_t N = (int64_t)P.S + M + P.R;      // tokens per slice in the caller's tensor
   const uint32_t step = Pb * (uint32_t)kRow;     // bytes between consecutive samples of one residue
   const uint32_t voff = sample_at<LOGQ>(16 * tid) * step;  // < 2^32: the launcher checks M
@@ -193,7 +263,6 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
   auto fetch = [&](Raw<NW>& z, const char* base, uint32_t off, int m) {
     z = load_raw<NW>(base + (int64_t)((((m & 3) << 2) | (m >> 2)) * (Q / 16)) * step + off);
   };
-  auto layer_of = [&](int item) { return layer_info(P, ((st_first + item / kGroups) >> 1) / spl); };
 
   uint32_t kk[NBT];
   auto fetch_bins = [&](uint32_t (&k)[NBT], int bin_off, int nb) {
@@ -223,7 +292,7 @@ __global__ __launch_bounds__(512, 2) void prefill_stream_kernel(Params P, const 
     const int s = (st >> 1) - ((st >> 1) / spl) * spl;
     float2* F = ((st & 1) ? P.FV : P.FK) + L.coef_off + ((int64_t)s * kHeadDim + (n % kGroups) * (NP * 2)) * L.Bp;
     const bool last_b = b + 1 == Pb;
-    const int n1 = last_b ? n + slots : n;
+    const int n1 = last_b ? with_bins(n + slots) : n;
     const bool more = n1 < n_items;
     const uint32_t b1 = last_b ? 0u : b + 1;
     // at the very end the current rows are fetched once more instead of a branch
@@ -322,7 +391,11 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   // against 547 without, fp32 876 / 861.
   const bool eq = P.scale_pairs != 0;
   hipError_t e = hipSuccess;
-  if (logM > kFftMaxLogQ && P.max_nb <= 4096 && P.M <= kStreamMaxM) {
+  // More than 4096 bins: launch after launch where the tokens are read again in less time than the sums in the output rows take
+  // (launches / rows, ms; 64 slices, M = 32768, 8192 bins: bf16 2.37 / 2.40, fp32 2.16 / 2.57; 8 slices: 0.277 / 0.240, 0.287 /
+  // 0.345; 8 slices, M = 65536, 16384 bins: 1.13 / 1.07, 1.12 / 1.06; M = 262144, 8192 bins: 2.14 / 2.26, 2.03 / 3.63).
+  const bool stream = P.M <= kStreamMaxM && (P.max_nb <= 4096 || P.M >= (BF16 ? 131072u : 32768u));
+  if (logM > kFftMaxLogQ && stream) {
 #define IWDFT_PF_STREAM(NBT, NP, EQ)                                                                          \
   {                                                                                                           \
     const size_t bytes = sizeof(float2) * fft_lds(kFftMaxLogQ) +                                              \
@@ -332,52 +405,69 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
     e = lim.ensure((const void*)prefill_stream_kernel<BF16, NBT, NP, EQ>, (int)bytes);                        \
     if (e != hipSuccess) return e;                                                                            \
     prefill_stream_kernel<BF16, NBT, NP, EQ><<<dim3((uint32_t)slots * 8), dim3(512), bytes, st>>>(            \
-        P, K, V, per_xcd, n_st, slots);                                                                       \
+        P, K, V, per_xcd, n_st, slots, bin0);                                                                 \
   }
     constexpr int kNp = BF16 ? 4 : 2;
-    if (P.max_nb > 2048) {
-      if (wide) IWDFT_PF_STREAM(8, kNp, false) else IWDFT_PF_STREAM(8, 1, false)
-    } else if (!eq) {
-      if (wide) IWDFT_PF_STREAM(4, kNp, false) else IWDFT_PF_STREAM(4, 1, false)
-    } else {
-      if (wide) IWDFT_PF_STREAM(4, kNp, true) else IWDFT_PF_STREAM(4, 1, true)
+    for (int bin0 = 0; bin0 < P.max_nb; bin0 += 4096) {
+      if (P.max_nb - bin0 > 2048) {
+        if (wide) IWDFT_PF_STREAM(8, kNp, false) else IWDFT_PF_STREAM(8, 1, false)
+      } else if (!eq) {
+        if (wide) IWDFT_PF_STREAM(4, kNp, false) else IWDFT_PF_STREAM(4, 1, false)
+      } else {
+        if (wide) IWDFT_PF_STREAM(4, kNp, true) else IWDFT_PF_STREAM(4, 1, true)
+      }
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
     }
 #undef IWDFT_PF_STREAM
+    return hipSuccess;
+  }
+  if (logM > kFftMaxLogQ) {
+    const size_t bytes = sizeof(float2) * (size_t)fft_lds_float2(kFftMaxLogQ);
+#define IWDFT_PF_ROWS(NP)                                                                                          \
+  {                                                                                                                \
+    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / (NP)) * 8;                                               \
+    if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                               \
+    static LdsLimit lim;                                                                                           \
+    e = lim.ensure((const void*)prefill_rows_kernel<BF16, NP>, (int)bytes);                                        \
+    if (e != hipSuccess) return e;                                                                                 \
+    prefill_rows_kernel<BF16, NP><<<dim3((uint32_t)blocks), dim3(kFftThreads), bytes, st>>>(P, K, V, per_xcd, n_st); \
+  }
+    constexpr int kNp = BF16 ? 2 : 1;  // what the register budget holds
+    if (wide) IWDFT_PF_ROWS(kNp) else IWDFT_PF_ROWS(1)
+#undef IWDFT_PF_ROWS
     return hipGetLastError();
   }
-  const int logQ = logM < kFftMaxLogQ ? logM : kFftMaxLogQ;
+  const int logQ = logM;
   // Pairs per thread: as many as the register budget (128) holds next to the transform (the staged samples take 16
   // registers per further bf16 pair), unless the device would not be full: then the pairs spread over more workgroups.  At 256
   // points the 32 transforms side by side cover 128 bytes of a row with one pair each (512 slices, 64 bins, two pairs / one:
   // 30 / 25 us, fp32 40 / 33).
   const bool few = (uint64_t)n_st * (kPairs / 4) < kFewWorkgroups * (uint64_t)side_ns(logQ);
-#define IWDFT_PF_CASE(LQ, MULTI, NP, EQ)                                                                    \
+#define IWDFT_PF_CASE(LQ, NP, EQ)                                                                           \
   {                                                                                                         \
     const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                          \
     const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LQ))) * 8;                     \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                        \
     static LdsLimit lim;                                                                                    \
-    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, MULTI, NP, EQ>, (int)lds);                     \
+    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, NP, EQ>, (int)lds);                     \
     if (e != hipSuccess) return e;                                                                          \
-    prefill_fft_kernel<LQ, BF16, MULTI, NP, EQ><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(            \
+    prefill_fft_kernel<LQ, BF16, NP, EQ><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(            \
         P, K, V, per_xcd, n_st);                                                                            \
   }
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
     constexpr int kNp = LQ == 8 ? 1 : BF16 ? 4 : 2;                                \
     if (!eq) {                                                                     \
-      if (wide && !few) IWDFT_PF_CASE(LQ, false, kNp, false)                       \
-      else IWDFT_PF_CASE(LQ, false, 1, false)                                      \
+      if (wide && !few) IWDFT_PF_CASE(LQ, kNp, false)                       \
+      else IWDFT_PF_CASE(LQ, 1, false)                                      \
     } else if (wide && !few) {                                                     \
-      IWDFT_PF_CASE(LQ, false, kNp, true)                                          \
+      IWDFT_PF_CASE(LQ, kNp, true)                                          \
     } else {                                                                       \
-      IWDFT_PF_CASE(LQ, false, 1, true)                                            \
+      IWDFT_PF_CASE(LQ, 1, true)                                            \
     }                                                                              \
   }
-  if (logM > kFftMaxLogQ) {
-    constexpr int kNpBig = BF16 ? 2 : 1;
-    if (wide) IWDFT_PF_CASE(kFftMaxLogQ, true, kNpBig, false) else IWDFT_PF_CASE(kFftMaxLogQ, true, 1, false)
-  } else switch (logQ) {
+  switch (logQ) {
     case 8: IWDFT_PF_SINGLE(8) break;
     case 9: IWDFT_PF_SINGLE(9) break;
     case 10: IWDFT_PF_SINGLE(10) break;

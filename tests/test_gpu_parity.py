@@ -704,6 +704,34 @@ def test_more_than_4096_kept_bins_per_layer(L, n_bins, group, dtype, S, R):
         d.close()
 
 
+@pytest.mark.parametrize("L,dtype", [(16384, "f32"), (32768, "f32"), (32768, "bf16"), (131072, "bf16")])
+def test_prefill_of_layers_with_few_and_with_more_than_4096_bins(L, dtype):
+    """Beyond 8192 tokens and 4096 bins the prefill either keeps its sums in the output rows or runs 4096 bins a launch, where
+    layers with fewer have nothing left to do: both sides of the rule, layer by layer against the oracle (2^-24 times ~log2 of the
+    points and the sums over the residues: 2e-6), and bit for bit on tensors that are 8 bytes off alignment."""
+    rng = np.random.default_rng(L)
+    counts = [100, 4097, 4096, 8200, 33]
+    bins = [np.sort(rng.choice(L, size=n, replace=False)).astype(np.int32) for n in counts]
+    cfg = small_cfg(L=L, n_bins=100, dtype=dtype, n_layers=5, batch=1, n_kv_heads=1, group=1)
+    K, V = wl.prefill_tensors(cfg, DEV)
+    flat = torch.empty(2 * K.numel() + 32, dtype=K.dtype, device=DEV)
+    off = 8 // K.element_size()
+    Ku, Vu = flat[off:off + K.numel()].view(K.shape), flat[2 * off + K.numel():2 * off + 2 * K.numel()].view(K.shape)
+    Ku.copy_(K)
+    Vu.copy_(V)
+    a, u = make_cache(cfg, bins), make_cache(cfg, bins)
+    assert B.iwdft_prefill_kind(a.ctx) == "fft"
+    a.prefill(K, V)
+    u.prefill(Ku, Vu)
+    for layer in range(5):
+        (ka, va), (ku, vu) = a.export_coeffs(layer), u.export_coeffs(layer)
+        assert torch.equal(ka, ku) and torch.equal(va, vu)
+        for X, got in ((K, ka), (V, va)):
+            assert rel_l2(c128(got[0, 0]), orc.prefill(f64(X[layer, 0, 0]), bins[layer])) < 2e-6, (layer, counts[layer])
+    a.close()
+    u.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,S,R,group,n_bins", [(33, 0, 0, 1, 9), (100, 2, 3, 2, 100), (129, 0, 0, 3, 40), (1000, 10, 50, 4, 250),
                                                 (2049, 0, 4, 2, 300), (3000, 0, 0, 8, 1500), (8191, 1, 1, 1, 700)])
