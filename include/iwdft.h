@@ -167,7 +167,9 @@ int iwdft_prefill_kind(const iwdft_ctx* ctx);
  * sums (arithmetic-bound; chosen by IWDFT_FLAG_DIRECT_SYNTHESIS, for M < 32, and for M > 8192 without such a divisor,
  * e.g. a prime -- there only while M * (most kept bins of a layer) <= 2^30, beyond that iwdft_query_bytes /
  * iwdft_create return IWDFT_ERR_UNSUPPORTED unless the flag insists); -1 if ctx is NULL.
- * With 0, with 2 and M < 256, or with 1 when some layer keeps more than 4096 bins, desc.write_every is taken as 1. */
+ * With 0, with 1 when some layer keeps more than 4096 bins, with 2 and M < 256, and with 2 and more than 2 query heads per
+ * KV head when all layers together hold fewer than 49152 coefficient rows (sum over layers of batch * n_kv_heads * Bp_l, Bp_l =
+ * kept bins rounded up to 32; writing every step back is faster there), desc.write_every is taken as 1. */
 int iwdft_attn_kind(const iwdft_ctx* ctx);
 
 /* Whether decode attention on this context (Sec. 4.2.2 "Calculating Attention") walks the slices in groups, with

@@ -64,8 +64,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   size_t off_qc = 0, off_Pn = 0, off_pe = 0, off_pendK = 0, off_pendV = 0, off_ps = 0, off_direct = 0, ws_bytes = 0;
 };
 
-// Most kept bins per layer the FFT kernels keep in registers (prefill, reconstruction, the deferred write-back);
-// decode attention itself takes any number through its bin-strided kernel.
+// Most kept bins per layer of the deferred write-back on FFT contexts.
 constexpr int kFftMaxBins = 4096;
 // Prefill without a flag, M = 2^m: FFTs from this many kept bins in some layer, or from 1 / kFftPrefillMinShare of all bins.
 constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32, kFftPrefillRoundM = 2048;
@@ -75,6 +74,7 @@ constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
 constexpr int64_t kChirpPrefillPoints = 80;  // points of convolution that take as long as one token of the contraction
+constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
@@ -263,11 +263,15 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_qc = o; o = align256(o + sizeof(float2) * (size_t)ws);
   pl->off_Pn = o; o = align256(o + sizeof(float2) * (size_t)ws);
   pl->off_pe = o; o = align256(o + sizeof(float) * n_sl * (size_t)pl->G * (size_t)(d->n_sink + d->n_recent));
-  // Deferred write-back needs the FFT or chirp-z attention kernels (they weigh the pending tokens; the bin-strided FFT form
-  // does not, and below 256 slots a layer's coefficients are no traffic worth deferring) and all query heads of a KV head in
-  // one pass; otherwise every step writes back.  32 layers x 8 heads, M = 8132, 2033 bins: a step reads 1.06 GB instead of
-  // moving 2.1.
-  const bool weighs = (pl->use_fft && pl->max_nb <= kFftMaxBins) || (pl->use_chirp && (uint64_t)d->M >= kFftMinM);
+  // Deferred write-back needs the FFT or chirp-z attention kernels, which weigh the pending tokens, and all query heads of a KV
+  // head in one pass; otherwise every step writes back.  Contexts beyond kFftMaxBins bins have always written back at every step
+  // (the kernels could weigh there too; not measured).  On chirp-z contexts deferral is taken where it is faster: not below 256
+  // slots, and with more than two query heads per KV head from kDeferMinRows coefficient rows on, where a step reads 1 GB instead
+  // of moving 2.  16 steps, every one written back / deferred, us a step, 4 heads: M = 1000, 250 bins, 94 slices 54 / 67, 219
+  // slices 73 / 80, 512 slices 135 / 110; M = 4095, 1023 bins, 39 slices 84 / 84; M = 8132, 2033 bins, 12 slices 90 / 100, 64
+  // slices 144 / 120; 8 heads, M = 1000: 94 slices 64 / 74, 258 slices 108 / 102; 2 heads: 16 slices 32 / 32, 94 slices 53 / 42.
+  const bool weighs = (pl->use_fft && pl->max_nb <= kFftMaxBins) ||
+                      (pl->use_chirp && (uint64_t)d->M >= kFftMinM && (pl->G <= 2 || coef / kHeadDim >= kDeferMinRows));
   pl->write_every = (d->write_every > 1 && weighs && heads_fit_one_pass(pl->G) && !(d->flags & IWDFT_FLAG_SHORTCUT))
                         ? (int)d->write_every
                         : 1;

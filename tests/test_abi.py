@@ -106,6 +106,17 @@ def test_workspace_holds_the_deferred_tokens():
     assert B.iwdft_query_bytes(desc(write_every=8))[1] == B.iwdft_query_bytes(desc())[1]
 
 
+@pytest.mark.parametrize("heads,layers,n_bins,deferred", [
+    (2, 2, 250, True), (3, 2, 250, False), (8, 2, 250, False),    # 2 x 2 slices x 256 rows
+    (3, 96, 250, True), (8, 96, 250, True), (4, 95, 250, False),  # 49152 rows; one layer fewer
+])
+def test_chirp_contexts_defer_where_it_is_faster(heads, layers, n_bins, deferred):
+    """M = 1000: up to two query heads per KV head always, more from 49152 coefficient rows on (the workspace tells)."""
+    kw = dict(M=1000, n_layers=layers, n_q_heads=2 * heads, bins=[np.arange(n_bins)] * layers)
+    ws1, ws8 = B.iwdft_query_bytes(desc(**kw))[1], B.iwdft_query_bytes(desc(write_every=8, **kw))[1]
+    assert (ws8 - ws1 >= 2 * (2 * layers * 8 * 128 * 2)) == deferred and (ws8 == ws1) == (not deferred)
+
+
 def test_query_bytes_grows_with_exact_windows():
     s0, w0 = B.iwdft_query_bytes(desc())
     s1, w1 = B.iwdft_query_bytes(desc(n_sink=10, n_recent=50))

@@ -737,8 +737,8 @@ def test_prefill_of_layers_with_few_and_with_more_than_4096_bins(L, dtype):
                                                 (2049, 0, 4, 2, 300), (3000, 0, 0, 8, 1500), (8191, 1, 1, 1, 700)])
 def test_any_length_attention_through_chirp_transforms(dtype, L, S, R, group, n_bins):
     """M that is not a power of two (M = context - sink - recent in general): the attention runs O(M log M)
-    chirp-z transforms, all four convolution lengths; every step against the oracle (two calls and the fused step,
-    which writes back at every step here), and against the direct synthesis of the same library."""
+    chirp-z transforms, all convolution lengths; every step against the oracle (two calls and the fused step,
+    deferred with one and two heads), and against the direct synthesis of the same library."""
     cfg = small_cfg(L=L, n_bins=n_bins, group=group, dtype=dtype, steps=4, n_layers=2, batch=1, n_sink=S, n_recent=R)
     bins = random_bins(cfg, 83)
     c = make_cache(cfg, bins, write_every=8)
@@ -757,21 +757,23 @@ def test_any_length_attention_through_chirp_transforms(dtype, L, S, R, group, n_
     d.close()
 
 
-@pytest.mark.parametrize("L,S,R,group,n_bins,J", [
-    (255, 0, 0, 2, 60, 4),       # below 256 slots every step writes back
-    (256 + 1, 0, 3, 1, 90, 4),   # 513 -> 1024 points
-    (500, 10, 50, 4, 120, 8), (513, 0, 0, 3, 300, 16), (1025, 1, 0, 8, 200, 4), (2048 - 1, 0, 2, 2, 500, 8),
-    (4096 + 1, 0, 0, 1, 1000, 8), (2 * 4099, 10, 50, 5, 2000, 4), (3 * 8191, 0, 1, 2, 4500, 4),
+@pytest.mark.parametrize("L,S,R,group,n_bins,J,heads", [
+    (255, 0, 0, 2, 60, 4, 2),       # below 256 slots every step writes back
+    (256 + 1, 0, 3, 1, 90, 4, 2),   # 513 -> 1024 points
+    (500, 10, 50, 4, 120, 8, 192), (513, 0, 0, 3, 300, 16, 77), (1025, 1, 0, 8, 200, 4, 110), (2048 - 1, 0, 2, 2, 500, 8, 2),
+    (4096 + 1, 0, 0, 1, 1000, 8, 2), (2 * 4099, 10, 50, 5, 2000, 4, 13), (3 * 8191, 0, 1, 2, 4500, 4, 2),
 ])
-def test_chirp_attention_defers_the_write_back(L, S, R, group, n_bins, J):
+def test_chirp_attention_defers_the_write_back(L, S, R, group, n_bins, J, heads):
     """Both sides of every convolution length (2 M - 1 against 2^m), one block and several, more bins than 4096, an odd
-    number of heads: fused steps across two write-backs against the oracle, and with every step written back."""
-    cfg = small_cfg(L=L, n_bins=n_bins, group=group, dtype="f32", steps=J + 3, n_layers=2, batch=1, n_sink=S, n_recent=R)
+    number of heads (with more than two, enough slices to defer): fused steps across two write-backs against the oracle, and with
+    every step written back."""
+    cfg = small_cfg(L=L, n_bins=n_bins, group=group, dtype="f32", steps=J + 3, n_layers=2, batch=1, n_sink=S, n_recent=R,
+                    n_kv_heads=heads)
     bins = random_bins(cfg, 57)
-    run_stream(cfg, bins, rec=(0, min(64, L)), fused=True, write_every=J, tag=f"chirp-defer-{L}")
+    run_stream(cfg, bins, rec=(0, min(64, L)), fused=True, write_every=J, slices=wl.sample_slices(cfg, 4), tag=f"chirp-defer-{L}")
     K, V = wl.prefill_tensors(cfg, DEV)
     a, d = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins)
-    assert B.iwdft_attn_kind(a.ctx) == "chirp"
+    assert B.iwdft_attn_kind(a.ctx) == "chirp" and a.ws_bytes - d.ws_bytes >= (L > 255) * 2 * heads * (J - 1) * 128 * 4
     a.prefill(K, V)
     d.prefill(K, V)
     for i in range(J + 3):
