@@ -535,15 +535,17 @@ __device__ __forceinline__ float2 cis_fast(uint32_t p, uint32_t M) {
   const float f = (float)p * rcp_pow2(M);
   return make_float2(__builtin_amdgcn_cosf(f), __builtin_amdgcn_sinf(f));
 }
-// Over the lanes of a workgroup of T threads (one wave of it).
-template <int T, typename Op>
-__device__ __forceinline__ float lanes_reduce(float v, Op op) {
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
 #pragma unroll
-  for (int o = (T < 64 ? T : 64) / 2; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
+  for (int o = 32; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
   return v;
 }
+// Threads of a workgroup: those of its transform, a whole wave at least -- below 64 the bins are many for the lanes of the
+// transform alone (8 slices, 4 heads, a deferred step: M = 512, 384 bins 46 -> 35 us, M = 256, 256 bins 48 -> 33).
+__host__ __device__ constexpr int attn_threads(int logQ) { return fft_threads(logQ) < 64 ? 64 : fft_threads(logQ); }
 
-// grid: slice * pairs + pair, Q / 16 threads.  Two query heads share one complex transform: head g0 travels in the real
+// grid: slice * pairs + pair, attn_threads(LOGQ) threads.  Two query heads share one complex transform: head g0 travels in the real
 // part, head g0 + 1 in the imaginary part (each head's spectrum is made Hermitian first, so its time-domain signal is
 // real).  Time index a = Pb * a' + b: block b of Q = M / Pb samples comes from the spectrum folded modulo Q with twiddle
 // e^{j 2 pi k b / M}; softmax runs online across the Pb blocks (MULTI).
@@ -559,7 +561,7 @@ template <int LOGQ, int NBT, bool MULTI>
 __device__ __forceinline__ void fft_body(const Params& P, const float2* __restrict__ qc, float2* __restrict__ Pn,
                                          float* __restrict__ pe, float scale, int pairs, int np, uint32_t ptsh,
                                          float* __restrict__ ps, uint32_t bid, float2* buf) {
-  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NWV = T < 64 ? 1 : T / 64;
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), TB = attn_threads(LOGQ), NWV = TB / 64;
   constexpr bool kRegs = MULTI && NBT > 0;  // running sums in registers
   constexpr bool kKeep = kRegs && NBT > 4;  // with the register budget of one workgroup per CU: the inputs stay as well
   constexpr int U = kRegs ? NBT : 4;  // bins whose inputs are fetched together
@@ -567,7 +569,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   __shared__ float2 smax[NWV], ssum[NWV];
   __shared__ float pscr[NWV][2 * kMaxPend];
   const TabMem tab{P.tab + tab_base(LOGQ)};
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, tx = t & (T - 1);  // TB > T: lanes T .. 63 run lane tx's part of the transforms beside it
   const int pair = bid % pairs;
   const int slice = bid / pairs;
   const int spl = P.batch * P.n_kv;
@@ -590,7 +592,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   auto max2 = [](float a, float b) { return fmaxf(a, b); };
   auto add2 = [](float a, float b) { return a + b; };
   auto block_max = [&](float2 v) {  // other barriers separate its reads from its next writes
-    v = make_float2(lanes_reduce<T>(v.x, max2), lanes_reduce<T>(v.y, max2));
+    v = make_float2(wave_reduce(v.x, max2), wave_reduce(v.y, max2));
     if constexpr (NWV > 1) {
       if ((t & 63) == 0) smax[t >> 6] = v;
       __syncthreads();
@@ -609,12 +611,12 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   const float escale = 1.44269504088896341f * scale;  // scores live in log2 units (exp2 softmax)
   if (E > 0) {
     float2 lm = mx;
-    for (int e = t; e < E; e += T) {
+    for (int e = t; e < E; e += TB) {
       lm.x = fmaxf(lm.x, pe0[e] * escale);
       if (has1) lm.y = fmaxf(lm.y, pe1[e] * escale);
     }
     mx = block_max(lm);
-    for (int e = t; e < E; e += T) {
+    for (int e = t; e < E; e += TB) {
       Z.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
       if (has1) Z.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
     }
@@ -666,7 +668,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     for (int v = 0; v < 2 * kMaxPend; ++v) sp[v] = 0.f;
   };
   auto publish_sum = [&] {
-    const float2 z = make_float2(lanes_reduce<T>(Z.x, add2), lanes_reduce<T>(Z.y, add2));
+    const float2 z = make_float2(wave_reduce(Z.x, add2), wave_reduce(Z.y, add2));
     if ((t & 63) == 0) ssum[t >> 6] = z;
   };
 
@@ -682,7 +684,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   auto load_fold = [&](int i0) {
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      const int i = i0 + j * T;
+      const int i = i0 + j * TB;
       fr[j] = i < L.nb ? (uint32_t)fold[i] : 0xffffu;
     }
   };
@@ -690,7 +692,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     float w[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      const int i = i0 + j * T, ic = i < L.nb ? i : L.nb - 1;
+      const int i = i0 + j * TB, ic = i < L.nb ? i : L.nb - 1;
       kj[j] = (uint32_t)bins[ic];
       w[j] = wts[ic] * gain;
       y0[j] = q0[ic];
@@ -717,10 +719,11 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     // instructions) instead of being hoisted out of the block loop into long-lived registers.
     int lt = t;
     if (MULTI) asm volatile("" : "+v"(lt));
+    const int lx = TB > T ? tx : lt;
     float2 x[16];
 #pragma unroll
     for (int m = 0; m < 16; ++m) x[m] = make_float2(0.f, 0.f);
-    write16(buf, lt, x);
+    write16(buf, lx, x);
     __syncthreads();
     auto fold_group = [&](int i0, int round) {
       if constexpr (!kKeep) {
@@ -757,11 +760,11 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
       if constexpr (kRegs) {
         fold_group(lt, round);
       } else {
-        for (int i0 = lt; i0 < L.nb; i0 += U * T) fold_group(i0, round);
+        for (int i0 = lt; i0 < L.nb; i0 += U * TB) fold_group(i0, round);
       }
       __syncthreads();
     }
-    fft_inverse<LOGQ>(buf, tab.tab, lt, x);
+    fft_inverse<LOGQ>(buf, tab.tab, lx, x);
 
     // softmax: real part head g0, imaginary part head g0 + 1
     float2 lm = x[0];
@@ -778,18 +781,19 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
       x[m] = make_float2(__builtin_amdgcn_exp2f(x[m].x - mn.x), has1 ? __builtin_amdgcn_exp2f(x[m].y - mn.y) : 0.f);
       ls = cadd(ls, x[m]);
     }
+    if (TB > T && t >= T) ls = make_float2(0.f, 0.f);  // counted by lane tx
     Z = make_float2(Z.x * f.x + ls.x, Z.y * f.y + ls.y);
     if constexpr (!MULTI) publish_sum();  // read behind the barriers of the transform
 
     auto fetch_bins = [&](int i0) {
 #pragma unroll
       for (int j = 0; j < U; ++j) {
-        const int i = i0 + j * T;
+        const int i = i0 + j * TB;
         kj[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
       }
     };
     if constexpr (!kKeep) fetch_bins(pin_index(lt));
-    fft_forward<LOGQ>(buf, tab, lt, x, [&](int pass) {  // the first bins' twiddles are fetched while the transform runs
+    fft_forward<LOGQ>(buf, tab, lx, x, [&](int pass) {  // the first bins' twiddles are fetched while the transform runs
       if constexpr (!kKeep) {
         if (pass == fft_np(LOGQ) - 1) load_tw();
       }
@@ -816,14 +820,14 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     } else {
       if constexpr (!MULTI) normalise();
       const int n = MULTI ? L.nb : L.Bp;
-      for (int i0 = lt; i0 < n; i0 += U * T) {
-        if (i0 >= U * T) {
+      for (int i0 = lt; i0 < n; i0 += U * TB) {
+        if (i0 >= U * TB) {
           fetch_bins(i0);
           load_tw();
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-          const int i = i0 + j * T;
+          const int i = i0 + j * TB;
           if (i >= n) continue;
           float2 p0, p1;
           gather(j, p0, p1);
@@ -855,45 +859,37 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     if constexpr (kRegs) {
 #pragma unroll
       for (int j = 0; j < NBT; ++j) {
-        const int i = j * T + t;
+        const int i = j * TB + t;
         if (i < L.Bp) finish(i, kj[j], A0[j], A1[j]);
       }
     } else {
-      for (int i = t; i < L.Bp; i += T) {
+      for (int i = t; i < L.Bp; i += TB) {
         const bool live = i < L.nb;
         finish(i, live ? (uint32_t)bins[i] : 0u, live ? o0[i] : none, live && has1 ? o1[i] : none);
       }
     }
   }
   if (np > 0) {
-    if constexpr (T >= 64) {
-      // all 2 * kMaxPend sums over the wave at once: afterwards lane l holds the total of entry l / rep
-      const float tot = wave_reduce_scatter<2 * kMaxPend>(sp, t & 63);
-      constexpr int rep = 64 / (2 * kMaxPend);  // lanes that end up with the same total
-      if ((t & 63) % rep == 0) pscr[t >> 6][(t & 63) / rep] = tot;
-    } else {
-#pragma unroll
-      for (int v = 0; v < 2 * kMaxPend; ++v) {
-        const float tot = lanes_reduce<T>(sp[v], add2);
-        if (t == 0) pscr[0][v] = tot;
-      }
-    }
+    // all 2 * kMaxPend sums over the wave at once: afterwards lane l holds the total of entry l / rep
+    const float tot = wave_reduce_scatter<2 * kMaxPend>(sp, t & 63);
+    constexpr int rep = 64 / (2 * kMaxPend);  // lanes that end up with the same total
+    if ((t & 63) % rep == 0) pscr[t >> 6][(t & 63) / rep] = tot;
     __syncthreads();
-    for (int v = t; v < 2 * np; v += T) {
+    for (int v = t; v < 2 * np; v += TB) {
       float sum = 0.f;
       for (int w = 0; w < NWV; ++w) sum += pscr[w][v];
       const int jp = v >> 1, head = v & 1;
       if (head == 0 || has1) ps[((int64_t)slice * P.G + g0 + head) * kMaxPend + jp] = sum;
     }
   }
-  for (int e = t; e < E; e += T) {  // raw scores -> weights p_e / Z (same thread, same entry)
+  for (int e = t; e < E; e += TB) {  // raw scores -> weights p_e / Z (same thread, same entry)
     pe0[e] = __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x) / Z.x;
     if (has1) pe1[e] = __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y) / Z.y;
   }
 }
 
 template <int LOGQ, int NBT, bool MULTI>
-__global__ __launch_bounds__(fft_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_kernel(Params P, const float2* __restrict__ qc,
+__global__ __launch_bounds__(attn_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_kernel(Params P, const float2* __restrict__ qc,
                                                                        float2* __restrict__ Pn, float* __restrict__ pe,
                                                                        float scale, int pairs, int np, uint32_t ptsh,
                                                                        float* __restrict__ ps) {
@@ -1131,7 +1127,7 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     static LdsLimit lim;                                                                                  \
     e = lim.ensure((const void*)attn_fft_kernel<LQ, NBT, MULTI>, lds);                                    \
     if (e != hipSuccess) return e;                                                                        \
-    attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(fft_threads(LQ)), lds, st>>>(                     \
+    attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(attn_threads(LQ)), lds, st>>>(                     \
         P, qc, Pn, pe, scale, pairs, np_plain, u.tsh, u.ps);                                              \
   }
     if (logM > logQ) {
