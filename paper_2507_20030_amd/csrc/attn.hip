@@ -541,9 +541,6 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
   for (int o = 32; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
   return v;
 }
-// Threads of a workgroup: those of its transform, a whole wave at least -- below 64 the bins are many for the lanes of the
-// transform alone (8 slices, 4 heads, a deferred step: M = 512, 384 bins 46 -> 35 us, M = 256, 256 bins 48 -> 33).
-__host__ __device__ constexpr int attn_threads(int logQ) { return fft_threads(logQ) < 64 ? 64 : fft_threads(logQ); }
 
 // grid: slice * pairs + pair, attn_threads(LOGQ) threads.  Two query heads share one complex transform: head g0 travels in the real
 // part, head g0 + 1 in the imaginary part (each head's spectrum is made Hermitian first, so its time-domain signal is

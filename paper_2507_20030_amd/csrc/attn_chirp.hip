@@ -4,7 +4,7 @@
 
 namespace iwdft {
 
-// One workgroup of N / 16 threads per (slice, pair of query heads: real and imaginary part of one signal).  Q = M up to 8192.
+// One workgroup of N / 16 threads, a wave at least, per (slice, pair of query heads: real and imaginary part of one signal).  Q = M up to 8192.
 // Longer M run Pb = M / Q blocks (Pb the smallest divisor of M that brings Q down to 8192): time index a = Pb a' + b, block b
 // comes from the spectrum folded modulo Q with twiddle e^{j 2 pi k b / M}, softmax runs online across the blocks and the
 // running sums of the weights live in the output rows (every bin belongs to one thread, which reads back its own earlier
@@ -15,18 +15,18 @@ namespace iwdft {
 // pass through LDS); with the write-back deferred a decode step takes 286 us instead of 510.
 // Pending tokens of the deferred write-back enter as in attn_fft_kernel (np, ptsh, ps).
 template <int LOGN>
-__global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params P, const float2* __restrict__ qc,
+__global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Params P, const float2* __restrict__ qc,
                                                                       float2* __restrict__ Pn, float* __restrict__ pe,
                                                                       float scale, int pairs, int np, uint32_t ptsh,
                                                                       float* __restrict__ ps) {
-  constexpr int T = fft_threads(LOGN), NWV = T < 64 ? 1 : T / 64;
+  constexpr int T = fft_threads(LOGN), TB = attn_threads(LOGN), NWV = TB / 64;
   constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
   extern __shared__ __attribute__((aligned(16))) float2 buf[];
   __shared__ float2 smax[NWV], ssum[NWV];
   __shared__ float pscr[NWV][2 * kMaxPend];
   const TabMem tab{P.tab + tab_base(LOGN)};
   const float4* __restrict__ H = P.chirpW;
-  const int t = threadIdx.x;
+  const int tid = threadIdx.x, t = tid & (T - 1);  // TB > T: lanes T .. 63 run lane t's part of the transforms beside it
   const int pair = blockIdx.x % pairs;
   const int slice = blockIdx.x / pairs;
   const int spl = P.batch * P.n_kv;
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
 
   auto wave_op = [&](float v, auto op) {
 #pragma unroll
-    for (int o = (T < 64 ? T : 64) / 2; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
+    for (int o = 32; o >= 1; o >>= 1) v = op(v, __shfl_xor(v, o));
     return v;
   };
   auto max2 = [](float a, float b) { return fmaxf(a, b); };
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
   // Over the workgroup; the barrier of the one separates the reads of the other from its next writes.
   auto block_max = [&](float2 v) {
     v = make_float2(wave_op(v.x, max2), wave_op(v.y, max2));
-    if ((t & 63) == 0) smax[t >> 6] = v;
+    if ((tid & 63) == 0) smax[tid >> 6] = v;
     __syncthreads();
     v = smax[0];
     for (int w = 1; w < NWV; ++w) v = make_float2(fmaxf(v.x, smax[w].x), fmaxf(v.y, smax[w].y));
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
   };
   auto block_sum = [&](float2 v) {
     v = make_float2(wave_op(v.x, add2), wave_op(v.y, add2));
-    if ((t & 63) == 0) ssum[t >> 6] = v;
+    if ((tid & 63) == 0) ssum[tid >> 6] = v;
     __syncthreads();
     v = ssum[0];
     for (int w = 1; w < NWV; ++w) v = cadd(v, ssum[w]);
@@ -84,13 +84,13 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
   const float escale = 1.44269504088896341f * scale;
   if (E > 0) {
     float2 lm = mx;
-    for (int e = t; e < E; e += T) {
+    for (int e = tid; e < E; e += TB) {
       lm.x = fmaxf(lm.x, pe0[e] * escale);
       if (has1) lm.y = fmaxf(lm.y, pe1[e] * escale);
     }
     mx = block_max(lm);
     float2 ls = make_float2(0.f, 0.f);
-    for (int e = t; e < E; e += T) {
+    for (int e = tid; e < E; e += TB) {
       ls.x += __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x);
       if (has1) ls.y += __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y);
     }
@@ -109,13 +109,13 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
     // Hermitian spectrum of both heads (head g0 real, head g0 + 1 imaginary in time), folded modulo Q.  A slot can receive
     // several terms: successive rounds (host-made schedule).
     for (int round = 0; round < L.fold_rounds; ++round) {
-      for (int i0 = t; i0 < L.nb; i0 += U * T) {
+      for (int i0 = tid; i0 < L.nb; i0 += U * TB) {
         uint32_t k[U], fr[U];
         float w[U];
         float2 y0[U], y1[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-          const int i = i0 + j * T, ic = i < L.nb ? i : L.nb - 1;
+          const int i = i0 + j * TB, ic = i < L.nb ? i : L.nb - 1;
           k[j] = (uint32_t)bins[ic];
           fr[j] = i < L.nb ? (uint32_t)fold[ic] : 0xffffu;  // 0xff: no round matches
           w[j] = wts[ic] * gain;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
       float2 p = make_float2(0.f, 0.f);
       if ((uint32_t)(t + T * i) < Q)
         p = make_float2(__builtin_amdgcn_exp2f(v[i].x - mn.x), has1 ? __builtin_amdgcn_exp2f(v[i].y - mn.y) : 0.f);
-      ls = cadd(ls, p);
+      if (TB == T || tid < T) ls = cadd(ls, p);  // else counted by lane t
       v[i] = cmul(p, conjf2(c[i]));
     }
     const float2 bs = block_sum(ls);
@@ -181,16 +181,16 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
     for (int i = 0; i < 8; ++i) own[i * SP] = cmul(v[i], conjf2(c[i]));
     __syncthreads();
 
-    for (int i0 = t; i0 < L.nb; i0 += U * T) {
+    for (int i0 = tid; i0 < L.nb; i0 += U * TB) {
       uint32_t k[U];
 #pragma unroll
       for (int j = 0; j < U; ++j) {
-        const int i = i0 + j * T;
+        const int i = i0 + j * TB;
         k[j] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
       }
 #pragma unroll
       for (int j = 0; j < U; ++j) {
-        const int i = i0 + j * T;
+        const int i = i0 + j * TB;
         if (i >= L.nb) continue;
         const uint32_t r = slot_of(k[j]), rm = r ? Q - r : 0u;
         const float2 w1 = buf[fpad((int)r)], w2 = buf[fpad((int)rm)];
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
   float sp[2 * kMaxPend];  // [token][head g0, head g0 + 1]: Re sum_k e^{j theta_jk} Pn[k] of the pending tokens
 #pragma unroll
   for (int j = 0; j < 2 * kMaxPend; ++j) sp[j] = 0.f;
-  for (int i = t; i < L.Bp; i += T) {  // padding entries are written as zeros: kernel C reads whole rows
+  for (int i = tid; i < L.Bp; i += TB) {  // padding entries are written as zeros: kernel C reads whole rows
     float2 r0 = make_float2(0.f, 0.f), r1 = r0;
     if (i < L.nb) {
       const float w = wts[i];
@@ -256,17 +256,17 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void attn_chirp_kernel(Params
     for (int j = 0; j < 2 * kMaxPend; ++j) {
       if (j < 2 * np) {
         const float tot = wave_op(sp[j], add2);
-        if ((t & 63) == 0) pscr[t >> 6][j] = tot;
+        if ((tid & 63) == 0) pscr[tid >> 6][j] = tot;
       }
     }
     __syncthreads();
-    for (int e = t; e < 2 * np; e += T) {
+    for (int e = tid; e < 2 * np; e += TB) {
       float sum = 0.f;
       for (int w = 0; w < NWV; ++w) sum += pscr[w][e];
       if ((e & 1) == 0 || has1) ps[((int64_t)slice * P.G + g0 + (e & 1)) * kMaxPend + (e >> 1)] = sum;
     }
   }
-  for (int e = t; e < E; e += T) {  // raw scores -> weights p_e / Z
+  for (int e = tid; e < E; e += TB) {  // raw scores -> weights p_e / Z
     pe0[e] = __builtin_amdgcn_exp2f(pe0[e] * escale - mx.x) / Z.x;
     if (has1) pe1[e] = __builtin_amdgcn_exp2f(pe1[e] * escale - mx.y) / Z.y;
   }
@@ -283,7 +283,7 @@ hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, floa
     static LdsLimit lim;                                                                                                \
     const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN>, bytes);                                         \
     if (e != hipSuccess) return e;                                                                                      \
-    attn_chirp_kernel<LN><<<dim3((uint32_t)grid), dim3(fft_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
+    attn_chirp_kernel<LN><<<dim3((uint32_t)grid), dim3(attn_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
                                                                                      ptsh, ps);                        \
   } break;
   switch (P.chirp_logN) {

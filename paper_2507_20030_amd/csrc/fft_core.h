@@ -10,6 +10,9 @@ namespace iwdft {
 
 constexpr int kFftMaxLogQ = 13;  // longest transform of the power-of-two paths
 __host__ __device__ constexpr int fft_threads(int logQ) { return 1 << (logQ - 4); }
+// Threads of a workgroup of the decode attention: those of its transform, a whole wave at least -- below 64 the bins are many for the lanes of the
+// transform alone (8 slices, 4 heads, a deferred step: M = 512, 384 bins 46 -> 35 us, M = 256, 256 bins 48 -> 33).
+__host__ __device__ constexpr int attn_threads(int logQ) { return fft_threads(logQ) < 64 ? 64 : fft_threads(logQ); }
 
 // LDS index of position i: two float2 of padding per 16 keep 16-byte accesses to a thread's 16 positions aligned and spread
 // both these and the strided accesses of the wide passes over all banks.
