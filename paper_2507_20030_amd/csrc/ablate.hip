@@ -14,6 +14,7 @@ namespace iwdft {
 
 namespace {
 constexpr int kAbPairs = kHeadDim / 2;
+constexpr int kCusPerXcd = 32;
 }  // namespace
 
 // Two adjacent channels of a slice travel as one complex signal: forward transform, weights
@@ -195,10 +196,12 @@ __global__ __launch_bounds__(kFftThreads, 2) void ablate_long_kernel(const char*
 template <bool BF16>
 static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int logQ, int lo, int hi, hipStream_t st) {
   const int per_xcd = (n_slices + 7) / 8;
-  // several pairs per load need 16-byte aligned tensors; not where the device would not be full (pair_io.h): the pairs spread over more
-  // workgroups then
-  const bool wide = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0 &&
-                    (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
+  // several pairs per load need 16-byte aligned tensors; not where the device would not be full (pair_io.h): the pairs spread over
+  // more workgroups then, two per load at 4096 and 8192 points as long as every CU has one (8 x 8192 tokens, one / two, us: bf16
+  // 44.5 / 34.2, fp32 48.3 / 38.6; 12 x 4096: 26.5 / 22.2, 26.2 / 23.8; but 48 x 2048 in fp32 27.2 / 29.5)
+  const bool aligned = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0;
+  const bool wide = aligned && (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
+  const bool two = aligned && (int64_t)per_xcd * (kAbPairs / 2) >= kCusPerXcd * side_ns(logQ);
   const float2* tab = nullptr;
   hipError_t e = fft_table(&tab);
   if (e != hipSuccess) return e;
@@ -215,8 +218,10 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
   }
 #define IWDFT_AB_CASE(LQ)                                                             \
   {                                                                                   \
-    constexpr int kNp = side_pairs(LQ, BF16);                                   \
-    if (wide) IWDFT_AB_LAUNCH(LQ, kNp) else IWDFT_AB_LAUNCH(LQ, 1)                    \
+    constexpr int kNp = side_pairs(LQ, BF16), kTwo = LQ < 12 ? 1 : 2;                 \
+    if (wide) IWDFT_AB_LAUNCH(LQ, kNp)                                                \
+    else if (two) IWDFT_AB_LAUNCH(LQ, kTwo)                                           \
+    else IWDFT_AB_LAUNCH(LQ, 1)                                                       \
   }
   switch (logQ) {
     case 8: IWDFT_AB_CASE(8) break;

@@ -263,8 +263,8 @@ __device__ __forceinline__ void fft_pass(float2* buf, const Tab& tab, int t, Tw1
   __syncthreads();
 }
 
-// The stage of radix 2^rem at the wide end as a pass of its own (NORM: as in fft_pass).
-template <int LOGQ, bool INV, bool NORM = false>
+// The stage of radix 2^rem at the wide end as a pass of its own.
+template <int LOGQ, bool INV>
 __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__ tab, int t) {
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), REM = fft_rem(LOGQ), R = 1 << REM, NB = Q / R;
   constexpr int SP = NB + NB / 8;
@@ -275,10 +275,7 @@ __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__
     float2* b = buf + fpad(k);
     float2 x[R];
 #pragma unroll
-    for (int m = 0; m < R; ++m) {
-      x[m] = b[m * SP];
-      if constexpr (NORM) x[m] = make_float2(x[m].x * (1.f / Q), x[m].y * (1.f / Q));
-    }
+    for (int m = 0; m < R; ++m) x[m] = b[m * SP];
     if constexpr (REM == 1) {
       if constexpr (INV) bfly1(x[0], x[1]);
       else {
@@ -317,8 +314,8 @@ __device__ __forceinline__ void fft_wide(float2* buf, const float2* __restrict__
 
 // Inverse transform of the natural-order spectrum in buf (complete: behind a barrier); on return x holds the samples at
 // positions 16 t + m.  buf may be overwritten position by position by the same thread without a
-// barrier, otherwise only behind one.  tab: this length's block of the tables.  NORM: with the factor 1 / Q, applied to the
-// spectrum, so that no sum exceeds the range that the samples and their spectrum have.
+// barrier, otherwise only behind one.  tab: this length's block of the tables.  NORM: with the factor 1 / Q, applied
+// ahead of the first stage whose twiddles are not constant, so that no sum exceeds the range of the samples and their spectrum.
 template <int LOGQ, int K = fft_np(LOGQ) - 1, bool NORM = false>
 __device__ __forceinline__ void fft_inv_passes(float2* buf, const TabMem& tab, int t, Tw16& w) {
   if constexpr (K >= 1) {
@@ -330,10 +327,10 @@ template <int LOGQ, bool NORM = false>
 __device__ __forceinline__ void fft_inverse(float2* buf, const float2* __restrict__ tab, int t, float2 (&x)[16]) {
   static_assert(fft_np(LOGQ) >= 2, "256 points at least");
   Tw16 w;
-  if constexpr (fft_rem(LOGQ) >= 2) fft_wide<LOGQ, true, NORM>(buf, tab, t);
+  if constexpr (fft_rem(LOGQ) >= 2) fft_wide<LOGQ, true>(buf, tab, t);
   const TabMem tm{tab};
   tm.load<LOGQ, fft_np(LOGQ) - 1, true>(w, t);
-  fft_inv_passes<LOGQ, fft_np(LOGQ) - 1, NORM && (fft_rem(LOGQ) < 2)>(buf, tm, t, w);
+  fft_inv_passes<LOGQ, fft_np(LOGQ) - 1, NORM>(buf, tm, t, w);
   read16(buf, t, x);
   dft16<true>(x, w);
 }

@@ -118,11 +118,12 @@ def test_ablate_chunk_matches_the_oracle(dtype, M, C, chunks):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
-def test_ablate_chunk_several_channel_pairs_per_load(dtype, M):
-    """Enough slices (one more than a multiple of 8) for the form that fetches several channel pairs at once, all transform
-    lengths: against the oracle, and bit for bit against the one-pair form that a tensor 8 bytes off alignment takes."""
-    n = (48 if M == 1024 else 16) * (8192 // M) + 1
+@pytest.mark.parametrize("M,n", [(256, 513), (512, 257), (1024, 385), (2048, 65), (4096, 33), (8192, 17),  # several pairs, bf16 and
+                                 (4096, 9), (4096, 20), (8192, 3), (8192, 10)])  # fp32 from where they pay; two of them
+def test_ablate_chunk_several_channel_pairs_per_load(dtype, M, n):
+    """Enough slices (one more than a multiple of 8) for the forms that fetch several channel pairs at once (bf16 from 2048 points
+    on, fp32 from 1024 on; shorter ones have the one-pair form only): against the oracle, and bit for bit against the one-pair form
+    that a tensor 8 bytes off alignment takes."""
     C = 5
     g = torch.Generator(device="cuda").manual_seed(M)
     x = torch.randn((n, M, 128), generator=g, device="cuda").to(dtype)
