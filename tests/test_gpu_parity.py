@@ -903,10 +903,11 @@ def test_most_exact_tokens():
                                           (32768, 3, 2, 2100)])
 def test_fft_prefill_all_transform_lengths(dtype, L, S, R, n_bins):
     # every transform length of the in-LDS FFT (2^8 .. 2^13) and the decimated form beyond it, ragged
-    # scattered bins (both halves of the spectrum, so k and M - k both occur), with and without windows
+    # scattered bins (both halves of the spectrum, so k and M - k both occur), with and without windows;
+    # slices enough for the form that takes several channel pairs per load (8 x 8192 / L; 256 points have one)
     big = L > 8192
     cfg = small_cfg(L=L, dtype=dtype, n_bins=n_bins, n_sink=S, n_recent=R, steps=2,
-                    n_layers=1 if big else 2, batch=1 if big else 2)
+                    n_layers=1 if big else 2, batch=1 if big else 2, n_kv_heads=2 if big else 2 * 8192 // L)
     bins = random_bins(cfg, 37)
     st = run_stream(cfg, bins, flags=B.IWDFT_FLAG_FFT_PREFILL, rec=(3, 50), tag=f"fftpf-{dtype}-L{L}")
     assert st["coef0"] < 2e-5
@@ -932,22 +933,29 @@ def test_fft_and_dense_prefill_give_the_same_state():
     b.close()
 
 
-@pytest.mark.parametrize("L,n_bins", [(1024, 400), (16384, 1100), (32768, 2100), (8192, 5000)])
-def test_fft_prefill_of_tensors_that_are_not_16_byte_aligned(L, n_bins):
-    """The FFT prefill fetches several channel pairs with one 8- or 16-byte load when K and V allow it; tensors that
-    start 8 bytes off take one pair per workgroup instead.  Every pair's transform is the same arithmetic either way:
-    the two states agree bit for bit."""
-    cfg = small_cfg(L=L, n_bins=n_bins, n_layers=1, batch=1, n_kv_heads=2, dtype="bf16", mask="low")
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,heads,flag", [
+    (512, 400, 128, True), (1024, 400, 64, True), (2048, 500, 33, True), (4096, 600, 17, True), (8192, 5000, 9, True),
+    (16384, 1100, 2, True), (32768, 2100, 2, True), (16384, 5000, 2, True),
+    (512, 100, 128, False), (1024, 200, 64, False), (2048, 300, 33, False), (4096, 200, 17, False), (8192, 300, 9, False),
+    (16384, 200, 2, False),  # channels of a pair scaled to one size
+])
+def test_fft_prefill_of_tensors_that_are_not_16_byte_aligned(dtype, L, n_bins, heads, flag):
+    """The FFT prefill fetches several channel pairs with one 8- or 16-byte load when K and V allow it and the slices fill the
+    device (8 x 8192 / L of them); tensors that start 8 bytes off take one pair per load instead.  Every pair's transform is
+    the same arithmetic either way: the two states agree bit for bit."""
+    cfg = small_cfg(L=L, n_bins=n_bins, n_layers=1, batch=1, n_kv_heads=heads, dtype=dtype, mask="low")
     bins = wl.layer_bins(cfg)
     K, V = wl.prefill_tensors(cfg, DEV)
-    pad = 4                                                    # bf16 elements = 8 bytes
+    pad = 8 // K.element_size()
     Ku = torch.empty(K.numel() + pad, dtype=K.dtype, device=DEV)[pad:].view_as(K)
     Vu = torch.empty(V.numel() + pad, dtype=V.dtype, device=DEV)[pad:].view_as(V)
     Ku.copy_(K)
     Vu.copy_(V)
     assert K.data_ptr() % 16 == 0 and Ku.data_ptr() % 16 == 8 and Vu.data_ptr() % 16 == 8
-    a = make_cache(cfg, bins, flags=B.IWDFT_FLAG_FFT_PREFILL)
-    b = make_cache(cfg, bins, flags=B.IWDFT_FLAG_FFT_PREFILL)
+    a = make_cache(cfg, bins, flags=B.IWDFT_FLAG_FFT_PREFILL if flag else 0)
+    b = make_cache(cfg, bins, flags=B.IWDFT_FLAG_FFT_PREFILL if flag else 0)
+    assert B.iwdft_prefill_kind(a.ctx) == "fft"
     a.prefill(K, V)
     b.prefill(Ku, Vu)
     (ka, va), (kb, vb) = a.export_coeffs(0), b.export_coeffs(0)
@@ -1082,8 +1090,9 @@ def test_fft_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one(
 @pytest.mark.parametrize("L,n_bins,batch", [(256, 100, 34), (512, 300, 17), (1024, 600, 25), (2048, 700, 5), (4096, 2100, 3),
                                             (8192, 900, 2), (16384, 2000, 2)])
 def test_reconstruct_several_channel_pairs_per_store(dtype, L, n_bins, batch):
-    """Enough slices for the form that stores several channel pairs at once, a range that starts and ends inside the rows and
-    wraps: against the oracle on three slices, and bit for bit against the one-pair form that outputs 8 bytes off take."""
+    """Enough slices for the form that stores several channel pairs at once (bf16 from 2048 points on, fp32 from 1024 on; shorter
+    ones have the one-pair form only), a range that starts and ends inside the rows and wraps: against the oracle on three slices,
+    and bit for bit against the one-pair form that outputs 8 bytes off take."""
     cfg = small_cfg(L=L, dtype=dtype, n_bins=n_bins, steps=3, group=1, n_layers=1, batch=batch, n_kv_heads=8)
     bins = random_bins(cfg, 79)
     K, V = wl.prefill_tensors(cfg, DEV)
