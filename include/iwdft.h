@@ -140,8 +140,10 @@ int iwdft_query_bytes(const iwdft_desc* desc, size_t* state_bytes, size_t* works
 
 /* Validates desc, copies the bin lists into d_state and zeroes the coefficients
  * (synchronous; not a hot call).  Both buffers must be 256-byte aligned and stay
- * alive and untouched by the caller until iwdft_destroy.  The HIP device that is
- * current at this call owns the context. */
+ * alive and untouched by the caller until iwdft_destroy.  Neither may serve two
+ * contexts at a time: the workspace holds data between calls as well (the table of
+ * the chirp-z transforms from this call on, the tokens of a deferred write-back).
+ * The HIP device that is current at this call owns the context. */
 int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void* d_workspace,
                  size_t workspace_bytes, iwdft_ctx** out);
 

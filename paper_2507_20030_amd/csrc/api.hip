@@ -51,9 +51,9 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   bool use_chirp_prefill = false;  // prefill through chirp-z transforms
   bool use_chirp = false;        // ... through chirp-z transforms (any M up to kChirpMaxM when use_fft is false)
   int chirp_logN = 0;            // length of its circular convolutions
-  int chirp_logS = 0;            // length of the table in the state buffer (kept for copies of it; nothing reads it)
+  int chirp_logS = 0;            // length of a table that the state buffer used to hold: its bytes stay, for copies of the buffer
   int64_t chirp_Q = 0;           // points per chirp-z transform: M / Pb (M itself up to 8192)
-  size_t off_chirp = 0, off_chirpS = 0, off_chirpW = 0;
+  size_t off_chirp = 0, off_chirpW = 0;
   int64_t tw_Q = 0;              // length of the transforms whose twiddle octant is at off_tw
   size_t off_tw = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
@@ -246,7 +246,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_weights = o; o = align256(o + sizeof(float) * (size_t)pl->n_bins_total);
   pl->off_fold = o;    o = align256(o + sizeof(uint16_t) * (size_t)pl->n_bins_total);
   pl->off_chirp = o;   o = align256(o + (pl->use_chirp ? sizeof(float2) * (size_t)pl->chirp_Q : 0));
-  pl->off_chirpS = o;  o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logS) : 0));
+  o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logS) : 0));
   pl->tw_Q = (pow2 && (uint64_t)d->M >= kFftMinM) ? (d->M < kFftMaxQ ? d->M : kFftMaxQ) : 0;
   pl->off_tw = o;      o = align256(o + (pl->tw_Q ? sizeof(float2) * (size_t)(pl->tw_Q / 8 + 1) : 0));
   pl->off_FK = o;      o = align256(o + sizeof(float2) * (size_t)coef);
@@ -512,6 +512,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       std::vector<float2> chirp, H, out;
       make_chirp(pl.chirp_Q, &chirp);
       e = hipMemcpy(c->state + pl.off_chirp, chirp.data(), sizeof(float2) * chirp.size(), hipMemcpyHostToDevice);
+      // In the workspace: a copy of the state buffer that is put back may be older than this order of the table.
       make_chirp_transform(pl.chirp_Q, pl.chirp_logN, &H);
       out.resize(H.size());
       const int64_t T = (int64_t)H.size() / 16;
@@ -521,11 +522,6 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       if (e == hipSuccess)
         e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
-      if (pl.chirp_logS != pl.chirp_logN) make_chirp_transform(pl.chirp_Q, pl.chirp_logS, &H);
-      out.resize(H.size());
-      for (int64_t m = 0; m < (int64_t)H.size(); ++m) out[(size_t)digit_position(m, pl.chirp_logS)] = H[(size_t)m];
-      if (e == hipSuccess)
-        e = hipMemcpy(c->state + pl.off_chirpS, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && pl.tw_Q) {
       const double kTwoPi = 6.28318530717958647692;

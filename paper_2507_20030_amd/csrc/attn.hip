@@ -633,8 +633,9 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     if (np > 0) {  // block-uniform
       // hardware sine / cosine (~1e-6 absolute): these are weights of value rows, far inside the tolerance.
       // u_n = Re(tw step^n r) for n = 0 .. np - 1 obeys u_{n+1} = 2 cos(phi) u_n - u_{n-1} (phi = the step's angle):
-      // one multiply-add per token and head instead of a complex rotation (at most 15 steps: no error growth
-      // that matters next to the 1e-6 of the hardware sine)
+      // one multiply-add per token and head instead of a complex rotation.  The step's 1e-6 grow with n; the weights of up
+      // to 15 tokens are off by 1.4e-6 .. 3.3e-6 (M = 512 .. 131072, fp32, relative 2-norm), against 5e-7 .. 2.1e-6 where
+      // every step writes back
       const float2 tw = cis_fast((k * ptsh) & (P.M - 1u), P.M), step = cis_fast(k, P.M), t1 = cmul(tw, step);
       const float c2 = 2.f * step.x;
       float u0 = tw.x * r0.x - tw.y * r0.y, u1 = t1.x * r0.x - t1.y * r0.y;

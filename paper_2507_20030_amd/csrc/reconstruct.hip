@@ -197,7 +197,7 @@ __global__ __launch_bounds__(512, 4) void reconstruct_fft_kernel(Params P, int l
   }
 }
 
-constexpr int kRecMaxBins = 4096;
+constexpr int kRecMaxBins = 4096;  // layers with more have always taken the contraction (the transforms walk any list; not measured)
 bool reconstruct_fft_ok(const Params& P) { return P.Mmask != 0 && P.M >= 256 && P.max_nb <= kRecMaxBins; }
 
 template <bool BF16>
