@@ -67,8 +67,9 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
 // Most kept bins per layer of the deferred write-back on FFT contexts.
 constexpr int kFftMaxBins = 4096;
 // Prefill without a flag, M = 2^m: FFTs from this many kept bins in some layer, or from 1 / kFftPrefillMinShare of all bins.
-constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32, kFftPrefillRoundM = 2048;
-constexpr int kFftPrefillRound16 = 144, kFftPrefillRound32 = 168;  // slices per round of the contraction, bf16 and fp32
+constexpr int kFftPrefillMinBins = 128, kFftPrefillMinShare = 32;
+// Most slices per round of the contraction at which the FFT is still ahead: bf16 at 4096 and from 8192 points, fp32 from 8192.
+constexpr int kFftPrefillRound16Mid = 208, kFftPrefillRound16 = 144, kFftPrefillRound32 = 168;
 constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit in LDS)
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
@@ -153,12 +154,16 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // grows with the bins in steps of 128 and walks the tokens once per round of 256 workgroups (slices x steps), whether or not
   // the last round is full.  Measured (bf16, dense / FFT, us): 128 slices, M = 1024, 64 bins 52 / 30; M = 4096, 256 bins
   // 235 / 134; M = 8192, 128 bins 336 / 282; one layer of 8, M = 1024, 64 bins, fp32: 78 / 7.3.  256 slices, 128 bins, one full
-  // round: M = 2048 127 / 131, M = 8192 471 / 622, M = 16384 930 / 1220 (fp32 838 / 876, 1664 / 2185); 160 slices 357 / 396,
-  // 713 / 761 (fp32 703 / 548, 1391 / 1326); 64 slices, M = 65536: 2594 / 1081.  So the contraction stays where a round has more
-  // than kFftPrefillRound16 / 32 slices.  Below kFftPrefillMinBins and kFftPrefillMinShare it stays as well, though not for speed
-  // (M = 4096, 64 bins, 128 slices: 177 / 116): such contexts keep its result.
+  // round: M = 2048 125 / 123, M = 4096 238 / 253, M = 8192 466 / 622, M = 16384 930 / 1220 (fp32 222 / 151, 422 / 336, 838 / 876,
+  // 1664 / 2185); 200 slices, M = 4096 209 / 203; 160 slices, M = 8192 357 / 396, M = 16384 713 / 761 (fp32 703 / 548, 1391 /
+  // 1326); 64 slices, M = 65536: 2594 / 1081.  So the contraction stays where a round has more than kFftPrefillRound.. slices.
+  // Below kFftPrefillMinBins and kFftPrefillMinShare it stays as well, though not for speed (M = 4096, 64 bins, 128 slices:
+  // 177 / 116): such contexts keep its result.
   const int64_t S = slices_per_layer * d->n_layers, rounds = (S * ((pl->max_nb + 127) / 128) + 255) / 256;
-  const int64_t round_slices = d->kv_dtype == IWDFT_BF16 ? kFftPrefillRound16 : kFftPrefillRound32;
+  const bool b16 = d->kv_dtype == IWDFT_BF16;
+  const int64_t round_slices = d->M >= 8192            ? (b16 ? kFftPrefillRound16 : kFftPrefillRound32)
+                               : b16 && d->M >= 4096 ? kFftPrefillRound16Mid
+                                                     : S;  // short contexts: the FFT
   const bool fft_pf_ok = pow2 && (uint64_t)d->M >= kFftMinM;
   if (d->flags & IWDFT_FLAG_FFT_PREFILL) {
     if (!fft_pf_ok)
@@ -167,7 +172,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   } else {
     pl->use_fft_prefill = fft_pf_ok && !(d->flags & IWDFT_FLAG_DENSE_PREFILL) &&
                           (pl->max_nb >= kFftAloneBins ||
-                           (d->M <= (int64_t)kStreamMaxM && (d->M < kFftPrefillRoundM || S <= round_slices * rounds) &&
+                           (d->M <= (int64_t)kStreamMaxM && S <= round_slices * rounds &&
                             (pl->max_nb >= kFftPrefillMinBins || (int64_t)pl->max_nb * kFftPrefillMinShare >= d->M)));
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
@@ -223,6 +228,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // a time, whether or not the last round is full.  S slices, dense / chirp in us: S = 8, M = 8132, 512 bins 361 / 75; S = 64:
   // 482 / 573, with 640 bins 818 / 578; S = 256, 2033 bins 7400 / 2300; S = 64, M = 1988, 256 bins 111 / 111, 640 bins
   // 224 / 113; S = 64, M = 9000, 640 bins 898 / 965; S = 32, M = 32708, 4096 bins 7300 / 1500.
+  // These are bf16; in fp32 the contraction takes 1.6 times as long and the transforms 1.25 times (S = 256, M = 8132, 2033 bins
+  // 11600 / 2860), so the line lies on the contraction's side there: contexts near it keep the path they had.
   // Longer M with blocks of a few points only stay with the contraction.
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
     const int64_t Pb = d->M / pl->chirp_Q;

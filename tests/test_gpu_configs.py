@@ -219,13 +219,23 @@ def test_pipelined_and_serial_phases_agree_bit_for_bit(group, n_bins, shape, dty
 
 @pytest.mark.parametrize("L,slices,n_bins,kind", [
     (16384, 144, 128, "fft"), (16384, 145, 128, "dense"), (8192, 256, 128, "dense"), (8192, 257, 128, "fft"),  # a second round
-    (8192, 256, 129, "fft"), (65536, 64, 128, "fft"), (8192, 256, 384, "fft"), (2048, 256, 128, "dense"), (1024, 256, 128, "fft"),
-    (16384, 64, 127, "dense"),
+    (8192, 256, 129, "fft"), (65536, 64, 128, "fft"), (8192, 256, 384, "fft"), (2048, 256, 128, "fft"), (1024, 256, 128, "fft"),
+    (16384, 64, 127, "dense"), (4096, 208, 128, "fft"), (4096, 256, 128, "dense"),
 ])
 def test_prefill_takes_the_contraction_where_its_workgroups_fill_the_device(L, slices, n_bins, kind):
     """Contexts of fewer than 384 kept bins: the FFT costs in proportion to the slices, the contraction one walk over the tokens
     per round of 256 workgroups (slices x tiles of 128 bins)."""
-    c = B.Cache(1, 1, slices, slices, 128, torch.bfloat16, L, [np.arange(n_bins, dtype=np.int32)], device=DEV)
+    check_prefill_kind(L, slices, n_bins, torch.bfloat16, kind)
+
+
+@pytest.mark.parametrize("L,slices,kind", [(8192, 168, "fft"), (8192, 169, "dense"), (4096, 256, "fft"), (2048, 256, "fft")])
+def test_prefill_takes_the_contraction_in_fp32_from_8192_tokens_only(L, slices, kind):
+    """There it takes 1.8 times as long as in bf16, the FFT 1.3 times."""
+    check_prefill_kind(L, slices, 128, torch.float32, kind)
+
+
+def check_prefill_kind(L, slices, n_bins, dtype, kind):
+    c = B.Cache(1, 1, slices, slices, 128, dtype, L, [np.arange(n_bins, dtype=np.int32)], device=DEV)
     assert B.iwdft_prefill_kind(c.ctx) == kind
     c.close()
 
