@@ -391,10 +391,13 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   // against 547 without, fp32 876 / 861.
   const bool eq = P.scale_pairs != 0;
   hipError_t e = hipSuccess;
-  // More than 4096 bins: launch after launch where the tokens are read again in less time than the sums in the output rows take
-  // (launches / rows, ms; 64 slices, M = 32768, 8192 bins: bf16 2.37 / 2.40, fp32 2.16 / 2.57; 8 slices: 0.277 / 0.240, 0.287 /
-  // 0.345; 8 slices, M = 65536, 16384 bins: 1.13 / 1.07, 1.12 / 1.06; M = 262144, 8192 bins: 2.14 / 2.26, 2.03 / 3.63).
-  const bool stream = P.M <= kStreamMaxM && (P.max_nb <= 4096 || P.M >= (BF16 ? 131072u : 32768u));
+  // More than 4096 bins: twice through the tokens where that takes less time than the sums in the output rows (launches / rows,
+  // ms; 64 slices, M = 32768, 8192 bins: bf16 2.37 / 2.40, fp32 2.16 / 2.57; 8 slices: 0.277 / 0.240, 0.287 / 0.345; M = 262144,
+  // 8192 bins, 8 slices: 2.14 / 2.26, 2.03 / 3.63, one slice: 1.37 / 1.01, 0.75 / 1.25).  More launches do not pay (M = 65536,
+  // 16384 bins, 8 slices: 1.06 / 1.06, 1.12 / 1.13, one slice 0.44 / 0.39, 0.38 / 0.35; M = 262144, 65536 bins, one slice: 11.0 /
+  // 5.7, 6.3 / 4.5).
+  const bool twice = P.max_nb <= 8192 && (BF16 ? P.M >= 131072u && P.n_slices >= 8 : P.M >= 32768u);
+  const bool stream = P.M <= kStreamMaxM && (P.max_nb <= 4096 || twice);
   if (logM > kFftMaxLogQ && stream) {
 #define IWDFT_PF_STREAM(NBT, NP, EQ)                                                                          \
   {                                                                                                           \
