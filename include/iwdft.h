@@ -73,14 +73,14 @@ enum {
                                        bf16 inputs below 2^-14 in magnitude lose bits
                                        (below 2^-24 they count as 0), fp32 inputs keep
                                        ~21 bits down to 2^-14 and an absolute 2^-25
-                                       below.  The FFT and chirp-z prefills have no such
+                                       below.  The other two prefills have no such
                                        limits, but two neighbouring channels (2 i, 2 i + 1)
                                        share a transform: in the FFT prefill of contexts
                                        with 384 or more kept bins in some layer, or with
                                        IWDFT_FLAG_FFT_PREFILL, the smaller one has the
                                        fp32 rounding of the larger one, and a value that
                                        is not finite reaches both.  Otherwise, and in the
-                                       chirp-z prefill, each is as exact as alone.  All
+                                       prefill of other M, each is as exact as alone.  All
                                        transforms of this library (attention,
                                        reconstruction and ablation too) hold sums up to
                                        2^97: values times their number's square root,
@@ -91,7 +91,7 @@ enum {
                                        keeps nothing per bin in registers).  With neither flag
                                        the library picks: FFT when it applies and some
                                        layer keeps >= 128 bins or >= M / 32 (with fewer
-                                       than 384 only where it is faster); other M: chirp-z
+                                       than 384 only where it is faster); other M: interpolated
                                        transforms where the attention has them (see
                                        iwdft_attn_kind) and they are faster        */
   IWDFT_FLAG_SHORTCUT = 8u,         /* the variant of the update that Sec. 4.1 mentions for long
@@ -141,8 +141,8 @@ int iwdft_query_bytes(const iwdft_desc* desc, size_t* state_bytes, size_t* works
 /* Validates desc, copies the bin lists into d_state and zeroes the coefficients
  * (synchronous; not a hot call).  Both buffers must be 256-byte aligned and stay
  * alive and untouched by the caller until iwdft_destroy.  Neither may serve two
- * contexts at a time: the workspace holds data between calls as well (the table of
- * the chirp-z transforms from this call on, the tokens of a deferred write-back).
+ * contexts at a time: the workspace holds data between calls as well (the tables of
+ * transforms of any length from this call on, the tokens of a deferred write-back).
  * The HIP device that is current at this call owns the context. */
 int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void* d_workspace,
                  size_t workspace_bytes, iwdft_ctx** out);
@@ -158,7 +158,8 @@ int iwdft_destroy(iwdft_ctx* ctx); /* frees host memory only; NULL is accepted *
 int iwdft_prefill(iwdft_ctx* ctx, const void* d_K, const void* d_V, void* hip_stream);
 
 /* Which transform iwdft_prefill runs for this context: 0 = dense contraction, 1 = FFTs + pruning
- * (M = 2^m), 2 = chirp-z transforms + pruning (other M); -1 if ctx is NULL. */
+ * (M = 2^m), 2 = transforms interpolated from a
+ * power-of-two grid + pruning (other M); -1 if ctx is NULL. */
 int iwdft_prefill_kind(const iwdft_ctx* ctx);
 
 /* Which synthesis compressed_decode_attn / iwdft_append_attn run for this context: 1 = scores and softmax

@@ -48,12 +48,13 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int64_t ws_total = 0;    // float2 per workspace array
   int32_t G = 1, max_nb = 0, max_Bp = 0;
   bool use_fft = false;          // decode attention through power-of-two FFTs
-  bool use_chirp_prefill = false;  // prefill through chirp-z transforms
+  bool use_any_prefill = false;  // prefill through interpolated transforms
   bool use_chirp = false;        // ... through chirp-z transforms (any M up to kChirpMaxM when use_fft is false)
   int chirp_logN = 0;            // length of its circular convolutions
   int chirp_logS = 0;            // length of a table that the state buffer used to hold: its bytes stay, for copies of the buffer
   int64_t chirp_Q = 0;           // points per chirp-z transform: M / Pb (M itself up to 8192)
   size_t off_chirp = 0, off_chirpW = 0;
+  size_t off_dec = 0, off_taps = 0;  // in the workspace
   int64_t tw_Q = 0;              // length of the transforms whose twiddle octant is at off_tw
   size_t off_tw = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
@@ -74,7 +75,8 @@ constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit 
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
-constexpr int64_t kChirpPrefillPoints = 80;  // points of convolution that take as long as one token of the contraction
+// grid points that take as long as one token of the contraction
+constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
@@ -222,19 +224,17 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     }
   }
 
-  // Prefill through chirp-z transforms where they are faster than the dense contraction.  Measured: the transforms take one
-  // slice's 128 pairs of channels at 1900 points of convolution per us, and 1.5 points per kept bin where blocks are summed
-  // in the output rows; the contraction walks the M tokens at 23 per us with 256 workgroups (slices x tiles of 128 bins) at
-  // a time, whether or not the last round is full.  S slices, dense / chirp in us: S = 8, M = 8132, 512 bins 361 / 75; S = 64:
-  // 482 / 573, with 640 bins 818 / 578; S = 256, 2033 bins 7400 / 2300; S = 64, M = 1988, 256 bins 111 / 111, 640 bins
-  // 224 / 113; S = 64, M = 9000, 640 bins 898 / 965; S = 32, M = 32708, 4096 bins 7300 / 1500.
-  // These are bf16; in fp32 the contraction takes 1.6 times as long and the transforms 1.25 times (S = 256, M = 8132, 2033 bins
-  // 11600 / 2860), so the line lies on the contraction's side there: contexts near it keep the path they had.
-  // Longer M with blocks of a few points only stay with the contraction.
+  // Prefill through interpolated transforms where they are faster than the dense contraction.  The transforms cost in proportion to
+  // slices and grid points, and 1.5 points per kept bin where blocks are summed in the output rows; the contraction walks the M
+  // tokens with 256 workgroups (slices x tiles of 128 bins) at a time, whether or not the last round is full.  The line is where the
+  // two meet over 11 lengths from 300 to 32708, 8 to 256 slices and 32 to 1024 bins: no call there is more than 1.28 (bf16) and
+  // 1.35 (fp32) times slower than on the other path, 0.4 and 0.5 % in the mean.  Dense / transforms in us, points per token and round:
+  // bf16 M = 8132, 64 slices, 512 bins (129) 462 / 348; M = 3000, 128 slices, 512 bins (175) 350 / 306; M = 5000, 64 slices, 128 bins
+  // (210) 226 / 250; fp32 the same three 755 / 483, 571 / 404, 399 / 377.  Blocks of a few points only stay with the contraction.
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
     const int64_t Pb = d->M / pl->chirp_Q;
     const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
-    pl->use_chirp_prefill = S * points <= kChirpPrefillPoints * d->M * rounds;
+    pl->use_any_prefill = S * points <= (b16 ? kAnyPrefillPoints16 : kAnyPrefillPoints32) * d->M * rounds;
   }
 
   // What is left takes the direct O(M |B|) sums: fine for short or sparse states, useless beyond -- refuse instead of
@@ -287,6 +287,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_pendV = o; o = align256(o + esz * n_sl * pend_rows * kHeadDim);
   pl->off_ps = o;    o = align256(o + (pl->write_every > 1 ? sizeof(float) * n_sl * (size_t)pl->G * kMaxPend : 0));
   pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
+  pl->off_dec = o;   o = align256(o + (pl->use_chirp ? sizeof(float) * ((size_t)1 << pl->chirp_logN) / 2 : 0));
+  pl->off_taps = o;  o = align256(o + (pl->use_chirp ? 10 * sizeof(float) * ((size_t)pl->chirp_Q / 2 + 1) : 0));
   pl->off_direct = o;
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
@@ -343,6 +345,64 @@ int64_t digit_position(int64_t m, int logN) {
   const int odd = logN & 1, even = logN - odd;
   for (int t = 0; t < even / 2; ++t) p |= ((m >> (odd + 2 * t)) & 3) << (even - 2 * t - 2);
   return odd ? p | ((m & 1) << even) : p;
+}
+
+// Tables of the interpolated transforms (interp.h), in double precision: 1 / W at the samples of every thread, [8][N / 16], and
+// the taps of the frequencies 0 .. Q / 2, [2][n][4] | [n][2].  W: transform of the window I0(beta sqrt(1 - (x / 4)^2)), |x| < 4, both divided by W(0); beta
+// after P. J. Beatty, D. G. Nishimura and J. M. Pauly, IEEE Trans. Med. Imaging 24 (2005).
+// I0(2 sqrt(q[j])) by its series: for q <= 120 (a grid of 4 Q points) term 50 is 1e-24 of the sum.
+void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
+  double term[kTaps];
+  for (int j = 0; j < kTaps; ++j) sum[j] = term[j] = 1.0;
+  for (int k = 1; k < 50; ++k) {
+    const double f = 1.0 / ((double)k * k);
+    for (int j = 0; j < kTaps; ++j) {
+      term[j] *= q[j] * f;
+      sum[j] += term[j];
+    }
+  }
+}
+void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float>* taps) {
+  const double kPi = 3.14159265358979323846;
+  const int64_t N = (int64_t)1 << logN, T = N / 16, n = Q / 2 + 1;
+  const double a = (double)kTaps * (1.0 - 0.5 * (double)Q / (double)N), beta = kPi * std::sqrt(a * a - 0.8);
+  const auto W = [&](int64_t m) {  // up to a constant factor; real for |m| <= N / 4
+    const double y = kPi * kTaps * (double)m / (double)N, r = std::sqrt(beta * beta - y * y);
+    return std::sinh(r) / r;
+  };
+  const double W0 = W(0);
+  dec->assign((size_t)(8 * T), 0.f);
+  for (int64_t t = 0; t < T; ++t) {
+    int64_t n0 = 0;  // time index of position 16 t (fft_core.h, sample_at)
+    {
+      const int64_t p = 16 * t;
+      const int odd = logN & 1, even = logN - odd;
+      for (int b = 0; b < even; b += 2) n0 |= ((p >> b) & 3) << (even - 2 - b);
+      if (odd) n0 = (n0 << 1) | (p >> (logN - 1));
+    }
+    for (int i = 0; i < 8; ++i) {
+      const int64_t m = n0 + (i < 4 ? i : i - 8) * (N / 16);
+      if (m >= 0 ? m < (Q + 1) / 2 : -m <= Q / 2) (*dec)[(size_t)(i * T + t)] = (float)(W0 / W(m));
+    }
+  }
+  taps->assign((size_t)(10 * n), 0.f);
+  const double scale = 2.0 / kTaps;  // the window itself has kTaps W(0) as its integral
+  for (int64_t r = 0; r < n; ++r) {
+    const int64_t f = r * N / Q, first = f - (kTaps / 2 - 1);
+    const int odd = (int)(first & 1);
+    const int32_t even = (int32_t)(first - odd);
+    memcpy(&(*taps)[(size_t)(8 * n + 2 * r + 1)], &even, sizeof(even));
+    double z[kTaps], w[kTaps];
+    for (int j = 0; j < kTaps; ++j) {
+      const double x = (double)(r * N - (first + j) * Q) / (double)Q * scale;
+      z[j] = 0.25 * beta * beta * (1.0 - x * x);
+    }
+    bessel_i0(z, w);
+    for (int j = 0; j < kTaps; ++j) {
+      const int e = odd + j;
+      (*taps)[(size_t)(e < 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r)] = z[j] > 0.0 ? (float)(w[j] / (kTaps * W0)) : 0.f;
+    }
+  }
 }
 
 }  // namespace
@@ -529,6 +589,10 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       if (e == hipSuccess)
         e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
+      std::vector<float> dec, taps;
+      make_interp(pl.chirp_Q, pl.chirp_logN, &dec, &taps);
+      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_dec, dec.data(), sizeof(float) * dec.size(), hipMemcpyHostToDevice);
+      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_taps, taps.data(), sizeof(float) * taps.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && pl.tw_Q) {
       const double kTwoPi = 6.28318530717958647692;
@@ -566,8 +630,10 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.fold = (const uint16_t*)(c->state + pl.off_fold);
     P.chirp = pl.use_chirp ? (const float2*)(c->state + pl.off_chirp) : nullptr;
     P.chirpW = pl.use_chirp ? (const float4*)(c->ws + pl.off_chirpW) : nullptr;
-    P.chirp_logN = pl.chirp_logN;
-    P.chirp_Q = (uint32_t)pl.chirp_Q;
+    P.any_dec = pl.use_chirp ? (const float*)(c->ws + pl.off_dec) : nullptr;
+    P.any_taps = pl.use_chirp ? (const float4*)(c->ws + pl.off_taps) : nullptr;
+    P.any_logN = pl.chirp_logN;
+    P.any_Q = (uint32_t)pl.chirp_Q;
     P.tab = tab;
     P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;
     P.FK = (float2*)(c->state + pl.off_FK);
@@ -633,7 +699,7 @@ int iwdft_phase_times(iwdft_ctx* ctx, double* ms, int64_t* n_calls) {
 int64_t iwdft_num_tokens(const iwdft_ctx* ctx) { return ctx ? ctx->T : -1; }
 
 int iwdft_prefill_kind(const iwdft_ctx* ctx) {
-  return ctx ? (ctx->plan.use_fft_prefill ? 1 : (ctx->plan.use_chirp_prefill ? 2 : 0)) : -1;
+  return ctx ? (ctx->plan.use_fft_prefill ? 1 : (ctx->plan.use_any_prefill ? 2 : 0)) : -1;
 }
 
 int iwdft_attn_pipelined(const iwdft_ctx* ctx) { return ctx ? (attn_pipelines(ctx->P, ctx->plan.use_fft) ? 1 : 0) : -1; }
@@ -661,8 +727,8 @@ int iwdft_prefill(iwdft_ctx* ctx, const void* d_K, const void* d_V, void* hip_st
   }
   ctx->pend = 0;  // the prefill overwrites the whole state
   rc = launched(ctx->plan.use_fft_prefill ? launch_prefill_fft(ctx->P, d_K, d_V, (hipStream_t)hip_stream)
-                : ctx->plan.use_chirp_prefill
-                    ? launch_prefill_chirp(ctx->P, d_K, d_V, (hipStream_t)hip_stream)
+                : ctx->plan.use_any_prefill
+                    ? launch_prefill_any(ctx->P, d_K, d_V, (hipStream_t)hip_stream)
                     : launch_prefill(ctx->P, d_K, d_V, (hipStream_t)hip_stream),
                 "prefill launch");
   if (rc != IWDFT_OK) return rc;

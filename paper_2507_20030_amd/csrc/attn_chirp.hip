@@ -35,7 +35,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
   const LayerInfo L = layer_info(P, layer);
   const int g0 = pair * 2;
   const bool has1 = (g0 + 1) < P.G;
-  const uint32_t M = P.M, Q = P.chirp_Q, Pb = M / Q;
+  const uint32_t M = P.M, Q = P.any_Q, Pb = M / Q;
   const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   const float2* q1 = has1 ? q0 + L.Bp : q0;
   float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
@@ -286,7 +286,7 @@ hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, floa
     attn_chirp_kernel<LN><<<dim3((uint32_t)grid), dim3(attn_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
                                                                                      ptsh, ps);                        \
   } break;
-  switch (P.chirp_logN) {
+  switch (P.any_logN) {
     IWDFT_CHIRP_CASE(8)
     IWDFT_CHIRP_CASE(9)
     IWDFT_CHIRP_CASE(10)

@@ -7,6 +7,7 @@
 #pragma once
 #include "common.h"
 #include "fft_core.h"
+#include "interp.h"
 
 namespace iwdft {
 
@@ -27,13 +28,6 @@ __device__ __forceinline__ void chirp_convolve(float2* buf, const TabMem& tab, c
   half_forward<LOGN>(buf, tab, t, x, v);
 }
 
-// k mod n for factors below 2^21 (M <= 256 * 8192), without an integer division.
-__device__ __forceinline__ uint32_t mod_small(uint32_t k, uint32_t n, float inv_n) {  // k < 2^29, k / n < 2^20
-  int32_t r = (int32_t)(k - (uint32_t)((float)k * inv_n) * n);  // the quotient is off by one at most
-  if (r < 0) r += (int32_t)n;
-  if (r >= (int32_t)n) r -= (int32_t)n;
-  return (uint32_t)r;
-}
 // e^{+j 2 pi a b / M} to fp32 rounding: M is not a power of two, so the phase is reduced in integers and split in double.
 __device__ __forceinline__ float2 cis_exact(uint32_t a, uint32_t b, uint32_t M, double inv_M) {
   const uint64_t p = (uint64_t)a * b;

@@ -10,6 +10,7 @@ namespace iwdft {
 
 constexpr int kHeadDim = 128;  // channels per head the kernels are written for
 constexpr int kMaxPend = 16;   // most tokens of a deferred write-back
+constexpr int kTaps = 8;       // grid points of the interpolation window (interp.h)
 constexpr int kRowPad = 32;    // a coefficient row is padded to a multiple of this many bins
 
 // Per-layer geometry, one entry per layer in device memory.
@@ -44,13 +45,16 @@ struct Params {
   const float* weights;
   const uint16_t* fold;  // per kept bin: low byte = round of its direct slot, high byte = round of its mirror slot
                          // (0xff: the mirror falls on the direct slot and is added in the same write)
-  // Chirp-z transforms (M that is not a power of two; null otherwise) of chirp_Q = M / Pb points, Pb the smallest divisor of
-  // M with M / Pb <= 8192 (1 for M <= 8192).  chirp[a] = exp(+j pi a^2 / chirp_Q), a < chirp_Q; chirpW: the transform of the
-  // conjugate chirp divided by its length 2^chirp_logN, laid out as chirp.h reads it.
+  // Chirp-z transforms (M that is not a power of two; null otherwise) of any_Q = M / Pb points, Pb the smallest divisor of
+  // M with M / Pb <= 8192 (1 for M <= 8192).  chirp[a] = exp(+j pi a^2 / any_Q), a < any_Q; chirpW: the transform of the
+  // conjugate chirp divided by its length 2^any_logN, laid out as chirp.h reads it.
   const float2* chirp;
   const float4* chirpW;
-  int32_t chirp_logN;
-  uint32_t chirp_Q;
+  // Interpolated transforms (interp.h) of any_Q points from a grid of 2^any_logN, for the same M; tables in the workspace.
+  int32_t any_logN;
+  uint32_t any_Q;
+  const float* any_dec;    // 1 / W per sample
+  const float4* any_taps;  // taps per frequency
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
   const float2* tw8;  // e^{j 2 pi m / Q}, m = 0 .. Q / 8, Q = min(M, 8192), for fft_lds.h (null unless M = 2^m >= 256)
   float2* FK;
@@ -169,8 +173,8 @@ constexpr int kFftAloneBins = 384;
 constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
-// ... and through chirp-z transforms (Params::chirp set).
-hipError_t launch_prefill_chirp(const Params& P, const void* K, const void* V, hipStream_t st);
+// ... and through interpolated transforms (Params::any_dec set).
+hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hipStream_t st);
 hipError_t launch_prefill_edges(const Params& P, const void* K, const void* V, hipStream_t st);
 // ring_pos: slot of the recent ring that holds the oldest token (ignored when R == 0).
 hipError_t launch_append(const Params& P, const void* tok_k, const void* tok_v, uint32_t t_shift,

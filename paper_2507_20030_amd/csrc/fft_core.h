@@ -191,13 +191,25 @@ __device__ __forceinline__ void dft16(float2 (&x)[16], const Tw16& w) {
   r4<INV, true>(x[2 * S], x[2 * S + G], x[2 * S + 2 * G], x[2 * S + 3 * G], w.a.x, w.a.y, w.c.x, w.c.y);
   r4<INV, true>(x[3 * S], x[3 * S + G], x[3 * S + 2 * G], x[3 * S + 3 * G], w.a.z, w.a.w, w.c.z, w.c.w);
 }
-template <bool INV>
+// WINGS (forward): the samples of the two middle quarters of the time axis, x[4 g + 1] and x[4 g + 2], are zero and not looked at.
+template <bool INV, bool WINGS = false>
 __device__ __forceinline__ void dft16_1(float2 (&x)[16]) {  // t = 1
   constexpr int S = INV ? 4 : 1, G = INV ? 1 : 4;
   constexpr float kC1 = 0.92387953251128674f, kT1 = 0.41421356237309505f;  // cos, tan 22.5 degrees
   constexpr float kC3 = 0.38268343236508977f, kT3 = 2.41421356237309505f;  // cos, tan 67.5 degrees
+  static_assert(!(INV && WINGS), "forward only");
 #pragma unroll
-  for (int g = 0; g < 4; ++g) r4_1<INV>(x[g * G], x[g * G + S], x[g * G + 2 * S], x[g * G + 3 * S]);
+  for (int g = 0; g < 4; ++g) {
+    if constexpr (WINGS) {
+      const float2 a = x[4 * g], b = x[4 * g + 3];
+      x[4 * g] = cadd(a, b);
+      x[4 * g + 1] = make_float2(a.x - b.y, a.y + b.x);
+      x[4 * g + 2] = csub(a, b);
+      x[4 * g + 3] = make_float2(a.x + b.y, a.y - b.x);
+    } else {
+      r4_1<INV>(x[g * G], x[g * G + S], x[g * G + 2 * S], x[g * G + 3 * S]);
+    }
+  }
   r4_1<INV>(x[0], x[G], x[2 * G], x[3 * G]);
   r4<INV>(x[S], x[S + G], x[S + 2 * G], x[S + 3 * G], kCos45, 1.f, kC1, kT1);
   r4_e<INV>(x[2 * S], x[2 * S + G], x[2 * S + 2 * G], x[2 * S + 3 * G]);
@@ -349,11 +361,12 @@ __device__ __forceinline__ void fft_fwd_passes(float2* buf, const Tab& tab, int 
   }
 }
 // hook(k) runs between the butterflies of radix-16 pass k = 0 .. fft_np(LOGQ) - 1 and its stores.
-template <int LOGQ, bool WIDE = false, typename Tab, typename Hook>
+// WINGS: see dft16_1.
+template <int LOGQ, bool WIDE = false, bool WINGS = false, typename Tab, typename Hook>
 __device__ __forceinline__ void fft_forward(float2* buf, const Tab& tab, int t, float2 (&x)[16], Hook hook) {
   Tw16 w;
   if constexpr (Tab::kEarly) tab.template load<LOGQ, 1, false>(w, t);
-  dft16_1<false>(x);
+  dft16_1<false, WINGS>(x);
   hook(0);
   write16(buf, t, x);
   __syncthreads();

@@ -1,0 +1,125 @@
+// Transforms of Q points for any Q <= 8192 by interpolation from a power-of-two grid (A. Dutt and V. Rokhlin, "Fast Fourier
+// transforms for nonequispaced data", SIAM J. Sci. Comput. 14 (1993); window after Kaiser and Bessel).  With a window w of kTaps
+// grid points and its Fourier transform W, and N = 2^LOGN >= 2 Q grid points,
+//   sum_n x[n] e^{-j 2 pi r n / Q} = sum_m w(r N / Q - m) Y[m],   Y[m] = sum_n x[n] / W(n / N) e^{-j 2 pi m n / N},  |n| <= Q / 2,
+// up to an aliasing error of 2e-8 or less (kTaps = 8, N >= 2 Q): one N-point transform of a signal that is zero in half of its points, where
+// the chirp-z identity takes two.  Host tables: 1 / W (one value per sample) and the taps of every r up to Q / 2 -- those of -r are
+// the same, mirrored.
+#pragma once
+#include "common.h"
+#include "fft_core.h"
+
+namespace iwdft {
+
+// k mod n for factors below 2^21 (M <= 256 * 8192), without an integer division.
+__device__ __forceinline__ uint32_t mod_small(uint32_t k, uint32_t n, float inv_n) {  // k < 2^29, k / n < 2^20
+  int32_t r = (int32_t)(k - (uint32_t)((float)k * inv_n) * n);  // the quotient is off by one at most
+  if (r < 0) r += (int32_t)n;
+  if (r >= (int32_t)n) r -= (int32_t)n;
+  return (uint32_t)r;
+}
+// Samples of thread t: time n0 + i N / 16, i = 0 .. 3 (positions 16 t + 4 i) and i = -4 .. -1 (positions 16 t + 4 (i + 4) + 3), n0 =
+// sample_at(16 t); all others are zero.  Index into the signal of sample i = 0 .. 7 (0 .. 3, then -4 .. -1), Q or more: none.
+template <int LOGN>
+__device__ __forceinline__ uint32_t wing_index(uint32_t n0, int i, uint32_t Q) {
+  if (i < 4) {
+    const uint32_t a = n0 + ((uint32_t)i << (LOGN - 4));
+    return a < ((Q + 1) >> 1) ? a : Q;
+  }
+  const uint32_t a = n0 + ((uint32_t)(i - 8) << (LOGN - 4)) + Q;  // wraps to a large number where n0 + ... < -Q
+  return a >= ((Q + 1) >> 1) ? a : Q;
+}
+constexpr int wing_position(int i) { return i < 4 ? 4 * i : 4 * (i - 4) + 3; }
+
+// The taps of frequency r as laid out by the host: nine weights for the grid points e, e + 1, ..., e + 8 with e even (one of the
+// outer two is zero) and e itself, -4 <= e: [2][n] float4 | [n] float2 (weight, e as bits), n = Q / 2 + 1.
+struct Taps {
+  float w[9];
+  int e;
+};
+__device__ __forceinline__ Taps load_taps(const float4* __restrict__ tab, uint32_t r, uint32_t Q) {
+  const uint32_t n = (Q >> 1) + 1;
+  const float4 a = tab[r], b = tab[n + r];
+  const float2 c = ((const float2*)(tab + 2 * n))[r];
+  Taps T;
+  T.w[0] = a.x, T.w[1] = a.y, T.w[2] = a.z, T.w[3] = a.w, T.w[4] = b.x, T.w[5] = b.y, T.w[6] = b.z, T.w[7] = b.w, T.w[8] = c.x;
+  T.e = __float_as_int(c.y);
+  return T;
+}
+
+// The transform leaves the grid in natural order without padding, kHalo entries of either end repeated beyond the other:
+// a window of taps is one address, and lanes with neighbouring bins read neighbouring 16 bytes.
+constexpr int kHalo = 16;
+constexpr int grid_lds(int logN) { return fft_lds(logN) > (1 << logN) + 2 * kHalo ? fft_lds(logN) : (1 << logN) + 2 * kHalo; }
+
+// Grid of the samples x (wing_position; the others not looked at).  Entry m at buf[kHalo + m].  Entries beyond +-reach need not be formed.
+template <int LOGN, typename Hook>
+__device__ __forceinline__ void grid_forward(float2* buf, const TabMem& tab, int t, float2 (&x)[16], int reach, Hook hook) {
+  constexpr int N = 1 << LOGN, T = fft_threads(LOGN), REM = fft_rem(LOGN), NP = fft_np(LOGN);
+  constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
+  Tw16 w;
+  tab.load<LOGN, 1, false>(w, t);
+  dft16_1<false, true>(x);
+  hook(0);
+  write16(buf, t, x);
+  __syncthreads();
+  constexpr int kLast = REM ? NP - 1 : NP - 2;  // last radix-16 pass that stays in place
+  if constexpr (kLast >= 1) fft_pass<LOGN, 1, false, (NP > 2 ? 2 : -1)>(buf, tab, t, w, [&] { hook(1); });
+  if constexpr (kLast >= 2) fft_pass<LOGN, 2, false, -1>(buf, tab, t, w, [&] { hook(2); });
+  static_assert(NP <= 3, "two passes in place at most");
+  const float2* own = buf + fpad(t);  // entries t + T i at i * SP
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = own[i * SP];
+  const float2* __restrict__ tw = tab.tab + tab_off_rem(LOGN);
+  const int k0 = pin_index(t);
+  if constexpr (REM == 0) {
+    dft16<false>(x, w);
+  } else if constexpr (REM == 1) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float2 v = tw[k0 + i * T];
+      bfly<false>(x[i], x[i + 8], v.x, v.y);
+    }
+  } else if constexpr (REM == 2) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = ((const float4*)tw)[k0 + i * T];
+      r4<false>(x[i], x[i + 4], x[i + 8], x[i + 12], v.x, v.y, v.z, v.w);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float4 v = ((const float4*)tw)[k0 + i * T], u = ((const float4*)(tw + N / 4))[k0 + i * T];
+      r4<false>(x[i], x[i + 2], x[i + 4], x[i + 6], v.x, v.y, v.z, v.w);
+      r4<false>(x[i + 8], x[i + 10], x[i + 12], x[i + 14], v.x, v.y, v.z, v.w);
+      bfly<false>(x[i], x[i + 8], u.x, u.y);
+      bfly<false>(x[i + 2], x[i + 10], u.z, u.w);
+      bfly_j<false>(x[i + 4], x[i + 12], u.x, u.y);
+      bfly_j<false>(x[i + 6], x[i + 14], u.z, u.w);
+    }
+  }
+  __syncthreads();
+  float2* out = buf + kHalo + t;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (i < 8 ? i * T <= reach : (16 - (i + 1)) * T < reach) out[i * T] = x[i];  // uniform
+  if (t < kHalo) out[N] = x[0];
+  if (t >= T - kHalo) out[15 * T - N] = x[15];
+  __syncthreads();
+}
+// Values of the Q-point transform at r and -r.
+__device__ __forceinline__ void grid_at(const float2* buf, int N, const Taps& T, float2& zr, float2& zm) {
+  const float4* up = (const float4*)(buf + (kHalo + T.e));           // e, e + 1, ...
+  const float4* dn = (const float4*)(buf + (kHalo + N - T.e - 8));   // -e - 8, -e - 7, ... modulo N
+  zr = zm = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const float4 p = up[i], m = dn[4 - i];  // e + 2 i, e + 2 i + 1; -(e + 2 i), -(e + 2 i - 1)
+    zr = make_float2(fmaf(T.w[2 * i], p.x, zr.x), fmaf(T.w[2 * i], p.y, zr.y));
+    zm = make_float2(fmaf(T.w[2 * i], m.x, zm.x), fmaf(T.w[2 * i], m.y, zm.y));
+    if (i < 4) zr = make_float2(fmaf(T.w[2 * i + 1], p.z, zr.x), fmaf(T.w[2 * i + 1], p.w, zr.y));
+    if (i > 0) zm = make_float2(fmaf(T.w[2 * i - 1], m.z, zm.x), fmaf(T.w[2 * i - 1], m.w, zm.y));
+  }
+}
+
+}  // namespace iwdft

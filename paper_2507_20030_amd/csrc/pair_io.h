@@ -60,7 +60,7 @@ __device__ __forceinline__ PairScale pair_scale(uint32_t m0, uint32_t m1) {  // 
   s.h1 = not_finite(m1) ? NAN : m1 ? 0.5f * __uint_as_float((uint32_t)(127 - de) << 23) : 0.f;
   return s;
 }
-// The same for all pairs of the raw words of a thread's 16 samples, in a workgroup of 512 threads with NS transforms interleaved
+// The same for all pairs of the raw words of a thread's C samples, in a workgroup of WAVES waves with NS transforms interleaved
 // over the lanes (this thread's: tid % NS): channels that are not finite are cleared in the words.  red is free again behind the
 // next barrier.  One lane reduction and one barrier serve all pairs of a load; the maxima of a bf16 pair are one packed word.
 template <bool BF16>
@@ -76,15 +76,15 @@ template <int N>
 __device__ __forceinline__ uint32_t row_ror(uint32_t v) {  // the value N lanes further in the row of 16
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xf, 0xf, false);
 }
-template <bool BF16, int NS, int NW, int NP>
-__device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[16], int tid, uint32_t (&red)[8][NS][NW], PairScale (&sc)[NP]) {
+template <bool BF16, int NS, int NW, int NP, int C, int WAVES>
+__device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[C], int tid, uint32_t (&red)[WAVES][NS][NW], PairScale (&sc)[NP]) {
   static_assert(NW == NP * (BF16 ? 1 : 2) && NS <= 32, "");
   uint32_t m[NW];
 #pragma unroll
   for (int n = 0; n < NW; ++n) {
     m[n] = 0u;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) m[n] = word_max<BF16>(m[n], z[i].w[n] & (BF16 ? 0x7fff7fffu : 0x7fffffffu));
+    for (int i = 0; i < C; ++i) m[n] = word_max<BF16>(m[n], z[i].w[n] & (BF16 ? 0x7fff7fffu : 0x7fffffffu));
     // over the lanes of the same transform: rotations inside the rows of 16 lanes, then the rows
     if constexpr (NS <= 8) m[n] = word_max<BF16>(m[n], row_ror<8>(m[n]));
     if constexpr (NS <= 4) m[n] = word_max<BF16>(m[n], row_ror<4>(m[n]));
@@ -105,14 +105,14 @@ __device__ __forceinline__ void scale_pairs(Raw<NW> (&z)[16], int tid, uint32_t 
 #pragma unroll
   for (int n = 0; n < NW; ++n) {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) m[n] = word_max<BF16>(m[n], red[w][tid & (NS - 1)][n]);
+    for (int w = 0; w < WAVES; ++w) m[n] = word_max<BF16>(m[n], red[w][tid & (NS - 1)][n]);
     if constexpr (NS == 1) m[n] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m[n]);
     uint32_t keep;
     if constexpr (BF16) keep = (not_finite(m[n] << 16) ? 0u : 0xffffu) | (not_finite(m[n] & 0xffff0000u) ? 0u : 0xffff0000u);
     else keep = not_finite(m[n]) ? 0u : ~0u;
     if (keep != ~0u) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) z[i].w[n] &= keep;
+      for (int i = 0; i < C; ++i) z[i].w[n] &= keep;
     }
   }
 #pragma unroll

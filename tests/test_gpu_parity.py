@@ -1024,6 +1024,27 @@ def test_chirp_prefill_all_convolution_lengths(dtype, L, S, R, n_bins, n_layers)
     assert st["coef0"] < 2e-5
 
 
+@pytest.mark.parametrize("L", [259, 511, 513, 1000, 2047, 2049, 4095, 4097, 8191, 2 * 6144, 3 * 8192, 3 * 8191])
+def test_interpolated_prefill_against_64_bit_transforms(L):
+    """Every grid length at both ends of its range (L / 2 up to a power of two: the widest and the closest spacing of the taps; 24576
+    = 3 x 8192: taps on grid points), a layer of low bins and one of bins anywhere.  Bar: aliasing 2e-8 + fp32 rounding, which grows
+    by at most 2^-24 per radix-2 stage in the 2-norm (16 stages with the two ends): 1e-6."""
+    rng = np.random.default_rng(L)
+    low = np.arange(min(L // 4, 700), dtype=np.int32)
+    wide = np.unique(np.r_[0, 1, 2, 3, L // 2 - 1, L // 2, L // 2 + 1, L - 3, L - 2, L - 1, rng.integers(0, L, 500)]).astype(np.int32)
+    K, V = torch.randn((2, 2, 1, 8, L, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(L))
+    c = B.Cache(2, 1, 8, 8, 128, torch.float32, L, [low, wide])
+    assert B.iwdft_prefill_kind(c.ctx) == "chirp"
+    c.prefill(K, V)
+    for layer, bins in enumerate((low, wide)):
+        for X, got in zip((K, V), c.export_coeffs(layer)):
+            ref = torch.fft.fft(X[layer, 0, ::7].cpu().double(), dim=1)[:, bins.astype(np.int64)] / L
+            got = got[0, ::7].cpu().to(torch.complex128)
+            assert float((got - ref).norm() / ref.norm()) < 1e-6
+            assert float((got - ref).abs().max() / ref.abs().pow(2).mean().sqrt()) < 1e-5
+    c.close()
+
+
 def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one():
     # neighbouring channels share a transform; every channel has to be as accurate as alone (fp32 rounding, 2^-24, times
     # ~log2 of the 16384 points of each of two transforms and the tables: below 1e-5)
