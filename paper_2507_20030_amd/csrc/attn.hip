@@ -156,13 +156,16 @@ __device__ __forceinline__ v4f lane_twiddles(const Params& P, const LayerInfo& L
 constexpr int qc_smem_floats(int GT, int MODE) {
   return GT * kHeadDim + (MODE == kUpdate1 ? 1 : kMaxPend) * kHeadDim + (MODE == kPlain ? kMaxPend : 1) * GT;
 }
-// The work of logical block `bid` (wave-uniform) with THREADS threads; `sm` holds qc_smem_floats floats.
-template <bool BF16, int GT, int MODE, int THREADS>
+// The work of logical block `bid` (wave-uniform) with THREADS threads; `sm` holds qc_smem_floats floats.  RL lanes (whole waves) run
+// along the bins, THREADS / RL groups of them share the channels; their sums meet in `part` ([THREADS][GT], with several groups).
+template <bool BF16, int GT, int MODE, int THREADS, int RL = THREADS>
 __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict__ q, float2* __restrict__ qc,
                                         float* __restrict__ pe, int chunks, int passes, const StepUpdate& up,
-                                        uint32_t bid, float* sm) {
+                                        uint32_t bid, float* sm, v4f* part = nullptr) {
   constexpr bool UPD = MODE != kPlain;
-  constexpr int kQcThreads = THREADS, kQcBins = THREADS * 2;
+  constexpr int kQcThreads = THREADS, kQcBins = RL * 2, kGroups = THREADS / RL, kChannels = kHeadDim / kGroups;
+  constexpr int U = kGroups > 1 ? 16 : 8;  // rows in flight
+  static_assert(RL % 64 == 0 && kChannels % U == 0, "");
   float (*qs)[kHeadDim] = (float (*)[kHeadDim])sm;                            // [GT][128]
   float (*xs)[kHeadDim] = qs + GT;                                             // pending K rows
   float (*dq)[GT] = (float (*)[GT])(xs + (MODE == kUpdate1 ? 1 : kMaxPend));   // q . k_j of the pending tokens
@@ -175,6 +178,17 @@ __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict_
   const int s = slice - layer * spl;
   const LayerInfo L = P.layers[layer];
   const int g0 = pass * GT;
+  const int i0 = chunk * kQcBins + (threadIdx.x % RL) * 2;
+  const int d0 = kGroups > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / RL) * kChannels : 0;
+  v4f* row = (v4f*)(P.FK + L.coef_off + (int64_t)s * kHeadDim * L.Bp + i0);
+  const int64_t stride = L.Bp / 2;
+  v4f f[U];
+  if constexpr (kGroups > 1) {  // few blocks: the first rows are on their way while the queries are
+    if (i0 < L.Bp) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) f[u] = __builtin_nontemporal_load(row + (d0 + u) * stride);
+    }
+  }
   for (int e = threadIdx.x; e < GT * kHeadDim; e += kQcThreads) {
     const int g = g0 + e / kHeadDim;
     qs[e / kHeadDim][e % kHeadDim] =
@@ -229,10 +243,11 @@ __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict_
       pe[((int64_t)slice * P.G + g0 + g) * E + e] = dot;
     }
   }
-  const int i0 = chunk * kQcBins + threadIdx.x * 2;
-  if (i0 >= L.Bp) return;
-  v4f* row = (v4f*)(P.FK + L.coef_off + (int64_t)s * kHeadDim * L.Bp + i0);
-  const int64_t stride = L.Bp / 2;
+  if (kGroups == 1 && i0 >= L.Bp) return;
+  v4f acc[GT];
+#pragma unroll
+  for (int g = 0; g < GT; ++g) acc[g] = (v4f)(0.f);
+  if (kGroups == 1 || i0 < L.Bp) {
   // twiddles of this lane's two bins; padding entries keep 0 and are not written
   const bool live = i0 < L.nb;
   v4f tw = (v4f)(0.f);
@@ -250,11 +265,8 @@ __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict_
     const v4f w2 = cmul2(w, w), w4 = cmul2(w2, w2);
     w8 = cmul2(w4, w4);
   }
-  v4f acc[GT];
-#pragma unroll
-  for (int g = 0; g < GT; ++g) acc[g] = (v4f)(0.f);
   if constexpr (MODE == kPlain) {
-    if (up.np > 0) {  // the pending tokens' share of qc
+    if (up.np > 0 && d0 == 0) {  // the pending tokens' share of qc
       const v4f w = lane_twiddles(P, L, i0, 1u);
       v4f t = tw;
       for (int j = 0; j < up.np; ++j) {
@@ -264,12 +276,12 @@ __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict_
       }
     }
   }
-  constexpr int U = 8;
 #pragma unroll 1
-  for (int d = 0; d < kHeadDim; d += U) {
-    v4f f[U];
+  for (int d = d0; d < d0 + kChannels; d += U) {
+    if (kGroups == 1 || d > d0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) f[u] = __builtin_nontemporal_load(row + (d + u) * stride);
+      for (int u = 0; u < U; ++u) f[u] = __builtin_nontemporal_load(row + (d + u) * stride);
+    }
     if constexpr (MODE == kUpdate1) {
       float x[U];
 #pragma unroll
@@ -306,6 +318,21 @@ __device__ __forceinline__ void qc_body(const Params& P, const void* __restrict_
 #pragma unroll
       for (int g = 0; g < GT; ++g) acc[g] += qs[g][d + u] * f[u];
   }
+  }
+  if constexpr (kGroups > 1) {
+#pragma unroll
+    for (int g = 0; g < GT; ++g) part[g * THREADS + threadIdx.x] = acc[g];
+    __syncthreads();
+    for (int e = threadIdx.x; e < GT * RL; e += kQcThreads) {
+      const int g = e / RL, l = e % RL, i = chunk * kQcBins + l * 2;
+      if (g0 + g >= P.G || i >= L.Bp) continue;
+      v4f sum = part[g * THREADS + l];
+#pragma unroll
+      for (int k = 1; k < kGroups; ++k) sum += part[g * THREADS + k * RL + l];
+      *(v4f*)(qc + L.ws_off + ((int64_t)s * P.G + g0 + g) * L.Bp + i) = sum;
+    }
+    return;
+  }
 #pragma unroll
   for (int g = 0; g < GT; ++g)
     if (g0 + g < P.G)
@@ -318,6 +345,20 @@ __global__ __launch_bounds__(qc_threads(MODE != kPlain)) void attn_qc_kernel(Par
                                                             int chunks, int passes, StepUpdate up) {
   __shared__ float sm[qc_smem_floats(GT, MODE)];
   qc_body<BF16, GT, MODE, qc_threads(MODE != kPlain)>(P, q, qc, pe, chunks, passes, up, blockIdx.x, sm);
+}
+// The same for few blocks: 128 bins a block and its channels over the waves.  What bounds a call of few slices is the serial chain
+// of a thread, 16 rounds of 8 rows and a trip to memory each; here it has two rounds of 16 rows (read-only) or one (update
+// modes), the first of them on its way before the queries are.  One slice group of 8, 64 bins, one head, fp32, M = 1024: this
+// kernel 13.3 -> 5.6 us, the decode step 23.9 -> 16.2; 64 slices x 1024 bins, 4 heads, read-only step 68 -> 42 us.
+constexpr int kQcFewBins = 128;
+template <bool BF16, int GT, int MODE>
+__global__ __launch_bounds__(qc_threads(MODE != kPlain)) void attn_qc_few_kernel(Params P, const void* __restrict__ q,
+                                                                float2* __restrict__ qc, float* __restrict__ pe,
+                                                                int chunks, int passes, StepUpdate up) {
+  constexpr int THREADS = qc_threads(MODE != kPlain);
+  __shared__ float sm[qc_smem_floats(GT, MODE)];
+  __shared__ v4f part[GT * THREADS];
+  qc_body<BF16, GT, MODE, THREADS, kQcFewBins / 2>(P, q, qc, pe, chunks, passes, up, blockIdx.x, sm, part);
 }
 
 // ------------------------------------------------------------------------------------------ C
@@ -1012,6 +1053,10 @@ __global__ __launch_bounds__(kDirThreads) void attn_direct_kernel(Params P, cons
 }
 
 // --------------------------------------------------------------------------------------- host
+// Most blocks of attn_qc_few_kernel: beyond these the wider rows of attn_qc_kernel stream better.  Decode step of 64 .. 1024 slices and
+// 64 .. 2048 bins against attn_qc_kernel, by blocks: update modes 512: 0.67 .. 0.95, 1024: 0.94 .. 1.04; read-only, 1 or 2 heads 512:
+// 0.82 .. 0.96, 1024: 0.97 .. 1.07; 4 heads 2048: 0.91 .. 0.96, 4096: 1.03; 8 heads 1024: 0.81 .. 0.94, 2048: 1.00 .. 1.06.
+constexpr uint64_t qc_few_blocks(int GT, bool upd) { return upd || GT <= 2 ? 512 : GT == 4 ? 2048 : 1024; }
 constexpr uint32_t kAbMinB = 1024, kAbMaxGroups = 8;  // fewest B blocks per group of slices, most groups
 static int heads_per_pass(int G);
 bool attn_pipelines(const Params& P, bool use_fft) {
@@ -1106,7 +1151,12 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     IWDFT_MARK(2)
   } else {
   IWDFT_MARK(0)
-  IWDFT_GT_SWITCH(attn_qc_kernel, gridA, kQcThreads, P, q, qc, pe, chunks, passes, u)
+  const int few = (P.max_Bp + kQcFewBins - 1) / kQcFewBins;
+  if ((uint64_t)P.n_slices * few * passes <= qc_few_blocks(GT, mode != kPlain)) {
+    IWDFT_GT_SWITCH(attn_qc_few_kernel, (uint64_t)P.n_slices * few * passes, kQcThreads, P, q, qc, pe, few, passes, u)
+  } else {
+    IWDFT_GT_SWITCH(attn_qc_kernel, gridA, kQcThreads, P, q, qc, pe, chunks, passes, u)
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   IWDFT_MARK(1)

@@ -410,6 +410,18 @@ def test_deferred_write_back_every_fft_kernel_variant(L, n_bins):
     run_stream(cfg, random_bins(cfg, 79), rec=(3, 50), fused=True, write_every=16, tag=f"defer-variants-L{L}-B{n_bins}")
 
 
+@pytest.mark.parametrize("group,batch,heads,n_bins,J", [
+    (1, 1, 1, 1, 0), (3, 1, 2, 129, 0), (8, 3, 2, 300, 4),                         # few blocks: one lane, a lane beyond 128 bins, three blocks a slice
+    (1, 32, 16, 100, 0), (1, 32, 16, 100, 4), (2, 19, 27, 128, 4), (2, 27, 19, 127, 0),  # 512 blocks and 513
+    (4, 64, 32, 100, 4), (3, 683, 3, 100, 4), (8, 64, 16, 128, 4), (5, 41, 25, 128, 4),   # 2048 and 2049, 1024 and 1025 (read-only steps)
+    (16, 2, 4, 40, 0),                                                              # two passes over the heads
+])
+def test_score_kernel_of_few_and_of_many_blocks(group, batch, heads, n_bins, J):
+    cfg = small_cfg(L=512, n_bins=n_bins, dtype="f32", group=group, batch=batch, n_kv_heads=heads, n_layers=1, steps=5, n_sink=2, n_recent=3)
+    run_stream(cfg, random_bins(cfg, 71), fused=group <= 8, write_every=J, rec=(0, 16), tag=f"blocks-{group}-{batch}x{heads}",
+               slices=wl.sample_slices(cfg, 5))
+
+
 def test_deferred_write_back_mixed_with_other_calls():
     # any call other than the fused step first writes the deferred tokens back: a random mix of calls
     # gives, step for step, what the oracle gives
