@@ -57,6 +57,10 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   size_t off_dec = 0, off_taps = 0;  // in the workspace
   int64_t tw_Q = 0;              // length of the transforms whose twiddle octant is at off_tw
   size_t off_tw = 0;
+  int dec_logN = 0;              // FFT prefill of a decimated grid of so many points (log2; 0: of the tokens themselves)
+  int64_t dec_reach = 0;         // largest |frequency| kept
+  int64_t dec_slices = 0;        // slices whose grids the workspace holds at a time
+  size_t off_window = 0, off_gain = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
   bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
@@ -79,6 +83,7 @@ constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 
 constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
+constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
 int make_plan(const iwdft_desc* d, Plan* pl) {
@@ -179,6 +184,22 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
   pl->scale_pairs = pl->use_fft_prefill && !(d->flags & IWDFT_FLAG_FFT_PREFILL) && pl->max_nb < kFftAloneBins;
+  // Low frequencies only: the grid that carries them (decimate.hip), at most kDecMaxD tokens per grid point.
+  if (pl->use_fft_prefill && d->M > kFftMaxQ) {
+    int64_t reach = 0;
+    for (int64_t i = 0; i < pl->n_bins_total; ++i) {
+      const int64_t k = d->bins[i];
+      reach = std::max(reach, k < d->M - k ? k : d->M - k);
+    }
+    int logN = kDecMinLogN;
+    while (((int64_t)1 << logN) < 4 * reach || ((int64_t)kDecMaxD << logN) < d->M) ++logN;
+    if (logN <= kDecMaxLogN && ((int64_t)1 << logN) < d->M) {
+      pl->dec_logN = logN;
+      pl->dec_reach = reach;
+      const int64_t most = kDecScratch / ((int64_t)2 * kHeadDim * sizeof(float) << logN);
+      pl->dec_slices = std::min<int64_t>(S, most);
+    }
+  }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
   // of M / Pb points, Pb the smallest divisor of M that brings the block down to 8192 (none: the direct sums).
   pl->use_chirp = false;
@@ -293,6 +314,13 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
                          (size_t)pl->G * (size_t)d->M);
+  // The grids of the prefill lie over everything above, which only lives between decode steps of the same context; their tables behind.
+  if (pl->dec_logN) {
+    const int D = (int)(d->M >> pl->dec_logN);
+    o = std::max(o, align256((size_t)pl->dec_slices * 2 * kHeadDim * sizeof(float) << pl->dec_logN));
+    pl->off_window = o; o = align256(o + (size_t)(D / 2 + 2 * dec_halo(D)) * 3 * 64 * 16);
+    pl->off_gain = o;   o = align256(o + sizeof(float) * (((size_t)1 << pl->dec_logN) / 4 + 1));
+  }
   pl->ws_bytes = o;
   return IWDFT_OK;
 }
@@ -403,6 +431,48 @@ void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float
       (*taps)[(size_t)(e < 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r)] = z[j] > 0.0 ? (float)(w[j] / (kTaps * W0)) : 0.f;
     }
   }
+}
+
+// Tables of the decimated prefill (decimate.hip), in double precision: the window as matrix operands, [group of 32 tokens][part][lane][8]
+// bf16 -- lane: grid point lane % 16 of a tile, tokens 8 (lane / 16) .. of the group, groups from dec_halo ahead of the tile's first
+// token on -- and 1 / W.  Window and transform as in make_interp.
+void make_decimation(int64_t M, int logN, int64_t reach, std::vector<uint16_t>* window, std::vector<float>* gain) {
+  const double kPi = 3.14159265358979323846;
+  const int64_t N = (int64_t)1 << logN, D = M / N;
+  const double a = (double)kTaps * (1.0 - (double)std::max<int64_t>(reach, 1) / (double)N), beta = kPi * std::sqrt(a * a - 0.8);
+  const auto W = [&](int64_t k) {
+    const double y = kPi * kTaps * (double)k / (double)N, r2 = beta * beta - y * y, r = std::sqrt(std::fabs(r2));
+    return r2 > 0.0 ? std::sinh(r) / r : (r > 0.0 ? std::sin(r) / r : 1.0);
+  };
+  const double W0 = W(0);
+  gain->resize((size_t)(N / 4 + 1));
+  for (int64_t k = 0; k <= N / 4; ++k) (*gain)[(size_t)k] = k <= reach ? (float)(W0 / W(k)) : 0.f;
+  const int halo = dec_halo((int)D), groups = (int)D / 2 + 2 * halo;
+  window->assign((size_t)groups * 3 * 64 * 8, 0);
+  for (int g = 0; g < groups; ++g)
+    for (int lane = 0; lane < 64; ++lane) {
+      double q[kTaps], w[kTaps], x[kTaps];
+      static_assert(kTaps == 8, "eight tokens per lane");
+      for (int i = 0; i < 8; ++i) {
+        x[i] = (double)(lane % 16) - (double)(32 * (g - halo) + 8 * (lane / 16) + i) / (double)D;
+        const double z = 1.0 - x[i] * x[i] * 4.0 / (kTaps * kTaps);
+        q[i] = z > 0.0 ? 0.25 * beta * beta * z : 0.0;
+      }
+      bessel_i0(q, w);
+      for (int i = 0; i < 8; ++i) {
+        double rest = std::fabs(x[i]) < 0.5 * kTaps ? w[i] / (kTaps * W0) : 0.0;
+        for (int part = 0; part < 3; ++part) {
+          const float f = (float)rest;
+          uint32_t u;
+          memcpy(&u, &f, sizeof(u));
+          u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+          float h;
+          memcpy(&h, &u, sizeof(h));
+          (*window)[(((size_t)g * 3 + part) * 64 + lane) * 8 + i] = (uint16_t)(u >> 16);
+          rest -= h;
+        }
+      }
+    }
 }
 
 }  // namespace
@@ -603,6 +673,13 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       e = hipMemcpy(c->state + pl.off_tw, tw.data(), sizeof(float2) * tw.size(), hipMemcpyHostToDevice);
     }
+    if (e == hipSuccess && pl.dec_logN) {
+      std::vector<uint16_t> window;
+      std::vector<float> gain;
+      make_decimation(desc->M, pl.dec_logN, pl.dec_reach, &window, &gain);
+      e = hipMemcpy(c->ws + pl.off_window, window.data(), sizeof(uint16_t) * window.size(), hipMemcpyHostToDevice);
+      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_gain, gain.data(), sizeof(float) * gain.size(), hipMemcpyHostToDevice);
+    }
     const float2* tab = nullptr;
     if (e == hipSuccess) e = fft_table(&tab);
     if (e != hipSuccess) {
@@ -633,6 +710,11 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.any_dec = pl.use_chirp ? (const float*)(c->ws + pl.off_dec) : nullptr;
     P.any_taps = pl.use_chirp ? (const float4*)(c->ws + pl.off_taps) : nullptr;
     P.any_logN = pl.chirp_logN;
+    P.dec_logN = pl.dec_logN;
+    P.dec_slices = (int32_t)pl.dec_slices;
+    P.dec_window = pl.dec_logN ? c->ws + pl.off_window : nullptr;
+    P.dec_gain = pl.dec_logN ? (const float*)(c->ws + pl.off_gain) : nullptr;
+    P.dec_scratch = pl.dec_logN ? (float*)c->ws : nullptr;
     P.any_Q = (uint32_t)pl.chirp_Q;
     P.tab = tab;
     P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;

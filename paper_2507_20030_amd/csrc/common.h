@@ -57,6 +57,12 @@ struct Params {
   const float4* any_taps;  // taps per frequency
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
   const float2* tw8;  // e^{j 2 pi m / Q}, m = 0 .. Q / 8, Q = min(M, 8192), for fft_lds.h (null unless M = 2^m >= 256)
+  // Decimation ahead of the FFT prefill (decimate.hip): grid of 2^dec_logN points (0: not used); in the workspace the window as matrix
+  // operands, 1 / W of the frequencies 0 .. 2^dec_logN / 4, and room for the grids of dec_slices slices.
+  int32_t dec_logN, dec_slices;
+  const void* dec_window;
+  const float* dec_gain;
+  float* dec_scratch;
   float2* FK;
   float2* FV;
   // Exact tokens (Sec. 4.2.1): S sink tokens and a ring of R recent tokens per slice, kv_dtype,
@@ -173,6 +179,11 @@ constexpr int kFftAloneBins = 384;
 constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
+// y of the slices slice0 .. slice0 + slices - 1 into Params::dec_scratch, [tensor][slice][N][128] fp32; kDecMaxD tokens per grid point at
+// most, 4-byte aligned tensors.
+constexpr int kDecMaxD = 16, kDecMinLogN = 10, kDecMaxLogN = 14;
+__host__ __device__ constexpr int dec_halo(int D) { return (D + 7) / 8; }  // blocks of 32 tokens beyond a tile of 16 grid points
+hipError_t launch_decimate(const Params& P, const void* K, const void* V, int slice0, int slices, hipStream_t st);
 // ... and through interpolated transforms (Params::any_dec set).
 hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hipStream_t st);
 hipError_t launch_prefill_edges(const Params& P, const void* K, const void* V, hipStream_t st);
