@@ -83,6 +83,7 @@ constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 
 constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
+constexpr int64_t kDecMinTokens = (int64_t)1 << 19;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
@@ -184,20 +185,26 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
   pl->scale_pairs = pl->use_fft_prefill && !(d->flags & IWDFT_FLAG_FFT_PREFILL) && pl->max_nb < kFftAloneBins;
-  // Low frequencies only: the grid that carries them (decimate.hip), at most kDecMaxD tokens per grid point.
-  if (pl->use_fft_prefill && d->M > kFftMaxQ) {
-    int64_t reach = 0;
+  // Low frequencies only: the smallest grid that carries them (decimate.hip), at most kDecMaxD tokens per grid point.
+  // Two tokens per point save the prefill little and cost it a grid in fp32 as large as the bf16 tokens: taken only in bf16 where the
+  // transforms of the tokens themselves hold more than 2048 bins (us without / with; 128 slices: M = 16384, 2048 bins, bf16 677 / 881,
+  // fp32 1028 / 1476; M = 32768, 4096 bins 2371 / 1962, 2144 / 3178).  Below kDecMinTokens tokens in all the decimation has too few
+  // waves (8 slices of 16384, 1024 bins: 46 / 50, fp32 56 / 79; of 32768, 2048 bins: 71 / 78, 127 / 110; of 65536, 4096 bins: 280 / 155,
+  // 282 / 221; 32 of 16384, 1024 bins: 160 / 128, 257 / 194); in fp32 with sixteen tokens per point below twice as many (8 of 65536,
+  // 1024 bins: 254 / 347; of 131072, 2048 bins: 494 / 421).
+  if (pow2 && d->M > kFftMaxQ) {
     for (int64_t i = 0; i < pl->n_bins_total; ++i) {
       const int64_t k = d->bins[i];
-      reach = std::max(reach, k < d->M - k ? k : d->M - k);
+      pl->dec_reach = std::max(pl->dec_reach, k < d->M - k ? k : d->M - k);
     }
     int logN = kDecMinLogN;
-    while (((int64_t)1 << logN) < 4 * reach || ((int64_t)kDecMaxD << logN) < d->M) ++logN;
+    while (((int64_t)1 << logN) < 4 * pl->dec_reach || ((int64_t)kDecMaxD << logN) < d->M) ++logN;
     if (logN <= kDecMaxLogN && ((int64_t)1 << logN) < d->M) {
-      pl->dec_logN = logN;
-      pl->dec_reach = reach;
-      const int64_t most = kDecScratch / ((int64_t)2 * kHeadDim * sizeof(float) << logN);
-      pl->dec_slices = std::min<int64_t>(S, most);
+      const int64_t D = d->M >> logN;
+      if (pl->use_fft_prefill && S * d->M >= (D < 16 || b16 ? kDecMinTokens : 2 * kDecMinTokens) && (D >= 4 || (b16 && pl->max_nb > 2048))) {
+        pl->dec_logN = logN;
+        pl->dec_slices = std::min<int64_t>(S, kDecScratch / ((int64_t)2 * kHeadDim * sizeof(float) << logN));
+      }
     }
   }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
@@ -433,34 +440,45 @@ void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float
   }
 }
 
-// Tables of the decimated prefill (decimate.hip), in double precision: the window as matrix operands, [group of 32 tokens][part][lane][8]
-// bf16 -- lane: grid point lane % 16 of a tile, tokens 8 (lane / 16) .. of the group, groups from dec_halo ahead of the tile's first
-// token on -- and 1 / W.  Window and transform as in make_interp.
-void make_decimation(int64_t M, int logN, int64_t reach, std::vector<uint16_t>* window, std::vector<float>* gain) {
-  const double kPi = 3.14159265358979323846;
-  const int64_t N = (int64_t)1 << logN, D = M / N;
-  const double a = (double)kTaps * (1.0 - (double)std::max<int64_t>(reach, 1) / (double)N), beta = kPi * std::sqrt(a * a - 0.8);
-  const auto W = [&](int64_t k) {
-    const double y = kPi * kTaps * (double)k / (double)N, r2 = beta * beta - y * y, r = std::sqrt(std::fabs(r2));
+// The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision; as in make_interp.
+struct GridWindow {
+  int64_t N, D, reach;
+  double taps, beta, W0;
+  GridWindow(int64_t M, int logN, int64_t reach_, int taps_) : N((int64_t)1 << logN), D(M / N), reach(reach_), taps(taps_) {
+    const double a = taps * (1.0 - (double)std::max<int64_t>(reach, 1) / (double)N);
+    beta = 3.14159265358979323846 * std::sqrt(a * a - 0.8);
+    W0 = W(0);
+  }
+  double W(int64_t k) const {
+    const double y = 3.14159265358979323846 * taps * (double)k / (double)N, r2 = beta * beta - y * y, r = std::sqrt(std::fabs(r2));
     return r2 > 0.0 ? std::sinh(r) / r : (r > 0.0 ? std::sin(r) / r : 1.0);
-  };
-  const double W0 = W(0);
-  gain->resize((size_t)(N / 4 + 1));
-  for (int64_t k = 0; k <= N / 4; ++k) (*gain)[(size_t)k] = k <= reach ? (float)(W0 / W(k)) : 0.f;
-  const int halo = dec_halo((int)D), groups = (int)D / 2 + 2 * halo;
+  }
+  void at(const double (&x)[8], double (&w)[8]) const {  // x in grid points
+    double q[8];
+    for (int i = 0; i < 8; ++i) {
+      const double z = 1.0 - x[i] * x[i] * 4.0 / (taps * taps);
+      q[i] = z > 0.0 ? 0.25 * beta * beta * z : 0.0;
+    }
+    bessel_i0(q, w);
+    for (int i = 0; i < 8; ++i) w[i] = std::fabs(x[i]) < 0.5 * taps ? w[i] / (taps * W0) : 0.0;
+  }
+  void gain(std::vector<float>* g) const {  // 1 / W of the frequencies 0 .. N / 4
+    g->resize((size_t)(N / 4 + 1));
+    for (int64_t k = 0; k <= N / 4; ++k) (*g)[(size_t)k] = k <= reach ? (float)(W0 / W(k)) : 0.f;
+  }
+};
+// The window as matrix operands (decimate.hip), [group of 32 tokens][part][lane][8] bf16 -- lane: grid point lane % 16 of a tile, tokens
+// 8 (lane / 16) .. of the group, groups from dec_halo ahead of the tile's first token on.
+void make_decimation(const GridWindow& gw, std::vector<uint16_t>* window) {
+  const int halo = dec_halo((int)gw.D), groups = (int)gw.D / 2 + 2 * halo;
   window->assign((size_t)groups * 3 * 64 * 8, 0);
   for (int g = 0; g < groups; ++g)
     for (int lane = 0; lane < 64; ++lane) {
-      double q[kTaps], w[kTaps], x[kTaps];
-      static_assert(kTaps == 8, "eight tokens per lane");
+      double w[8], x[8];
+      for (int i = 0; i < 8; ++i) x[i] = (double)(lane % 16) - (double)(32 * (g - halo) + 8 * (lane / 16) + i) / (double)gw.D;
+      gw.at(x, w);
       for (int i = 0; i < 8; ++i) {
-        x[i] = (double)(lane % 16) - (double)(32 * (g - halo) + 8 * (lane / 16) + i) / (double)D;
-        const double z = 1.0 - x[i] * x[i] * 4.0 / (kTaps * kTaps);
-        q[i] = z > 0.0 ? 0.25 * beta * beta * z : 0.0;
-      }
-      bessel_i0(q, w);
-      for (int i = 0; i < 8; ++i) {
-        double rest = std::fabs(x[i]) < 0.5 * kTaps ? w[i] / (kTaps * W0) : 0.0;
+        double rest = w[i];
         for (int part = 0; part < 3; ++part) {
           const float f = (float)rest;
           uint32_t u;
@@ -474,7 +492,6 @@ void make_decimation(int64_t M, int logN, int64_t reach, std::vector<uint16_t>* 
       }
     }
 }
-
 }  // namespace
 
 struct iwdft_ctx {
@@ -673,12 +690,17 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       e = hipMemcpy(c->state + pl.off_tw, tw.data(), sizeof(float2) * tw.size(), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess && pl.dec_logN) {
+    const auto to_ws = [&](size_t off, const auto& v) {
+      if (e == hipSuccess) e = hipMemcpy(c->ws + off, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice);
+    };
+    if (pl.dec_logN) {
+      const GridWindow gw(desc->M, pl.dec_logN, pl.dec_reach, kDecTaps);
       std::vector<uint16_t> window;
       std::vector<float> gain;
-      make_decimation(desc->M, pl.dec_logN, pl.dec_reach, &window, &gain);
-      e = hipMemcpy(c->ws + pl.off_window, window.data(), sizeof(uint16_t) * window.size(), hipMemcpyHostToDevice);
-      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_gain, gain.data(), sizeof(float) * gain.size(), hipMemcpyHostToDevice);
+      make_decimation(gw, &window);
+      gw.gain(&gain);
+      to_ws(pl.off_window, window);
+      to_ws(pl.off_gain, gain);
     }
     const float2* tab = nullptr;
     if (e == hipSuccess) e = fft_table(&tab);

@@ -182,7 +182,8 @@ hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hip
 // y of the slices slice0 .. slice0 + slices - 1 into Params::dec_scratch, [tensor][slice][N][128] fp32; kDecMaxD tokens per grid point at
 // most, 4-byte aligned tensors.
 constexpr int kDecMaxD = 16, kDecMinLogN = 10, kDecMaxLogN = 14;
-__host__ __device__ constexpr int dec_halo(int D) { return (D + 7) / 8; }  // blocks of 32 tokens beyond a tile of 16 grid points
+constexpr int kDecTaps = 10;
+__host__ __device__ constexpr int dec_halo(int D) { return (D * kDecTaps / 2 + 31) / 32; }  // blocks of 32 tokens beyond a tile of 16 grid points
 hipError_t launch_decimate(const Params& P, const void* K, const void* V, int slice0, int slices, hipStream_t st);
 // ... and through interpolated transforms (Params::any_dec set).
 hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hipStream_t st);

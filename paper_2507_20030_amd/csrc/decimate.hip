@@ -1,8 +1,9 @@
 // Decimation ahead of the FFT prefill: contexts of M = 2^m >= 16384 tokens that keep low frequencies only (|k| <= reach, k and M - k
-// alike, in every layer) do not need M points.  With a window w of kTaps points of a grid of N = 2^LOGN >= 4 reach points, D = M / N tokens apart,
+// alike, in every layer) do not need M points.  With a window w of kDecTaps points of a grid of N = 2^LOGN >= 4 reach points, D = M / N tokens apart,
 //   y[m] = sum_n w(m - n / D) x[n]   (n modulo M)   gives   U[k] = DFT_N(y)[k] / W(k / N),  |k| <= N / 4,
-// up to an aliasing error of 2e-8 (see interp.h: the same window, the roles of time and frequency exchanged).  y is a banded matrix
-// product: 16 grid points x (20 D) tokens x 128 channels at a time on the matrix cores, whose left operand is the same everywhere.
+// up to an aliasing error of 1.4e-9 of a tone at the worst frequency (see interp.h: the same window, the roles of time and frequency
+// exchanged; with its eight taps it is 9.7e-8, which a strong tone among the frequencies that are not kept would show).  y is a banded matrix
+// product: 16 grid points x (25 D) tokens x 128 channels at a time on the matrix cores, whose left operand is the same everywhere.
 // bf16 tokens are exact operands; the window is split into three bf16 parts (24 bits), fp32 tokens as well (six of the nine
 // products: what is left out is below 2^-24), sums are fp32.
 #include "common.h"
@@ -25,7 +26,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
 // every token once: a block counts for its own tile and, within dec_halo blocks of a tile's end, for the neighbour.  A lane holds 8
 // tokens x 8 channels of a block (whole rows over 16 lanes), which are the operand of channel 8 (lane % 16) + j, j = 0 .. 7, after
 // a permutation of halves: no LDS trip.  y: [tensor][slice of the launch][N][128].
-// What bounds it is HBM: one read of the tokens, 1 / D of twice (bf16) their bytes written; 144 matrix instructions (16 cycles) per 32 KB at D = 8.
+// What bounds it is HBM: one read of the tokens, 1 / D of twice (bf16) their bytes written; 192 matrix instructions (16 cycles) per 32 KB at D = 8.
 template <bool BF16, int D, bool WIDE>
 __global__ __launch_bounds__(kDecThreads, 2) void decimate_kernel(Params P, const void* __restrict__ K, const void* __restrict__ V,
                                                                  int slice0, int slices) {

@@ -1057,6 +1057,44 @@ def test_interpolated_prefill_against_64_bit_transforms(L):
     c.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,reach,heads,S,R,off", [
+    (16384, 256, 32, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # grids of 1024, 2048 and 4096 points
+    (32768, 512, 16, 0, 0, 8), (32768, 2048, 17, 0, 5, 0), (32768, 4096, 17, 0, 0, 0),   # ... 8192; 16384 (bf16): three groups of slices
+    (65536, 1000, 9, 10, 50, 0), (131072, 4096, 9, 0, 0, 8), (262144, 4096, 2, 1, 0, 0),
+])
+def test_prefill_of_low_frequencies_against_64_bit_transforms(dtype, L, reach, heads, S, R, off):
+    """Two to sixteen tokens per grid point, bins up to a quarter of the grid and their mirrors; 8-byte aligned tensors.  Bar: aliasing
+    2e-9 + fp32 rounding of at most 2^-24 per radix-2 stage (14, window and gain): 1e-6.  Channel 5 carries a tone of 30 at the
+    frequency that aliases onto the last bin: 2e-9 of it there, and the rounding of its samples, which may repeat with it, 2^-25."""
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    rng = np.random.default_rng(L + reach)
+    N = 1024
+    while N < 4 * reach or 16 * N < L:
+        N *= 2
+    low = np.arange(reach + 1) if reach <= 512 or reach >= 4096 else rng.integers(0, reach, reach // 2)
+    bins = np.unique(np.r_[0, 1, low, reach, L - reach, L - reach + 1, L - 1]).astype(np.int32)
+    X = [torch.randn((1, 1, heads, S + L + R, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(L + i)) for i in range(2)]
+    n = torch.arange(L, device=DEV, dtype=torch.float64)
+    for x in X:
+        x[..., S:S + L, 5] += (30 * torch.cos(2 * np.pi / L * torch.remainder(n * (N - reach), L))).float()
+    pad = off // td.itemsize
+    K, V = (torch.empty(x.numel() + pad, dtype=td, device=DEV)[pad:].view(x.shape).copy_(x) for x in X)
+    c = B.Cache(1, 1, heads, heads, 128, td, L, [bins], n_sink=S, n_recent=R)
+    assert B.iwdft_prefill_kind(c.ctx) == "fft"
+    c.prefill(K, V)
+    for x, got in zip((K, V), c.export_coeffs(0)):
+        for h in (0, heads - 1):
+            ref = torch.fft.fft(x[0, 0, h, S:S + L].cpu().double().T.contiguous(), dim=1)[:, bins.astype(np.int64)] / L
+            err = got[0, h].cpu().to(torch.complex128)
+            err = (err if err.shape == ref.shape else err.T) - ref
+            rest = [i for i in range(128) if i not in (4, 5)]  # the tone's transform also holds channel 4
+            assert float(err[rest].norm() / ref[rest].norm()) < 1e-6
+            assert float(err[rest].abs().max() / ref[rest].abs().pow(2).mean().sqrt()) < 1e-5
+            assert float(err[4:6].abs().max()) < 30 * (2e-9 + 2.0 ** -25)
+    c.close()
+
+
 def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one():
     # neighbouring channels share a transform; every channel has to be as accurate as alone (fp32 rounding, 2^-24, times
     # ~log2 of the 16384 points of each of two transforms and the tables: below 1e-5)
