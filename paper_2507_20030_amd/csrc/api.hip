@@ -60,7 +60,8 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int dec_logN = 0;              // FFT prefill of a decimated grid of so many points (log2; 0: of the tokens themselves)
   int64_t dec_reach = 0;         // largest |frequency| kept
   int64_t dec_slices = 0;        // slices whose grids the workspace holds at a time
-  size_t off_window = 0, off_gain = 0;
+  int low_logN = 0;              // decode attention on such a grid
+  size_t off_window = 0, off_gain = 0, off_low = 0, off_low_gain = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
   bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
@@ -84,6 +85,7 @@ constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr int64_t kDecMinTokens = (int64_t)1 << 19;
+constexpr int kLowMinLogN = 12;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
@@ -185,18 +187,21 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
   pl->scale_pairs = pl->use_fft_prefill && !(d->flags & IWDFT_FLAG_FFT_PREFILL) && pl->max_nb < kFftAloneBins;
-  // Low frequencies only: the smallest grid that carries them (decimate.hip), at most kDecMaxD tokens per grid point.
+  // Low frequencies only: the smallest grid that carries them (decimate.hip, attn_low_kernel), at most kDecMaxD tokens per grid point.
   // Two tokens per point save the prefill little and cost it a grid in fp32 as large as the bf16 tokens: taken only in bf16 where the
   // transforms of the tokens themselves hold more than 2048 bins (us without / with; 128 slices: M = 16384, 2048 bins, bf16 677 / 881,
   // fp32 1028 / 1476; M = 32768, 4096 bins 2371 / 1962, 2144 / 3178).  Below kDecMinTokens tokens in all the decimation has too few
   // waves (8 slices of 16384, 1024 bins: 46 / 50, fp32 56 / 79; of 32768, 2048 bins: 71 / 78, 127 / 110; of 65536, 4096 bins: 280 / 155,
   // 282 / 221; 32 of 16384, 1024 bins: 160 / 128, 257 / 194); in fp32 with sixteen tokens per point below twice as many (8 of 65536,
   // 1024 bins: 254 / 347; of 131072, 2048 bins: 494 / 421).
+  bool mirrored = false;
+  int low_logN = 0;
+  for (int64_t i = 0; i < pl->n_bins_total; ++i) {
+    const int64_t k = d->bins[i];
+    mirrored |= k > d->M - k;
+    pl->dec_reach = std::max(pl->dec_reach, k < d->M - k ? k : d->M - k);
+  }
   if (pow2 && d->M > kFftMaxQ) {
-    for (int64_t i = 0; i < pl->n_bins_total; ++i) {
-      const int64_t k = d->bins[i];
-      pl->dec_reach = std::max(pl->dec_reach, k < d->M - k ? k : d->M - k);
-    }
     int logN = kDecMinLogN;
     while (((int64_t)1 << logN) < 4 * pl->dec_reach || ((int64_t)kDecMaxD << logN) < d->M) ++logN;
     if (logN <= kDecMaxLogN && ((int64_t)1 << logN) < d->M) {
@@ -205,6 +210,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
         pl->dec_logN = logN;
         pl->dec_slices = std::min<int64_t>(S, kDecScratch / ((int64_t)2 * kHeadDim * sizeof(float) << logN));
       }
+      low_logN = std::max(logN, kLowMinLogN);
     }
   }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
@@ -264,6 +270,12 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
     pl->use_any_prefill = S * points <= (b16 ? kAnyPrefillPoints16 : kAnyPrefillPoints32) * d->M * rounds;
   }
+
+  // Decode attention on the grid, from four tokens per point on (read-only step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144:
+  // 0.42 to 1.0 of the time; two tokens: M = 16384 1.00 .. 1.08, M = 32768 0.95 .. 1.0) and with 4096 points at least: what few threads
+  // save in transforms they lose in the chain over the tokens of each (M = 16384, 256 bins, 8 slices, one head: 31 us without, 41 with
+  // 1024 points).  Bins that are each other's mirror would share a slot.
+  if (low_logN && pl->use_fft && !mirrored && (d->M >> low_logN) >= 4) pl->low_logN = low_logN;
 
   // What is left takes the direct O(M |B|) sums: fine for short or sparse states, useless beyond -- refuse instead of
   // running for minutes per step (a prime M of 2^20 with 4096 kept bins is 2^32 sine / cosine pairs per query head).
@@ -328,6 +340,10 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     pl->off_window = o; o = align256(o + (size_t)(D / 2 + 2 * dec_halo(D)) * 3 * 64 * 16);
     pl->off_gain = o;   o = align256(o + sizeof(float) * (((size_t)1 << pl->dec_logN) / 4 + 1));
   }
+  if (pl->low_logN) {
+    pl->off_low_gain = o; o = align256(o + sizeof(float) * (((size_t)1 << pl->low_logN) / 4 + 1));
+    pl->off_low = o;      o = align256(o + sizeof(float) * (size_t)(d->M >> pl->low_logN) * kTaps);
+  }
   pl->ws_bytes = o;
   return IWDFT_OK;
 }
@@ -385,7 +401,7 @@ int64_t digit_position(int64_t m, int logN) {
 // Tables of the interpolated transforms (interp.h), in double precision: 1 / W at the samples of every thread, [8][N / 16], and
 // the taps of the frequencies 0 .. Q / 2, [2][n][4] | [n][2].  W: transform of the window I0(beta sqrt(1 - (x / 4)^2)), |x| < 4, both divided by W(0); beta
 // after P. J. Beatty, D. G. Nishimura and J. M. Pauly, IEEE Trans. Med. Imaging 24 (2005).
-// I0(2 sqrt(q[j])) by its series: for q <= 120 (a grid of 4 Q points) term 50 is 1e-24 of the sum.
+// I0(2 sqrt(q[j])) by its series: for q <= 250 (ten taps, lowest frequencies only) term 50 is below 1e-18 of the sum.
 void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
   double term[kTaps];
   for (int j = 0; j < kTaps; ++j) sum[j] = term[j] = 1.0;
@@ -397,55 +413,12 @@ void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
     }
   }
 }
-void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float>* taps) {
-  const double kPi = 3.14159265358979323846;
-  const int64_t N = (int64_t)1 << logN, T = N / 16, n = Q / 2 + 1;
-  const double a = (double)kTaps * (1.0 - 0.5 * (double)Q / (double)N), beta = kPi * std::sqrt(a * a - 0.8);
-  const auto W = [&](int64_t m) {  // up to a constant factor; real for |m| <= N / 4
-    const double y = kPi * kTaps * (double)m / (double)N, r = std::sqrt(beta * beta - y * y);
-    return std::sinh(r) / r;
-  };
-  const double W0 = W(0);
-  dec->assign((size_t)(8 * T), 0.f);
-  for (int64_t t = 0; t < T; ++t) {
-    int64_t n0 = 0;  // time index of position 16 t (fft_core.h, sample_at)
-    {
-      const int64_t p = 16 * t;
-      const int odd = logN & 1, even = logN - odd;
-      for (int b = 0; b < even; b += 2) n0 |= ((p >> b) & 3) << (even - 2 - b);
-      if (odd) n0 = (n0 << 1) | (p >> (logN - 1));
-    }
-    for (int i = 0; i < 8; ++i) {
-      const int64_t m = n0 + (i < 4 ? i : i - 8) * (N / 16);
-      if (m >= 0 ? m < (Q + 1) / 2 : -m <= Q / 2) (*dec)[(size_t)(i * T + t)] = (float)(W0 / W(m));
-    }
-  }
-  taps->assign((size_t)(10 * n), 0.f);
-  const double scale = 2.0 / kTaps;  // the window itself has kTaps W(0) as its integral
-  for (int64_t r = 0; r < n; ++r) {
-    const int64_t f = r * N / Q, first = f - (kTaps / 2 - 1);
-    const int odd = (int)(first & 1);
-    const int32_t even = (int32_t)(first - odd);
-    memcpy(&(*taps)[(size_t)(8 * n + 2 * r + 1)], &even, sizeof(even));
-    double z[kTaps], w[kTaps];
-    for (int j = 0; j < kTaps; ++j) {
-      const double x = (double)(r * N - (first + j) * Q) / (double)Q * scale;
-      z[j] = 0.25 * beta * beta * (1.0 - x * x);
-    }
-    bessel_i0(z, w);
-    for (int j = 0; j < kTaps; ++j) {
-      const int e = odd + j;
-      (*taps)[(size_t)(e < 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r)] = z[j] > 0.0 ? (float)(w[j] / (kTaps * W0)) : 0.f;
-    }
-  }
-}
-
-// The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision; as in make_interp.
+// The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision.
 struct GridWindow {
-  int64_t N, D, reach;
-  double taps, beta, W0;
-  GridWindow(int64_t M, int logN, int64_t reach_, int taps_) : N((int64_t)1 << logN), D(M / N), reach(reach_), taps(taps_) {
-    const double a = taps * (1.0 - (double)std::max<int64_t>(reach, 1) / (double)N);
+  int64_t N, D;
+  double reach, taps, beta, W0;
+  GridWindow(int64_t M, int logN, double reach_, int taps_) : N((int64_t)1 << logN), D(M / N), reach(reach_), taps(taps_) {
+    const double a = taps * (1.0 - std::max(reach, 1.0) / (double)N);
     beta = 3.14159265358979323846 * std::sqrt(a * a - 0.8);
     W0 = W(0);
   }
@@ -464,9 +437,48 @@ struct GridWindow {
   }
   void gain(std::vector<float>* g) const {  // 1 / W of the frequencies 0 .. N / 4
     g->resize((size_t)(N / 4 + 1));
-    for (int64_t k = 0; k <= N / 4; ++k) (*g)[(size_t)k] = k <= reach ? (float)(W0 / W(k)) : 0.f;
+    for (int64_t k = 0; k <= N / 4; ++k) (*g)[(size_t)k] = (double)k <= reach ? (float)(W0 / W(k)) : 0.f;
   }
 };
+// Taps of points r = 0 .. P / 2 of one period P on a grid of G, [2][n][4] | [n][2] (interp.h), n = P / 2 + 1; unit: a step of G in points of
+// the window's grid.
+void make_taps(const GridWindow& gw, int64_t P, int64_t G, double unit, std::vector<float>* taps) {
+  const int64_t n = P / 2 + 1;
+  taps->assign((size_t)(10 * n), 0.f);
+  for (int64_t r = 0; r < n; ++r) {
+    const int64_t first = r * G / P - (kTaps / 2 - 1);
+    const int odd = (int)(first & 1);
+    const int32_t even = (int32_t)(first - odd);
+    memcpy(&(*taps)[(size_t)(8 * n + 2 * r + 1)], &even, sizeof(even));
+    double x[kTaps], w[kTaps];
+    for (int j = 0; j < kTaps; ++j) x[j] = (double)(r * G - (first + j) * P) / (double)P * unit;
+    gw.at(x, w);
+    for (int j = 0; j < kTaps; ++j) {
+      const int e = odd + j;
+      (*taps)[(size_t)(e < 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r)] = (float)w[j];
+    }
+  }
+}
+void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float>* taps) {
+  const GridWindow gw(Q, logN, 0.5 * (double)Q, kTaps);
+  const int64_t N = gw.N, T = N / 16;
+  dec->assign((size_t)(8 * T), 0.f);
+  for (int64_t t = 0; t < T; ++t) {
+    int64_t n0 = 0;  // time index of position 16 t (fft_core.h, sample_at)
+    {
+      const int64_t p = 16 * t;
+      const int odd = logN & 1, even = logN - odd;
+      for (int b = 0; b < even; b += 2) n0 |= ((p >> b) & 3) << (even - 2 - b);
+      if (odd) n0 = (n0 << 1) | (p >> (logN - 1));
+    }
+    for (int i = 0; i < 8; ++i) {
+      const int64_t m = n0 + (i < 4 ? i : i - 8) * (N / 16);
+      if (m >= 0 ? m < (Q + 1) / 2 : -m <= Q / 2) (*dec)[(size_t)(i * T + t)] = (float)(gw.W0 / gw.W(m));
+    }
+  }
+  make_taps(gw, Q, N, 1.0, taps);
+}
+
 // The window as matrix operands (decimate.hip), [group of 32 tokens][part][lane][8] bf16 -- lane: grid point lane % 16 of a tile, tokens
 // 8 (lane / 16) .. of the group, groups from dec_halo ahead of the tile's first token on.
 void make_decimation(const GridWindow& gw, std::vector<uint16_t>* window) {
@@ -492,6 +504,17 @@ void make_decimation(const GridWindow& gw, std::vector<uint16_t>* window) {
       }
     }
 }
+// The same in fp32 for the tokens d = 0 .. D - 1 behind a grid point (attn_low_kernel), [d][i]: at d / D + 3 - i.
+void make_low_taps(const GridWindow& gw, std::vector<float>* taps) {
+  for (int64_t d = 0; d < gw.D; ++d) {
+    static_assert(kTaps == 8, "");
+    double w[8], x[8];
+    for (int i = 0; i < kTaps; ++i) x[i] = (double)d / (double)gw.D + 3.0 - i;
+    gw.at(x, w);
+    for (int i = 0; i < kTaps; ++i) taps->push_back((float)w[i]);
+  }
+}
+
 }  // namespace
 
 struct iwdft_ctx {
@@ -702,6 +725,14 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       to_ws(pl.off_window, window);
       to_ws(pl.off_gain, gain);
     }
+    if (pl.low_logN) {
+      const GridWindow gw(desc->M, pl.low_logN, pl.dec_reach, kTaps);
+      std::vector<float> gain, taps;
+      gw.gain(&gain);
+      make_low_taps(gw, &taps);
+      to_ws(pl.off_low_gain, gain);
+      to_ws(pl.off_low, taps);
+    }
     const float2* tab = nullptr;
     if (e == hipSuccess) e = fft_table(&tab);
     if (e != hipSuccess) {
@@ -733,6 +764,9 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.any_taps = pl.use_chirp ? (const float4*)(c->ws + pl.off_taps) : nullptr;
     P.any_logN = pl.chirp_logN;
     P.dec_logN = pl.dec_logN;
+    P.low_logN = pl.low_logN;
+    P.low_gain = pl.low_logN ? (const float*)(c->ws + pl.off_low_gain) : nullptr;
+    P.low_taps = pl.low_logN ? (const float*)(c->ws + pl.off_low) : nullptr;
     P.dec_slices = (int32_t)pl.dec_slices;
     P.dec_window = pl.dec_logN ? c->ws + pl.off_window : nullptr;
     P.dec_gain = pl.dec_logN ? (const float*)(c->ws + pl.off_gain) : nullptr;

@@ -583,6 +583,115 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
   return v;
 }
 
+// Scores at all M = D N tokens from the grid x (positions 16 t + m of the digit-reversed order) by interpolation, softmax, and the
+// weights folded back onto the grid by the same taps (decimate.hip has the window; its identities hold in both directions):
+//   s[m D + d] = sum_i w(d / D + 3 - i) y[m + i - 3],   z[m + i - 3] += w(d / D + 3 - i) p[m D + d],   i = 0 .. 7.
+// A thread takes 16 grid points with the 7 around them, y and z in registers: a token costs 16 multiply-adds per head either way and no
+// LDS trip; its eight weights are wave-uniform.  Maximum: a trigonometric polynomial of degree N / 4 is nowhere above the
+// largest magnitude on 2 N points divided by cos(pi / 8) (H. Ehlich and K. Zeller, Math. Zeitschrift 86 (1964)), so the tokens d = 0 and D / 2 give it up to
+// 0.083 max|s|; where that is more than 2^64 in the weights all tokens are looked at.
+template <int LOGN>
+__device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const float* __restrict__ taps, int t, bool has1,
+                                            float2 (&x)[16], float2& mx, float2& Z, float2& f) {
+  constexpr int N = 1 << LOGN, T = fft_threads(LOGN), NWV = T / 64;
+  static_assert(T >= 64, "whole waves");
+  __shared__ float4 lmax[NWV];
+  const int D = (int)(P.M >> LOGN);
+  const uint32_t n0 = sample_at<LOGN>(16 * t);
+  __syncthreads();  // the last reads of the inverse transform
+#pragma unroll
+  for (int m = 0; m < 16; ++m) buf[fpad((int)n0 + sample_step<LOGN>(m))] = x[m];
+  __syncthreads();
+  float2 y[24];  // grid points 16 t - 4 .. 16 t + 19
+  {
+    const float4 *lo = (const float4*)(buf + 18 * ((t - 1) & (T - 1)) + 12), *own = (const float4*)(buf + 18 * t),
+                 *hi = (const float4*)(buf + 18 * ((t + 1) & (T - 1)));
+#pragma unroll
+    for (int j = 0; j < 12; ++j) {
+      const float4 v = j < 2 ? lo[j] : j < 10 ? own[j - 2] : hi[j - 10];
+      y[2 * j] = make_float2(v.x, v.y);
+      y[2 * j + 1] = make_float2(v.z, v.w);
+    }
+  }
+  auto score = [&](const float (&w)[8], int m) {
+    float2 s = make_float2(w[0] * y[m + 1].x, w[0] * y[m + 1].y);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) s = make_float2(fmaf(w[i], y[m + 1 + i].x, s.x), fmaf(w[i], y[m + 1 + i].y, s.y));
+    return s;
+  };
+  float2 lm = make_float2(-INFINITY, -INFINITY);
+  float la = 0.f;
+  auto scan = [&](int d) {
+    float w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = taps[8 * d + i];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const float2 s = score(w, m);
+      lm = make_float2(fmaxf(lm.x, s.x), fmaxf(lm.y, s.y));
+      la = fmaxf(la, fmaxf(fabsf(s.x), fabsf(s.y)));
+    }
+  };
+  auto block_max = [&] {
+    auto max2 = [](float a, float b) { return fmaxf(a, b); };
+    lm = make_float2(wave_reduce(lm.x, max2), wave_reduce(lm.y, max2));
+    la = wave_reduce(la, max2);
+    if constexpr (NWV > 1) {
+      if ((t & 63) == 0) lmax[t >> 6] = make_float4(lm.x, lm.y, la, 0.f);
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < NWV; ++v) {
+        const float4 o = lmax[v];
+        lm = make_float2(fmaxf(lm.x, o.x), fmaxf(lm.y, o.y));
+        la = fmaxf(la, o.z);
+      }
+    }
+  };
+#pragma unroll 1
+  for (int d = 0; d < D; d += D / 2) scan(d);
+  block_max();
+  if (!(0.083f * la <= 64.f)) {  // block-uniform
+#pragma unroll 1
+    for (int d = 0; d < D; ++d) scan(d);
+    __syncthreads();
+    block_max();
+  }
+  const float2 mn = make_float2(fmaxf(mx.x, lm.x), fmaxf(mx.y, lm.y));
+  f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
+  mx = mn;
+  float2 z[23], ls = make_float2(0.f, 0.f);  // grid points 16 t - 3 .. 16 t + 19
+#pragma unroll
+  for (int j = 0; j < 23; ++j) z[j] = make_float2(0.f, 0.f);
+#pragma unroll 1
+  for (int d = 0; d < D; ++d) {
+    float w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = taps[8 * d + i];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const float2 s = score(w, m);
+      const float2 e = make_float2(__builtin_amdgcn_exp2f(s.x - mn.x), has1 ? __builtin_amdgcn_exp2f(s.y - mn.y) : 0.f);
+      ls = cadd(ls, e);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) z[m + i] = make_float2(fmaf(w[i], e.x, z[m + i].x), fmaf(w[i], e.y, z[m + i].y));
+    }
+  }
+  Z = make_float2(Z.x * f.x + ls.x, Z.y * f.y + ls.y);
+  // Grid point g lies at position g + 3; the last seven belong to the next thread's sixteen.
+#pragma unroll
+  for (int m = 0; m < 16; ++m) x[m] = z[m];
+  __syncthreads();  // one wave: its own barrier ahead of the overwriting
+  write16(buf, t, x);
+  __syncthreads();
+  float2* nxt = buf + 18 * ((t + 1) & (T - 1));
+#pragma unroll
+  for (int j = 0; j < 7; ++j) nxt[j] = cadd(nxt[j], z[16 + j]);
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 16; ++m) x[m] = buf[fpad(((int)n0 + sample_step<LOGN>(m) + 3) & (N - 1))];
+  __syncthreads();  // the forward transform writes to other positions
+}
+
 // grid: slice * pairs + pair, attn_threads(LOGQ) threads.  Two query heads share one complex transform: head g0 travels in the real
 // part, head g0 + 1 in the imaginary part (each head's spectrum is made Hermitian first, so its time-domain signal is
 // real).  Time index a = Pb * a' + b: block b of Q = M / Pb samples comes from the spectrum folded modulo Q with twiddle
@@ -594,16 +703,19 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
 // Weights: with one block they are normalised and written as the spectrum is gathered; MULTI keeps the running sums of the
 // thread's NBT bins in registers, or (NBT = 0, more than 4096 kept bins) in the output rows themselves -- every bin belongs
 // to one thread, which reads back its own earlier store.
+// LOW: low frequencies only (see attn_low_kernel): one transform of a grid that carries them, low_softmax between it and the tokens.
 // The work of logical block `bid` (wave-uniform); buf: fft_lds(LOGQ) float2.
-template <int LOGQ, int NBT, bool MULTI>
+template <int LOGQ, int NBT, bool MULTI, bool LOW = false>
 __device__ __forceinline__ void fft_body(const Params& P, const float2* __restrict__ qc, float2* __restrict__ Pn,
                                          float* __restrict__ pe, float scale, int pairs, int np, uint32_t ptsh,
-                                         float* __restrict__ ps, uint32_t bid, float2* buf) {
+                                         float* __restrict__ ps, uint32_t bid, float2* buf,
+                                         const float* __restrict__ taps = nullptr) {
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), TB = attn_threads(LOGQ), NWV = TB / 64;
   constexpr bool kRegs = MULTI && NBT > 0;  // running sums in registers
   constexpr bool kKeep = kRegs && NBT > 4;  // with the register budget of one workgroup per CU: the inputs stay as well
   constexpr int U = kRegs ? NBT : 4;  // bins whose inputs are fetched together
   static_assert(MULTI || NBT == 0, "one block: nothing to keep");
+  static_assert(!LOW || (!MULTI && TB == T), "");
   __shared__ float2 smax[NWV], ssum[NWV];
   __shared__ float pscr[NWV][2 * kMaxPend];
   const TabMem tab{P.tab + tab_base(LOGQ)};
@@ -724,7 +836,9 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       const int i = i0 + j * TB;
-      fr[j] = i < L.nb ? (uint32_t)fold[i] : 0xffffu;
+      // LOW: no bin above a quarter of the grid, so that only the mirror of bin 0 shares a slot
+      if constexpr (LOW) fr[j] = i >= L.nb ? 0xffffu : bins[i] ? 0u : 0xff00u;
+      else fr[j] = i < L.nb ? (uint32_t)fold[i] : 0xffffu;
     }
   };
   auto load_in = [&](int i0) {
@@ -734,6 +848,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
       const int i = i0 + j * TB, ic = i < L.nb ? i : L.nb - 1;
       kj[j] = (uint32_t)bins[ic];
       w[j] = wts[ic] * gain;
+      if constexpr (LOW) w[j] *= P.low_gain[kj[j]];
       y0[j] = q0[ic];
       y1[j] = q1[ic];
     }
@@ -795,7 +910,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
         }
       }
     };
-    for (int round = 0; round < L.fold_rounds; ++round) {
+    for (int round = 0; round < (LOW ? 1 : L.fold_rounds); ++round) {
       if constexpr (kRegs) {
         fold_group(lt, round);
       } else {
@@ -806,13 +921,17 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     fft_inverse<LOGQ>(buf, tab.tab, lx, x);
 
     // softmax: real part head g0, imaginary part head g0 + 1
+    float2 f;
+    if constexpr (LOW) {
+      low_softmax<LOGQ>(P, buf, taps, lx, has1, x, mx, Z, f);
+    } else {
     float2 lm = x[0];
 #pragma unroll
     for (int m = 1; m < 16; ++m) lm = make_float2(fmaxf(lm.x, x[m].x), fmaxf(lm.y, x[m].y));
     const float2 bm = block_max(lm);
     const float2 mn = make_float2(fmaxf(mx.x, bm.x), fmaxf(mx.y, bm.y));
     // exp2(-inf) = 0 the first time
-    const float2 f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
+    f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
     mx = mn;
     float2 ls = make_float2(0.f, 0.f);
 #pragma unroll
@@ -822,6 +941,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     }
     if (TB > T && t >= T) ls = make_float2(0.f, 0.f);  // counted by lane tx
     Z = make_float2(Z.x * f.x + ls.x, Z.y * f.y + ls.y);
+    }
     if constexpr (!MULTI) publish_sum();  // read behind the barriers of the transform
 
     auto fetch_bins = [&](int i0) {
@@ -842,6 +962,11 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
       spectrum_pair<LOGQ>(buf, kj[j] & (Q - 1), wj[j], w1, w2);
       p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
       p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+      if constexpr (LOW) {
+        const float g = P.low_gain[kj[j]];
+        p0 = make_float2(g * p0.x, g * p0.y);
+        p1 = make_float2(g * p1.x, g * p1.y);
+      }
       if constexpr (MULTI) {
         const float2 twc = conjf2(cis_fast((kj[j] * b) & (P.M - 1u), P.M));
         p0 = cmul(twc, p0);
@@ -934,6 +1059,20 @@ __global__ __launch_bounds__(attn_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_
                                                                        float* __restrict__ ps) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
   fft_body<LOGQ, NBT, MULTI>(P, qc, Pn, pe, scale, pairs, np, ptsh, ps, blockIdx.x, smem);
+}
+
+// Long contexts that keep low frequencies only, |k| <= N / 4 on a grid of N = 2^LOGN points, D = M / N tokens apart: see low_softmax.
+// What bounds it is the vector ALU, 48 instructions a token and pair of heads (82 of 150 us), beside the transforms of one workgroup per
+// CU.  32 x 8 slices of 131072 tokens, 4096 bins, 4 heads: 300 (attn_fft_kernel, 16 pairs of 8192-point transforms each) -> 150 us, a
+// read-only decode step 683 -> 524.
+template <int LOGN>
+__global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_low_kernel(Params P, const float2* __restrict__ qc,
+                                                                        float2* __restrict__ Pn, float* __restrict__ pe,
+                                                                        float scale, int pairs, int np, uint32_t ptsh,
+                                                                        float* __restrict__ ps,
+                                                                        const float* __restrict__ taps) {
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
+  fft_body<LOGN, 0, false, true>(P, qc, Pn, pe, scale, pairs, np, ptsh, ps, blockIdx.x, smem, taps);
 }
 
 // ----------------------------------------------------------------------------------- A + B
@@ -1059,10 +1198,11 @@ __global__ __launch_bounds__(kDirThreads) void attn_direct_kernel(Params P, cons
 constexpr uint64_t qc_few_blocks(int GT, bool upd) { return upd || GT <= 2 ? 512 : GT == 4 ? 2048 : 1024; }
 constexpr uint32_t kAbMinB = 1024, kAbMaxGroups = 8;  // fewest B blocks per group of slices, most groups
 static int heads_per_pass(int G);
+static bool attn_is_low(const Params& P) { return P.low_logN != 0; }
 bool attn_pipelines(const Params& P, bool use_fft) {
   const int GT = heads_per_pass(P.G);
   const int per_thread = (P.max_Bp + kAbThreads - 1) / kAbThreads;
-  return use_fft && P.G <= GT && (GT == 4 || GT == 8) && P.M >= 16384u && per_thread > 2 && per_thread <= 8 &&
+  return use_fft && !attn_is_low(P) && P.G <= GT && (GT == 4 || GT == 8) && P.M >= 16384u && per_thread > 2 && per_thread <= 8 &&
          (uint64_t)P.n_slices * ((P.G + 1) / 2) >= 2 * kAbMinB && !P.serial_phases;
 }
 static int heads_per_pass(int G) { return G <= 2 ? G : (G <= 4 ? 4 : 8); }  // 1, 2, 4 or 8; heads beyond G are masked
@@ -1178,7 +1318,25 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(attn_threads(LQ)), lds, st>>>(                     \
         P, qc, Pn, pe, scale, pairs, np_plain, u.tsh, u.ps);                                              \
   }
-    if (logM > logQ) {
+    if (attn_is_low(P)) {
+#define IWDFT_LOW_CASE(LN)                                                                                \
+  case LN: {                                                                                              \
+    constexpr int lds = (int)sizeof(float2) * fft_lds(LN);                                                \
+    static LdsLimit lim;                                                                                  \
+    e = lim.ensure((const void*)attn_low_kernel<LN>, lds);                                                \
+    if (e != hipSuccess) return e;                                                                        \
+    attn_low_kernel<LN><<<dim3(gridB), dim3(attn_threads(LN)), lds, st>>>(                                \
+        P, qc, Pn, pe, scale, pairs, np_plain, u.tsh, u.ps, P.low_taps);                                  \
+    break;                                                                                                \
+  }
+      switch (P.low_logN) {
+        IWDFT_LOW_CASE(12)
+        IWDFT_LOW_CASE(13)
+        IWDFT_LOW_CASE(14)
+        default: return hipErrorInvalidValue;
+      }
+#undef IWDFT_LOW_CASE
+    } else if (logM > logQ) {
       const int per_thread = (P.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
       if (per_thread <= 2) IWDFT_FFT_CASE(kFftMaxLogQ, 2, true)
       else if (per_thread <= 4) IWDFT_FFT_CASE(kFftMaxLogQ, 4, true)

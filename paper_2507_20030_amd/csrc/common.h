@@ -63,6 +63,11 @@ struct Params {
   const void* dec_window;
   const float* dec_gain;
   float* dec_scratch;
+  // Decode attention of the same contexts (attn_low_kernel): grid of 2^low_logN points (0: not used), 1 / W of 0 .. 2^low_logN / 4 and
+  // eight taps per token between two grid points.
+  int32_t low_logN;
+  const float* low_gain;
+  const float* low_taps;
   float2* FK;
   float2* FV;
   // Exact tokens (Sec. 4.2.1): S sink tokens and a ring of R recent tokens per slice, kv_dtype,

@@ -1059,9 +1059,9 @@ def test_interpolated_prefill_against_64_bit_transforms(L):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,reach,heads,S,R,off", [
-    (16384, 256, 32, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # grids of 1024, 2048 and 4096 points
-    (32768, 512, 16, 0, 0, 8), (32768, 2048, 17, 0, 5, 0), (32768, 4096, 17, 0, 0, 0),   # ... 8192; 16384 (bf16): three groups of slices
-    (65536, 1000, 9, 10, 50, 0), (131072, 4096, 9, 0, 0, 8), (262144, 4096, 2, 1, 0, 0),
+    (16384, 256, 64, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # grids of 1024, 2048 and 4096 points
+    (32768, 512, 32, 0, 0, 8), (32768, 2048, 17, 0, 5, 0), (32768, 4096, 17, 0, 0, 0),   # ... 8192; 16384 (bf16): three groups of slices
+    (65536, 1000, 9, 10, 50, 0), (131072, 4096, 9, 0, 0, 8), (262144, 4096, 4, 1, 0, 0),
 ])
 def test_prefill_of_low_frequencies_against_64_bit_transforms(dtype, L, reach, heads, S, R, off):
     """Two to sixteen tokens per grid point, bins up to a quarter of the grid and their mirrors; 8-byte aligned tensors.  Bar: aliasing
@@ -1092,6 +1092,38 @@ def test_prefill_of_low_frequencies_against_64_bit_transforms(dtype, L, reach, h
             assert float(err[rest].norm() / ref[rest].norm()) < 1e-6
             assert float(err[rest].abs().max() / ref[rest].abs().pow(2).mean().sqrt()) < 1e-5
             assert float(err[4:6].abs().max()) < 30 * (2e-9 + 2.0 ** -25)
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,group,heads,gain", [
+    (16384, 256, 1, 2, 1), (16384, 1025, 3, 2, 1), (32768, 2049, 4, 2, 1),  # 4 tokens per grid point of 4096 points (two cases), of 8192
+    (32768, 500, 2, 3, 1), (65536, 1025, 8, 1, 1), (65536, 4097, 2, 1, 1),  # 8 of 4096, 16 of 4096, 4 of 16384 points
+    (262144, 4096, 2, 1, 1),                                               # 16 of 16384
+    (16384, 256, 2, 2, 300), (65536, 4096, 2, 1, 300),                      # scores whose maximum needs a look at every token
+])
+def test_attention_of_low_frequencies_against_64_bit_transforms(dtype, L, n_bins, group, heads, gain):
+    """Scores carry 2^-24 of their size per radix-2 stage and tap (about 4 x 2^-24 in the 2-norm, 2^-21 with the worst token), the same
+    as weights; outputs in bf16 are rounded to 2^-9."""
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(DEV).manual_seed(L + n_bins)
+    K, V = (torch.randn((1, 1, heads, L, 128), device=DEV, generator=gen).to(td) for _ in range(2))
+    q = (gain * torch.randn((1, 1, heads * group, 128), device=DEV, generator=gen) * (L / n_bins) ** 0.5).to(td)
+    c = B.Cache(1, 1, heads, heads * group, 128, td, L, [np.arange(n_bins, dtype=np.int32)])
+    c.prefill(K, V)
+    out = c.attend(q)
+    keep = torch.zeros(L, dtype=torch.float64)
+    keep[:n_bins] = 1
+    largest = 0.0
+    for h in range(heads):
+        k, v = (torch.fft.ifft(torch.fft.fft(x[0, 0, h].cpu().double().T.contiguous()) * keep).real for x in (K, V))
+        s = q[0, 0, h * group:(h + 1) * group].cpu().double() @ k / 128 ** 0.5
+        ref = torch.softmax(s, 1) @ v.T
+        err = float((out[0, 0, h * group:(h + 1) * group].cpu().double() - ref).norm() / ref.norm())
+        big = float(s.abs().max())
+        largest = max(largest, big)
+        assert err < 1e-5 + 2.0 ** -21 * big + (2.0 ** -9 if dtype == "bf16" else 0), (err, big)
+    assert (largest > 64 / 0.083 / 1.4427) == (gain > 1), largest
     c.close()
 
 
