@@ -164,7 +164,8 @@ int iwdft_prefill_kind(const iwdft_ctx* ctx);
 
 /* Which synthesis compressed_decode_attn / iwdft_append_attn run for this context: 1 = scores and softmax
  * weights through in-LDS FFTs (M = 2^m >= 256: O(M log M) per query head, the HBM-bound path; layers with more than
- * 4096 kept bins run a form of it that keeps nothing per bin in registers); 2 = through chirp-z transforms (any
+ * 4096 kept bins run a form of it that keeps nothing per bin in registers, contexts of M >= 16384 that keep low frequencies
+ * only one on a shorter grid); 2 = through transforms interpolated from a power-of-two grid (256 <= M <= 8192) or chirp-z transforms (any
  * other M >= 32 that is at most 8192 or has a divisor Pb <= 256 with 32 <= M / Pb <= 8192, e.g. M = context - sink -
  * recent = 16384 - 60 = 2 * 8162: O(M log M) as well, 2 to 4 times the arithmetic of 1); 0 = the direct O(M |B|)
  * sums (arithmetic-bound; chosen by IWDFT_FLAG_DIRECT_SYNTHESIS, for M < 32, and for M > 8192 without such a divisor,

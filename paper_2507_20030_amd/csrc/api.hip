@@ -61,7 +61,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int64_t dec_reach = 0;         // largest |frequency| kept
   int64_t dec_slices = 0;        // slices whose grids the workspace holds at a time
   int low_logN = 0;              // decode attention on such a grid
-  size_t off_window = 0, off_gain = 0, off_low = 0, off_low_gain = 0;
+  size_t off_window = 0, off_gain = 0, off_low = 0, off_low_gain = 0, off_grid = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
   bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
@@ -86,6 +86,7 @@ constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x p
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr int64_t kDecMinTokens = (int64_t)1 << 19;
 constexpr int kLowMinLogN = 12;
+constexpr int64_t kGridMinM = 2048;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
@@ -276,6 +277,14 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // save in transforms they lose in the chain over the tokens of each (M = 16384, 256 bins, 8 slices, one head: 31 us without, 41 with
   // 1024 points).  Bins that are each other's mirror would share a slot.
   if (low_logN && pl->use_fft && !mirrored && (d->M >> low_logN) >= 4) pl->low_logN = low_logN;
+  // M that is not a power of two, one block: interpolated transforms in place of the chirp-z ones (attn_chirp.hip) where the grid is half as
+  // long as the chirp's convolution and the transforms are long enough to matter.  Attention, us, chirp-z / grid: M = 8132, 64 slices, 4 heads, 508 bins
+  // 52 / 43, 2033 bins 83 / 75; 512 slices, 8 heads 346 / 228, 647 / 520; M = 3000, 64 slices, 4 heads, 750 bins 44 / 42.  Up to 2048 tokens
+  // 0.91 .. 1.14 of the time (M = 2040, 64 slices, 510 bins 33 / 38), with a grid as long as the convolution 0.95 .. 1.14.
+  if (pl->use_chirp && pl->chirp_Q == d->M && d->M > kGridMinM) {
+    const int logN = pl->chirp_logN - 1;
+    if (((int64_t)1 << logN) >= d->M && ((int64_t)1 << logN) > 4 * pl->dec_reach) pl->low_logN = logN;
+  }
 
   // What is left takes the direct O(M |B|) sums: fine for short or sparse states, useless beyond -- refuse instead of
   // running for minutes per step (a prime M of 2^20 with 4096 kept bins is 2^32 sine / cosine pairs per query head).
@@ -342,7 +351,9 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   }
   if (pl->low_logN) {
     pl->off_low_gain = o; o = align256(o + sizeof(float) * (((size_t)1 << pl->low_logN) / 4 + 1));
-    pl->off_low = o;      o = align256(o + sizeof(float) * (size_t)(d->M >> pl->low_logN) * kTaps);
+    pl->off_low = o;
+    o = align256(o + sizeof(float) * (pl->use_chirp ? 10 * ((size_t)d->M / 2 + 1) : (size_t)(d->M >> pl->low_logN) * kTaps));
+    pl->off_grid = o;     o = align256(o + (pl->use_chirp ? 10 * sizeof(float) * (((size_t)1 << pl->low_logN) / 2 + 1) : 0));
   }
   pl->ws_bytes = o;
   return IWDFT_OK;
@@ -729,7 +740,14 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       const GridWindow gw(desc->M, pl.low_logN, pl.dec_reach, kTaps);
       std::vector<float> gain, taps;
       gw.gain(&gain);
-      make_low_taps(gw, &taps);
+      if (pl.use_chirp) {
+        make_taps(gw, desc->M, gw.N, 1.0, &taps);
+        std::vector<float> grid;
+        make_taps(gw, gw.N, desc->M, (double)gw.N / (double)desc->M, &grid);
+        to_ws(pl.off_grid, grid);
+      } else {
+        make_low_taps(gw, &taps);
+      }
       to_ws(pl.off_low_gain, gain);
       to_ws(pl.off_low, taps);
     }
@@ -767,6 +785,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.low_logN = pl.low_logN;
     P.low_gain = pl.low_logN ? (const float*)(c->ws + pl.off_low_gain) : nullptr;
     P.low_taps = pl.low_logN ? (const float*)(c->ws + pl.off_low) : nullptr;
+    P.grid_taps = pl.low_logN && pl.use_chirp ? (const float4*)(c->ws + pl.off_grid) : nullptr;
     P.dec_slices = (int32_t)pl.dec_slices;
     P.dec_window = pl.dec_logN ? c->ws + pl.off_window : nullptr;
     P.dec_gain = pl.dec_logN ? (const float*)(c->ws + pl.off_gain) : nullptr;

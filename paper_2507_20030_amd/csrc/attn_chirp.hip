@@ -1,6 +1,7 @@
 // Kernel B of the decode attention (see attn.hip) for M that is not a power of two (e.g. M = context - sink - recent,
 // Sec. 4.2.1, which is a power of two only by arrangement): scores, softmax and weights through chirp-z transforms (chirp.h).
 #include "chirp.h"
+#include "interp.h"
 
 namespace iwdft {
 
@@ -14,7 +15,11 @@ namespace iwdft {
 // 32 x 8 slices, 4 query heads each, M = 8132, 2033 bins: 75 us (134 with one transform of 16384 points by 512 threads, every
 // pass through LDS); with the write-back deferred a decode step takes 286 us instead of 510.
 // Pending tokens of the deferred write-back enter as in attn_fft_kernel (np, ptsh, ps).
-template <int LOGN>
+//
+// GRID (M <= 2^LOGN, all |frequencies| < 2^LOGN / 4): two transforms of half the length in place of four.  The scores are interpolated from a grid of N points
+// and the weights folded back onto it by the same eight taps (interp.h: bins in the place of samples, tokens in that of frequencies; the
+// way back is its transpose, gathered per grid point from tables of its own).  The decode step above: 286 -> 250 us.
+template <int LOGN, bool GRID>
 __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Params P, const float2* __restrict__ qc,
                                                                       float2* __restrict__ Pn, float* __restrict__ pe,
                                                                       float scale, int pairs, int np, uint32_t ptsh,
@@ -35,7 +40,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
   const LayerInfo L = layer_info(P, layer);
   const int g0 = pair * 2;
   const bool has1 = (g0 + 1) < P.G;
-  const uint32_t M = P.M, Q = P.any_Q, Pb = M / Q;
+  const uint32_t M = P.M, Q = GRID ? P.M : P.any_Q, Pb = GRID ? 1u : M / Q;
   const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   const float2* q1 = has1 ? q0 + L.Bp : q0;
   float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
@@ -72,9 +77,9 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
     return v;
   };
 
-  float2 c[8];  // chirp of the thread's entries, 0 from Q on
+  float2 c[GRID ? 1 : 8];  // chirp of the thread's entries, 0 from Q on
 #pragma unroll
-  for (int i = 0; i < 8; ++i) c[i] = (uint32_t)(t + T * i) < Q ? P.chirp[t + T * i] : make_float2(0.f, 0.f);
+  for (int i = 0; i < (GRID ? 0 : 8); ++i) c[i] = (uint32_t)(t + T * i) < Q ? P.chirp[t + T * i] : make_float2(0.f, 0.f);
 
   // Exact tokens open the softmax (raw scores q . k_e from kernel A).
   float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);
@@ -102,9 +107,22 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
     auto block_tw = [&](uint32_t k) {  // e^{j 2 pi k b / M}
       return Pb == 1 ? make_float2(1.f, 0.f) : cis_rev((float)mod_small(k * b, M, inv_Mf) * inv_Mf);
     };
+    // Where the entry of slot r lies; GRID: frequency f = r or r - M as sample -f of N, padded so that both consecutive samples and those
+    // that consecutive threads transform, 4 or 8 apart, fall into distinct banks.
+    auto grid_pad = [](uint32_t n) { return (int)(n + (n >> 3)); };
+    auto entry = [&](uint32_t r) {
+      if constexpr (GRID) return grid_pad((r <= M / 2 ? 0u - r : M - r) & ((1u << LOGN) - 1u));
+      else return fpad((int)r);
+    };
     auto slot_of = [&](uint32_t k) { return Pb == 1 ? k : mod_small(k, Q, inv_Q); };
+    if constexpr (GRID) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) own[i * SP] = make_float2(0.f, 0.f);
+      for (int i = 0; i < 16; ++i)
+        if (i < 4 || i >= 12) buf[grid_pad((uint32_t)(t + T * i))] = make_float2(0.f, 0.f);  // the quarters that hold frequencies
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) own[i * SP] = make_float2(0.f, 0.f);
+    }
     __syncthreads();
     // Hermitian spectrum of both heads (head g0 real, head g0 + 1 imaginary in time), folded modulo Q.  A slot can receive
     // several terms: successive rounds (host-made schedule).
@@ -119,6 +137,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
           k[j] = (uint32_t)bins[ic];
           fr[j] = i < L.nb ? (uint32_t)fold[ic] : 0xffffu;  // 0xff: no round matches
           w[j] = wts[ic] * gain;
+          if constexpr (GRID) w[j] *= P.low_gain[k[j] <= M / 2 ? k[j] : M - k[j]];
           y0[j] = q0[ic];
           y1[j] = q1[ic];
         }
@@ -133,29 +152,54 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
           if (direct) {  //      z0  + j z1
             float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
             if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
-            if (round) v = cadd(v, buf[fpad((int)r)]);
-            buf[fpad((int)r)] = v;
+            if (round) v = cadd(v, buf[entry(r)]);
+            buf[entry(r)] = v;
           }
           if (mirror) {  // conj z0  + j conj z1
             float2 v = make_float2(z0.x + z1.y, z1.x - z0.y);
-            if (round) v = cadd(v, buf[fpad((int)rm)]);
-            buf[fpad((int)rm)] = v;
+            if (round) v = cadd(v, buf[entry(rm)]);
+            buf[entry(rm)] = v;
           }
         }
       }
       __syncthreads();
     }
-    float2 v[8];
+    // scores of slot a < Q of this block: real part head g0, imaginary part head g0 + 1; v[i]: slot t + T i, or (GRID) v[2 i] and
+    // v[2 i + 1]: tokens t + T i and M - (t + T i)
+    constexpr int V = GRID ? 16 : 8;
+    float2 v[V];
+    auto live = [&](int i) {
+      const uint32_t a = (uint32_t)(t + T * (GRID ? i >> 1 : i));
+      if constexpr (GRID) return (i & 1) ? a > 0 && 2 * a < M : 2 * a <= M;
+      else return a < Q;
+    };
+    if constexpr (GRID) {
+      float2 x[16];
+      const uint32_t n0 = sample_at<LOGN>(16 * t);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = cmul(own[i * SP], c[i]);
-    chirp_convolve<LOGN, false>(buf, tab, H, t, v);
-
-    // scores of slot a < Q of this block: real part head g0, imaginary part head g0 + 1
+      for (int i = 0; i < 8; ++i)
+        x[wing_position(i)] = buf[grid_pad((n0 + ((uint32_t)(i < 4 ? i : i - 8) << (LOGN - 4))) & ((1u << LOGN) - 1u))];
+      __syncthreads();
+      grid_forward<LOGN>(buf, tab, t, x, 1 << LOGN, [](int) {});
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        v[2 * i] = v[2 * i + 1] = make_float2(0.f, 0.f);
+        if (live(2 * i)) {
+          const uint32_t r = (uint32_t)pin_index(t + T * i);  // keeps the taps of one or two items in registers, not of all
+          grid_at(buf, 1 << LOGN, load_taps((const float4*)P.low_taps, r, M), v[2 * i], v[2 * i + 1]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = cmul(own[i * SP], c[i]);
+      chirp_convolve<LOGN, false>(buf, tab, H, t, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = cmul(v[i], c[i]);
+    }
     float2 lm = make_float2(-INFINITY, -INFINITY);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      v[i] = cmul(v[i], c[i]);
-      if ((uint32_t)(t + T * i) < Q) {
+    for (int i = 0; i < V; ++i) {
+      if (live(i)) {
         lm.x = fmaxf(lm.x, v[i].x);
         lm.y = fmaxf(lm.y, v[i].y);
       }
@@ -167,18 +211,57 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
     mx = mn;
     float2 ls = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < V; ++i) {
       float2 p = make_float2(0.f, 0.f);
-      if ((uint32_t)(t + T * i) < Q)
+      if (live(i))
         p = make_float2(__builtin_amdgcn_exp2f(v[i].x - mn.x), has1 ? __builtin_amdgcn_exp2f(v[i].y - mn.y) : 0.f);
       if (TB == T || tid < T) ls = cadd(ls, p);  // else counted by lane t
-      v[i] = cmul(p, conjf2(c[i]));
+      if constexpr (GRID) {
+        if (live(i)) {  // the grid was last read ahead of block_max's barrier
+          const uint32_t a = (i & 1) ? M - (uint32_t)(t + T * (i >> 1)) : (uint32_t)(t + T * (i >> 1));
+          buf[kHalo + a] = p;
+          if (a < (uint32_t)kHalo) buf[kHalo + M + a] = p;
+          if (a + kHalo >= M) buf[kHalo + a - M] = p;
+        }
+      } else {
+        v[i] = cmul(p, conjf2(c[i]));
+      }
     }
     const float2 bs = block_sum(ls);
     Z = make_float2(Z.x * f.x + bs.x, Z.y * f.y + bs.y);
-    chirp_convolve<LOGN, true>(buf, tab, H, t, v);
+    if constexpr (GRID) {
+      constexpr int N = 1 << LOGN;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) own[i * SP] = cmul(v[i], conjf2(c[i]));
+      for (int i = 0; i < 8; ++i) {
+        float2 &u = v[2 * i], &d = v[2 * i + 1];
+        grid_at<true>(buf, (int)M, load_taps(P.grid_taps, (uint32_t)pin_index(t + T * i), N), u, d);
+        asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(d.x), "+v"(d.y));  // one item after the other: 300 registers spilled otherwise
+      }
+      float2 top = make_float2(0.f, 0.f), unused;
+      if (t == 0) grid_at<true>(buf, (int)M, load_taps(P.grid_taps, N / 2, N), top, unused);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = t + T * i;
+        buf[fpad(r)] = v[2 * i];
+        if (r) buf[fpad(N - r)] = v[2 * i + 1];
+      }
+      if (t == 0) buf[fpad(N / 2)] = top;
+      __syncthreads();
+      float2 x[16];
+      fft_inverse<LOGN>(buf, tab.tab, t, x);  // entry f of the forward transform is entry -f of the inverse one
+      const uint32_t n0 = sample_at<LOGN>(16 * t);
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        const int n = (int)n0 + sample_step<LOGN>(m);
+        if (sample_step<LOGN>(m) < N / 4 || sample_step<LOGN>(m) >= 3 * (N / 4)) buf[grid_pad((uint32_t)n)] = x[m];
+      }
+    } else {
+      chirp_convolve<LOGN, true>(buf, tab, H, t, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) own[i * SP] = cmul(v[i], conjf2(c[i]));
+    }
     __syncthreads();
 
     for (int i0 = tid; i0 < L.nb; i0 += U * TB) {
@@ -193,9 +276,14 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
         const int i = i0 + j * TB;
         if (i >= L.nb) continue;
         const uint32_t r = slot_of(k[j]), rm = r ? Q - r : 0u;
-        const float2 w1 = buf[fpad((int)r)], w2 = buf[fpad((int)rm)];
-        float2 p0 = make_float2(0.5f * (w1.x + w2.x), 0.5f * (w1.y - w2.y));
-        float2 p1 = make_float2(0.5f * (w1.y + w2.y), 0.5f * (w2.x - w1.x));
+        float2 w1 = buf[entry(r)], w2 = buf[entry(rm)];
+        float half = 0.5f;
+        if constexpr (GRID) {
+          if (2 * r == M) w2 = w1;  // e^{j pi a} is its own mirror at the tokens, not on the grid
+          half *= P.low_gain[r <= M / 2 ? r : M - r];
+        }
+        float2 p0 = make_float2(half * (w1.x + w2.x), half * (w1.y - w2.y));
+        float2 p1 = make_float2(half * (w1.y + w2.y), half * (w2.x - w1.x));
         if (Pb > 1) {
           const float2 twc = conjf2(block_tw(k[j]));
           p0 = cmul(twc, p0);
@@ -277,23 +365,31 @@ hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, floa
   const int pairs = (P.G + 1) / 2;
   const uint64_t grid = (uint64_t)P.n_slices * pairs;
   if (grid > 0x7fffffffull || np > kMaxPend) return hipErrorInvalidConfiguration;
-#define IWDFT_CHIRP_CASE(LN)                                                                                            \
-  case LN: {                                                                                                            \
-    constexpr int bytes = (int)sizeof(float2) * fft_lds(LN);                                                            \
-    static LdsLimit lim;                                                                                                \
-    const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN>, bytes);                                         \
-    if (e != hipSuccess) return e;                                                                                      \
-    attn_chirp_kernel<LN><<<dim3((uint32_t)grid), dim3(attn_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
-                                                                                     ptsh, ps);                        \
+#define IWDFT_CHIRP_CASE(LN, GRID)                                                                                            \
+  case LN: {                                                                                                                  \
+    constexpr int bytes = (int)sizeof(float2) * (GRID ? grid_lds(LN) : fft_lds(LN));                                          \
+    static LdsLimit lim;                                                                                                      \
+    const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN, GRID>, bytes);                                         \
+    if (e != hipSuccess) return e;                                                                                            \
+    attn_chirp_kernel<LN, GRID><<<dim3((uint32_t)grid), dim3(attn_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
+                                                                                           ptsh, ps);                        \
   } break;
+  if (P.low_logN) {
+    switch (P.low_logN) {
+      IWDFT_CHIRP_CASE(12, true)
+      IWDFT_CHIRP_CASE(13, true)
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   switch (P.any_logN) {
-    IWDFT_CHIRP_CASE(8)
-    IWDFT_CHIRP_CASE(9)
-    IWDFT_CHIRP_CASE(10)
-    IWDFT_CHIRP_CASE(11)
-    IWDFT_CHIRP_CASE(12)
-    IWDFT_CHIRP_CASE(13)
-    IWDFT_CHIRP_CASE(14)
+    IWDFT_CHIRP_CASE(8, false)
+    IWDFT_CHIRP_CASE(9, false)
+    IWDFT_CHIRP_CASE(10, false)
+    IWDFT_CHIRP_CASE(11, false)
+    IWDFT_CHIRP_CASE(12, false)
+    IWDFT_CHIRP_CASE(13, false)
+    IWDFT_CHIRP_CASE(14, false)
     default: return hipErrorInvalidValue;
   }
 #undef IWDFT_CHIRP_CASE

@@ -68,6 +68,7 @@ struct Params {
   int32_t low_logN;
   const float* low_gain;
   const float* low_taps;
+  const float4* grid_taps;  // M that is not a power of two: low_taps as in interp.h (tokens), and the grid points' likewise
   float2* FK;
   float2* FV;
   // Exact tokens (Sec. 4.2.1): S sink tokens and a ring of R recent tokens per slice, kv_dtype,

@@ -107,14 +107,22 @@ __device__ __forceinline__ void grid_forward(float2* buf, const TabMem& tab, int
   if (t >= T - kHalo) out[15 * T - N] = x[15];
   __syncthreads();
 }
-// Values of the Q-point transform at r and -r.
+// Values of the Q-point transform at r and -r.  ODD: N may be odd, which takes 8-byte reads on the way down.
+template <bool ODD = false>
 __device__ __forceinline__ void grid_at(const float2* buf, int N, const Taps& T, float2& zr, float2& zm) {
-  const float4* up = (const float4*)(buf + (kHalo + T.e));           // e, e + 1, ...
-  const float4* dn = (const float4*)(buf + (kHalo + N - T.e - 8));   // -e - 8, -e - 7, ... modulo N
+  const float4* up = (const float4*)(buf + (kHalo + T.e));  // e, e + 1, ...
+  const float2* dn = buf + (kHalo + N - T.e - 8);           // -e - 8, -e - 7, ... modulo N
   zr = zm = make_float2(0.f, 0.f);
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    const float4 p = up[i], m = dn[4 - i];  // e + 2 i, e + 2 i + 1; -(e + 2 i), -(e + 2 i - 1)
+    const float4 p = up[i];  // e + 2 i, e + 2 i + 1
+    float4 m;                // -(e + 2 i), -(e + 2 i - 1)
+    if constexpr (ODD) {
+      const float2 m0 = dn[8 - 2 * i], m1 = dn[9 - 2 * i];
+      m = make_float4(m0.x, m0.y, m1.x, m1.y);
+    } else {
+      m = ((const float4*)dn)[4 - i];
+    }
     zr = make_float2(fmaf(T.w[2 * i], p.x, zr.x), fmaf(T.w[2 * i], p.y, zr.y));
     zm = make_float2(fmaf(T.w[2 * i], m.x, zm.x), fmaf(T.w[2 * i], m.y, zm.y));
     if (i < 4) zr = make_float2(fmaf(T.w[2 * i + 1], p.z, zr.x), fmaf(T.w[2 * i + 1], p.w, zr.y));

@@ -1127,6 +1127,33 @@ def test_attention_of_low_frequencies_against_64_bit_transforms(dtype, L, n_bins
     c.close()
 
 
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("L", [2047, 2049, 2050, 3001, 4095, 4097, 6000, 8132, 8191])
+def test_attention_of_any_length_against_64_bit_transforms(L, wide):
+    """Low bins up to the last one that a grid of the next power of two carries (interpolation; chirp-z transforms up to 2048 tokens), and
+    bins anywhere, L / 2 and mirrors among them (chirp-z).  Bar as above: 2^-21 of the scores."""
+    gen = torch.Generator(DEV).manual_seed(L)
+    rng = np.random.default_rng(L)
+    N = 1 << (L - 1).bit_length()
+    low = np.r_[np.arange(3, L // 6), L - 1, L - 2, (N // 4 - 1) if 2 * N > 4 * (N // 4 - 1) and N // 4 - 1 < L // 2 else 7]
+    bins = np.unique(low) if not wide else np.unique(np.r_[0, 1, 2, L // 2 - 1, L // 2, L // 2 + 1, L - 2, L - 1, rng.integers(0, L, L // 5)])
+    heads, group = 3, 3
+    K, V = (torch.randn((1, 1, heads, L, 128), device=DEV, generator=gen) for _ in range(2))
+    q = torch.randn((1, 1, heads * group, 128), device=DEV, generator=gen) * (L / len(bins)) ** 0.5
+    c = B.Cache(1, 1, heads, heads * group, 128, torch.float32, L, [bins.astype(np.int32)])
+    c.prefill(K, V)
+    out = c.attend(q)
+    keep = torch.zeros(L, dtype=torch.float64)
+    keep[torch.from_numpy(bins).long()] = 1
+    for h in range(heads):
+        k, v = (torch.fft.ifft(torch.fft.fft(x[0, 0, h].cpu().double().T.contiguous()) * keep).real for x in (K, V))
+        s = q[0, 0, h * group:(h + 1) * group].cpu().double() @ k / 128 ** 0.5
+        ref = torch.softmax(s, 1) @ v.T
+        err = float((out[0, 0, h * group:(h + 1) * group].cpu().double() - ref).norm() / ref.norm())
+        assert err < 2e-6 + 2.0 ** -21 * float(s.abs().max()), err
+    c.close()
+
+
 def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one():
     # neighbouring channels share a transform; every channel has to be as accurate as alone (fp32 rounding, 2^-24, times
     # ~log2 of the 16384 points of each of two transforms and the tables: below 1e-5)
