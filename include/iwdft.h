@@ -107,7 +107,8 @@ enum {
                                        heads in all, more than 1024 kept bins in some layer, 4 or 8 query
                                        heads per pass) walk the slices in groups and put the transforms
                                        of one group into the same launches as the K-coefficient stream of
-                                       the next.  Same arithmetic, same results bit for bit.          */
+                                       the next, except where all kept bins lie below a quarter of M / 4
+                                       (the softmax then runs on a shorter grid, by itself).  Same arithmetic, same results bit for bit.          */
 };
 
 typedef struct {

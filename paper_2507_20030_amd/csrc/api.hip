@@ -701,19 +701,22 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       make_chirp(pl.chirp_Q, &chirp);
       e = hipMemcpy(c->state + pl.off_chirp, chirp.data(), sizeof(float2) * chirp.size(), hipMemcpyHostToDevice);
       // In the workspace: a copy of the state buffer that is put back may be older than this order of the table.
-      make_chirp_transform(pl.chirp_Q, pl.chirp_logN, &H);
-      out.resize(H.size());
-      const int64_t T = (int64_t)H.size() / 16;
-      for (int64_t m = 0; m < (int64_t)H.size(); ++m) {  // chirp.h: thread t owns the positions 16 t .. 16 t + 15, two per load
-        const int64_t p = digit_position(m, pl.chirp_logN), t = p >> 4, j = (p & 15) >> 1;
-        out[(size_t)((j * T + t) * 2 + (p & 1))] = H[(size_t)m];
-      }
-      if (e == hipSuccess)
+      if (e == hipSuccess && !pl.low_logN) {
+        make_chirp_transform(pl.chirp_Q, pl.chirp_logN, &H);
+        out.resize(H.size());
+        const int64_t T = (int64_t)H.size() / 16;
+        for (int64_t m = 0; m < (int64_t)H.size(); ++m) {  // chirp.h: thread t owns the positions 16 t .. 16 t + 15, two per load
+          const int64_t p = digit_position(m, pl.chirp_logN), t = p >> 4, j = (p & 15) >> 1;
+          out[(size_t)((j * T + t) * 2 + (p & 1))] = H[(size_t)m];
+        }
         e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
-      std::vector<float> dec, taps;
-      make_interp(pl.chirp_Q, pl.chirp_logN, &dec, &taps);
-      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_dec, dec.data(), sizeof(float) * dec.size(), hipMemcpyHostToDevice);
-      if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_taps, taps.data(), sizeof(float) * taps.size(), hipMemcpyHostToDevice);
+      }
+      if (e == hipSuccess && pl.use_any_prefill) {
+        std::vector<float> dec, taps;
+        make_interp(pl.chirp_Q, pl.chirp_logN, &dec, &taps);
+        e = hipMemcpy(c->ws + pl.off_dec, dec.data(), sizeof(float) * dec.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_taps, taps.data(), sizeof(float) * taps.size(), hipMemcpyHostToDevice);
+      }
     }
     if (e == hipSuccess && pl.tw_Q) {
       const double kTwoPi = 6.28318530717958647692;
@@ -777,9 +780,9 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.weights = (const float*)(c->state + pl.off_weights);
     P.fold = (const uint16_t*)(c->state + pl.off_fold);
     P.chirp = pl.use_chirp ? (const float2*)(c->state + pl.off_chirp) : nullptr;
-    P.chirpW = pl.use_chirp ? (const float4*)(c->ws + pl.off_chirpW) : nullptr;
-    P.any_dec = pl.use_chirp ? (const float*)(c->ws + pl.off_dec) : nullptr;
-    P.any_taps = pl.use_chirp ? (const float4*)(c->ws + pl.off_taps) : nullptr;
+    P.chirpW = pl.use_chirp && !pl.low_logN ? (const float4*)(c->ws + pl.off_chirpW) : nullptr;
+    P.any_dec = pl.use_any_prefill ? (const float*)(c->ws + pl.off_dec) : nullptr;
+    P.any_taps = pl.use_any_prefill ? (const float4*)(c->ws + pl.off_taps) : nullptr;
     P.any_logN = pl.chirp_logN;
     P.dec_logN = pl.dec_logN;
     P.low_logN = pl.low_logN;

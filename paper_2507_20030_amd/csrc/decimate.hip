@@ -27,6 +27,8 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
 // tokens x 8 channels of a block (whole rows over 16 lanes), which are the operand of channel 8 (lane % 16) + j, j = 0 .. 7, after
 // a permutation of halves: no LDS trip.  y: [tensor][slice of the launch][N][128].
 // What bounds it is HBM: one read of the tokens, 1 / D of twice (bf16) their bytes written; 192 matrix instructions (16 cycles) per 32 KB at D = 8.
+// 8 slices of 131072 tokens, K and V, bf16: 135 us, 4.0 TB/s read; 64 of them, 4096 bins, with the transforms: 4200 (sixteen 8192-point transforms
+// per channel pair) -> 1665 us.
 template <bool BF16, int D, bool WIDE>
 __global__ __launch_bounds__(kDecThreads, 2) void decimate_kernel(Params P, const void* __restrict__ K, const void* __restrict__ V,
                                                                  int slice0, int slices) {

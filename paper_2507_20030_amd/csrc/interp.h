@@ -2,7 +2,7 @@
 // transforms for nonequispaced data", SIAM J. Sci. Comput. 14 (1993); window after Kaiser and Bessel).  With a window w of kTaps
 // grid points and its Fourier transform W, and N = 2^LOGN >= 2 Q grid points,
 //   sum_n x[n] e^{-j 2 pi r n / Q} = sum_m w(r N / Q - m) Y[m],   Y[m] = sum_n x[n] / W(n / N) e^{-j 2 pi m n / N},  |n| <= Q / 2,
-// up to an aliasing error of 2e-8 or less (kTaps = 8, N >= 2 Q): one N-point transform of a signal that is zero in half of its points, where
+// up to an aliasing error of 1e-7 of a single sample at the worst place, 2e-8 in the 2-norm of noise (kTaps = 8, N >= 2 Q): one N-point transform of a signal that is zero in half of its points, where
 // the chirp-z identity takes two.  Host tables: 1 / W (one value per sample) and the taps of every r up to Q / 2 -- those of -r are
 // the same, mirrored.
 #pragma once
