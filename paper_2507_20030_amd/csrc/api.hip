@@ -1,6 +1,7 @@
 // C ABI of libiwdft: descriptor validation, buffer layout, call ordering, error reporting.
 // All arithmetic lives in the kernels; this file only decides what to launch.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <complex>
 #include <cstdarg>
@@ -414,15 +415,14 @@ int64_t digit_position(int64_t m, int logN) {
 // after P. J. Beatty, D. G. Nishimura and J. M. Pauly, IEEE Trans. Med. Imaging 24 (2005).
 // I0(2 sqrt(q[j])) by its series: for q <= 250 (ten taps, lowest frequencies only) term 50 is below 1e-18 of the sum.
 void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
-  double term[kTaps];
-  for (int j = 0; j < kTaps; ++j) sum[j] = term[j] = 1.0;
-  for (int k = 1; k < 50; ++k) {
-    const double f = 1.0 / ((double)k * k);
-    for (int j = 0; j < kTaps; ++j) {
-      term[j] *= q[j] * f;
-      sum[j] += term[j];
-    }
-  }
+  static const std::array<double, 50> c = [] {  // 1 / (k!)^2
+    std::array<double, 50> a{1.0};
+    for (int k = 1; k < 50; ++k) a[k] = a[k - 1] / ((double)k * k);
+    return a;
+  }();
+  for (int j = 0; j < kTaps; ++j) sum[j] = c[49];
+  for (int k = 48; k >= 0; --k)
+    for (int j = 0; j < kTaps; ++j) sum[j] = sum[j] * q[j] + c[k];
 }
 // The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision.
 struct GridWindow {
