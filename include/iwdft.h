@@ -143,7 +143,9 @@ int iwdft_query_bytes(const iwdft_desc* desc, size_t* state_bytes, size_t* works
  * (synchronous; not a hot call).  Both buffers must be 256-byte aligned and stay
  * alive and untouched by the caller until iwdft_destroy.  Neither may serve two
  * contexts at a time: the workspace holds data between calls as well (the tables of
- * transforms of any length from this call on, the tokens of a deferred write-back).
+ * transforms of any length from this call on, the tokens of a deferred write-back; in
+ * contexts of M = 2^m >= 16384 that keep low frequencies only also up to 128 MiB of
+ * scratch of iwdft_prefill).
  * The HIP device that is current at this call owns the context. */
 int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void* d_workspace,
                  size_t workspace_bytes, iwdft_ctx** out);

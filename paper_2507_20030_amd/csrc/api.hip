@@ -58,11 +58,11 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   size_t off_dec = 0, off_taps = 0;  // in the workspace
   int64_t tw_Q = 0;              // length of the transforms whose twiddle octant is at off_tw
   size_t off_tw = 0;
+  int64_t reach = 0;             // largest |frequency| kept
   int dec_logN = 0;              // FFT prefill of a decimated grid of so many points (log2; 0: of the tokens themselves)
-  int64_t dec_reach = 0;         // largest |frequency| kept
   int64_t dec_slices = 0;        // slices whose grids the workspace holds at a time
-  int low_logN = 0;              // decode attention on such a grid
-  size_t off_window = 0, off_gain = 0, off_low = 0, off_low_gain = 0, off_grid = 0;
+  int low_logN = 0;              // decode attention on a grid of so many points (log2; 0: on the tokens themselves)
+  size_t off_dec_w = 0, off_dec_tw = 0, off_dec_gain = 0, off_low = 0, off_low_gain = 0, off_grid = 0;
   bool use_fft_prefill = false;  // prefill through FFTs (else the dense MFMA contraction)
   bool scale_pairs = false;      // ... with the channels of a pair scaled to one size
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
@@ -85,8 +85,8 @@ constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 
 constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
-constexpr int64_t kDecMinTokens = (int64_t)1 << 19;
-constexpr int kLowMinLogN = 12;
+constexpr int kLowMinLogN = 12, kLowMaxLogN = 14;  // grids of prefill and decode attention on low frequencies, M = 2^m
+constexpr int64_t kLowMinD = 4, kLowMaxD = 16;     // ... tokens per grid point
 constexpr int64_t kGridMinM = 2048;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
@@ -189,32 +189,6 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   }
   // Contexts that take the FFT for its speed only, where the contraction would keep every channel alone; see prefill_fft.hip.
   pl->scale_pairs = pl->use_fft_prefill && !(d->flags & IWDFT_FLAG_FFT_PREFILL) && pl->max_nb < kFftAloneBins;
-  // Low frequencies only: the smallest grid that carries them (decimate.hip, attn_low_kernel), at most kDecMaxD tokens per grid point.
-  // Two tokens per point save the prefill little and cost it a grid in fp32 as large as the bf16 tokens: taken only in bf16 where the
-  // transforms of the tokens themselves hold more than 2048 bins (us without / with; 128 slices: M = 16384, 2048 bins, bf16 677 / 881,
-  // fp32 1028 / 1476; M = 32768, 4096 bins 2371 / 1962, 2144 / 3178).  Below kDecMinTokens tokens in all the decimation has too few
-  // waves (8 slices of 16384, 1024 bins: 46 / 50, fp32 56 / 79; of 32768, 2048 bins: 71 / 78, 127 / 110; of 65536, 4096 bins: 280 / 155,
-  // 282 / 221; 32 of 16384, 1024 bins: 160 / 128, 257 / 194); in fp32 with sixteen tokens per point below twice as many (8 of 65536,
-  // 1024 bins: 254 / 347; of 131072, 2048 bins: 494 / 421).
-  bool mirrored = false;
-  int low_logN = 0;
-  for (int64_t i = 0; i < pl->n_bins_total; ++i) {
-    const int64_t k = d->bins[i];
-    mirrored |= k > d->M - k;
-    pl->dec_reach = std::max(pl->dec_reach, k < d->M - k ? k : d->M - k);
-  }
-  if (pow2 && d->M > kFftMaxQ) {
-    int logN = kDecMinLogN;
-    while (((int64_t)1 << logN) < 4 * pl->dec_reach || ((int64_t)kDecMaxD << logN) < d->M) ++logN;
-    if (logN <= kDecMaxLogN && ((int64_t)1 << logN) < d->M) {
-      const int64_t D = d->M >> logN;
-      if (pl->use_fft_prefill && S * d->M >= (D < 16 || b16 ? kDecMinTokens : 2 * kDecMinTokens) && (D >= 4 || (b16 && pl->max_nb > 2048))) {
-        pl->dec_logN = logN;
-        pl->dec_slices = std::min<int64_t>(S, kDecScratch / ((int64_t)2 * kHeadDim * sizeof(float) << logN));
-      }
-      low_logN = std::max(logN, kLowMinLogN);
-    }
-  }
   // Chirp-z attention for M that is not a power of two: M itself up to 8192 points; longer M in Pb decimated blocks
   // of M / Pb points, Pb the smallest divisor of M that brings the block down to 8192 (none: the direct sums).
   pl->use_chirp = false;
@@ -273,18 +247,41 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     pl->use_any_prefill = S * points <= (b16 ? kAnyPrefillPoints16 : kAnyPrefillPoints32) * d->M * rounds;
   }
 
-  // Decode attention on the grid, from four tokens per point on (read-only step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144:
+  // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144:
   // 0.42 to 1.0 of the time; two tokens: M = 16384 1.00 .. 1.08, M = 32768 0.95 .. 1.0) and with 4096 points at least: what few threads
   // save in transforms they lose in the chain over the tokens of each (M = 16384, 256 bins, 8 slices, one head: 31 us without, 41 with
   // 1024 points).  Bins that are each other's mirror would share a slot.
-  if (low_logN && pl->use_fft && !mirrored && (d->M >> low_logN) >= 4) pl->low_logN = low_logN;
+  bool mirrored = false;
+  for (int64_t i = 0; i < pl->n_bins_total; ++i) {
+    const int64_t k = d->bins[i];
+    mirrored |= k > d->M - k;
+    pl->reach = std::max(pl->reach, k < d->M - k ? k : d->M - k);
+  }
+  if (pow2 && d->M > kFftMaxQ) {
+    int logN = kLowMinLogN;
+    while (((int64_t)1 << logN) < 4 * pl->reach || (kLowMaxD << logN) < d->M) ++logN;
+    if (logN <= kLowMaxLogN && (d->M >> logN) >= kLowMinD) {
+      if (pl->use_fft && !mirrored) pl->low_logN = logN;
+    }
+    // Prefill through that grid (decimate.hip) where it is faster than the transforms of the tokens.  us without / with, 64 slices: 16 tokens
+    // per grid point, M = 131072, 2048 bins bf16 2164 / 1686, fp32 3795 / 2370; 8, M = 131072, 4096 bins 4171 / 2273, 4183 / 3057; 8,
+    // M = 65536, 2048 bins 1102 / 1070, 1880 / 1535; 4, M = 65536, 4096 bins 2147 / 1707, 2092 / 2107; M = 32768, 2048 bins 608 / 787,
+    // 937 / 988.  Grids of 4096 points have too few waves below 16 slices (M = 32768, 1024 bins, 8 slices 67 / 85, 120 / 101; 64
+    // slices 578 / 521, 930 / 752); there four tokens per point gain in fp32 only (M = 16384, 1024 bins, 64 slices 308 / 385, 494 / 482).
+    const int64_t D = d->M >> logN;
+    const bool dec = D >= 8 ? logN > kLowMinLogN || S >= 16 : D == 4 && (logN == kLowMaxLogN || (logN == kLowMinLogN && !b16 && S >= 32));
+    if (logN <= kLowMaxLogN && dec && pl->use_fft_prefill) {
+      pl->dec_logN = logN;
+      pl->dec_slices = std::min<int64_t>(S, kDecScratch / ((int64_t)2 * kHeadDim * sizeof(double) << logN));
+    }
+  }
   // M that is not a power of two, one block: interpolated transforms in place of the chirp-z ones (attn_chirp.hip) where the grid is half as
   // long as the chirp's convolution and the transforms are long enough to matter.  Attention, us, chirp-z / grid: M = 8132, 64 slices, 4 heads, 508 bins
   // 52 / 43, 2033 bins 83 / 75; 512 slices, 8 heads 346 / 228, 647 / 520; M = 3000, 64 slices, 4 heads, 750 bins 44 / 42.  Up to 2048 tokens
   // 0.91 .. 1.14 of the time (M = 2040, 64 slices, 510 bins 33 / 38), with a grid as long as the convolution 0.95 .. 1.14.
   if (pl->use_chirp && pl->chirp_Q == d->M && d->M > kGridMinM) {
     const int logN = pl->chirp_logN - 1;
-    if (((int64_t)1 << logN) >= d->M && ((int64_t)1 << logN) > 4 * pl->dec_reach) pl->low_logN = logN;
+    if (((int64_t)1 << logN) >= d->M && ((int64_t)1 << logN) > 4 * pl->reach) pl->low_logN = logN;
   }
 
   // What is left takes the direct O(M |B|) sums: fine for short or sparse states, useless beyond -- refuse instead of
@@ -345,10 +342,11 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
                          (size_t)pl->G * (size_t)d->M);
   // The grids of the prefill lie over everything above, which only lives between decode steps of the same context; their tables behind.
   if (pl->dec_logN) {
-    const int D = (int)(d->M >> pl->dec_logN);
-    o = std::max(o, align256((size_t)pl->dec_slices * 2 * kHeadDim * sizeof(float) << pl->dec_logN));
-    pl->off_window = o; o = align256(o + (size_t)(D / 2 + 2 * dec_halo(D)) * 3 * 64 * 16);
-    pl->off_gain = o;   o = align256(o + sizeof(float) * (((size_t)1 << pl->dec_logN) / 4 + 1));
+    const size_t n = ((size_t)1 << pl->dec_logN) / 4 + 1;
+    o = std::max(o, align256((size_t)pl->dec_slices * 2 * kHeadDim * sizeof(double) << pl->dec_logN));
+    pl->off_dec_w = o;    o = align256(o + sizeof(double) * kDecTaps * (size_t)(d->M >> pl->dec_logN));
+    pl->off_dec_tw = o;   o = align256(o + sizeof(double2) * n);
+    pl->off_dec_gain = o; o = align256(o + sizeof(double) * n);
   }
   if (pl->low_logN) {
     pl->off_low_gain = o; o = align256(o + sizeof(float) * (((size_t)1 << pl->low_logN) / 4 + 1));
@@ -490,32 +488,7 @@ void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float
   make_taps(gw, Q, N, 1.0, taps);
 }
 
-// The window as matrix operands (decimate.hip), [group of 32 tokens][part][lane][8] bf16 -- lane: grid point lane % 16 of a tile, tokens
-// 8 (lane / 16) .. of the group, groups from dec_halo ahead of the tile's first token on.
-void make_decimation(const GridWindow& gw, std::vector<uint16_t>* window) {
-  const int halo = dec_halo((int)gw.D), groups = (int)gw.D / 2 + 2 * halo;
-  window->assign((size_t)groups * 3 * 64 * 8, 0);
-  for (int g = 0; g < groups; ++g)
-    for (int lane = 0; lane < 64; ++lane) {
-      double w[8], x[8];
-      for (int i = 0; i < 8; ++i) x[i] = (double)(lane % 16) - (double)(32 * (g - halo) + 8 * (lane / 16) + i) / (double)gw.D;
-      gw.at(x, w);
-      for (int i = 0; i < 8; ++i) {
-        double rest = w[i];
-        for (int part = 0; part < 3; ++part) {
-          const float f = (float)rest;
-          uint32_t u;
-          memcpy(&u, &f, sizeof(u));
-          u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-          float h;
-          memcpy(&h, &u, sizeof(h));
-          (*window)[(((size_t)g * 3 + part) * 64 + lane) * 8 + i] = (uint16_t)(u >> 16);
-          rest -= h;
-        }
-      }
-    }
-}
-// The same in fp32 for the tokens d = 0 .. D - 1 behind a grid point (attn_low_kernel), [d][i]: at d / D + 3 - i.
+// Taps of the tokens d = 0 .. D - 1 behind a grid point (attn_low_kernel), [d][i]: at d / D + 3 - i.
 void make_low_taps(const GridWindow& gw, std::vector<float>* taps) {
   for (int64_t d = 0; d < gw.D; ++d) {
     static_assert(kTaps == 8, "");
@@ -524,6 +497,17 @@ void make_low_taps(const GridWindow& gw, std::vector<float>* taps) {
     gw.at(x, w);
     for (int i = 0; i < kTaps; ++i) taps->push_back((float)w[i]);
   }
+}
+// Taps of the decimation for the same tokens, [d][i]: grid point i - 4.
+void make_dec_taps(const GridWindow& gw, std::vector<double>* taps) {
+  taps->resize((size_t)(gw.D * kDecTaps));
+  for (int64_t d = 0; d < gw.D; ++d)
+    for (int i = 0; i < kDecTaps; i += 8) {
+      double w[8], x[8];
+      for (int j = 0; j < 8; ++j) x[j] = (double)(i + j - 4) - (double)d / (double)gw.D;
+      gw.at(x, w);
+      for (int j = 0; j < 8 && i + j < kDecTaps; ++j) (*taps)[(size_t)(d * kDecTaps + i + j)] = w[j];
+    }
 }
 
 }  // namespace
@@ -731,16 +715,17 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       if (e == hipSuccess) e = hipMemcpy(c->ws + off, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice);
     };
     if (pl.dec_logN) {
-      const GridWindow gw(desc->M, pl.dec_logN, pl.dec_reach, kDecTaps);
-      std::vector<uint16_t> window;
-      std::vector<float> gain;
-      make_decimation(gw, &window);
-      gw.gain(&gain);
-      to_ws(pl.off_window, window);
-      to_ws(pl.off_gain, gain);
+      const GridWindow gw(desc->M, pl.dec_logN, pl.reach, kDecTaps);
+      std::vector<double> w;
+      make_dec_taps(gw, &w);
+      to_ws(pl.off_dec_w, w);
+      if (e == hipSuccess)
+        e = launch_low_tables((double2*)(c->ws + pl.off_dec_tw), (double*)(c->ws + pl.off_dec_gain), 1 << pl.dec_logN, gw.beta, gw.W0, kDecTaps,
+                              pl.reach);
+      if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     }
     if (pl.low_logN) {
-      const GridWindow gw(desc->M, pl.low_logN, pl.dec_reach, kTaps);
+      const GridWindow gw(desc->M, pl.low_logN, pl.reach, kTaps);
       std::vector<float> gain, taps;
       gw.gain(&gain);
       if (pl.use_chirp) {
@@ -785,14 +770,15 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.any_taps = pl.use_any_prefill ? (const float4*)(c->ws + pl.off_taps) : nullptr;
     P.any_logN = pl.chirp_logN;
     P.dec_logN = pl.dec_logN;
+    P.dec_slices = (int32_t)pl.dec_slices;
+    P.dec_weights = pl.dec_logN ? (const double*)(c->ws + pl.off_dec_w) : nullptr;
+    P.dec_tw = pl.dec_logN ? (const double2*)(c->ws + pl.off_dec_tw) : nullptr;
+    P.dec_gain = pl.dec_logN ? (const double*)(c->ws + pl.off_dec_gain) : nullptr;
+    P.dec_scratch = pl.dec_logN ? (double*)c->ws : nullptr;
     P.low_logN = pl.low_logN;
     P.low_gain = pl.low_logN ? (const float*)(c->ws + pl.off_low_gain) : nullptr;
     P.low_taps = pl.low_logN ? (const float*)(c->ws + pl.off_low) : nullptr;
     P.grid_taps = pl.low_logN && pl.use_chirp ? (const float4*)(c->ws + pl.off_grid) : nullptr;
-    P.dec_slices = (int32_t)pl.dec_slices;
-    P.dec_window = pl.dec_logN ? c->ws + pl.off_window : nullptr;
-    P.dec_gain = pl.dec_logN ? (const float*)(c->ws + pl.off_gain) : nullptr;
-    P.dec_scratch = pl.dec_logN ? (float*)c->ws : nullptr;
     P.any_Q = (uint32_t)pl.chirp_Q;
     P.tab = tab;
     P.tw8 = pl.tw_Q ? (const float2*)(c->state + pl.off_tw) : nullptr;

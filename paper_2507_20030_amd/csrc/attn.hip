@@ -584,7 +584,7 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
 }
 
 // Scores at all M = D N tokens from the grid x (positions 16 t + m of the digit-reversed order) by interpolation, softmax, and the
-// weights folded back onto the grid by the same taps (decimate.hip has the window; its identities hold in both directions):
+// weights folded back onto the grid by the same taps (interp.h, time and frequency exchanged: 1 / W multiplies the bins):
 //   s[m D + d] = sum_i w(d / D + 3 - i) y[m + i - 3],   z[m + i - 3] += w(d / D + 3 - i) p[m D + d],   i = 0 .. 7.
 // A thread takes 16 grid points with the 7 around them, y and z in registers: a token costs 16 multiply-adds per head either way and no
 // LDS trip; its eight weights are wave-uniform.  Maximum: a trigonometric polynomial of degree N / 4 is nowhere above the

@@ -11,6 +11,7 @@ namespace iwdft {
 constexpr int kHeadDim = 128;  // channels per head the kernels are written for
 constexpr int kMaxPend = 16;   // most tokens of a deferred write-back
 constexpr int kTaps = 8;       // grid points of the interpolation window (interp.h)
+constexpr int kDecTaps = 10;   // ... of the decimating one (decimate.hip)
 constexpr int kRowPad = 32;    // a coefficient row is padded to a multiple of this many bins
 
 // Per-layer geometry, one entry per layer in device memory.
@@ -57,13 +58,15 @@ struct Params {
   const float4* any_taps;  // taps per frequency
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
   const float2* tw8;  // e^{j 2 pi m / Q}, m = 0 .. Q / 8, Q = min(M, 8192), for fft_lds.h (null unless M = 2^m >= 256)
-  // Decimation ahead of the FFT prefill (decimate.hip): grid of 2^dec_logN points (0: not used); in the workspace the window as matrix
-  // operands, 1 / W of the frequencies 0 .. 2^dec_logN / 4, and room for the grids of dec_slices slices.
+  // Prefill of contexts that keep low frequencies only (decimate.hip): grid of 2^dec_logN points (0: not used); in the workspace the taps of
+  // the tokens between two grid points, the transforms' twiddles, 1 / W of the frequencies 0 .. 2^dec_logN / 4, and room for the
+  // grids of dec_slices slices.
   int32_t dec_logN, dec_slices;
-  const void* dec_window;
-  const float* dec_gain;
-  float* dec_scratch;
-  // Decode attention of the same contexts (attn_low_kernel): grid of 2^low_logN points (0: not used), 1 / W of 0 .. 2^low_logN / 4 and
+  const double* dec_weights;
+  const double2* dec_tw;
+  const double* dec_gain;
+  double* dec_scratch;
+  // Decode attention of contexts that keep low frequencies only (attn_low_kernel; tables in the workspace): grid of 2^low_logN points (0: not used), 1 / W of 0 .. 2^low_logN / 4 and
   // eight taps per token between two grid points.
   int32_t low_logN;
   const float* low_gain;
@@ -185,12 +188,9 @@ constexpr int kFftAloneBins = 384;
 constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
-// y of the slices slice0 .. slice0 + slices - 1 into Params::dec_scratch, [tensor][slice][N][128] fp32; kDecMaxD tokens per grid point at
-// most, 4-byte aligned tensors.
-constexpr int kDecMaxD = 16, kDecMinLogN = 10, kDecMaxLogN = 14;
-constexpr int kDecTaps = 10;
-__host__ __device__ constexpr int dec_halo(int D) { return (D * kDecTaps / 2 + 31) / 32; }  // blocks of 32 tokens beyond a tile of 16 grid points
-hipError_t launch_decimate(const Params& P, const void* K, const void* V, int slice0, int slices, hipStream_t st);
+// ... of contexts that keep low frequencies only (Params::dec_logN set; prefill_edges is the caller's), and their tables.
+hipError_t launch_prefill_low(const Params& P, const void* K, const void* V, hipStream_t st);
+hipError_t launch_low_tables(double2* tw, double* gain, int N, double beta, double W0, double taps, int64_t reach);
 // ... and through interpolated transforms (Params::any_dec set).
 hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hipStream_t st);
 hipError_t launch_prefill_edges(const Params& P, const void* K, const void* V, hipStream_t st);

@@ -22,7 +22,7 @@ __host__ __device__ constexpr int fft_lds(int logQ) { return (1 << logQ) + (1 <<
 // Transforms of 2^logQ points that a workgroup of 512 threads runs side by side, interleaved over the lanes (thread = t NS + g
 // for thread t of transform g), and the distance of their buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses
 // fall into distinct banks.
-__host__ __device__ constexpr int side_ns(int logQ) { return logQ > 13 ? 1 : 1 << (13 - logQ); }
+__host__ __device__ constexpr int side_ns(int logQ) { return 1 << (13 - logQ); }
 __host__ __device__ constexpr int side_bs(int logQ) {
   return fft_lds(logQ) + (side_ns(logQ) == 1 ? 0 : side_ns(logQ) >= 8 ? 2 : 16 / side_ns(logQ));
 }

@@ -22,7 +22,6 @@
 namespace iwdft {
 
 constexpr int kPairs = kHeadDim / 2;  // channel pairs per (slice, tensor)
-constexpr int side_threads(int logQ) { return logQ > 13 ? fft_threads(logQ) : 512; }
 
 // hardware block id -> (xcd = id & 7, idx = id >> 3); XCD x owns the (slice, tensor) pairs
 // x * per_xcd .. (x + 1) * per_xcd - 1, 64 / (NS NP) consecutive idx each.
@@ -34,20 +33,16 @@ constexpr int side_threads(int logQ) { return logQ > 13 ? fft_threads(logQ) : 51
 // loaded words and the samples go to LDS once, behind it; the last radix-2 stage (M >= 8192, M = 512) is formed at the kept
 // bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
 // EQ: the two channels of a pair are scaled to one size on the way (pair_scale), each as exact as alone; see the launcher.
-// LOW: the samples are the decimated grid of the slices slice0, slice0 + 1, ... (fp32, no windows around it), the bins are
-// multiplied by 1 / W; 16384 points take 1024 threads.
-template <int LOGQ, bool BF16, int NP, bool EQ, bool LOW = false>
-__global__ __launch_bounds__(side_threads(LOGQ), 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
-                                                                         const void* __restrict__ V, int per_xcd, int n_st,
-                                                                         int slice0) {
+template <int LOGQ, bool BF16, int NP, bool EQ>
+__global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
+                                                            const void* __restrict__ V, int per_xcd, int n_st) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
-  constexpr int NT = side_threads(LOGQ);
-  static_assert(T * NS == NT && NS * NP <= kPairs && !(LOW && BF16), "");
+  static_assert(T * NS == 512 && NS * NP <= kPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;  // bytes per token row
   constexpr int NW = NP * (BF16 ? 1 : 2);
-  __shared__ uint32_t maxima[EQ ? NT / 64 : 1][EQ ? NS : 1][EQ ? NW : 1];
+  __shared__ uint32_t maxima[EQ ? 8 : 1][EQ ? NS : 1][EQ ? NW : 1];
   __shared__ float2 halves[EQ ? NS : 1][EQ ? NP : 1];  // (h0, h1): transforms are pruned by other threads than those that fetch
   constexpr int kGroups = kPairs / (NP * NS);  // workgroups per (slice, tensor)
   const TabMem tab{P.tab + tab_base(LOGQ)};
@@ -57,16 +52,16 @@ __global__ __launch_bounds__(side_threads(LOGQ), 4) void prefill_fft_kernel(Para
   if (st >= (uint32_t)n_st) return;
   const int pair0 = (idx % kGroups) * (NS * NP);
   const int tensor = st & 1;
-  const int slice = (int)(st >> 1) + (LOW ? slice0 : 0);
+  const int slice = st >> 1;
   const int spl = P.batch * P.n_kv;
   const int layer = slice / spl;
   const int s = slice - layer * spl;
   const LayerInfo L = layer_info(P, layer);
   const int32_t* bins = P.bins + L.bin_off;
-  const int64_t N = LOW ? (int64_t)Q : (int64_t)P.S + P.M + P.R;  // rows per slice in the caller's tensor (LOW: of the grid)
+  const int64_t N = (int64_t)P.S + P.M + P.R;  // tokens per slice in the caller's tensor
   const int t = tid / NS;                      // thread of transform tid % NS
   float2* buf = smem + (tid % NS) * BS;
-  const char* X = (const char*)(tensor ? V : K) + ((int64_t)(LOW ? (int)(st >> 1) : slice) * N + (LOW ? 0 : P.S)) * kRow + (pair0 + (tid % NS) * NP) * 2 * kElem;
+  const char* X = (const char*)(tensor ? V : K) + ((int64_t)slice * N + P.S) * kRow + (pair0 + (tid % NS) * NP) * 2 * kElem;
   // the pruning goes through the transforms one after the other: consecutive threads, consecutive bins
   const int tp = tid % T;
   const float2* spec = smem + (tid / T) * BS;
@@ -98,7 +93,6 @@ __global__ __launch_bounds__(side_threads(LOGQ), 4) void prefill_fft_kernel(Para
     constexpr int U = 4;
     uint32_t kj[U];
     float2 wj[U];
-    float gj[LOW ? U : 1];
     auto fetch_bins = [&](int i0) {
 #pragma unroll
       for (int j = 0; j < U; ++j) {
@@ -109,11 +103,7 @@ __global__ __launch_bounds__(side_threads(LOGQ), 4) void prefill_fft_kernel(Para
     auto fetch_tw = [&](int k) {
       if (k != fft_np(LOGQ) - 1) return;
 #pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t r = kj[j] & (Q - 1);
-        wj[j] = pair_twiddle<LOGQ>(tab.tab, r);
-        if constexpr (LOW) gj[j] = P.dec_gain[r <= Q / 2 ? r : Q - r];
-      }
+      for (int j = 0; j < U; ++j) wj[j] = pair_twiddle<LOGQ>(tab.tab, kj[j] & (Q - 1));
     };
     fetch_bins(pin_index(tp));
     fft_forward<LOGQ>(buf, tab, t, x, fetch_tw);
@@ -129,15 +119,9 @@ __global__ __launch_bounds__(side_threads(LOGQ), 4) void prefill_fft_kernel(Para
         const int i = i0 + j * T;
         if (i < L.nb) {
           float2 w1, w2;
-          const uint32_t r = kj[j] & (Q - 1);
-          spectrum_pair<LOGQ>(spec, r, wj[j], w1, w2);
-          float2 hj = h;
-          if constexpr (LOW) {
-            const float g = gj[j];
-            hj = make_float2(h.x * g, h.y * g);
-          }
-          F0[i] = make_float2(hj.x * (w1.x + w2.x), hj.x * (w1.y - w2.y));
-          F0[L.Bp + i] = make_float2(hj.y * (w1.y + w2.y), hj.y * (w2.x - w1.x));
+          spectrum_pair<LOGQ>(spec, kj[j] & (Q - 1), wj[j], w1, w2);
+          F0[i] = make_float2(h.x * (w1.x + w2.x), h.x * (w1.y - w2.y));
+          F0[L.Bp + i] = make_float2(h.y * (w1.y + w2.y), h.y * (w2.x - w1.x));
         }
       }
     }
@@ -472,7 +456,7 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
     e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, NP, EQ>, (int)lds);                     \
     if (e != hipSuccess) return e;                                                                          \
     prefill_fft_kernel<LQ, BF16, NP, EQ><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(            \
-        P, K, V, per_xcd, n_st, 0);                                                                         \
+        P, K, V, per_xcd, n_st);                                                                            \
   }
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
@@ -497,50 +481,6 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
 #undef IWDFT_PF_SINGLE
 #undef IWDFT_PF_CASE
   return hipGetLastError();
-}
-
-// Contexts of low frequencies only: groups of slices, decimated onto a grid that stays in the memory-side cache and transformed from there.
-template <int LOGQ, bool EQ>
-static hipError_t launch_low(const Params& P, const float* Y, int slice0, int slices, hipStream_t st) {
-  const int n_st = slices * 2, per_xcd = (n_st + 7) / 8;
-  const float* YV = Y + ((int64_t)slices << LOGQ) * kHeadDim;
-  constexpr size_t lds = sizeof(float2) * (size_t)(side_ns(LOGQ) * side_bs(LOGQ));
-  const bool few = (uint64_t)n_st * (kPairs / 4) < kFewWorkgroups * (uint64_t)side_ns(LOGQ);
-#define IWDFT_PF_LOW(NP)                                                                                                     \
-  {                                                                                                                          \
-    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LOGQ))) * 8;                                       \
-    static LdsLimit lim;                                                                                                     \
-    const hipError_t e = lim.ensure((const void*)prefill_fft_kernel<LOGQ, false, NP, EQ, true>, (int)lds);                   \
-    if (e != hipSuccess) return e;                                                                                           \
-    prefill_fft_kernel<LOGQ, false, NP, EQ, true><<<dim3((uint32_t)blocks), dim3(side_threads(LOGQ)), lds, st>>>(            \
-        P, Y, YV, per_xcd, n_st, slice0);                                                                                    \
-  }
-  if (few) IWDFT_PF_LOW(1) else IWDFT_PF_LOW(2)
-#undef IWDFT_PF_LOW
-  return hipGetLastError();
-}
-static hipError_t launch_prefill_low(const Params& P, const void* K, const void* V, hipStream_t st) {
-  for (int s0 = 0; s0 < P.n_slices; s0 += P.dec_slices) {
-    const int n = P.n_slices - s0 < P.dec_slices ? P.n_slices - s0 : P.dec_slices;
-    hipError_t e = launch_decimate(P, K, V, s0, n, st);
-    if (e != hipSuccess) return e;
-#define IWDFT_LOW_CASE(LQ)                                                              \
-  case LQ:                                                                              \
-    e = P.scale_pairs ? launch_low<LQ, true>(P, P.dec_scratch, s0, n, st)               \
-                      : launch_low<LQ, false>(P, P.dec_scratch, s0, n, st);             \
-    break;
-    switch (P.dec_logN) {
-      IWDFT_LOW_CASE(10)
-      IWDFT_LOW_CASE(11)
-      IWDFT_LOW_CASE(12)
-      IWDFT_LOW_CASE(13)
-      IWDFT_LOW_CASE(14)
-      default: return hipErrorInvalidValue;
-    }
-#undef IWDFT_LOW_CASE
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
 }
 
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st) {

@@ -1059,12 +1059,12 @@ def test_interpolated_prefill_against_64_bit_transforms(L):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,reach,heads,S,R,off", [
-    (16384, 256, 64, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # grids of 1024, 2048 and 4096 points
-    (32768, 512, 32, 0, 0, 8), (32768, 2048, 17, 0, 5, 0), (32768, 4096, 17, 0, 0, 0),   # ... 8192; 16384 (bf16): three groups of slices
-    (65536, 1000, 9, 10, 50, 0), (131072, 4096, 9, 0, 0, 8), (262144, 4096, 4, 1, 0, 0),
+    (16384, 256, 64, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # a grid of 4096 points (fp32, 32 slices)
+    (32768, 512, 32, 0, 0, 8), (32768, 2048, 17, 0, 5, 0), (32768, 4096, 17, 0, 0, 0),   # ... 4096 (two groups of slices); the tokens themselves
+    (65536, 1000, 9, 10, 50, 0), (131072, 4096, 9, 0, 0, 8), (262144, 4096, 4, 1, 0, 0),  # ... 16384: three groups
 ])
 def test_prefill_of_low_frequencies_against_64_bit_transforms(dtype, L, reach, heads, S, R, off):
-    """Two to sixteen tokens per grid point, bins up to a quarter of the grid and their mirrors; 8-byte aligned tensors.  Bar: aliasing
+    """Tokens themselves and four to sixteen per grid point, bins up to a quarter of the grid and their mirrors; 8-byte aligned tensors.  Bar: aliasing
     2e-9 + fp32 rounding of at most 2^-24 per radix-2 stage (14, window and gain): 1e-6.  Channel 5 carries a tone of 30 at the
     frequency that aliases onto the last bin: 2e-9 of it there, and the rounding of its samples, which may repeat with it, 2^-25."""
     td = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -1092,6 +1092,44 @@ def test_prefill_of_low_frequencies_against_64_bit_transforms(dtype, L, reach, h
             assert float(err[rest].norm() / ref[rest].norm()) < 1e-6
             assert float(err[rest].abs().max() / ref[rest].abs().pow(2).mean().sqrt()) < 1e-5
             assert float(err[4:6].abs().max()) < 30 * (2e-9 + 2.0 ** -25)
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,heads", [(16384, 1024, 32), (32768, 1000, 17), (32768, 4096, 16), (65536, 1000, 16), (65536, 4096, 2), (131072, 2048, 3),
+                                             (131072, 4096, 4), (262144, 4096, 2)])
+def test_prefill_is_as_exact_beside_an_offset_or_a_strong_tone(dtype, L, n_bins, heads):
+    """Channels 0 .. 31: noise of size 1 beside an offset of 30, 32 .. 63 beside a tone of 30 at three periods, 64 .. 95 at six tenths of the
+    kept band, the rest noise alone; every eighth of the kept bins is judged by itself, without the tone and its neighbours.  Bar: roundings of
+    2^-24 of the signal, white over all L bins and growing by at most one per radix-2 stage: below 2^-20 of its root mean square.  bf16
+    samples with an offset: their sums over the first butterflies are exact (24 bits hold 256 sums of 8-bit values of one size), so that
+    nothing of the offset is left, and the noise alone has 1e-6."""
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(DEV).manual_seed(L + n_bins)
+    n = torch.arange(L, device=DEV, dtype=torch.float64)[:, None]
+    mid = n_bins * 6 // 10
+    X = [torch.randn((1, 1, heads, L, 128), device=DEV, generator=gen) for _ in range(2)]
+    for x in X:
+        x[..., :32] += 30
+        for c, k in ((slice(32, 64), 3), (slice(64, 96), mid)):
+            phase = 6.28 * torch.rand(32, device=DEV, generator=gen, dtype=torch.float64)
+            x[..., c] += (30 * torch.cos(2 * np.pi / L * torch.remainder(n * k, L) + phase)).float()
+    K, V = (x.to(td) for x in X)
+    c = B.Cache(1, 1, heads, heads, 128, td, L, [np.arange(n_bins, dtype=np.int32)])
+    assert B.iwdft_prefill_kind(c.ctx) == "fft"
+    c.prefill(K, V)
+    exact_sums = 1e-6 if dtype == "bf16" else 30 * 2.0 ** -20
+    for x, got in zip((K, V), c.export_coeffs(0)):
+        for h in (0, heads - 1):
+            ref = torch.fft.fft(x[0, 0, h].cpu().double().T.contiguous(), dim=1)[:, :n_bins] / L
+            err = got[0, h].cpu().to(torch.complex128)
+            err = (err if err.shape == ref.shape else err.T) - ref
+            for chans, tone, bar in ((slice(0, 32), 0, exact_sums), (slice(32, 64), 3, 21.2 * 2.0 ** -20),
+                                     (slice(64, 96), mid, 21.2 * 2.0 ** -20), (slice(96, 128), 0, 1e-6)):
+                for e in range(8):
+                    rest = [k for k in range(e * n_bins // 8, (e + 1) * n_bins // 8) if abs(k - tone) > 2]
+                    got_rel = float(err[chans][:, rest].abs().pow(2).mean().sqrt()) * L ** 0.5
+                    assert got_rel < bar, (chans, e, got_rel, bar)
     c.close()
 
 
