@@ -91,6 +91,8 @@ constexpr int64_t kGridMinM = 2048;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
+constexpr int64_t tap_floats(int taps) { return taps > 8 ? 12 : 10; }  // of one point (interp.h, load_taps)
+
 int make_plan(const iwdft_desc* d, Plan* pl) {
   if (!d) return fail(IWDFT_ERR_ARG, "desc is NULL");
   if (d->n_layers <= 0 || d->batch <= 0 || d->n_kv_heads <= 0 || d->n_q_heads <= 0)
@@ -335,7 +337,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_ps = o;    o = align256(o + (pl->write_every > 1 ? sizeof(float) * n_sl * (size_t)pl->G * kMaxPend : 0));
   pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
   pl->off_dec = o;   o = align256(o + (pl->use_chirp ? sizeof(float) * ((size_t)1 << pl->chirp_logN) / 2 : 0));
-  pl->off_taps = o;  o = align256(o + (pl->use_chirp ? 10 * sizeof(float) * ((size_t)pl->chirp_Q / 2 + 1) : 0));
+  pl->off_taps = o;  o = align256(o + (pl->use_chirp ? sizeof(float) * tap_floats(d->M > pl->chirp_Q ? kSumTaps : kTaps) * ((size_t)pl->chirp_Q / 2 + 1) : 0));
   pl->off_direct = o;
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
@@ -425,7 +427,8 @@ void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
 // The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision.
 struct GridWindow {
   int64_t N, D;
-  double reach, taps, beta, W0;
+  double reach, beta, W0;
+  int taps;
   GridWindow(int64_t M, int logN, double reach_, int taps_) : N((int64_t)1 << logN), D(M / N), reach(reach_), taps(taps_) {
     const double a = taps * (1.0 - std::max(reach, 1.0) / (double)N);
     beta = 3.14159265358979323846 * std::sqrt(a * a - 0.8);
@@ -449,27 +452,28 @@ struct GridWindow {
     for (int64_t k = 0; k <= N / 4; ++k) (*g)[(size_t)k] = (double)k <= reach ? (float)(W0 / W(k)) : 0.f;
   }
 };
-// Taps of points r = 0 .. P / 2 of one period P on a grid of G, [2][n][4] | [n][2] (interp.h), n = P / 2 + 1; unit: a step of G in points of
-// the window's grid.
+// Taps of points r = 0 .. P / 2 of one period P on a grid of G, [2][n][4] | [n][2] (eight taps) or [3][n][4] (ten; interp.h), n = P / 2 + 1;
+// unit: a step of G in points of the window's grid.
 void make_taps(const GridWindow& gw, int64_t P, int64_t G, double unit, std::vector<float>* taps) {
   const int64_t n = P / 2 + 1;
-  taps->assign((size_t)(10 * n), 0.f);
+  const int NT = gw.taps;
+  taps->assign((size_t)(tap_floats(NT) * n), 0.f);
   for (int64_t r = 0; r < n; ++r) {
-    const int64_t first = r * G / P - (kTaps / 2 - 1);
+    const int64_t first = r * G / P - (NT / 2 - 1);
     const int odd = (int)(first & 1);
+    const auto at = [&](int e) { return (size_t)(e < 8 || NT > 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r + (e - 8)); };
     const int32_t even = (int32_t)(first - odd);
-    memcpy(&(*taps)[(size_t)(8 * n + 2 * r + 1)], &even, sizeof(even));
-    double x[kTaps], w[kTaps];
-    for (int j = 0; j < kTaps; ++j) x[j] = (double)(r * G - (first + j) * P) / (double)P * unit;
-    gw.at(x, w);
-    for (int j = 0; j < kTaps; ++j) {
-      const int e = odd + j;
-      (*taps)[(size_t)(e < 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r)] = (float)w[j];
+    memcpy(&(*taps)[at(NT > 8 ? 11 : 9)], &even, sizeof(even));
+    for (int j0 = 0; j0 < NT; j0 += 8) {
+      double x[8], w[8];
+      for (int j = 0; j < 8; ++j) x[j] = (double)(r * G - (first + j0 + j) * P) / (double)P * unit;
+      gw.at(x, w);
+      for (int j = 0; j < 8 && j0 + j < NT; ++j) (*taps)[at(odd + j0 + j)] = (float)w[j];
     }
   }
 }
-void make_interp(int64_t Q, int logN, std::vector<float>* dec, std::vector<float>* taps) {
-  const GridWindow gw(Q, logN, 0.5 * (double)Q, kTaps);
+void make_interp(int64_t Q, int logN, int n_taps, std::vector<float>* dec, std::vector<float>* taps) {
+  const GridWindow gw(Q, logN, 0.5 * (double)Q, n_taps);
   const int64_t N = gw.N, T = N / 16;
   dec->assign((size_t)(8 * T), 0.f);
   for (int64_t t = 0; t < T; ++t) {
@@ -697,7 +701,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       if (e == hipSuccess && pl.use_any_prefill) {
         std::vector<float> dec, taps;
-        make_interp(pl.chirp_Q, pl.chirp_logN, &dec, &taps);
+        make_interp(pl.chirp_Q, pl.chirp_logN, desc->M > pl.chirp_Q ? kSumTaps : kTaps, &dec, &taps);
         e = hipMemcpy(c->ws + pl.off_dec, dec.data(), sizeof(float) * dec.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_taps, taps.data(), sizeof(float) * taps.size(), hipMemcpyHostToDevice);
       }

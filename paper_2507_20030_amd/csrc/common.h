@@ -11,6 +11,7 @@ namespace iwdft {
 constexpr int kHeadDim = 128;  // channels per head the kernels are written for
 constexpr int kMaxPend = 16;   // most tokens of a deferred write-back
 constexpr int kTaps = 8;       // grid points of the interpolation window (interp.h)
+constexpr int kSumTaps = 10;   // ... where the blocks of a longer M are summed (prefill_any.hip)
 constexpr int kDecTaps = 10;   // ... of the decimating one (decimate.hip)
 constexpr int kRowPad = 32;    // a coefficient row is padded to a multiple of this many bins
 

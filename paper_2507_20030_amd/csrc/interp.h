@@ -2,7 +2,8 @@
 // transforms for nonequispaced data", SIAM J. Sci. Comput. 14 (1993); window after Kaiser and Bessel).  With a window w of kTaps
 // grid points and its Fourier transform W, and N = 2^LOGN >= 2 Q grid points,
 //   sum_n x[n] e^{-j 2 pi r n / Q} = sum_m w(r N / Q - m) Y[m],   Y[m] = sum_n x[n] / W(n / N) e^{-j 2 pi m n / N},  |n| <= Q / 2,
-// up to an aliasing error of 1e-7 of a single sample at the worst place, 2e-8 in the 2-norm of noise (kTaps = 8, N >= 2 Q): one N-point transform of a signal that is zero in half of its points, where
+// up to an aliasing error of 1e-7 of a single sample at the worst place, 2e-8 in the 2-norm of noise (eight taps, N >= 2 Q; the sums
+// of several blocks take ten, see prefill_any.hip): one N-point transform of a signal that is zero in half of its points, where
 // the chirp-z identity takes two.  Host tables: 1 / W (one value per sample) and the taps of every r up to Q / 2 -- those of -r are
 // the same, mirrored.
 #pragma once
@@ -31,19 +32,27 @@ __device__ __forceinline__ uint32_t wing_index(uint32_t n0, int i, uint32_t Q) {
 }
 constexpr int wing_position(int i) { return i < 4 ? 4 * i : 4 * (i - 4) + 3; }
 
-// The taps of frequency r as laid out by the host: nine weights for the grid points e, e + 1, ..., e + 8 with e even (one of the
-// outer two is zero) and e itself, -4 <= e: [2][n] float4 | [n] float2 (weight, e as bits), n = Q / 2 + 1.
+// The taps of frequency r as laid out by the host: NT + 1 weights for the grid points e, e + 1, ..., e + NT with e even (one of the
+// outer two is zero) and e itself, -4 <= e: [2][n] float4 | [n] float2 (weight, e as bits) for eight taps, [3][n] float4 for ten, n = Q / 2 + 1.
+template <int NT>
 struct Taps {
-  float w[9];
+  float w[NT + 1];
   int e;
 };
-__device__ __forceinline__ Taps load_taps(const float4* __restrict__ tab, uint32_t r, uint32_t Q) {
+template <int NT = kTaps>
+__device__ __forceinline__ Taps<NT> load_taps(const float4* __restrict__ tab, uint32_t r, uint32_t Q) {
+  static_assert(NT == 8 || NT == 10, "");
   const uint32_t n = (Q >> 1) + 1;
   const float4 a = tab[r], b = tab[n + r];
-  const float2 c = ((const float2*)(tab + 2 * n))[r];
-  Taps T;
-  T.w[0] = a.x, T.w[1] = a.y, T.w[2] = a.z, T.w[3] = a.w, T.w[4] = b.x, T.w[5] = b.y, T.w[6] = b.z, T.w[7] = b.w, T.w[8] = c.x;
-  T.e = __float_as_int(c.y);
+  Taps<NT> T;
+  T.w[0] = a.x, T.w[1] = a.y, T.w[2] = a.z, T.w[3] = a.w, T.w[4] = b.x, T.w[5] = b.y, T.w[6] = b.z, T.w[7] = b.w;
+  if constexpr (NT == 8) {
+    const float2 c = ((const float2*)(tab + 2 * n))[r];
+    T.w[8] = c.x, T.e = __float_as_int(c.y);
+  } else {
+    const float4 c = tab[2 * n + r];
+    T.w[8] = c.x, T.w[9] = c.y, T.w[10] = c.z, T.e = __float_as_int(c.w);
+  }
   return T;
 }
 
@@ -108,24 +117,24 @@ __device__ __forceinline__ void grid_forward(float2* buf, const TabMem& tab, int
   __syncthreads();
 }
 // Values of the Q-point transform at r and -r.  ODD: N may be odd, which takes 8-byte reads on the way down.
-template <bool ODD = false>
-__device__ __forceinline__ void grid_at(const float2* buf, int N, const Taps& T, float2& zr, float2& zm) {
+template <bool ODD = false, int NT = kTaps>
+__device__ __forceinline__ void grid_at(const float2* buf, int N, const Taps<NT>& T, float2& zr, float2& zm) {
   const float4* up = (const float4*)(buf + (kHalo + T.e));  // e, e + 1, ...
-  const float2* dn = buf + (kHalo + N - T.e - 8);           // -e - 8, -e - 7, ... modulo N
+  const float2* dn = buf + (kHalo + N - T.e - NT);          // -e - NT, -e - NT + 1, ... modulo N
   zr = zm = make_float2(0.f, 0.f);
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
+  for (int i = 0; i <= NT / 2; ++i) {
     const float4 p = up[i];  // e + 2 i, e + 2 i + 1
     float4 m;                // -(e + 2 i), -(e + 2 i - 1)
     if constexpr (ODD) {
-      const float2 m0 = dn[8 - 2 * i], m1 = dn[9 - 2 * i];
+      const float2 m0 = dn[NT - 2 * i], m1 = dn[NT + 1 - 2 * i];
       m = make_float4(m0.x, m0.y, m1.x, m1.y);
     } else {
-      m = ((const float4*)dn)[4 - i];
+      m = ((const float4*)dn)[NT / 2 - i];
     }
     zr = make_float2(fmaf(T.w[2 * i], p.x, zr.x), fmaf(T.w[2 * i], p.y, zr.y));
     zm = make_float2(fmaf(T.w[2 * i], m.x, zm.x), fmaf(T.w[2 * i], m.y, zm.y));
-    if (i < 4) zr = make_float2(fmaf(T.w[2 * i + 1], p.z, zr.x), fmaf(T.w[2 * i + 1], p.w, zr.y));
+    if (i < NT / 2) zr = make_float2(fmaf(T.w[2 * i + 1], p.z, zr.x), fmaf(T.w[2 * i + 1], p.w, zr.y));
     if (i > 0) zm = make_float2(fmaf(T.w[2 * i - 1], m.z, zm.x), fmaf(T.w[2 * i - 1], m.w, zm.y));
   }
 }

@@ -5,7 +5,10 @@
 // Two channels of a slice travel as real and imaginary part of one signal and are separated at the kept bins, as in the
 // power-of-two prefill; the second one is scaled to the first one's size on the way (scale_pairs).
 // M > 8192 runs in Pb = M / Q decimated blocks: U[k] = sum_b e^{-j 2 pi k b / M} DFT_Q(x[Pb a + b])[k mod Q],
-// the running sums live in the output rows (every bin belongs to one thread, which reads back its own earlier store).
+// the running sums live in the output rows (every bin belongs to one thread, which reads back its own earlier store).  There the taps are
+// ten: what an offset or a low tone leaves on its neighbours (1.6e-7 of it with eight taps, N / Q = 2) is the same in every block
+// and adds up, where roundings of different samples do not (noise beside an offset of 30, error of the bins 1 .. 63 in units of it and of
+// the noise: 3 blocks of 8191 1.6e-6 -> 5.4e-7, 64 blocks 7.1e-6 -> 2.2e-6).
 #include "interp.h"
 #include "pair_io.h"
 
@@ -18,7 +21,7 @@ namespace iwdft {
 // maxima of all pairs are reduced at once (one by one: 1.66), the next pair's 1 / W is fetched while the bins are read.
 // 32 x 8 slices, M = 8132, 2033 bins, bf16: 2.30 ms (two chirp-z transforms of the same length) -> 1.56 ms, dense contraction
 // 7.43; relative error 2.3e-7 -> 1.5e-7, dense 8.5e-7.
-template <int LOGN, bool BF16, int NP>
+template <int LOGN, bool BF16, int NP, int NT>
 __global__ __launch_bounds__(fft_threads(LOGN), 4) void prefill_any_kernel(Params P, const void* __restrict__ K,
                                                                        const void* __restrict__ V, int per_xcd,
                                                                        int n_st, int slots) {
@@ -107,20 +110,20 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void prefill_any_kernel(Param
       float2* F0 = F + (int64_t)(2 * p) * L.Bp;
       for (int i0 = t; i0 < L.nb; i0 += U * T) {
         if (i0 >= U * T) fetch_bins(i0);
-        Taps taps[U];
+        Taps<NT> taps[U];
         bool up[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
           const uint32_t r = Pb == 1 ? k[j] : mod_small(k[j], Q, inv_Q);
           up[j] = 2u * r > Q;  // upper half: the taps of the mirror
-          taps[j] = load_taps(P.any_taps, up[j] ? Q - r : r, Q);
+          taps[j] = load_taps<NT>(P.any_taps, up[j] ? Q - r : r, Q);
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
           const int i = i0 + j * T;
           if (i >= L.nb) continue;
           float2 wl, wh;
-          grid_at(buf, 1 << LOGN, taps[j], wl, wh);
+          grid_at<false, NT>(buf, 1 << LOGN, taps[j], wl, wh);
           const float2 w1 = up[j] ? wh : wl, w2 = up[j] ? wl : wh;
           float2 d0 = make_float2(h0 * (w1.x + w2.x), h0 * (w1.y - w2.y));
           float2 d1 = make_float2(h1 * (w1.y + w2.y), h1 * (w2.x - w1.x));
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void prefill_any_kernel(Param
 
 constexpr int kCusPerXcd = 32;
 
-template <bool BF16>
+template <bool BF16, int NT>
 static hipError_t launch_prefill_any_t(const Params& P, const void* K, const void* V, hipStream_t st) {
   const int n_st = P.n_slices * 2;
   const int per_xcd = (n_st + 7) / 8;
@@ -162,9 +165,9 @@ static hipError_t launch_prefill_any_t(const Params& P, const void* K, const voi
     const int64_t items = (int64_t)per_xcd * (kHeadDim / 2 / (NP));                                              \
     const int slots = items < max_slots ? (int)items : max_slots;                                                \
     static LdsLimit lim;                                                                                         \
-    const hipError_t e = lim.ensure((const void*)prefill_any_kernel<LN, BF16, NP>, bytes);                     \
+    const hipError_t e = lim.ensure((const void*)prefill_any_kernel<LN, BF16, NP, NT>, bytes);                 \
     if (e != hipSuccess) return e;                                                                               \
-    prefill_any_kernel<LN, BF16, NP><<<dim3((uint32_t)slots * 8), dim3(fft_threads(LN)), bytes, st>>>(         \
+    prefill_any_kernel<LN, BF16, NP, NT><<<dim3((uint32_t)slots * 8), dim3(fft_threads(LN)), bytes, st>>>(     \
         P, K, V, per_xcd, n_st, slots);                                                                          \
   }
 #define IWDFT_PA_CASE(LN)                             \
@@ -189,7 +192,9 @@ hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hip
   if (!P.any_dec) return hipErrorInvalidValue;
   const hipError_t e = launch_prefill_edges(P, K, V, st);
   if (e != hipSuccess) return e;
-  return P.kv_dtype == 1 ? launch_prefill_any_t<true>(P, K, V, st) : launch_prefill_any_t<false>(P, K, V, st);
+  if (P.M > P.any_Q)
+    return P.kv_dtype == 1 ? launch_prefill_any_t<true, kSumTaps>(P, K, V, st) : launch_prefill_any_t<false, kSumTaps>(P, K, V, st);
+  return P.kv_dtype == 1 ? launch_prefill_any_t<true, kTaps>(P, K, V, st) : launch_prefill_any_t<false, kTaps>(P, K, V, st);
 }
 
 }  // namespace iwdft

@@ -1057,6 +1057,27 @@ def test_interpolated_prefill_against_64_bit_transforms(L):
     c.close()
 
 
+@pytest.mark.parametrize("blocks,Q,heads", [(2, 8162, 16), (3, 8191, 16), (5, 6005, 16), (8, 8191, 8), (16, 8191, 8), (64, 8191, 8)])
+def test_interpolated_prefill_of_several_blocks_is_as_exact_beside_an_offset(blocks, Q, heads):
+    """Noise of size 1 beside an offset of 30.  Near the offset's own bin, 0, the interpolation sums values of its size, whose taps and
+    twiddles are rounded to 2^-25; that is the same in every block and adds up.  Bar in units of the offset and of the noise's sums:
+    2^-20 for the roundings of one block (at most 2^-24 per radix-2 stage, 16 with the two ends), 2^-21 sqrt(blocks) for what adds up.  The
+    first 64 bins without 0, and the rest, which roundings alone reach."""
+    L = blocks * Q
+    assert next(p for p in range(1, L) if L % p == 0 and L // p <= 8192) == blocks
+    K = 30 + torch.randn((1, 1, heads, L, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(L))
+    n_bins = 2000
+    c = B.Cache(1, 1, heads, heads, 128, torch.float32, L, [np.arange(n_bins, dtype=np.int32)])
+    assert B.iwdft_prefill_kind(c.ctx) == "chirp"
+    c.prefill(K, K)
+    got = c.export_coeffs(0)[1][0, heads - 1].cpu().to(torch.complex128)
+    ref = torch.fft.fft(K[0, 0, heads - 1].cpu().double().T.contiguous(), dim=1)[:, :n_bins] / L
+    err = (got if got.shape == ref.shape else got.T) - ref
+    for rest, bar in ((slice(1, 64), 2.0 ** -20 + 2.0 ** -21 * blocks ** 0.5), (slice(64, n_bins), 2.0 ** -20)):
+        assert float(err[:, rest].abs().pow(2).mean().sqrt()) * L ** 0.5 < 30 * bar, rest
+    c.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,reach,heads,S,R,off", [
     (16384, 256, 64, 0, 0, 0), (16384, 257, 35, 2, 3, 0), (16384, 1024, 32, 0, 0, 8),    # a grid of 4096 points (fp32, 32 slices)
