@@ -583,16 +583,25 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
   return v;
 }
 
+// A value that all lanes share, in scalar registers.
+__device__ __forceinline__ float2 wave_uniform(float2 v) {
+  return make_float2(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.x))), __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.y))));
+}
+
 // Scores at all M = D N tokens from the grid x (positions 16 t + m of the digit-reversed order) by interpolation, softmax, and the
 // weights folded back onto the grid by the same taps (interp.h, time and frequency exchanged: 1 / W multiplies the bins):
 //   s[m D + d] = sum_i w(d / D + 3 - i) y[m + i - 3],   z[m + i - 3] += w(d / D + 3 - i) p[m D + d],   i = 0 .. 7.
-// A thread takes 16 grid points with the 7 around them, y and z in registers: a token costs 16 multiply-adds per head either way and no
+// A thread takes 16 grid points with the 7 around them, y and z in registers: a token costs 8 multiply-adds per head each way and no
 // LDS trip; its eight weights are wave-uniform.  Maximum: a trigonometric polynomial of degree N / 4 is nowhere above the
 // largest magnitude on 2 N points divided by cos(pi / 8) (H. Ehlich and K. Zeller, Math. Zeitschrift 86 (1964)), so the tokens d = 0 and D / 2 give it up to
 // 0.083 max|s|; where that is more than 2^64 in the weights all tokens are looked at.
+// Constants stay out of either direction, where their roundings would spread over the kept bins with those of N points only: the scores
+// come in without their mean (the caller's bin 0), and what is folded back is e^s - level, the weight that a token at the mean has; the
+// caller adds M level to bin 0.  Error against 64 bits, M = 65536, 1000 bins, flat scores 1.5e-7 -> 1.1e-7, beside a mean of 19 3.0e-7 ->
+// 1.0e-7 (attn_fft_kernel: 1.4e-7, 1.6e-7), for two subtractions a token: a decode step of 32 x 8 slices of 131072 tokens 525 -> 530 us.
 template <int LOGN>
 __device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const float* __restrict__ taps, int t, bool has1,
-                                            float2 (&x)[16], float2& mx, float2& Z, float2& f) {
+                                            float2 (&x)[16], float2& mx, float2& Z, float2& f, float2& level) {
   constexpr int N = 1 << LOGN, T = fft_threads(LOGN), NWV = T / 64;
   static_assert(T >= 64, "whole waves");
   __shared__ float4 lmax[NWV];
@@ -659,6 +668,7 @@ __device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const 
   const float2 mn = make_float2(fmaxf(mx.x, lm.x), fmaxf(mx.y, lm.y));
   f = make_float2(__builtin_amdgcn_exp2f(mx.x - mn.x), __builtin_amdgcn_exp2f(mx.y - mn.y));
   mx = mn;
+  level = wave_uniform(make_float2(__builtin_amdgcn_exp2f(-mn.x), has1 ? __builtin_amdgcn_exp2f(-mn.y) : 0.f));
   float2 z[23], ls = make_float2(0.f, 0.f);  // grid points 16 t - 3 .. 16 t + 19
 #pragma unroll
   for (int j = 0; j < 23; ++j) z[j] = make_float2(0.f, 0.f);
@@ -672,8 +682,9 @@ __device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const 
       const float2 s = score(w, m);
       const float2 e = make_float2(__builtin_amdgcn_exp2f(s.x - mn.x), has1 ? __builtin_amdgcn_exp2f(s.y - mn.y) : 0.f);
       ls = cadd(ls, e);
+      const float2 v = csub(e, level);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) z[m + i] = make_float2(fmaf(w[i], e.x, z[m + i].x), fmaf(w[i], e.y, z[m + i].y));
+      for (int i = 0; i < 8; ++i) z[m + i] = make_float2(fmaf(w[i], v.x, z[m + i].x), fmaf(w[i], v.y, z[m + i].y));
     }
   }
   Z = make_float2(Z.x * f.x + ls.x, Z.y * f.y + ls.y);
@@ -899,7 +910,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
         const int r = kj[j] & (Q - 1), rm = (Q - r) & (Q - 1);
         if ((fr[j] & 0xffu) == (uint32_t)round) {  //      z0  + j z1
           float2 v = make_float2(z0.x - z1.y, z0.y + z1.x);
-          if (r == rm) v = make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
+          if (r == rm) v = LOW ? make_float2(0.f, 0.f) : make_float2(2.f * z0.x, 2.f * z1.x);  // ... plus the mirror term, same slot
           if (round) v = cadd(v, buf[fpad(r)]);
           buf[fpad(r)] = v;
         }
@@ -921,9 +932,13 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     fft_inverse<LOGQ>(buf, tab.tab, lx, x);
 
     // softmax: real part head g0, imaginary part head g0 + 1
-    float2 f;
+    float2 f, level;
     if constexpr (LOW) {
-      low_softmax<LOGQ>(P, buf, taps, lx, has1, x, mx, Z, f);
+      float2 mean = make_float2(0.f, 0.f);  // of the scores: bin 0, which the spectrum above leaves out
+      if (bins[0] == 0) mean = wave_uniform(make_float2(2.f * gain * wts[0] * q0[0].x, has1 ? 2.f * gain * wts[0] * q1[0].x : 0.f));
+      mx = csub(mx, mean);
+      low_softmax<LOGQ>(P, buf, taps, lx, has1, x, mx, Z, f, level);
+      mx = cadd(mx, mean);
     } else {
     float2 lm = x[0];
 #pragma unroll
@@ -966,6 +981,10 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
         const float g = P.low_gain[kj[j]];
         p0 = make_float2(g * p0.x, g * p0.y);
         p1 = make_float2(g * p1.x, g * p1.y);
+        if (kj[j] == 0) {
+          p0.x = fmaf((float)P.M, level.x, p0.x);
+          p1.x = fmaf((float)P.M, level.y, p1.x);
+        }
       }
       if constexpr (MULTI) {
         const float2 twc = conjf2(cis_fast((kj[j] * b) & (P.M - 1u), P.M));
@@ -1062,8 +1081,8 @@ __global__ __launch_bounds__(attn_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_
 }
 
 // Long contexts that keep low frequencies only, |k| <= N / 4 on a grid of N = 2^LOGN points, D = M / N tokens apart: see low_softmax.
-// What bounds it is the vector ALU, 48 instructions a token and pair of heads (82 of 150 us), beside the transforms of one workgroup per
-// CU.  32 x 8 slices of 131072 tokens, 4096 bins, 4 heads: 300 (attn_fft_kernel, 16 pairs of 8192-point transforms each) -> 150 us, a
+// What bounds it is the vector ALU, 50 instructions a token and pair of heads (32 of them the multiply-adds), beside the transforms of one
+// workgroup per CU.  32 x 8 slices of 131072 tokens, 4096 bins, 4 heads: 300 (attn_fft_kernel, 16 pairs of 8192-point transforms each) -> 150 us, a
 // read-only decode step 683 -> 524.
 template <int LOGN>
 __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_low_kernel(Params P, const float2* __restrict__ qc,

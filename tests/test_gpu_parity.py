@@ -1186,6 +1186,33 @@ def test_attention_of_low_frequencies_against_64_bit_transforms(dtype, L, n_bins
     c.close()
 
 
+@pytest.mark.parametrize("L,n_bins", [(65536, 1000), (131072, 4096), (262144, 4096)])
+def test_attention_of_low_frequencies_is_as_exact_beside_a_mean_score(L, n_bins):
+    """Scores of size 2 beside a mean of 13 to 19, which softmax does not see: it must not cost precision either.  Reference in 64 bits from the
+    stored coefficients.  Bar: what is left are roundings of scores of size 2, of exponentials and of the transforms' values, 2^-24
+    each and independent from token to token: 2e-7 (seen 1.0e-7 .. 1.4e-7; 2.2e-7 .. 3.0e-7 with the mean inside the transforms)."""
+    heads, group = 4, 4
+    gen = torch.Generator().manual_seed(L + n_bins)
+    K, V = (torch.randn((heads, L, 128), generator=gen) for _ in range(2))
+    K[..., ::3] += 30
+    q = torch.randn((1, 1, heads * group, 128), generator=gen) * (L / n_bins) ** 0.5 / 16
+    c = B.Cache(1, 1, heads, heads * group, 128, torch.float32, L, [np.arange(n_bins, dtype=np.int32)])
+    c.prefill(K.to(DEV)[None, None], V.to(DEV)[None, None])
+    out = c.attend(q.to(DEV)).cpu().double()
+    Bp = -(-n_bins // 32) * 32
+    U = c.state[c.state_bytes - 16 * heads * 128 * Bp:].view(torch.float32).view(2, heads, 128, Bp, 2).cpu().double()
+    U = torch.view_as_complex(U.contiguous())
+    errs = []
+    for h in range(heads):
+        full = torch.zeros((2, 128, L), dtype=torch.complex128)
+        full[:, :, :n_bins] = U[:, h, :, :n_bins]
+        k, v = torch.fft.ifft(full, dim=-1).real
+        ref = torch.softmax(q[0, 0, h * group:(h + 1) * group].double() @ k / 128 ** 0.5, 1) @ v.T
+        errs.append(float((out[0, 0, h * group:(h + 1) * group] - ref).norm() / ref.norm()))
+    assert np.mean(errs) < 2e-7, errs
+    c.close()
+
+
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("L", [2047, 2049, 2050, 3001, 4095, 4097, 6000, 8132, 8191])
 def test_attention_of_any_length_against_64_bit_transforms(L, wide):
