@@ -1,7 +1,6 @@
 // C ABI of libiwdft: descriptor validation, buffer layout, call ordering, error reporting.
 // All arithmetic lives in the kernels; this file only decides what to launch.
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <complex>
 #include <cstdarg>
@@ -15,6 +14,7 @@
 #include "../../include/iwdft.h"
 #include "common.h"
 #include "fft_tab.h"
+#include "tables.h"
 
 using namespace iwdft;
 
@@ -254,10 +254,14 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // save in transforms they lose in the chain over the tokens of each (M = 16384, 256 bins, 8 slices, one head: 31 us without, 41 with
   // 1024 points).  Bins that are each other's mirror would share a slot.
   bool mirrored = false;
-  for (int64_t i = 0; i < pl->n_bins_total; ++i) {
-    const int64_t k = d->bins[i];
-    mirrored |= k > d->M - k;
-    pl->reach = std::max(pl->reach, k < d->M - k ? k : d->M - k);
+  for (int l = 0; l < d->n_layers; ++l) {  // ascending: the bins next to M / 2 on either side are the highest
+    const int32_t *b0 = d->bins + d->bin_offsets[l], *b1 = d->bins + d->bin_offsets[l + 1];
+    const int32_t* up = std::upper_bound(b0, b1, (int32_t)(d->M / 2));
+    if (up > b0) pl->reach = std::max<int64_t>(pl->reach, up[-1]);
+    if (up < b1) {
+      pl->reach = std::max<int64_t>(pl->reach, d->M - *up);
+      mirrored = true;
+    }
   }
   if (pow2 && d->M > kFftMaxQ) {
     int logN = kLowMinLogN;
@@ -360,16 +364,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   return IWDFT_OK;
 }
 
-// Tables of the chirp-z transforms, in double precision: c[a] = exp(+j pi a^2 / M) and the length-N transform (sign +) of
-// h[n] = exp(-j pi n^2 / M), |n| < M, wrapped modulo N, divided by N.
-void make_chirp(int64_t M, std::vector<float2>* chirp) {
-  const double kPi = 3.14159265358979323846;
-  chirp->resize((size_t)M);
-  for (int64_t n = 0; n < M; ++n) {
-    const double ph = kPi * (double)((n * n) % (2 * M)) / (double)M;  // exact phase reduction
-    (*chirp)[(size_t)n] = make_float2((float)std::cos(ph), (float)std::sin(ph));
-  }
-}
+// The length-N transform (sign +) of h[n] = exp(-j pi n^2 / M), |n| < M, wrapped modulo N, divided by N, in double precision.
 void make_chirp_transform(int64_t M, int logN, std::vector<float2>* H) {
   const double kPi = 3.14159265358979323846;
   const int64_t N = (int64_t)1 << logN;
@@ -410,108 +405,14 @@ int64_t digit_position(int64_t m, int logN) {
   return odd ? p | ((m & 1) << even) : p;
 }
 
-// Tables of the interpolated transforms (interp.h), in double precision: 1 / W at the samples of every thread, [8][N / 16], and
-// the taps of the frequencies 0 .. Q / 2, [2][n][4] | [n][2].  W: transform of the window I0(beta sqrt(1 - (x / 4)^2)), |x| < 4, both divided by W(0); beta
-// after P. J. Beatty, D. G. Nishimura and J. M. Pauly, IEEE Trans. Med. Imaging 24 (2005).
-// I0(2 sqrt(q[j])) by its series: for q <= 250 (ten taps, lowest frequencies only) term 50 is below 1e-18 of the sum.
-void bessel_i0(const double (&q)[kTaps], double (&sum)[kTaps]) {
-  static const std::array<double, 50> c = [] {  // 1 / (k!)^2
-    std::array<double, 50> a{1.0};
-    for (int k = 1; k < 50; ++k) a[k] = a[k - 1] / ((double)k * k);
-    return a;
-  }();
-  for (int j = 0; j < kTaps; ++j) sum[j] = c[49];
-  for (int k = 48; k >= 0; --k)
-    for (int j = 0; j < kTaps; ++j) sum[j] = sum[j] * q[j] + c[k];
-}
-// The window of a grid of N = 2^logN points, D = M / N tokens apart, and its transform, in double precision.
-struct GridWindow {
-  int64_t N, D;
-  double reach, beta, W0;
-  int taps;
-  GridWindow(int64_t M, int logN, double reach_, int taps_) : N((int64_t)1 << logN), D(M / N), reach(reach_), taps(taps_) {
-    const double a = taps * (1.0 - std::max(reach, 1.0) / (double)N);
-    beta = 3.14159265358979323846 * std::sqrt(a * a - 0.8);
-    W0 = W(0);
-  }
-  double W(int64_t k) const {
-    const double y = 3.14159265358979323846 * taps * (double)k / (double)N, r2 = beta * beta - y * y, r = std::sqrt(std::fabs(r2));
-    return r2 > 0.0 ? std::sinh(r) / r : (r > 0.0 ? std::sin(r) / r : 1.0);
-  }
-  void at(const double (&x)[8], double (&w)[8]) const {  // x in grid points
-    double q[8];
-    for (int i = 0; i < 8; ++i) {
-      const double z = 1.0 - x[i] * x[i] * 4.0 / (taps * taps);
-      q[i] = z > 0.0 ? 0.25 * beta * beta * z : 0.0;
-    }
-    bessel_i0(q, w);
-    for (int i = 0; i < 8; ++i) w[i] = std::fabs(x[i]) < 0.5 * taps ? w[i] / (taps * W0) : 0.0;
-  }
-  void gain(std::vector<float>* g) const {  // 1 / W of the frequencies 0 .. N / 4
-    g->resize((size_t)(N / 4 + 1));
-    for (int64_t k = 0; k <= N / 4; ++k) (*g)[(size_t)k] = (double)k <= reach ? (float)(W0 / W(k)) : 0.f;
-  }
-};
-// Taps of points r = 0 .. P / 2 of one period P on a grid of G, [2][n][4] | [n][2] (eight taps) or [3][n][4] (ten; interp.h), n = P / 2 + 1;
-// unit: a step of G in points of the window's grid.
-void make_taps(const GridWindow& gw, int64_t P, int64_t G, double unit, std::vector<float>* taps) {
-  const int64_t n = P / 2 + 1;
-  const int NT = gw.taps;
-  taps->assign((size_t)(tap_floats(NT) * n), 0.f);
-  for (int64_t r = 0; r < n; ++r) {
-    const int64_t first = r * G / P - (NT / 2 - 1);
-    const int odd = (int)(first & 1);
-    const auto at = [&](int e) { return (size_t)(e < 8 || NT > 8 ? (e / 4 * n + r) * 4 + e % 4 : 8 * n + 2 * r + (e - 8)); };
-    const int32_t even = (int32_t)(first - odd);
-    memcpy(&(*taps)[at(NT > 8 ? 11 : 9)], &even, sizeof(even));
-    for (int j0 = 0; j0 < NT; j0 += 8) {
-      double x[8], w[8];
-      for (int j = 0; j < 8; ++j) x[j] = (double)(r * G - (first + j0 + j) * P) / (double)P * unit;
-      gw.at(x, w);
-      for (int j = 0; j < 8 && j0 + j < NT; ++j) (*taps)[at(odd + j0 + j)] = (float)w[j];
-    }
-  }
-}
-void make_interp(int64_t Q, int logN, int n_taps, std::vector<float>* dec, std::vector<float>* taps) {
-  const GridWindow gw(Q, logN, 0.5 * (double)Q, n_taps);
-  const int64_t N = gw.N, T = N / 16;
-  dec->assign((size_t)(8 * T), 0.f);
-  for (int64_t t = 0; t < T; ++t) {
-    int64_t n0 = 0;  // time index of position 16 t (fft_core.h, sample_at)
-    {
-      const int64_t p = 16 * t;
-      const int odd = logN & 1, even = logN - odd;
-      for (int b = 0; b < even; b += 2) n0 |= ((p >> b) & 3) << (even - 2 - b);
-      if (odd) n0 = (n0 << 1) | (p >> (logN - 1));
-    }
-    for (int i = 0; i < 8; ++i) {
-      const int64_t m = n0 + (i < 4 ? i : i - 8) * (N / 16);
-      if (m >= 0 ? m < (Q + 1) / 2 : -m <= Q / 2) (*dec)[(size_t)(i * T + t)] = (float)(gw.W0 / gw.W(m));
-    }
-  }
-  make_taps(gw, Q, N, 1.0, taps);
-}
-
-// Taps of the tokens d = 0 .. D - 1 behind a grid point (attn_low_kernel), [d][i]: at d / D + 3 - i.
-void make_low_taps(const GridWindow& gw, std::vector<float>* taps) {
-  for (int64_t d = 0; d < gw.D; ++d) {
-    static_assert(kTaps == 8, "");
-    double w[8], x[8];
-    for (int i = 0; i < kTaps; ++i) x[i] = (double)d / (double)gw.D + 3.0 - i;
-    gw.at(x, w);
-    for (int i = 0; i < kTaps; ++i) taps->push_back((float)w[i]);
-  }
-}
-// Taps of the decimation for the same tokens, [d][i]: grid point i - 4.
-void make_dec_taps(const GridWindow& gw, std::vector<double>* taps) {
-  taps->resize((size_t)(gw.D * kDecTaps));
-  for (int64_t d = 0; d < gw.D; ++d)
-    for (int i = 0; i < kDecTaps; i += 8) {
-      double w[8], x[8];
-      for (int j = 0; j < 8; ++j) x[j] = (double)(i + j - 4) - (double)d / (double)gw.D;
-      gw.at(x, w);
-      for (int j = 0; j < 8 && i + j < kDecTaps; ++j) (*taps)[(size_t)(d * kDecTaps + i + j)] = w[j];
-    }
+// The window of a grid of N = 2^logN points (tables.hip has its formulas).  beta after P. J. Beatty, D. G. Nishimura and
+// J. M. Pauly, IEEE Trans. Med. Imaging 24 (2005).
+Window grid_window(int logN, double reach, int taps) {
+  Window w{(int64_t)1 << logN, reach, 0.0, 0.0, taps};
+  const double a = taps * (1.0 - std::max(reach, 1.0) / (double)w.N);
+  w.beta = 3.14159265358979323846 * std::sqrt(a * a - 0.8);
+  w.W0 = std::sinh(w.beta) / w.beta;
+  return w;
 }
 
 }  // namespace
@@ -685,9 +586,8 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       e = hipMemcpy(c->state + pl.off_fold, pl.fold.data(), sizeof(uint16_t) * pl.fold.size(),
                     hipMemcpyHostToDevice);
     if (e == hipSuccess && pl.use_chirp) {
-      std::vector<float2> chirp, H, out;
-      make_chirp(pl.chirp_Q, &chirp);
-      e = hipMemcpy(c->state + pl.off_chirp, chirp.data(), sizeof(float2) * chirp.size(), hipMemcpyHostToDevice);
+      std::vector<float2> H, out;
+      e = make_chirp((float2*)(c->state + pl.off_chirp), pl.chirp_Q);
       // In the workspace: a copy of the state buffer that is put back may be older than this order of the table.
       if (e == hipSuccess && !pl.low_logN) {
         make_chirp_transform(pl.chirp_Q, pl.chirp_logN, &H);
@@ -699,11 +599,10 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
         }
         e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
       }
-      if (e == hipSuccess && pl.use_any_prefill) {
-        std::vector<float> dec, taps;
-        make_interp(pl.chirp_Q, pl.chirp_logN, desc->M > pl.chirp_Q ? kSumTaps : kTaps, &dec, &taps);
-        e = hipMemcpy(c->ws + pl.off_dec, dec.data(), sizeof(float) * dec.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(c->ws + pl.off_taps, taps.data(), sizeof(float) * taps.size(), hipMemcpyHostToDevice);
+      if (pl.use_any_prefill) {
+        const Window gw = grid_window(pl.chirp_logN, 0.5 * (double)pl.chirp_Q, desc->M > pl.chirp_Q ? kSumTaps : kTaps);
+        if (e == hipSuccess) e = make_samples((float*)(c->ws + pl.off_dec), pl.chirp_Q, pl.chirp_logN, gw);
+        if (e == hipSuccess) e = make_taps((float*)(c->ws + pl.off_taps), pl.chirp_Q, gw.N, 1.0, gw);
       }
     }
     if (e == hipSuccess && pl.tw_Q) {
@@ -715,34 +614,23 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
       }
       e = hipMemcpy(c->state + pl.off_tw, tw.data(), sizeof(float2) * tw.size(), hipMemcpyHostToDevice);
     }
-    const auto to_ws = [&](size_t off, const auto& v) {
-      if (e == hipSuccess) e = hipMemcpy(c->ws + off, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice);
-    };
-    if (pl.dec_logN) {
-      const GridWindow gw(desc->M, pl.dec_logN, pl.reach, kDecTaps);
-      std::vector<double> w;
-      make_dec_taps(gw, &w);
-      to_ws(pl.off_dec_w, w);
-      if (e == hipSuccess)
-        e = launch_low_tables((double2*)(c->ws + pl.off_dec_tw), (double*)(c->ws + pl.off_dec_gain), 1 << pl.dec_logN, gw.beta, gw.W0, kDecTaps,
-                              pl.reach);
-      if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e == hipSuccess && pl.dec_logN) {
+      const Window gw = grid_window(pl.dec_logN, (double)pl.reach, kDecTaps);
+      e = make_token_taps((double*)(c->ws + pl.off_dec_w), desc->M >> pl.dec_logN, gw);
+      if (e == hipSuccess) e = make_low((double2*)(c->ws + pl.off_dec_tw), (double*)(c->ws + pl.off_dec_gain), gw);
     }
-    if (pl.low_logN) {
-      const GridWindow gw(desc->M, pl.low_logN, pl.reach, kTaps);
-      std::vector<float> gain, taps;
-      gw.gain(&gain);
-      if (pl.use_chirp) {
-        make_taps(gw, desc->M, gw.N, 1.0, &taps);
-        std::vector<float> grid;
-        make_taps(gw, gw.N, desc->M, (double)gw.N / (double)desc->M, &grid);
-        to_ws(pl.off_grid, grid);
+    if (e == hipSuccess && pl.low_logN) {
+      const Window gw = grid_window(pl.low_logN, (double)pl.reach, kTaps);
+      e = make_gain((float*)(c->ws + pl.off_low_gain), gw);
+      if (e != hipSuccess) {
+      } else if (!pl.use_chirp) {
+        e = make_token_taps((float*)(c->ws + pl.off_low), desc->M >> pl.low_logN, gw);
       } else {
-        make_low_taps(gw, &taps);
+        e = make_taps((float*)(c->ws + pl.off_low), desc->M, gw.N, 1.0, gw);
+        if (e == hipSuccess) e = make_taps((float*)(c->ws + pl.off_grid), gw.N, desc->M, (double)gw.N / (double)desc->M, gw);
       }
-      to_ws(pl.off_low_gain, gain);
-      to_ws(pl.off_low, taps);
     }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // the tables above
     const float2* tab = nullptr;
     if (e == hipSuccess) e = fft_table(&tab);
     if (e != hipSuccess) {

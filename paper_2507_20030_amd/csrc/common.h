@@ -189,9 +189,8 @@ constexpr int kFftAloneBins = 384;
 constexpr uint32_t kStreamMaxM = 1u << 26;  // 32-bit offsets of a lane's samples
 bool prefill_fft_ok(const Params& P);
 hipError_t launch_prefill_fft(const Params& P, const void* K, const void* V, hipStream_t st);
-// ... of contexts that keep low frequencies only (Params::dec_logN set; prefill_edges is the caller's), and their tables.
+// ... of contexts that keep low frequencies only (Params::dec_logN set; prefill_edges is the caller's).
 hipError_t launch_prefill_low(const Params& P, const void* K, const void* V, hipStream_t st);
-hipError_t launch_low_tables(double2* tw, double* gain, int N, double beta, double W0, double taps, int64_t reach);
 // ... and through interpolated transforms (Params::any_dec set).
 hipError_t launch_prefill_any(const Params& P, const void* K, const void* V, hipStream_t st);
 hipError_t launch_prefill_edges(const Params& P, const void* K, const void* V, hipStream_t st);

@@ -268,17 +268,6 @@ __global__ __launch_bounds__(low_threads(LOGN), 2) void prefill_low_kernel(Param
   }
 }
 
-// Tables of a context: e^{-j 2 pi k / N} and 1 / W(k / N), k = 0 .. N / 4 (0 beyond the reach).
-__global__ void low_tables_kernel(double2* tw, double* gain, int N, double beta, double W0, double taps, int64_t reach) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > N / 4) return;
-  double s, c;
-  sincospi(2.0 * (double)k / (double)N, &s, &c);
-  tw[k] = make_double2(c, -s);
-  const double y = 3.14159265358979323846 * taps * (double)k / (double)N, r2 = beta * beta - y * y, r = sqrt(fabs(r2));
-  gain[k] = k <= reach ? W0 / (r2 > 0.0 ? sinh(r) / r : r > 0.0 ? sin(r) / r : 1.0) : 0.0;
-}
-
 template <int LOGN>
 hipError_t launch_transforms(const Params& P, int slice0, int slices, hipStream_t st) {
   constexpr int bytes = low_lds(LOGN), kSlots = 256 << (14 - LOGN);  // workgroups that the device holds at once
@@ -304,11 +293,6 @@ hipError_t launch_decimate(const Params& P, const void* K, const void* V, int sl
 }
 
 }  // namespace
-
-hipError_t launch_low_tables(double2* tw, double* gain, int N, double beta, double W0, double taps, int64_t reach) {
-  low_tables_kernel<<<dim3((uint32_t)(N / 4 + 256) / 256), dim3(256), 0, nullptr>>>(tw, gain, N, beta, W0, taps, reach);
-  return hipGetLastError();
-}
 
 hipError_t launch_prefill_low(const Params& P, const void* K, const void* V, hipStream_t st) {
   for (int s0 = 0; s0 < P.n_slices; s0 += P.dec_slices) {

@@ -4,7 +4,7 @@
 //   sum_n x[n] e^{-j 2 pi r n / Q} = sum_m w(r N / Q - m) Y[m],   Y[m] = sum_n x[n] / W(n / N) e^{-j 2 pi m n / N},  |n| <= Q / 2,
 // up to an aliasing error of 1e-7 of a single sample at the worst place, 2e-8 in the 2-norm of noise (eight taps, N >= 2 Q; the sums
 // of several blocks take ten, see prefill_any.hip): one N-point transform of a signal that is zero in half of its points, where
-// the chirp-z identity takes two.  Host tables: 1 / W (one value per sample) and the taps of every r up to Q / 2 -- those of -r are
+// the chirp-z identity takes two.  Tables (tables.hip): 1 / W (one value per sample) and the taps of every r up to Q / 2 -- those of -r are
 // the same, mirrored.
 #pragma once
 #include "common.h"
@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t wing_index(uint32_t n0, int i, uint32_t Q) {
 }
 constexpr int wing_position(int i) { return i < 4 ? 4 * i : 4 * (i - 4) + 3; }
 
-// The taps of frequency r as laid out by the host: NT + 1 weights for the grid points e, e + 1, ..., e + NT with e even (one of the
+// The taps of frequency r as laid out by taps_kernel: NT + 1 weights for the grid points e, e + 1, ..., e + NT with e even (one of the
 // outer two is zero) and e itself, -4 <= e: [2][n] float4 | [n] float2 (weight, e as bits) for eight taps, [3][n] float4 for ten, n = Q / 2 + 1.
 template <int NT>
 struct Taps {

@@ -8,6 +8,8 @@ Tolerances (relative L2 over the compared tensor):
   reconstruction, fp32 / bf16 storage    1e-4 / 4e-3 (bf16 rounding alone is 2^-9 per element)
 Kept-bin masks read back from the device must be bit-exact.
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -1238,6 +1240,24 @@ def test_attention_of_any_length_against_64_bit_transforms(L, wide):
         err = float((out[0, 0, h * group:(h + 1) * group].cpu().double() - ref).norm() / ref.norm())
         assert err < 2e-6 + 2.0 ** -21 * float(s.abs().max()), err
     c.close()
+
+
+def test_create_of_a_length_that_is_no_power_of_two_costs_what_another_does():
+    """A context's tables (taps, 1 / W, chirp) are made on the device: with the same bins and slices M = 8132 differs from M = 8192 by a few
+    launches and one wait, where tables of 8132 entries each made on the host took 15 times as long (best of 20 calls each)."""
+    best = {}
+    for L in (8192, 8132):
+        d = B.Descriptor(1, 1, 8, 32, 128, B.IWDFT_BF16, L, [np.arange(2033, dtype=np.int32)], write_every=16)
+        state, ws = (torch.empty(n, dtype=torch.uint8, device=DEV) for n in B.iwdft_query_bytes(d))
+        times = []
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ctx = B.iwdft_create(d, state, ws)
+            times.append(time.perf_counter() - t)
+            B.iwdft_destroy(ctx)
+        best[L] = min(times)
+    assert best[8132] < 4 * best[8192], best
 
 
 def test_chirp_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one():
