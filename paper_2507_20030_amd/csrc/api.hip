@@ -81,8 +81,8 @@ constexpr int kMaxExact = 1024;  // most sink + recent tokens (their scores sit 
 constexpr uint32_t kFftMinM = 256;
 constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kernel holds in LDS
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
-// grid points that take as long as one token of the contraction
-constexpr int64_t kAnyPrefillPoints16 = 180, kAnyPrefillPoints32 = 250;
+// grid points that take as long as one token of the contraction: bf16, fp32, grids of up to 4096 points and longer ones
+constexpr int64_t kAnyPrefillPoints[2][2] = {{180, 160}, {250, 185}};
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr int kLowMinLogN = 12, kLowMaxLogN = 14;  // grids of prefill and decode attention on low frequencies, M = 2^m
@@ -238,15 +238,16 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
 
   // Prefill through interpolated transforms where they are faster than the dense contraction.  The transforms cost in proportion to
   // slices and grid points, and 1.5 points per kept bin where blocks are summed in the output rows; the contraction walks the M
-  // tokens with 256 workgroups (slices x tiles of 128 bins) at a time, whether or not the last round is full.  The line is where the
-  // two meet over 11 lengths from 300 to 32708, 8 to 256 slices and 32 to 1024 bins: no call there is more than 1.28 (bf16) and
-  // 1.35 (fp32) times slower than on the other path, 0.4 and 0.5 % in the mean.  Dense / transforms in us, points per token and round:
-  // bf16 M = 8132, 64 slices, 512 bins (129) 462 / 348; M = 3000, 128 slices, 512 bins (175) 350 / 306; M = 5000, 64 slices, 128 bins
-  // (210) 226 / 250; fp32 the same three 755 / 483, 571 / 404, 399 / 377.  Blocks of a few points only stay with the contraction.
+  // tokens with 256 workgroups (slices x tiles of 128 bins) at a time, whether or not the last round is full.  The line keeps every call that
+  // the transforms do not make slower over 15 lengths from 300 to 32708, 8 to 512 slices and 32 to 2000 bins.  Dense / transforms in us,
+  // points per token and round: bf16 M = 3000, 64 slices, 128 bins (175) 140 / 127, 128 slices, 384 bins (175) 277 / 287;
+  // M = 4036, 256 slices, 384 bins (173) 569 / 641; M = 8132, 64 slices, 512 bins (129) 462 / 348, 256 slices, 384 bins (172) 1111 / 1350;
+  // fp32 M = 5000, 64 slices, 128 bins (210) 399 / 377; M = 6000, 256 slices, 384 bins (233) 1418 / 1619; M = 24573, 96 slices, 256 bins (197)
+  // 1915 / 2300; M = 8132, 96 slices, 128 bins (193) 646 / 723.  Blocks of a few points only stay with the contraction.
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
     const int64_t Pb = d->M / pl->chirp_Q;
     const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
-    pl->use_any_prefill = S * points <= (b16 ? kAnyPrefillPoints16 : kAnyPrefillPoints32) * d->M * rounds;
+    pl->use_any_prefill = S * points <= kAnyPrefillPoints[b16 ? 0 : 1][pl->chirp_logN > 12 ? 1 : 0] * d->M * rounds;
   }
 
   // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144:

@@ -234,6 +234,17 @@ def test_prefill_takes_the_contraction_in_fp32_from_8192_tokens_only(L, slices, 
     check_prefill_kind(L, slices, 128, torch.float32, kind)
 
 
+@pytest.mark.parametrize("dtype,L,slices,n_bins,kind", [
+    (torch.bfloat16, 8132, 64, 512, "chirp"), (torch.bfloat16, 8132, 256, 384, "dense"), (torch.bfloat16, 4036, 256, 384, "dense"),
+    (torch.bfloat16, 2040, 64, 128, "chirp"), (torch.bfloat16, 16324, 256, 384, "dense"), (torch.float32, 5000, 64, 128, "dense"),
+    (torch.float32, 8132, 96, 128, "dense"), (torch.float32, 8132, 64, 128, "chirp"), (torch.float32, 24573, 96, 256, "dense"),
+    (torch.float32, 2040, 96, 128, "chirp"),
+])
+def test_prefill_of_other_lengths_takes_the_contraction_where_that_is_faster(dtype, L, slices, n_bins, kind):
+    """Grid points per token and round of the contraction: up to 160 (bf16) and 185 (fp32), on grids of up to 4096 points 180 and 250."""
+    check_prefill_kind(L, slices, n_bins, dtype, kind)
+
+
 def check_prefill_kind(L, slices, n_bins, dtype, kind):
     c = B.Cache(1, 1, slices, slices, 128, dtype, L, [np.arange(n_bins, dtype=np.int32)], device=DEV)
     assert B.iwdft_prefill_kind(c.ctx) == kind
