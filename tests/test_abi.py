@@ -43,6 +43,59 @@ def test_query_bytes_accounts_for_padded_rows():
     assert state % 256 == 0 and ws % 256 == 0
 
 
+def padded(*sizes):
+    return sum(-(-n // 256) * 256 for n in sizes)
+
+
+@pytest.mark.parametrize("M,reach,points", [
+    (2047, 400, 0), (2049, 1023, 4096), (2049, 1024, 0), (2050, 1023, 4096), (2050, 1024, 0), (4095, 1023, 4096), (4095, 1024, 0), (4097, 2047, 8192),
+    (5000, 700, 8192), (8132, 2032, 8192), (8132, 2047, 8192), (8132, 2048, 0), (8191, 2047, 8192), (8194, 100, 0),
+])
+def test_attention_of_other_lengths_takes_the_grid_by_rule(M, reach, points):
+    """2049 .. 8191 tokens and all frequencies below a quarter of the next power of two: the workspace then holds that grid's 1 / W and
+    the taps of the tokens and of the grid's points, ten floats each."""
+    low, high = (B.iwdft_query_bytes(desc(M=M, bins=[np.array([0, reach]), np.array([k])], flags=B.IWDFT_FLAG_DENSE_PREFILL))[1]
+                 for k in (3, M // 2))
+    assert low - high == (padded(4 * (points // 4 + 1), 40 * (M // 2 + 1), 40 * (points // 2 + 1)) if points else 0)
+    mirrored = B.iwdft_query_bytes(desc(M=M, bins=[np.array([0, reach]), np.array([M - 1])], flags=B.IWDFT_FLAG_DENSE_PREFILL))[1]
+    assert mirrored == low
+
+
+@pytest.mark.parametrize("M,reach,points", [
+    (8192, 100, 0), (16384, 1024, 4096), (16384, 1025, 0), (32768, 1024, 4096), (32768, 1025, 8192), (32768, 2049, 0), (65536, 4096, 16384),
+    (65536, 10, 4096), (131072, 10, 8192), (262144, 4096, 16384), (262144, 4097, 0), (524288, 10, 0),
+])
+def test_attention_of_long_contexts_takes_the_grid_by_rule(M, reach, points):
+    """M = 2^m, four to sixteen tokens per point of a grid of 4096 to 16384 points that is four times as long as the highest kept frequency, no
+    bin beyond M / 2: the workspace then holds 1 / W and eight taps per token between two points."""
+    low, high = (B.iwdft_query_bytes(desc(M=M, bins=[np.array([0, reach]), np.array([k])], flags=B.IWDFT_FLAG_DENSE_PREFILL))[1]
+                 for k in (3, M - 1))
+    assert low - high == (padded(4 * (points // 4 + 1), 32 * (M // points)) if points else 0)
+
+
+@pytest.mark.parametrize("M,n_bins,heads,dtype,points", [
+    (131072, 4097, 1, B.IWDFT_BF16, 16384), (131072, 4098, 1, B.IWDFT_BF16, 0), (65536, 4096, 1, B.IWDFT_BF16, 16384),
+    (65536, 2048, 2, B.IWDFT_BF16, 8192), (32768, 4096, 64, B.IWDFT_BF16, 0), (32768, 1024, 15, B.IWDFT_F32, 0), (32768, 1024, 16, B.IWDFT_F32, 4096),
+    (16384, 1024, 64, B.IWDFT_BF16, 0), (16384, 1024, 31, B.IWDFT_F32, 0), (16384, 1024, 32, B.IWDFT_F32, 4096), (262144, 4096, 3, B.IWDFT_F32, 16384),
+    (131072, 127, 1, B.IWDFT_BF16, 0),
+])
+def test_prefill_of_long_contexts_takes_the_grid_by_rule(M, n_bins, heads, dtype, points):
+    """Low bins: grids of 8192 points and more from eight tokens per point on, of 4096 from 16 slices on, four tokens per point with 16384
+    points, or with 4096 in fp32 from 32 slices on; never where the contraction runs.  The workspace then holds up to 128 MiB of grids
+    (64-bit, 2 tensors x 128 channels), their transforms' twiddles and 1 / W, and ten taps per token between two points."""
+    kw = dict(M=M, n_layers=1, n_kv_heads=heads, n_q_heads=heads, kv_dtype=dtype, bins=[np.arange(n_bins)])
+    ws = B.iwdft_query_bytes(desc(**kw))[1]
+    dense = B.iwdft_query_bytes(desc(**kw, flags=B.IWDFT_FLAG_DENSE_PREFILL))[1]
+    if not points:
+        assert ws == dense
+        return
+    rows = -(-n_bins // 32) * 32
+    arrays = 2 * padded(8 * heads * rows)
+    grids = min(heads, 2 ** 27 // (2048 * points)) * 2048 * points
+    tables = padded(80 * (M // points), 16 * (points // 4 + 1), 8 * (points // 4 + 1))
+    assert ws - dense == max(grids, arrays) + tables - arrays
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_layers=0, bins=[]), B.IWDFT_ERR_ARG),
     (dict(n_q_heads=3), B.IWDFT_ERR_ARG),
