@@ -180,7 +180,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
       for (int i = 0; i < 8; ++i)
         x[wing_position(i)] = buf[grid_pad((n0 + ((uint32_t)(i < 4 ? i : i - 8) << (LOGN - 4))) & ((1u << LOGN) - 1u))];
       __syncthreads();
-      grid_forward<LOGN>(buf, tab, t, x, 1 << LOGN, [](int) {});
+      grid_forward<LOGN>(buf, tab, t, x, 1 << LOGN);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         v[2 * i] = v[2 * i + 1] = make_float2(0.f, 0.f);
@@ -279,7 +279,6 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
         float2 w1 = buf[entry(r)], w2 = buf[entry(rm)];
         float half = 0.5f;
         if constexpr (GRID) {
-          if (2 * r == M) w2 = w1;  // e^{j pi a} is its own mirror at the tokens, not on the grid
           half *= P.low_gain[r <= M / 2 ? r : M - r];
         }
         float2 p0 = make_float2(half * (w1.x + w2.x), half * (w1.y - w2.y));

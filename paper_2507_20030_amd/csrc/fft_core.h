@@ -361,12 +361,11 @@ __device__ __forceinline__ void fft_fwd_passes(float2* buf, const Tab& tab, int 
   }
 }
 // hook(k) runs between the butterflies of radix-16 pass k = 0 .. fft_np(LOGQ) - 1 and its stores.
-// WINGS: see dft16_1.
-template <int LOGQ, bool WIDE = false, bool WINGS = false, typename Tab, typename Hook>
+template <int LOGQ, bool WIDE = false, typename Tab, typename Hook>
 __device__ __forceinline__ void fft_forward(float2* buf, const Tab& tab, int t, float2 (&x)[16], Hook hook) {
   Tw16 w;
   if constexpr (Tab::kEarly) tab.template load<LOGQ, 1, false>(w, t);
-  dft16_1<false, WINGS>(x);
+  dft16_1<false>(x);
   hook(0);
   write16(buf, t, x);
   __syncthreads();

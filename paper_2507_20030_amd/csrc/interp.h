@@ -62,19 +62,18 @@ constexpr int kHalo = 16;
 constexpr int grid_lds(int logN) { return fft_lds(logN) > (1 << logN) + 2 * kHalo ? fft_lds(logN) : (1 << logN) + 2 * kHalo; }
 
 // Grid of the samples x (wing_position; the others not looked at).  Entry m at buf[kHalo + m].  Entries beyond +-reach need not be formed.
-template <int LOGN, typename Hook>
-__device__ __forceinline__ void grid_forward(float2* buf, const TabMem& tab, int t, float2 (&x)[16], int reach, Hook hook) {
+template <int LOGN>
+__device__ __forceinline__ void grid_forward(float2* buf, const TabMem& tab, int t, float2 (&x)[16], int reach) {
   constexpr int N = 1 << LOGN, T = fft_threads(LOGN), REM = fft_rem(LOGN), NP = fft_np(LOGN);
   constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
   Tw16 w;
   tab.load<LOGN, 1, false>(w, t);
   dft16_1<false, true>(x);
-  hook(0);
   write16(buf, t, x);
   __syncthreads();
   constexpr int kLast = REM ? NP - 1 : NP - 2;  // last radix-16 pass that stays in place
-  if constexpr (kLast >= 1) fft_pass<LOGN, 1, false, (NP > 2 ? 2 : -1)>(buf, tab, t, w, [&] { hook(1); });
-  if constexpr (kLast >= 2) fft_pass<LOGN, 2, false, -1>(buf, tab, t, w, [&] { hook(2); });
+  if constexpr (kLast >= 1) fft_pass<LOGN, 1, false, (NP > 2 ? 2 : -1)>(buf, tab, t, w, [] {});
+  if constexpr (kLast >= 2) fft_pass<LOGN, 2, false, -1>(buf, tab, t, w, [] {});
   static_assert(NP <= 3, "two passes in place at most");
   const float2* own = buf + fpad(t);  // entries t + T i at i * SP
 #pragma unroll

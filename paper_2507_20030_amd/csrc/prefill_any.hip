@@ -105,7 +105,7 @@ __global__ __launch_bounds__(fft_threads(LOGN), 4) void prefill_any_kernel(Param
         }
       };
       fetch_bins(pin_index(t));
-      grid_forward<LOGN>(buf, tab, t, x, reach, [](int) {});
+      grid_forward<LOGN>(buf, tab, t, x, reach);
       fetch_dec();
       float2* F0 = F + (int64_t)(2 * p) * L.Bp;
       for (int i0 = t; i0 < L.nb; i0 += U * T) {
@@ -157,7 +157,7 @@ static hipError_t launch_prefill_any_t(const Params& P, const void* K, const voi
   constexpr int kNp = BF16 ? 4 : 2;
   const int logN = P.any_logN;
   const int max_slots = kCusPerXcd << (kTabMaxLogQ - logN);  // workgroups that an XCD holds at once
-  // one pair per item where the device would not be full with several; 1024 points only come with few slices (see the plan)
+  // one pair per item where the device would not be full with several, and on grids of 1024 points
   const bool few = logN == 10 || (int64_t)per_xcd * (kHeadDim / 2 / kNp) < max_slots;
 #define IWDFT_PA_LAUNCH(LN, NP)                                                                                  \
   {                                                                                                              \
