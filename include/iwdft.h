@@ -79,8 +79,10 @@ enum {
                                        with 384 or more kept bins in some layer, or with
                                        IWDFT_FLAG_FFT_PREFILL, the smaller one has the
                                        fp32 rounding of the larger one, and a value that
-                                       is not finite reaches both.  Otherwise, and in the
-                                       prefill of other M, each is as exact as alone.  All
+                                       is not finite reaches both.  Otherwise, in the
+                                       prefill of other M, and where M = 2^m >= 16384 keeps
+                                       low frequencies only and is decimated first (in 64
+                                       bits), each is as exact as alone.  All
                                        transforms of this library (attention,
                                        reconstruction and ablation too) hold sums up to
                                        2^97: values times their number's square root,
@@ -107,8 +109,10 @@ enum {
                                        heads in all, more than 1024 kept bins in some layer, 4 or 8 query
                                        heads per pass) walk the slices in groups and put the transforms
                                        of one group into the same launches as the K-coefficient stream of
-                                       the next, except where all kept bins lie below a quarter of M / 4
-                                       (the softmax then runs on a shorter grid, by itself).  Same arithmetic, same results bit for bit.          */
+                                       the next, except where the softmax runs on a
+                                       shorter grid, by itself (M <= 262144 and no kept bin
+                                       of any layer above min(M / 16, 4096)).  Same
+                                       arithmetic, same results bit for bit.               */
 };
 
 typedef struct {
@@ -168,7 +172,8 @@ int iwdft_prefill_kind(const iwdft_ctx* ctx);
 /* Which synthesis compressed_decode_attn / iwdft_append_attn run for this context: 1 = scores and softmax
  * weights through in-LDS FFTs (M = 2^m >= 256: O(M log M) per query head, the HBM-bound path; layers with more than
  * 4096 kept bins run a form of it that keeps nothing per bin in registers, contexts of M >= 16384 that keep low frequencies
- * only one on a shorter grid); 2 = through transforms interpolated from a power-of-two grid (256 <= M <= 8192) or chirp-z transforms (any
+ * only (see IWDFT_FLAG_SERIAL_PHASES) one on a shorter grid); 2 = through transforms interpolated from a power-of-two grid (2048 < M < 8192 where every kept
+ * frequency, k or M - k, lies below a quarter of the next power of two) or chirp-z transforms (any
  * other M >= 32 that is at most 8192 or has a divisor Pb <= 256 with 32 <= M / Pb <= 8192, e.g. M = context - sink -
  * recent = 16384 - 60 = 2 * 8162: O(M log M) as well, 2 to 4 times the arithmetic of 1); 0 = the direct O(M |B|)
  * sums (arithmetic-bound; chosen by IWDFT_FLAG_DIRECT_SYNTHESIS, for M < 32, and for M > 8192 without such a divisor,
@@ -226,7 +231,8 @@ int compressed_decode_attn(iwdft_ctx* ctx, const void* d_q, void* d_out, float s
  * (Bp_l = kept bins of layer l rounded up to 32) + 4 * n_layers * batch * n_q_heads * (S + R) bytes, each part
  * rounded up to 256 (+ 4 * M bytes per query head with the direct synthesis).  All calls on one GPU share that
  * GPU's array: calls that overlap in time on one GPU (different streams or contexts) race; calls ordered on one
- * stream do not.  Nothing in the array needs to survive between calls. */
+ * stream do not.  Nothing in the array needs to survive between calls.  The tables that iwdft_create has placed in the
+ * workspace are read all the same. */
 #define IWDFT_STATIC_SCRATCH_BYTES (64u << 20)
 int compressed_decode_attn_static(iwdft_ctx* ctx, const void* d_q, void* d_out, float scale,
                                   void* hip_stream);
