@@ -223,10 +223,12 @@ def iwdft_flush(ctx, stream=None) -> None:
 
 
 def iwdft_prefill_kind(ctx) -> str:
+    """"chirp" stands for all lengths that are no power of two: their prefill is interpolated from power-of-two transforms."""
     return {0: "dense", 1: "fft", 2: "chirp"}[load_library().iwdft_prefill_kind(ctx)]
 
 
 def iwdft_attn_kind(ctx) -> str:
+    """"chirp" stands for all lengths that are no power of two: chirp-z transforms or transforms interpolated from a power-of-two grid."""
     return {0: "direct", 1: "fft", 2: "chirp"}[load_library().iwdft_attn_kind(ctx)]
 
 

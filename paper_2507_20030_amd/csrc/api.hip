@@ -631,7 +631,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
         if (e == hipSuccess) e = make_taps((float*)(c->ws + pl.off_grid), gw.N, desc->M, (double)gw.N / (double)desc->M, gw);
       }
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // the tables above
+    if (e == hipSuccess && (pl.use_chirp || pl.dec_logN || pl.low_logN)) e = hipStreamSynchronize(nullptr);  // the tables above
     const float2* tab = nullptr;
     if (e == hipSuccess) e = fft_table(&tab);
     if (e != hipSuccess) {
