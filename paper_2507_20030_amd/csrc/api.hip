@@ -271,10 +271,10 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
       if (pl->use_fft && !mirrored) pl->low_logN = logN;
     }
     // Prefill through that grid (decimate.hip) where it is faster than the transforms of the tokens.  us without / with, 64 slices: 16 tokens
-    // per grid point, M = 131072, 2048 bins bf16 2164 / 1686, fp32 3795 / 2370; 8, M = 131072, 4096 bins 4171 / 2273, 4183 / 3057; 8,
-    // M = 65536, 2048 bins 1102 / 1070, 1880 / 1535; 4, M = 65536, 4096 bins 2147 / 1707, 2092 / 2107; M = 32768, 2048 bins 608 / 787,
+    // per grid point, M = 131072, 2048 bins bf16 2131 / 1564, fp32 3816 / 2274; 8, M = 131072, 4096 bins 4163 / 2123, 4145 / 2884; 8,
+    // M = 65536, 2048 bins 1145 / 997, 1857 / 1452; 4, M = 65536, 4096 bins 2147 / 1629, 2095 / 1985; M = 32768, 2048 bins 608 / 787,
     // 937 / 988.  Grids of 4096 points have too few waves below 16 slices (M = 32768, 1024 bins, 8 slices 67 / 85, 120 / 101; 64
-    // slices 578 / 521, 930 / 752); there four tokens per point gain in fp32 only (M = 16384, 1024 bins, 64 slices 308 / 385, 494 / 482).
+    // slices 581 / 493, 930 / 715); there four tokens per point gain in fp32 only (M = 16384, 1024 bins, 64 slices 308 / 385, 494 / 482).
     const int64_t D = d->M >> logN;
     const bool dec = D >= 8 ? logN > kLowMinLogN || S >= 16 : D == 4 && (logN == kLowMaxLogN || (logN == kLowMinLogN && !b16 && S >= 32));
     if (logN <= kLowMaxLogN && dec && pl->use_fft_prefill) {

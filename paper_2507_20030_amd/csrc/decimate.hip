@@ -15,21 +15,21 @@ namespace iwdft {
 namespace {
 
 constexpr int kDecThreads = 256, kDecRun = 64;  // grid points of a wave
-constexpr int kDecTile = 8, kDecPitch = kDecTile + 1;  // grid points of a channel that leave together, 64 bytes; padding: distinct banks
+constexpr int kDecTile = 16, kDecPitch = kDecTile + 1;  // grid points of a channel that leave together, a whole line; padding: distinct banks
 typedef const __attribute__((address_space(4))) double* ScalarDoubles;
 
 // A wave forms kDecRun grid points of 64 channels of one (slice, tensor), one channel a lane; token q D + d counts for the grid points
 // q - 4 .. q + 5, whose sums are a window of ten registers that a loop unrolled ten times shifts by renaming.  The weights are wave-uniform
 // and come through scalar loads, which the products of a token and the other waves cover.  y: [slice of the launch, tensor][channel][N].
-// What bounds it is the vector ALU (66 % of the wave cycles of four waves per SIMD; ten products a token and channel, 14 % of them for the runs'
-// ends) beside HBM: 4 slices of 131072 tokens, K and V, bf16: 97 us, 0.27 GB read and 0.13 written.  Two channels a lane:
-// 2440 us for 64 slices with the transforms against 2370, plain loads in place of non-temporal ones 2370 against 2310, twice the slices per launch,
-// whose grids no longer fit the memory-side cache, 2580.
+// What bounds it is the vector ALU (82 % of the wave cycles of four waves per SIMD; ten products a token and channel, 14 % of them for the runs'
+// ends) beside HBM: 4 slices of 131072 tokens, K and V, bf16: 87 us, 0.31 GB read and 0.13 written.  64 slices with the transforms: two
+// channels a lane 2440 us against 2370, plain loads 2370 against 2310 with non-temporal ones, 64 bytes of a channel at a time and two steps in
+// flight 2300 against 2210, twice the slices per launch, whose grids no longer fit the memory-side cache, 2580 against 2370.
 template <bool BF16, int D>
 __global__ __launch_bounds__(kDecThreads, 4) void decimate_kernel(Params P, const void* __restrict__ K, const void* __restrict__ V,
                                                                  int slice0, int slices) {
   constexpr int kElem = BF16 ? 2 : 4, kRow = kHeadDim * kElem;
-  constexpr int kAhead = D >= 16 ? 1 : D == 8 ? 2 : 5;  // steps of D tokens in flight; a divisor of 10
+  constexpr int kAhead = D >= 16 ? 2 : 5;  // steps of D tokens in flight; a divisor of 10
   static_assert(kDecTaps == 10 && kDecRun % kDecTile == 0, "");
   __shared__ double tiles[kDecThreads / 64][64 * kDecPitch];
   const uint32_t M = P.M, N = M / D, runs = N / kDecRun;
@@ -93,10 +93,11 @@ __global__ __launch_bounds__(kDecThreads, 4) void decimate_kernel(Params P, cons
       if (o >= 0) tile[lane * kDecPitch + (o & (kDecTile - 1))] = acc[u];
       acc[u] = 0.0;
       if (o >= 0 && (o & (kDecTile - 1)) == kDecTile - 1) {
-        const int c0 = lane >> 2, m = (lane & 3) * 2;
+        constexpr int kLanes = kDecTile / 2;
+        const int c0 = lane / kLanes, m = (lane & (kLanes - 1)) * 2;
         double* y = Y + (int64_t)c0 * N + (o - (kDecTile - 1)) + m;
 #pragma unroll
-        for (int c = 0; c < 64; c += 16) {
+        for (int c = 0; c < 64; c += 64 / kLanes) {
           const double* t = tile + (c0 + c) * kDecPitch + m;
           *(double2*)(y + (int64_t)c * N) = make_double2(t[0], t[1]);
         }
@@ -158,8 +159,8 @@ __device__ __forceinline__ int lpad(int i) { return i + (i >> 4); }  // 16-byte 
 //   2 Y[k] = Z[k] + conj Z[-k] - j e^{-j 2 pi k / N} (Z[k] - conj Z[-k]).
 // A persistent workgroup of C / 16 threads walks the (slice, tensor, channel) rows; the next row is fetched under the current one.
 // Twiddles are the powers of one table entry a pass.  What bounds it: waits (three quarters of the wave cycles) of the one workgroup that the LDS of
-// a CU holds; vector ALU 18 us, LDS 12 and memory 28 of 58 us for 1024 rows of 16384 points.
-// 8 x 8 slices of 131072 tokens, 4096 bins, bf16, with the decimation: 4170 us (sixteen 8192-point transforms per channel pair) -> 2310.
+// a CU holds; vector ALU 18 us, LDS 12 and memory 28 of 51 us for 1024 rows of 16384 points.
+// 8 x 8 slices of 131072 tokens, 4096 bins, bf16, with the decimation: 4170 us (sixteen 8192-point transforms per channel pair) -> 2210.
 constexpr int low_threads(int logN) { return 1 << (logN - 5); }
 constexpr int low_lds(int logN) { return ((1 << (logN - 1)) + (1 << (logN - 5))) * (int)sizeof(double2); }
 template <int LOGN>
