@@ -1372,6 +1372,36 @@ def test_fft_prefill_keeps_the_precision_of_a_small_channel_next_to_a_large_one(
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,n_bins,heads", [(32768, 800, 16), (65536, 4000, 1), (65536, 2048, 2), (131072, 1000, 1)])
+def test_decimated_prefill_keeps_every_channel_alone(dtype, L, n_bins, heads):
+    """Low bins of long contexts, grids of 4096 to 16384 points: every channel goes through transforms of its own in 64 bits, however large or
+    small its neighbours are, zero stays zero, and one that is not finite reaches no other.  Bar: rounding of the result, 2^-25 per part."""
+    cfg = small_cfg(L=L, n_bins=n_bins, dtype=dtype, n_layers=1, batch=1, n_kv_heads=heads)
+    bins = [np.arange(n_bins, dtype=np.int32)]
+    K, V = wl.prefill_tensors(cfg, DEV)
+    K[..., 0::4] *= 2.0 ** 40
+    K[..., 3::4] *= 2.0 ** -40
+    K[..., L // 2:, 9] = 0.0
+    V[..., 1] = 0.0
+    V[..., 100, 6] = float("inf")
+    V[..., L - 1, 11] = float("nan")
+    V[..., 8, 20:22] = float("-inf")
+    c = make_cache(cfg, bins)
+    assert B.iwdft_prefill_kind(c.ctx) == "fft"
+    c.prefill(K, V)
+    for name, X, got in zip("KV", (K, V), c.export_coeffs(0)):
+        ref = torch.fft.fft(X[0, 0, -1].cpu().double().nan_to_num(0.0, 0.0, 0.0).T.contiguous(), dim=1)[:, :n_bins] / L
+        g = got[0, -1].cpu().to(torch.complex128)
+        g = g if g.shape == ref.shape else g.T
+        for ch in range(128):
+            if name == "V" and ch in (6, 11, 20, 21):
+                assert not torch.isfinite(g[ch].abs()).any(), ch
+            else:
+                assert float((g[ch] - ref[ch]).norm()) <= 2.0 ** -24 * float(ref[ch].norm()), (name, ch)
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,n_bins,batch", [(256, 100, 34), (512, 300, 17), (1024, 600, 25), (2048, 700, 5), (4096, 2100, 3),
                                             (8192, 900, 2), (16384, 2000, 2)])
 def test_reconstruct_several_channel_pairs_per_store(dtype, L, n_bins, batch):
