@@ -250,8 +250,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     pl->use_any_prefill = S * points <= kAnyPrefillPoints[b16 ? 0 : 1][pl->chirp_logN > 12 ? 1 : 0] * d->M * rounds;
   }
 
-  // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144:
-  // 0.42 to 1.0 of the time; two tokens: M = 16384 1.00 .. 1.08, M = 32768 0.95 .. 1.0) and with 4096 points at least: what few threads
+  // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only
+  // step of 8 .. 1024 slices, 1 to 8 heads, M = 16384 .. 262144: 0.42 to 1.0 of the time; two tokens: M = 16384 1.00 .. 1.08, M = 32768 0.95 .. 1.0) and with 4096 points at least: what few threads
   // save in transforms they lose in the chain over the tokens of each (M = 16384, 256 bins, 8 slices, one head: 31 us without, 41 with
   // 1024 points).  Bins that are each other's mirror would share a slot.
   bool mirrored = false;

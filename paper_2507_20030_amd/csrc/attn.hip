@@ -585,7 +585,8 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
 
 // A value that all lanes share, in scalar registers.
 __device__ __forceinline__ float2 wave_uniform(float2 v) {
-  return make_float2(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.x))), __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.y))));
+  return make_float2(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.x))),
+                     __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.y))));
 }
 
 // Scores at all M = D N tokens from the grid x (positions 16 t + m of the digit-reversed order) by interpolation, softmax, and the

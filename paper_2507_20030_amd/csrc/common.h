@@ -67,7 +67,8 @@ struct Params {
   const double2* dec_tw;
   const double* dec_gain;
   double* dec_scratch;
-  // Decode attention of contexts that keep low frequencies only (attn_low_kernel; tables in the workspace): grid of 2^low_logN points (0: not used), 1 / W of 0 .. 2^low_logN / 4 and
+  // Decode attention of contexts that keep low frequencies only (attn_low_kernel; tables in the workspace): grid of 2^low_logN points (0: not
+  // used), 1 / W of 0 .. 2^low_logN / 4 and
   // eight taps per token between two grid points.
   int32_t low_logN;
   const float* low_gain;

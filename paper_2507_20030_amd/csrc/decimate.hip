@@ -7,7 +7,7 @@
 // All of it is in 64 bits, which gfx950 issues at the rate of unpacked fp32.  The grid concentrates what the kept bins hold: a rounding of the
 // size of an offset or a strong tone is white over N points instead of M and 1 / W multiplies it, so that 32-bit sums
 // and transforms of the grid showed up to 10 times the error of 32-bit transforms of the tokens (bf16 tokens with an offset, whose sums
-// cancel exactly there, up to 100 times).  In 64 bits nothing is left but the rounding of the result.
+// cancel exactly there, up to 300 times).  In 64 bits nothing is left but the rounding of the result.
 #include "common.h"
 
 namespace iwdft {
