@@ -112,7 +112,11 @@ enum {
                                        the next, except where the softmax runs on a
                                        shorter grid, by itself (M <= 262144 and no kept bin
                                        of any layer above min(M / 16, 4096)).  Same
-                                       arithmetic, same results bit for bit.               */
+                                       arithmetic, same results bit for bit.  Short contexts (M = 2^m <= 4096,
+                                       no layer with more than M / 4 bins, no bin kept beside
+                                       its mirror, up to 8 query heads per KV head) run as one
+                                       launch where that is faster, equal up to rounding;
+                                       the flag keeps them to the three kernels.           */
 };
 
 typedef struct {
@@ -188,7 +192,8 @@ int iwdft_attn_kind(const iwdft_ctx* ctx);
  * the transforms of one group in the same launches as the K-coefficient stream of the next (see
  * IWDFT_FLAG_SERIAL_PHASES for the conditions): 1 = yes, 0 = the three kernels run one after the other;
  * -1 if ctx is NULL.  Results are identical either way; with 1 the marks of iwdft_phase_timing cannot separate
- * the first two kernels (their time is reported as phase 0, phase 1 reads ~0). */
+ * the first two kernels (their time is reported as phase 0, phase 1 reads ~0); nor can they for short contexts that run as
+ * one launch (all of it phase 0). */
 int iwdft_attn_pipelined(const iwdft_ctx* ctx);
 
 /* Streaming update with one new token per sequence (Eq. infi-dft, Eq. update-iwdft).

@@ -679,6 +679,8 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.FV = (float2*)(c->state + pl.off_FV);
     P.gain = 1.0f;
     P.x_scale = 1.0f;
+    P.one_fold = pl.use_fft && 4 * (int64_t)pl.max_Bp <= desc->M ? 1 : 0;
+    for (const LayerInfo& L : pl.layers) P.one_fold &= L.fold_rounds == 1;
     P.scale_pairs = pl.scale_pairs ? 1 : 0;
     P.serial_phases = (desc->flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : 0;
     P.S = desc->n_sink;

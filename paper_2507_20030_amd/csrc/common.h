@@ -82,6 +82,7 @@ struct Params {
   // absorbed token enters scaled by x_scale = M / (T + 1), and everything that reads the coefficients as the
   // paper's S_T (reconstruction, scores, outputs) applies the extra gain = T / M.
   float gain, x_scale;
+  int32_t one_fold;       // power-of-two attention: no two entries of a layer's spectrum share a slot, and no row has more than M / 4 bins
   int32_t scale_pairs;    // FFT prefill: channels of a pair scaled to one size
   int32_t serial_phases;  // IWDFT_FLAG_SERIAL_PHASES: never pipeline kernels A and B over groups of slices
   int32_t S, R;

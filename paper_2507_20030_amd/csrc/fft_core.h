@@ -373,6 +373,10 @@ __device__ __forceinline__ void fft_forward(float2* buf, const Tab& tab, int t, 
   if constexpr (fft_rem(LOGQ) >= 2 || (WIDE && fft_rem(LOGQ) == 1)) fft_wide<LOGQ, false>(buf, tab.tab, t);
 }
 
+// Workgroup barriers inside the two, for waves beside them that have no transform.
+constexpr int fft_inverse_barriers(int logQ) { return (fft_rem(logQ) >= 2) + (fft_np(logQ) - 1) + (fft_rem(logQ) == 1); }
+constexpr int fft_forward_barriers(int logQ) { return 1 + (fft_np(logQ) - 1) + (fft_rem(logQ) >= 2); }
+
 // The two transforms between signals of at most N / 2 points, for convolutions of length N = 2^LOGN (chirp.h): thread t holds
 // entries t + T i, i < 8, T = N / 16, in registers; the upper half of the inverse transform's input is zero, that of the
 // forward transform's output is not formed.  Neither needs a barrier in front as long as buf was last touched at these and

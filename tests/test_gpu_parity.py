@@ -424,6 +424,43 @@ def test_score_kernel_of_few_and_of_many_blocks(group, batch, heads, n_bins, J):
                slices=wl.sample_slices(cfg, 5))
 
 
+@pytest.mark.parametrize("L,group,n_bins,dims,S,R,J,dtype", [
+    (256, 1, 1, (2, 1, 1), 0, 0, 0, "f32"), (256, 8, 64, (2, 1, 4), 1, 0, 4, "bf16"),       # one bin; a full quarter, 16 lanes a transform
+    (512, 5, 33, (3, 2, 2), 3, 70, 0, "bf16"), (512, 2, 128, (2, 1, 4), 0, 9, 16, "f32"),     # more exact tokens than lanes; a last head pair with one head
+    (1024, 4, 65, (2, 2, 3), 0, 0, 16, "bf16"), (1024, 7, 129, (2, 8, 8), 2, 3, 5, "f32"),    # 64 and 128 lanes a row
+    (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16"), (2048, 8, 512, (2, 6, 8), 0, 2, 2, "bf16"),   # all lanes two rows of a head group
+    (4096, 4, 1023, (1, 12, 8), 2, 5, 4, "bf16"), (4096, 3, 900, (2, 8, 8), 0, 0, 0, "f32"),  # one row over all lanes
+    (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16"),  # states beyond 160 MiB: streaming accesses
+])
+def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
+    """One workgroup per slice (attn_slice.hip) against the oracle and against the three kernels, which IWDFT_FLAG_SERIAL_PHASES
+    keeps: masks up to M / 2 without shared slots, ragged rows, layers of different lengths, update and read-only steps.  Same sums in
+    another order: fp32 outputs agree to 1e-5 (scores of magnitude 50 times 2^-23), bf16 to one rounding (2^-8 of the largest)."""
+    cfg = small_cfg(L=L, group=group, dtype=dtype, n_bins=n_bins, n_layers=dims[0], batch=dims[1], n_kv_heads=dims[2], n_sink=S,
+                    n_recent=R, steps=6)
+    rng = np.random.default_rng(L + n_bins)
+    bins = [np.sort(rng.choice(L // 2 + 1, size=max(1, n_bins - 7 * (l % 3)), replace=False)).astype(np.int32) for l in range(dims[0])]
+    bins[0][0] = 0
+    run_stream(cfg, bins, fused=True, write_every=J, rec=(0, 16), tag=f"slice-L{L}-G{group}-B{n_bins}")
+    K, V = wl.prefill_tensors(cfg, DEV)
+    a, b = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins, flags=B.IWDFT_FLAG_SERIAL_PHASES, write_every=J)
+    a.prefill(K, V)
+    b.prefill(K, V)
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -8
+    for i in range(cfg.steps):
+        tk, tv, q = wl.decode_step(cfg, i, DEV)
+        for x, y in ((a.step(tk, tv, q), b.step(tk, tv, q)),) + (((a.attend(q), b.attend(q)),) if i == 4 else ()):
+            assert torch.isfinite(x.float()).all()
+            assert float((x.float() - y.float()).abs().max()) <= tol * float(y.float().abs().max()), f"step {i}"
+    a.flush()
+    b.flush()
+    for l in range(dims[0]):
+        for x, y in zip(a.export_coeffs(l), b.export_coeffs(l)):
+            assert float((x - y).abs().max()) <= 1e-6 * float(y.abs().max())
+    a.close()
+    b.close()
+
+
 def test_deferred_write_back_mixed_with_other_calls():
     # any call other than the fused step first writes the deferred tokens back: a random mix of calls
     # gives, step for step, what the oracle gives
