@@ -115,8 +115,10 @@ enum {
                                        arithmetic, same results bit for bit.  Short contexts (M = 2^m <= 4096,
                                        no layer with more than M / 4 bins, no bin kept beside
                                        its mirror, up to 8 query heads per KV head) run as one
-                                       launch where that is faster, equal up to rounding;
-                                       the flag keeps them to the three kernels.           */
+                                       launch where that is faster, and several workgroups
+                                       share the softmax of few slices of a long context
+                                       (M > 8192), both equal up to rounding; the flag keeps
+                                       them to the three kernels.                          */
 };
 
 typedef struct {

@@ -13,6 +13,7 @@
 
 #include "../../include/iwdft.h"
 #include "common.h"
+#include "fft_core.h"
 #include "fft_tab.h"
 #include "tables.h"
 
@@ -68,6 +69,8 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
   size_t off_layers = 0, off_bins = 0, off_weights = 0, off_fold = 0, off_FK = 0, off_FV = 0, state_bytes = 0;
   size_t off_sinkK = 0, off_sinkV = 0, off_ringK = 0, off_ringV = 0;
+  int parts = 1;                 // workgroups per pair of query heads in the softmax (attn_parts.hip)
+  size_t off_parts = 0, off_stats = 0;
   size_t off_qc = 0, off_Pn = 0, off_pe = 0, off_pendK = 0, off_pendV = 0, off_ps = 0, off_direct = 0, ws_bytes = 0;
 };
 
@@ -89,9 +92,55 @@ constexpr int kLowMinLogN = 12, kLowMaxLogN = 14;  // grids of prefill and decod
 constexpr int64_t kLowMinD = 4, kLowMaxD = 16;     // ... tokens per grid point
 constexpr int64_t kGridMinM = 2048;
 constexpr int64_t kDecScratch = (int64_t)128 << 20;  // bytes of the grids of a group of slices: they fit the memory-side cache
+constexpr int kCus = 256;
+constexpr int64_t kPartBytes = (int64_t)64 << 20;  // most bytes of the rows that the parts of a softmax leave
 constexpr uint64_t kDirectMaxTerms = 1ull << 30;  // most M * |B| the direct sums are chosen for without being asked
 
 constexpr int64_t tap_floats(int taps) { return taps > 8 ? 12 : 10; }  // of one point (interp.h, load_taps)
+
+// Workgroups per pair of query heads in the softmax: where one each leaves the chip idle they share the blocks of a long context (low
+// frequencies: the tokens behind every grid point), as many as the device holds at a time.  What they save in blocks they pay with the launch of
+// attn_merge_kernel and its trip over their rows.  Decode step, 16 deferred, one workgroup / shared, us: two blocks (M = 16384), 16 pairs of heads
+// 48.7 / 45.8, 64 63.8 / 62.1, 128 132.8 / 138.2; more blocks, M = 65536, 4096 bins, 32 pairs 146 / 89, 128 283 / 252; M = 131072, 1500 bins, 64 pairs
+// 199 / 93, 256 242 / 215; chirp-z, M = 32708, 2040 bins, 32 pairs 160 / 83, 96 219 / 164; M = 25419 (37 blocks of 687), 20 pairs 3882 / 1183.
+// Low frequencies repeat the two transforms in every part: grids of 16384 points, M = 131072, 16 pairs 109 / 95, 64 134 / 120, two parts for 128
+// pairs 268 / 268; shorter grids slow down beside each other: 8192 points, M = 65536, 8 pairs 59 / 53, 504 workgroups for 72 pairs 106 / 111;
+// 4096 points, M = 65536, 8 pairs 49 / 39; four tokens per grid point gain on 16384 points only (M = 32768, 8 pairs 50 / 50, 32 64 / 64).
+int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws) {
+  int64_t units, slots, least = 2;  // what can be shared out, workgroups at a time, fewest parts that pay
+  if (pl.use_fft && M > kFftMaxQ) {
+    const int per_thread = (pl.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
+    if (pl.low_logN) {
+      units = M >> pl.low_logN;
+      slots = pl.low_logN < kLowMaxLogN || units < 8 ? kCus / 2 : kCus;
+      least = 3;
+      if (units < 8 && pl.low_logN < kLowMaxLogN) return 1;
+    } else {
+      units = M / kFftMaxQ;
+      slots = units == 2 ? kCus / 2 : per_thread > 4 && per_thread <= 8 ? kCus : 2 * kCus;
+    }
+  } else if (pl.use_chirp && M > pl.chirp_Q) {
+    units = M / pl.chirp_Q;
+    slots = (int64_t)kCus << std::min(kTabMaxLogQ - pl.chirp_logN, 4);
+  } else {
+    return 1;
+  }
+  const int64_t room = kPartBytes / (int64_t)(sizeof(float2) * (size_t)ws);
+  const int64_t n = std::min(std::min(units, room), std::min<int64_t>(slots / (slices * ((pl.G + 1) / 2)), kMaxParts));
+  if (n < least) return 1;
+  const int64_t share = (units + n - 1) / n;
+  return (int)((units + share - 1) / share);  // no more than the longest share asks for
+}
+size_t stats_bytes(const Plan& pl, int64_t slices) { return sizeof(float4) * (size_t)(slices * ((pl.G + 1) / 2) * pl.parts); }
+// The parts' buffers at `rows` and `stats`.
+Parts parts_at(const Plan& pl, char* rows, char* stats) {
+  Parts p;
+  p.n = pl.parts;
+  p.stride = pl.ws_total;
+  p.rows = (float2*)rows;
+  p.stats = (float4*)stats;
+  return p;
+}
 
 int make_plan(const iwdft_desc* d, Plan* pl) {
   if (!d) return fail(IWDFT_ERR_ARG, "desc is NULL");
@@ -301,6 +350,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
                 "divisor (e.g. move tokens to the sink / recent windows) or pass IWDFT_FLAG_DIRECT_SYNTHESIS to insist",
                 (long long)d->M, pl->max_nb, (int)kChirpMaxBlocks, (int)kChirpMaxM);
 
+  pl->parts = (d->flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : softmax_parts(*pl, d->M, S, ws);
+
   size_t o = 0;
   pl->off_layers = o;  o = align256(o + sizeof(LayerInfo) * (size_t)d->n_layers);
   pl->off_bins = o;    o = align256(o + sizeof(int32_t) * (size_t)pl->n_bins_total);
@@ -343,6 +394,10 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
   pl->off_dec = o;   o = align256(o + (pl->use_chirp ? sizeof(float) * ((size_t)1 << pl->chirp_logN) / 2 : 0));
   pl->off_taps = o;  o = align256(o + (pl->use_chirp ? sizeof(float) * tap_floats(d->M > pl->chirp_Q ? kSumTaps : kTaps) * ((size_t)pl->chirp_Q / 2 + 1) : 0));
+  if (pl->parts > 1) {
+    pl->off_parts = o; o = align256(o + sizeof(float2) * (size_t)ws * (size_t)pl->parts);
+    pl->off_stats = o; o = align256(o + stats_bytes(*pl, (int64_t)n_sl));
+  }
   pl->off_direct = o;
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
@@ -862,7 +917,8 @@ int compressed_decode_attn(iwdft_ctx* ctx, const void* d_q, void* d_out, float s
   return launched(launch_attn(ctx->P, d_q, d_out, scale, (float2*)(ctx->ws + pl.off_qc),
                               (float2*)(ctx->ws + pl.off_Pn), (float*)(ctx->ws + pl.off_pe),
                               (float*)(ctx->ws + pl.off_direct),
-                              pl.use_fft, marks, (hipStream_t)hip_stream),
+                              pl.use_fft, parts_at(pl, ctx->ws + pl.off_parts, ctx->ws + pl.off_stats), marks,
+                              (hipStream_t)hip_stream),
                   "decode attention launch");
 }
 
@@ -884,14 +940,19 @@ int compressed_decode_attn_static(iwdft_ctx* ctx, const void* d_q, void* d_out, 
   if (need > kStaticScratchBytes)
     return fail(IWDFT_ERR_SIZE, "compressed_decode_attn_static needs %zu bytes of scratch, the library holds %zu", need,
                 kStaticScratchBytes);
+  // ... and the parts of the softmax; where they do not fit, one workgroup per pair of heads does all of it (equal up to rounding).
+  Parts parts;
+  const size_t part_bytes = align256(sizeof(float2) * (size_t)pl.ws_total * (size_t)pl.parts);
+  const bool split = pl.parts > 1 && need + part_bytes + stats_bytes(pl, ctx->P.n_slices) <= kStaticScratchBytes;
   char* sc = nullptr;
   if ((rc = static_scratch(ctx->device, &sc)) != IWDFT_OK) return rc;
   if ((rc = flush_pending(ctx, (hipStream_t)hip_stream)) != IWDFT_OK) return rc;
   set_read_gain(ctx);
-  // Every entry of the four arrays is written by the kernels before it is read, so nothing needs clearing
+  if (split) parts = parts_at(pl, sc + need, sc + need + part_bytes);
+  // Every entry of the arrays is written by the kernels before it is read, so nothing needs clearing
   // although the scratch still holds the previous call's contents.
   return launched(launch_attn(ctx->P, d_q, d_out, scale, (float2*)sc, (float2*)(sc + rows), (float*)(sc + 2 * rows),
-                              (float*)(sc + 2 * rows + pe_bytes), pl.use_fft, nullptr, (hipStream_t)hip_stream),
+                              (float*)(sc + 2 * rows + pe_bytes), pl.use_fft, parts, nullptr, (hipStream_t)hip_stream),
                   "decode attention launch (static scratch)");
 }
 
@@ -920,7 +981,8 @@ int iwdft_append_attn(iwdft_ctx* ctx, const void* d_tok_k, const void* d_tok_v, 
                             (float2*)(ctx->ws + pl.off_Pn), (float*)(ctx->ws + pl.off_pe),
                             ctx->ws + pl.off_pendK, ctx->ws + pl.off_pendV, (float*)(ctx->ws + pl.off_ps),
                             (float*)(ctx->ws + pl.off_direct), pl.use_fft, tsh0, ring_pos, ctx->pend,
-                            pl.write_every, marks, (hipStream_t)hip_stream),
+                            pl.write_every, parts_at(pl, ctx->ws + pl.off_parts, ctx->ws + pl.off_stats), marks,
+                            (hipStream_t)hip_stream),
                 "fused decode step launch");
   if (rc != IWDFT_OK) return rc;
   ctx->pend = (ctx->pend + 1) % pl.write_every;  // back to 0: this step wrote the coefficients

@@ -445,9 +445,10 @@ __device__ __forceinline__ float2 wave_uniform(float2 v) {
 // come in without their mean (the caller's bin 0), and what is folded back is e^s - level, the weight that a token at the mean has; the
 // caller adds M level to bin 0.  Error against 64 bits, M = 65536, 1000 bins, flat scores 1.5e-7 -> 1.1e-7, beside a mean of 19 3.0e-7 ->
 // 1.0e-7 (attn_fft_kernel: 1.4e-7, 1.6e-7), for two subtractions a token: a decode step of 32 x 8 slices of 131072 tokens 525 -> 530 us.
+// Tokens m D + d_lo .. m D + d_hi - 1 enter the sums; the maximum is that of all tokens.
 template <int LOGN>
-__device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const float* __restrict__ taps, int t, bool has1,
-                                            float2 (&x)[16], float2& mx, float2& Z, float2& f, float2& level) {
+__device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const float* __restrict__ taps, int t, int d_lo,
+                                            int d_hi, bool has1, float2 (&x)[16], float2& mx, float2& Z, float2& f, float2& level) {
   constexpr int N = 1 << LOGN, T = fft_threads(LOGN), NWV = T / 64;
   static_assert(T >= 64, "whole waves");
   __shared__ float4 lmax[NWV];
@@ -519,7 +520,7 @@ __device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const 
 #pragma unroll
   for (int j = 0; j < 23; ++j) z[j] = make_float2(0.f, 0.f);
 #pragma unroll 1
-  for (int d = 0; d < D; ++d) {
+  for (int d = d_lo; d < d_hi; ++d) {
     float w[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = taps[8 * d + i];
@@ -561,12 +562,14 @@ __device__ __forceinline__ void low_softmax(const Params& P, float2* buf, const 
 // thread's NBT bins in registers, or (NBT = 0, more than 4096 kept bins) in the output rows themselves -- every bin belongs
 // to one thread, which reads back its own earlier store.
 // LOW: low frequencies only (see attn_low_kernel): one transform of a grid that carries them, low_softmax between it and the tokens.
+// PART: `parts.n` workgroups per pair of heads take their share of the blocks (LOW: of the tokens behind every grid point) each and leave
+// sums that are not normalised, see attn_parts.hip.
 // The work of logical block `bid` (wave-uniform); buf: fft_lds(LOGQ) float2.
-template <int LOGQ, int NBT, bool MULTI, bool LOW = false>
+template <int LOGQ, int NBT, bool MULTI, bool LOW = false, bool PART = false>
 __device__ __forceinline__ void fft_body(const Params& P, const float2* __restrict__ qc, float2* __restrict__ Pn,
                                          float* __restrict__ pe, float scale, int pairs, int np, uint32_t ptsh,
                                          float* __restrict__ ps, uint32_t bid, float2* buf,
-                                         const float* __restrict__ taps = nullptr) {
+                                         const float* __restrict__ taps = nullptr, const Parts& parts = Parts{}) {
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), TB = attn_threads(LOGQ), NWV = TB / 64;
   constexpr bool kRegs = MULTI && NBT > 0;  // running sums in registers
   constexpr bool kKeep = kRegs && NBT > 4;  // with the register budget of one workgroup per CU: the inputs stay as well
@@ -577,8 +580,9 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   __shared__ float pscr[NWV][2 * kMaxPend];
   const TabMem tab{P.tab + tab_base(LOGQ)};
   const int t = threadIdx.x, tx = t & (T - 1);  // TB > T: lanes T .. 63 run lane tx's part of the transforms beside it
-  const int pair = bid % pairs;
-  const int slice = bid / pairs;
+  const uint32_t pid = PART ? bid / (uint32_t)parts.n : bid, part = PART ? bid - pid * (uint32_t)parts.n : 0u;
+  const int pair = pid % pairs;
+  const int slice = pid / pairs;
   const int spl = P.batch * P.n_kv;
   const int layer = slice / spl;
   const int s = slice - layer * spl;
@@ -588,7 +592,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
   const uint32_t Pb = MULTI ? (P.M >> LOGQ) : 1u;
   const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   const float2* q1 = has1 ? q0 + L.Bp : q0;
-  float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
+  float2* o0 = (PART ? parts.rows + (int64_t)part * parts.stride : Pn) + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   float2* o1 = o0 + L.Bp;  // written only if has1
   const int32_t* bins = P.bins + L.bin_off;
   const float* wts = P.weights + L.bin_off;
@@ -612,7 +616,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
 
   // Exact tokens open the online softmax: their raw scores q . k_e come from kernel A.
   float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);  // Z: this thread's share
-  const int E = P.S + P.R;
+  const int E = PART ? 0 : P.S + P.R;
   float* pe0 = pe + ((int64_t)slice * P.G + g0) * E;
   float* pe1 = pe0 + E;
   const float escale = 1.44269504088896341f * scale;  // scores live in log2 units (exp2 softmax)
@@ -725,7 +729,12 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     load_tw();
   }
 
-  for (uint32_t b = 0; b < Pb; ++b) {
+  const uint32_t b_lo = PART && MULTI ? part * Pb / (uint32_t)parts.n : 0u;
+  const uint32_t b_hi = PART && MULTI ? (part + 1) * Pb / (uint32_t)parts.n : Pb;
+  // LOW: tokens d_lo .. d_hi - 1 behind every grid point
+  const int D = LOW ? (int)(P.M >> LOGQ) : 0;
+  const int d_lo = PART && LOW ? (int)part * D / parts.n : 0, d_hi = PART && LOW ? ((int)part + 1) * D / parts.n : D;
+  for (uint32_t b = b_lo; b < b_hi; ++b) {
     // The thread index is made opaque per iteration so that the address arithmetic of the transforms is recomputed (a few
     // instructions) instead of being hoisted out of the block loop into long-lived registers.
     int lt = t;
@@ -783,7 +792,7 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
       float2 mean = make_float2(0.f, 0.f);  // of the scores: bin 0, which the spectrum above leaves out
       if (bins[0] == 0) mean = wave_uniform(make_float2(2.f * gain * wts[0] * q0[0].x, has1 ? 2.f * gain * wts[0] * q1[0].x : 0.f));
       mx = csub(mx, mean);
-      low_softmax<LOGQ>(P, buf, taps, lx, has1, x, mx, Z, f, level);
+      low_softmax<LOGQ>(P, buf, taps, lx, d_lo, d_hi, has1, x, mx, Z, f, level);
       mx = cadd(mx, mean);
     } else {
     float2 lm = x[0];
@@ -828,8 +837,9 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
         p0 = make_float2(g * p0.x, g * p0.y);
         p1 = make_float2(g * p1.x, g * p1.y);
         if (kj[j] == 0) {
-          p0.x = fmaf((float)P.M, level.x, p0.x);
-          p1.x = fmaf((float)P.M, level.y, p1.x);
+          const float tokens = PART ? (float)((uint32_t)(d_hi - d_lo) << LOGQ) : (float)P.M;
+          p0.x = fmaf(tokens, level.x, p0.x);
+          p1.x = fmaf(tokens, level.y, p1.x);
         }
       }
       if constexpr (MULTI) {
@@ -847,8 +857,8 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
         A1[j] = make_float2(fmaf(A1[j].x, f.y, p1.x), fmaf(A1[j].y, f.y, p1.y));
       }
     } else {
-      if constexpr (!MULTI) normalise();
-      const int n = MULTI ? L.nb : L.Bp;
+      if constexpr (!MULTI && !PART) normalise();
+      const int n = MULTI || PART ? L.nb : L.Bp;
       for (int i0 = lt; i0 < n; i0 += U * TB) {
         if (i0 >= U * TB) {
           fetch_bins(i0);
@@ -860,10 +870,10 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
           if (i >= n) continue;
           float2 p0, p1;
           gather(j, p0, p1);
-          if constexpr (!MULTI) {
+          if constexpr (!MULTI && !PART) {
             finish(i, kj[j], p0, p1);
           } else {
-            if (b) {  // this thread's own running sums, scaled to the new maximum
+            if (b > b_lo) {  // this thread's own running sums, scaled to the new maximum
               const float2 a0 = o0[i];
               p0 = make_float2(a0.x * f.x + p0.x, a0.y * f.x + p0.y);
               if (has1) {
@@ -880,6 +890,28 @@ __device__ __forceinline__ void fft_body(const Params& P, const float2* __restri
     if (MULTI) __syncthreads();
   }
 
+  if constexpr (PART) {
+    if constexpr (MULTI) {
+      publish_sum();
+      __syncthreads();
+    }
+    if (t == 0) {
+      float2 z = ssum[0];
+#pragma unroll
+      for (int w = 1; w < NWV; ++w) z = cadd(z, ssum[w]);
+      parts.stats[bid] = make_float4(mx.x, mx.y, z.x, z.y);
+    }
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int j = 0; j < NBT; ++j) {
+        const int i = j * TB + t;
+        if (i >= L.nb) continue;
+        o0[i] = A0[j];
+        if (has1) o1[i] = A1[j];
+      }
+    }
+    return;
+  }
   if constexpr (MULTI) {
     publish_sum();
     __syncthreads();
@@ -924,6 +956,13 @@ __global__ __launch_bounds__(attn_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_fft_
                                                                        float* __restrict__ ps) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
   fft_body<LOGQ, NBT, MULTI>(P, qc, Pn, pe, scale, pairs, np, ptsh, ps, blockIdx.x, smem);
+}
+// Several workgroups per pair of heads (attn_parts.hip); LOW: as attn_low_kernel.
+template <int LOGQ, int NBT, bool LOW>
+__global__ __launch_bounds__(attn_threads(LOGQ), NBT > 4 ? 2 : 4) void attn_part_kernel(Params P, const float2* __restrict__ qc,
+                                                                        float scale, int pairs, Parts parts) {
+  extern __shared__ __attribute__((aligned(16))) float2 smem[];
+  fft_body<LOGQ, NBT, !LOW, LOW, true>(P, qc, nullptr, nullptr, scale, pairs, 0, 0u, nullptr, blockIdx.x, smem, P.low_taps, parts);
 }
 
 // Long contexts that keep low frequencies only, |k| <= N / 4 on a grid of N = 2^LOGN points, D = M / N tokens apart: see low_softmax.
@@ -1076,7 +1115,7 @@ static int heads_per_pass(int G) { return G <= 2 ? G : (G <= 4 ? 4 : 8); }  // 1
 template <bool BF16>
 static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float scale, float2* qc,
                                 float2* Pn, float* pe, float* direct_scratch, bool use_fft,
-                                const StepUpdate* up, int mode, const PhaseEvents* marks, hipStream_t st) {
+                                const StepUpdate* up, int mode, const Parts& parts, const PhaseEvents* marks, hipStream_t st) {
   const int GT = heads_per_pass(P.G);
   const int passes = (P.G + GT - 1) / GT;
   const StepUpdate u = up ? *up : StepUpdate{nullptr, nullptr, 0, 0, 0, nullptr, nullptr, nullptr, -1};
@@ -1192,7 +1231,30 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     attn_fft_kernel<LQ, NBT, MULTI><<<dim3(gridB), dim3(attn_threads(LQ)), lds, st>>>(                     \
         P, qc, Pn, pe, scale, pairs, np_plain, u.tsh, u.ps);                                              \
   }
-    if (attn_is_low(P)) {
+#define IWDFT_PART_CASE(LQ, NBT, LOW)                                                                     \
+  {                                                                                                       \
+    constexpr int lds = (int)sizeof(float2) * fft_lds(LQ);                                                \
+    static LdsLimit lim;                                                                                  \
+    e = lim.ensure((const void*)attn_part_kernel<LQ, NBT, LOW>, lds);                                     \
+    if (e != hipSuccess) return e;                                                                        \
+    attn_part_kernel<LQ, NBT, LOW><<<dim3(gridB * (uint32_t)parts.n), dim3(attn_threads(LQ)), lds, st>>>( \
+        P, qc, scale, pairs, parts);                                                                      \
+  }
+    if (parts.n > 1) {
+      const int per_thread = (P.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
+      if (attn_is_low(P)) {
+        if (P.low_logN == 12) IWDFT_PART_CASE(12, 0, true)
+        else if (P.low_logN == 13) IWDFT_PART_CASE(13, 0, true)
+        else if (P.low_logN == 14) IWDFT_PART_CASE(14, 0, true)
+        else return hipErrorInvalidValue;
+      } else if (per_thread <= 2) IWDFT_PART_CASE(kFftMaxLogQ, 2, false)
+      else if (per_thread <= 4) IWDFT_PART_CASE(kFftMaxLogQ, 4, false)
+      else if (per_thread <= 8) IWDFT_PART_CASE(kFftMaxLogQ, 8, false)
+      else IWDFT_PART_CASE(kFftMaxLogQ, 0, false)
+      e = hipGetLastError();
+      if (e == hipSuccess) e = launch_merge(P, parts, Pn, pe, scale, np_plain, u.tsh, u.ps, st);
+      if (e != hipSuccess) return e;
+    } else if (attn_is_low(P)) {
 #define IWDFT_LOW_CASE(LN)                                                                                \
   case LN: {                                                                                              \
     constexpr int lds = (int)sizeof(float2) * fft_lds(LN);                                                \
@@ -1210,6 +1272,7 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
         default: return hipErrorInvalidValue;
       }
 #undef IWDFT_LOW_CASE
+#undef IWDFT_PART_CASE
     } else if (logM > logQ) {
       const int per_thread = (P.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
       if (per_thread <= 2) IWDFT_FFT_CASE(kFftMaxLogQ, 2, true)
@@ -1226,7 +1289,7 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
     }
 #undef IWDFT_FFT_CASE
   } else if (P.chirp) {
-    e = launch_attn_chirp(P, qc, Pn, pe, scale, np_plain, u.tsh, u.ps, st);
+    e = launch_attn_chirp(P, qc, Pn, pe, scale, np_plain, u.tsh, u.ps, parts, st);
     if (e != hipSuccess) return e;
   } else {
     attn_direct_kernel<<<dim3((uint32_t)gridBd), dim3(kDirThreads), 0, st>>>(P, qc, Pn, pe, scale, direct_scratch);
@@ -1252,11 +1315,11 @@ static hipError_t launch_attn_t(const Params& P, const void* q, void* out, float
 }
 
 hipError_t launch_attn(const Params& P, const void* q, void* out, float scale, float2* qc, float2* Pn,
-                       float* pe, float* direct_scratch, bool use_fft, const PhaseEvents* marks,
+                       float* pe, float* direct_scratch, bool use_fft, const Parts& parts, const PhaseEvents* marks,
                        hipStream_t st) {
   return P.kv_dtype == 1
-             ? launch_attn_t<true>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, nullptr, kPlain, marks, st)
-             : launch_attn_t<false>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, nullptr, kPlain, marks, st);
+             ? launch_attn_t<true>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, nullptr, kPlain, parts, marks, st)
+             : launch_attn_t<false>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, nullptr, kPlain, parts, marks, st);
 }
 
 bool heads_fit_one_pass(int G) { return (G + heads_per_pass(G) - 1) / heads_per_pass(G) == 1; }
@@ -1265,7 +1328,7 @@ bool step_can_fuse(const Params& P) { return heads_fit_one_pass(P.G); }
 hipError_t launch_step(const Params& P, const void* tok_k, const void* tok_v, const void* q, void* out,
                        float scale, float2* qc, float2* Pn, float* pe, void* pend_k, void* pend_v, float* ps,
                        float* direct_scratch, bool use_fft, uint32_t tsh0, uint32_t ring_pos, int pend_before,
-                       int write_every, const PhaseEvents* marks, hipStream_t st) {
+                       int write_every, const Parts& parts, const PhaseEvents* marks, hipStream_t st) {
   if (write_every < 1 || write_every > kMaxPend || pend_before < 0 || pend_before >= write_every)
     return hipErrorInvalidValue;
   StepUpdate up{tok_k, tok_v, kHeadDim, tsh0, pend_before + 1, ps, nullptr, nullptr, -1};
@@ -1279,8 +1342,8 @@ hipError_t launch_step(const Params& P, const void* tok_k, const void* tok_v, co
   }
   const int mode = up.np < write_every ? kPlain : (write_every == 1 ? kUpdate1 : kUpdateN);
   return P.kv_dtype == 1
-             ? launch_attn_t<true>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, &up, mode, marks, st)
-             : launch_attn_t<false>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, &up, mode, marks, st);
+             ? launch_attn_t<true>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, &up, mode, parts, marks, st)
+             : launch_attn_t<false>(P, q, out, scale, qc, Pn, pe, direct_scratch, use_fft, &up, mode, parts, marks, st);
 }
 
 }  // namespace iwdft

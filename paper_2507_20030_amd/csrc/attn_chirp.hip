@@ -14,16 +14,17 @@ namespace iwdft {
 // half of every output is not wanted, so the wide stages run on registers, and scores, softmax and weights never leave them.
 // 32 x 8 slices, 4 query heads each, M = 8132, 2033 bins: 75 us (134 with one transform of 16384 points by 512 threads, every
 // pass through LDS); with the write-back deferred a decode step takes 286 us instead of 510.
-// Pending tokens of the deferred write-back enter as in attn_fft_kernel (np, ptsh, ps).
+// Pending tokens of the deferred write-back enter as in attn_fft_kernel (np, ptsh, ps).  PART: several workgroups share the blocks, see
+// attn_parts.hip.
 //
 // GRID (M <= 2^LOGN, all |frequencies| < 2^LOGN / 4): two transforms of half the length in place of four.  The scores are interpolated from a grid of N points
 // and the weights folded back onto it by the same eight taps (interp.h: bins in the place of samples, tokens in that of frequencies; the
 // way back is its transpose, gathered per grid point from tables of its own).  The decode step above: 286 -> 250 us.
-template <int LOGN, bool GRID>
+template <int LOGN, bool GRID, bool PART = false>
 __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Params P, const float2* __restrict__ qc,
                                                                       float2* __restrict__ Pn, float* __restrict__ pe,
                                                                       float scale, int pairs, int np, uint32_t ptsh,
-                                                                      float* __restrict__ ps) {
+                                                                      float* __restrict__ ps, Parts parts) {
   constexpr int T = fft_threads(LOGN), TB = attn_threads(LOGN), NWV = TB / 64;
   constexpr int SP = T + T / 8;  // distance in LDS of entries T apart
   extern __shared__ __attribute__((aligned(16))) float2 buf[];
@@ -32,8 +33,9 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
   const TabMem tab{P.tab + tab_base(LOGN)};
   const float4* __restrict__ H = P.chirpW;
   const int tid = threadIdx.x, t = tid & (T - 1);  // TB > T: lanes T .. 63 run lane t's part of the transforms beside it
-  const int pair = blockIdx.x % pairs;
-  const int slice = blockIdx.x / pairs;
+  const uint32_t pid = PART ? blockIdx.x / (uint32_t)parts.n : blockIdx.x, part = PART ? blockIdx.x - pid * (uint32_t)parts.n : 0u;
+  const int pair = pid % pairs;
+  const int slice = pid / pairs;
   const int spl = P.batch * P.n_kv;
   const int layer = slice / spl;
   const int s = slice - layer * spl;
@@ -43,7 +45,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
   const uint32_t M = P.M, Q = GRID ? P.M : P.any_Q, Pb = GRID ? 1u : M / Q;
   const float2* q0 = qc + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   const float2* q1 = has1 ? q0 + L.Bp : q0;
-  float2* o0 = Pn + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
+  float2* o0 = (PART ? parts.rows + (int64_t)part * parts.stride : Pn) + L.ws_off + ((int64_t)s * P.G + g0) * L.Bp;
   float2* o1 = o0 + L.Bp;  // written only if has1
   const int32_t* bins = P.bins + L.bin_off;
   const float* wts = P.weights + L.bin_off;
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
 
   // Exact tokens open the softmax (raw scores q . k_e from kernel A).
   float2 mx = make_float2(-INFINITY, -INFINITY), Z = make_float2(0.f, 0.f);
-  const int E = P.S + P.R;
+  const int E = PART ? 0 : P.S + P.R;
   float* pe0 = pe + ((int64_t)slice * P.G + g0) * E;
   float* pe1 = pe0 + E;
   const float escale = 1.44269504088896341f * scale;
@@ -103,7 +105,8 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
   }
 
   constexpr int U = 4;  // bins whose inputs are fetched together
-  for (uint32_t b = 0; b < Pb; ++b) {
+  const uint32_t b_lo = PART ? part * Pb / (uint32_t)parts.n : 0u, b_hi = PART ? (part + 1) * Pb / (uint32_t)parts.n : Pb;
+  for (uint32_t b = b_lo; b < b_hi; ++b) {
     auto block_tw = [&](uint32_t k) {  // e^{j 2 pi k b / M}
       return Pb == 1 ? make_float2(1.f, 0.f) : cis_rev((float)mod_small(k * b, M, inv_Mf) * inv_Mf);
     };
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
           const float2 twc = conjf2(block_tw(k[j]));
           p0 = cmul(twc, p0);
           p1 = cmul(twc, p1);
-          if (b) {  // this thread's own running sums, scaled to the new maximum
+          if (b > b_lo) {  // this thread's own running sums, scaled to the new maximum
             const float2 a0 = o0[i];
             p0 = make_float2(a0.x * f.x + p0.x, a0.y * f.x + p0.y);
             if (has1) {
@@ -303,6 +306,10 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
     __syncthreads();
   }
 
+  if constexpr (PART) {
+    if (tid == 0) parts.stats[blockIdx.x] = make_float4(mx.x, mx.y, Z.x, Z.y);
+    return;
+  }
   const float inv_M = P.gain / (float)M;
   const float iz0 = inv_M / Z.x, iz1 = has1 ? inv_M / Z.y : 0.f;
   const double inv_Md = 1.0 / (double)M;
@@ -360,7 +367,7 @@ __global__ __launch_bounds__(attn_threads(LOGN), 4) void attn_chirp_kernel(Param
 }
 
 hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, float* pe, float scale, int np, uint32_t ptsh,
-                             float* ps, hipStream_t st) {
+                             float* ps, const Parts& parts, hipStream_t st) {
   const int pairs = (P.G + 1) / 2;
   const uint64_t grid = (uint64_t)P.n_slices * pairs;
   if (grid > 0x7fffffffull || np > kMaxPend) return hipErrorInvalidConfiguration;
@@ -371,8 +378,31 @@ hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, floa
     const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN, GRID>, bytes);                                         \
     if (e != hipSuccess) return e;                                                                                            \
     attn_chirp_kernel<LN, GRID><<<dim3((uint32_t)grid), dim3(attn_threads(LN)), bytes, st>>>(P, qc, Pn, pe, scale, pairs, np, \
-                                                                                           ptsh, ps);                        \
+                                                                                           ptsh, ps, parts);                 \
   } break;
+#define IWDFT_CHIRP_PART(LN)                                                                                                  \
+  case LN: {                                                                                                                  \
+    constexpr int bytes = (int)sizeof(float2) * fft_lds(LN);                                                                  \
+    static LdsLimit lim;                                                                                                      \
+    const hipError_t e = lim.ensure((const void*)attn_chirp_kernel<LN, false, true>, bytes);                                  \
+    if (e != hipSuccess) return e;                                                                                            \
+    attn_chirp_kernel<LN, false, true><<<dim3((uint32_t)grid * (uint32_t)parts.n), dim3(attn_threads(LN)), bytes, st>>>(      \
+        P, qc, Pn, pe, scale, pairs, np, ptsh, ps, parts);                                                                    \
+  } break;
+  if (parts.n > 1) {
+    switch (P.any_logN) {
+      IWDFT_CHIRP_PART(8)
+      IWDFT_CHIRP_PART(9)
+      IWDFT_CHIRP_PART(10)
+      IWDFT_CHIRP_PART(11)
+      IWDFT_CHIRP_PART(12)
+      IWDFT_CHIRP_PART(13)
+      IWDFT_CHIRP_PART(14)
+      default: return hipErrorInvalidValue;
+    }
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_merge(P, parts, Pn, pe, scale, np, ptsh, ps, st) : e;
+  }
   if (P.low_logN) {
     switch (P.low_logN) {
       IWDFT_CHIRP_CASE(12, true)
@@ -392,6 +422,7 @@ hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, floa
     default: return hipErrorInvalidValue;
   }
 #undef IWDFT_CHIRP_CASE
+#undef IWDFT_CHIRP_PART
   return hipGetLastError();
 }
 

@@ -211,15 +211,25 @@ hipError_t launch_reconstruct(const Params& P, int layer, uint32_t a0, uint32_t 
 struct PhaseEvents {
   hipEvent_t ev[4];
 };
+// Kernel B of few slices (attn_parts.hip): n workgroups per pair of query heads (1: one, nothing below is used).
+struct Parts {
+  int32_t n = 1;
+  int64_t stride = 0;       // float2 from one part's rows to the next one's
+  float2* rows = nullptr;   // [part], laid out as Pn: sums over the part's tokens relative to its own maximum
+  float4* stats = nullptr;  // [slice][pair][part]: (maximum, sum of weights) of the two heads, (m0, m1, z0, z1)
+};
+constexpr int kMaxParts = 64;
+hipError_t launch_merge(const Params& P, const Parts& parts, float2* Pn, float* pe, float scale, int np, uint32_t ptsh, float* ps,
+                        hipStream_t st);
 // pe: [slice][query head][S + R] normalised softmax weights of the exact tokens (workspace).
 // marks may be null.
 hipError_t launch_attn(const Params& P, const void* q, void* out, float scale, float2* qc,
-                       float2* Pn, float* pe, float* direct_scratch, bool use_fft,
+                       float2* Pn, float* pe, float* direct_scratch, bool use_fft, const Parts& parts,
                        const PhaseEvents* marks, hipStream_t st);
 
 // The softmax through chirp-z transforms (Params::chirp set).
 hipError_t launch_attn_chirp(const Params& P, const float2* qc, float2* Pn, float* pe, float scale, int np, uint32_t ptsh,
-                             float* ps, hipStream_t st);
+                             float* ps, const Parts& parts, hipStream_t st);
 
 // One decode step = append + attention with the update fused into the attention kernels.
 // write_every = 1: every coefficient is read once and written once per step.  write_every = J > 1: the
@@ -235,7 +245,7 @@ bool step_can_fuse(const Params& P);
 hipError_t launch_step(const Params& P, const void* tok_k, const void* tok_v, const void* q, void* out,
                        float scale, float2* qc, float2* Pn, float* pe, void* pend_k, void* pend_v, float* ps,
                        float* direct_scratch, bool use_fft, uint32_t t_shift0, uint32_t ring_pos,
-                       int pend_before, int write_every, const PhaseEvents* marks, hipStream_t st);
+                       int pend_before, int write_every, const Parts& parts, const PhaseEvents* marks, hipStream_t st);
 // The streaming update alone for one row per slice, x[slice * x_slice_stride + channel] (no ring hand-over).
 hipError_t launch_absorb(const Params& P, const void* xk, const void* xv, int64_t x_slice_stride,
                          uint32_t t_shift, hipStream_t st);

@@ -461,6 +461,42 @@ def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
     b.close()
 
 
+@pytest.mark.parametrize("L,n_bins,group,dims,S,R,J,dtype,low", [
+    (16384, 900, 3, (2, 1, 2), 0, 0, 4, "bf16", False), (16384, 2500, 1, (1, 1, 5), 3, 40, 0, "f32", False),   # two blocks; 2 and 8 bins a thread
+    (32768, 1500, 8, (1, 2, 3), 0, 0, 16, "bf16", False), (65536, 3100, 2, (1, 1, 9), 1, 2, 3, "bf16", False),  # fewer parts than blocks
+    (16384, 4200, 5, (1, 1, 1), 0, 9, 2, "f32", False),                                                          # sums in the rows themselves
+    (65536, 4096, 2, (1, 1, 3), 2, 0, 16, "f32", True), (131072, 4000, 3, (1, 1, 5), 0, 5, 4, "bf16", True),     # low frequencies: grids of 16384,
+    (65536, 2048, 4, (1, 2, 2), 0, 0, 8, "bf16", True), (65536, 1000, 1, (2, 1, 3), 0, 0, 0, "bf16", True),      # 8192 and 4096 points
+    (2 * 8162, 2000, 3, (1, 1, 2), 10, 50, 16, "bf16", False), (37 * 353, 700, 4, (2, 1, 2), 0, 3, 0, "f32", False),  # chirp-z blocks
+    (11 * 33 * 32, 300, 2, (1, 1, 3), 0, 0, 4, "bf16", False),
+])
+def test_softmax_of_few_slices_shared_between_workgroups(L, n_bins, group, dims, S, R, J, dtype, low):
+    """attn_parts.hip against the oracle and against one workgroup per pair of heads, which IWDFT_FLAG_SERIAL_PHASES keeps: the same sums in
+    another order (tolerances as in test_short_contexts_in_one_launch)."""
+    cfg = small_cfg(L=L, group=group, dtype=dtype, n_bins=n_bins, n_layers=dims[0], batch=dims[1], n_kv_heads=dims[2], n_sink=S,
+                    n_recent=R, steps=6)
+    rng = np.random.default_rng(L + n_bins)
+    top = n_bins if low else L // 2 + 1
+    bins = [np.sort(rng.choice(top, size=n_bins - 7 * (l % 3), replace=False)).astype(np.int32) for l in range(dims[0])]
+    bins[0][0] = 0
+    if not low:
+        bins[0][-1] = L // 2  # no grid of low frequencies
+    run_stream(cfg, bins, fused=True, write_every=J, steps=3, slices=wl.sample_slices(cfg, 2), rec=(0, 4), tag=f"parts-L{L}-G{group}")
+    K, V = wl.prefill_tensors(cfg, DEV)
+    a, b = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins, flags=B.IWDFT_FLAG_SERIAL_PHASES, write_every=J)
+    assert low or a.ws_bytes > b.ws_bytes  # the parts' rows (beneath the prefill's grids of low frequencies)
+    a.prefill(K, V)
+    b.prefill(K, V)
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -8
+    for i in range(cfg.steps):
+        tk, tv, q = wl.decode_step(cfg, i, DEV)
+        for x, y in ((a.step(tk, tv, q), b.step(tk, tv, q)),) + (((a.attend(q), b.attend(q)),) if i == 4 else ()):
+            assert torch.isfinite(x.float()).all()
+            assert float((x.float() - y.float()).abs().max()) <= tol * float(y.float().abs().max()), f"step {i}"
+    a.close()
+    b.close()
+
+
 def test_deferred_write_back_mixed_with_other_calls():
     # any call other than the fused step first writes the deferred tokens back: a random mix of calls
     # gives, step for step, what the oracle gives
