@@ -27,13 +27,14 @@ constexpr int kCusPerXcd = 32;
 // starts and the inverse one ends in registers, so samples cross LDS only inside the transforms; results take the place of
 // the inputs in the loaded words.  Only the chunk's entries and their mirrors are weighed.  64 slices of 8192 tokens, bf16:
 // 310 -> 167 us (0.27 GB read and written: 1.6 TB/s); what is left is the vector arithmetic of the two transforms.
-template <int LOGQ, bool BF16, int NP>
-__global__ __launch_bounds__(512, 4) void ablate_kernel(const char* __restrict__ x, char* __restrict__ out,
+// TWO (8192 points): two transforms by 1024 threads, see prefill_fft.hip.
+template <int LOGQ, bool BF16, int NP, bool TWO = false>
+__global__ __launch_bounds__(side_threads(LOGQ, TWO), 4) void ablate_kernel(const char* __restrict__ x, char* __restrict__ out,
                                                        const float2* __restrict__ tabs, int n_slices, int per_xcd, int lo,
                                                        int hi) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
-  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
-  static_assert(T * NS == 512 && NS * NP <= kAbPairs, "");
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ, TWO), BS = side_bs(LOGQ, TWO);
+  static_assert(T * NS == (TWO ? 1024 : 512) && NS * NP <= kAbPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;
   constexpr int NW = NP * (BF16 ? 1 : 2);
@@ -202,26 +203,28 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
   const bool aligned = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0;
   const bool wide = aligned && (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
   const bool two = aligned && (int64_t)per_xcd * (kAbPairs / 2) >= kCusPerXcd * side_ns(logQ);
+  const bool side = logQ == 13 && two_transforms((int64_t)per_xcd * (kAbPairs / (BF16 ? 8 : 4)));
   const float2* tab = nullptr;
   hipError_t e = fft_table(&tab);
   if (e != hipSuccess) return e;
-#define IWDFT_AB_LAUNCH(LQ, NP)                                                                                 \
+#define IWDFT_AB_LAUNCH(LQ, NP, TWO)                                                                            \
   {                                                                                                             \
-    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                                    \
-    const uint64_t blocks = (uint64_t)per_xcd * (kAbPairs / ((NP) * side_ns(LQ))) * 8;                          \
+    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ, TWO) * side_bs(LQ, TWO));                          \
+    const uint64_t blocks = (uint64_t)per_xcd * (kAbPairs / ((NP) * side_ns(LQ, TWO))) * 8;                     \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                            \
     static LdsLimit lim;                                                                                        \
-    e = lim.ensure((const void*)ablate_kernel<LQ, BF16, NP>, (int)lds);                                         \
+    e = lim.ensure((const void*)ablate_kernel<LQ, BF16, NP, TWO>, (int)lds);                                    \
     if (e != hipSuccess) return e;                                                                              \
-    ablate_kernel<LQ, BF16, NP><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>((const char*)x, (char*)out, tab, \
-                                                                                n_slices, per_xcd, lo, hi);     \
+    ablate_kernel<LQ, BF16, NP, TWO><<<dim3((uint32_t)blocks), dim3(side_threads(LQ, TWO)), lds, st>>>(         \
+        (const char*)x, (char*)out, tab, n_slices, per_xcd, lo, hi);                                            \
   }
 #define IWDFT_AB_CASE(LQ)                                                             \
   {                                                                                   \
     constexpr int kNp = side_pairs(LQ, BF16), kTwo = LQ < 12 ? 1 : 2;                 \
-    if (wide) IWDFT_AB_LAUNCH(LQ, kNp)                                                \
-    else if (two) IWDFT_AB_LAUNCH(LQ, kTwo)                                           \
-    else IWDFT_AB_LAUNCH(LQ, 1)                                                       \
+    if (wide && side) IWDFT_AB_LAUNCH(LQ, kNp, LQ == 13)                              \
+    else if (wide) IWDFT_AB_LAUNCH(LQ, kNp, false)                                    \
+    else if (two) IWDFT_AB_LAUNCH(LQ, kTwo, false)                                    \
+    else IWDFT_AB_LAUNCH(LQ, 1, false)                                                \
   }
   switch (logQ) {
     case 8: IWDFT_AB_CASE(8) break;

@@ -19,12 +19,14 @@ __host__ __device__ constexpr int attn_threads(int logQ) { return fft_threads(lo
 __device__ __forceinline__ int fpad(int i) { return i + ((i >> 4) << 1); }
 __host__ __device__ constexpr int fft_lds(int logQ) { return (1 << logQ) + (1 << logQ) / 8; }
 
-// Transforms of 2^logQ points that a workgroup of 512 threads runs side by side, interleaved over the lanes (thread = t NS + g
-// for thread t of transform g), and the distance of their buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses
-// fall into distinct banks.
-__host__ __device__ constexpr int side_ns(int logQ) { return 1 << (13 - logQ); }
-__host__ __device__ constexpr int side_bs(int logQ) {
-  return fft_lds(logQ) + (side_ns(logQ) == 1 ? 0 : side_ns(logQ) >= 8 ? 2 : 16 / side_ns(logQ));
+// Transforms of 2^logQ points that a workgroup runs side by side, interleaved over the lanes (thread = t NS + g for thread t of
+// transform g), its threads, and the distance of the buffers: 8 lanes with 16-byte and 16 lanes with 8-byte accesses fall into
+// distinct banks.  512 threads; TWO: two transforms of 8192 points by 1024, see prefill_fft.hip.
+__host__ __device__ constexpr int side_ns(int logQ, bool two = false) { return two ? 2 : 1 << (13 - logQ); }
+__host__ __device__ constexpr int side_threads(int logQ, bool two = false) { return side_ns(logQ, two) * fft_threads(logQ); }
+__host__ __device__ constexpr int side_bs(int logQ, bool two = false) {
+  const int ns = side_ns(logQ, two);
+  return fft_lds(logQ) + (ns == 1 ? 0 : ns >= 8 ? 2 : 16 / ns);
 }
 // Time index of position 16 t + m relative to that of position 16 t: the digits of m reversed, times Q / 16.
 template <int LOGQ>

@@ -33,16 +33,19 @@ constexpr int kPairs = kHeadDim / 2;  // channel pairs per (slice, tensor)
 // loaded words and the samples go to LDS once, behind it; the last radix-2 stage (M >= 8192, M = 512) is formed at the kept
 // bins only (spectrum_pair).  32 x 8 slices of 8192 tokens, 2048 bins: 0.80 -> 0.72 ms; 0.33 ms of it are the transforms.
 // EQ: the two channels of a pair are scaled to one size on the way (pair_scale), each as exact as alone; see the launcher.
-template <int LOGQ, bool BF16, int NP, bool EQ>
-__global__ __launch_bounds__(512, 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
+// TWO (M = 8192): 1024 threads run two transforms, so that 32 adjacent bytes of a row are fetched at a time.  There the loads weigh most, 380 us
+// of the 727 that 32 x 8 slices take with one (the transforms alone 260, loads and stores without transforms 576); with two 668 us (469).
+// At 4096 points and below, where several transforms share a workgroup anyway, twice as many are slower (4096 points 0.93 .. 0.97, 1024 0.7).
+template <int LOGQ, bool BF16, int NP, bool EQ, bool TWO = false>
+__global__ __launch_bounds__(side_threads(LOGQ, TWO), 4) void prefill_fft_kernel(Params P, const void* __restrict__ K,
                                                             const void* __restrict__ V, int per_xcd, int n_st) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
-  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
-  static_assert(T * NS == 512 && NS * NP <= kPairs, "");
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ, TWO), BS = side_bs(LOGQ, TWO);
+  static_assert(T * NS == (TWO ? 1024 : 512) && NS * NP <= kPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;  // bytes per token row
   constexpr int NW = NP * (BF16 ? 1 : 2);
-  __shared__ uint32_t maxima[EQ ? 8 : 1][EQ ? NS : 1][EQ ? NW : 1];
+  __shared__ uint32_t maxima[EQ ? T * NS / 64 : 1][EQ ? NS : 1][EQ ? NW : 1];
   __shared__ float2 halves[EQ ? NS : 1][EQ ? NP : 1];  // (h0, h1): transforms are pruned by other threads than those that fetch
   constexpr int kGroups = kPairs / (NP * NS);  // workgroups per (slice, tensor)
   const TabMem tab{P.tab + tab_base(LOGQ)};
@@ -447,27 +450,32 @@ static hipError_t launch_prefill_fft_t(const Params& P, const void* K, const voi
   // points the 32 transforms side by side cover 128 bytes of a row with one pair each (512 slices, 64 bins, two pairs / one:
   // 30 / 25 us, fp32 40 / 33).
   const bool few = (uint64_t)n_st * (kPairs / 4) < kFewWorkgroups * (uint64_t)side_ns(logQ);
-#define IWDFT_PF_CASE(LQ, NP, EQ)                                                                           \
+  const bool two = logQ == 13 && two_transforms((int64_t)per_xcd * (kPairs / (BF16 ? 8 : 4)));
+#define IWDFT_PF_CASE(LQ, NP, EQ, TWO)                                                                      \
   {                                                                                                         \
-    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                          \
-    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LQ))) * 8;                     \
+    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ, TWO) * side_bs(LQ, TWO));                      \
+    const uint64_t blocks = (uint64_t)per_xcd * (kPairs / ((NP) * side_ns(LQ, TWO))) * 8;                   \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                        \
     static LdsLimit lim;                                                                                    \
-    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, NP, EQ>, (int)lds);                     \
+    e = lim.ensure((const void*)prefill_fft_kernel<LQ, BF16, NP, EQ, TWO>, (int)lds);                       \
     if (e != hipSuccess) return e;                                                                          \
-    prefill_fft_kernel<LQ, BF16, NP, EQ><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(            \
-        P, K, V, per_xcd, n_st);                                                                            \
+    prefill_fft_kernel<LQ, BF16, NP, EQ, TWO>                                                               \
+        <<<dim3((uint32_t)blocks), dim3(side_threads(LQ, TWO)), lds, st>>>(P, K, V, per_xcd, n_st);         \
   }
 #define IWDFT_PF_SINGLE(LQ)                                                        \
   {                                                                                \
     constexpr int kNp = LQ == 8 ? 1 : BF16 ? 4 : 2;                                \
+    constexpr bool kTwo = LQ == 13;                                                \
     if (!eq) {                                                                     \
-      if (wide && !few) IWDFT_PF_CASE(LQ, kNp, false)                       \
-      else IWDFT_PF_CASE(LQ, 1, false)                                      \
+      if (wide && two) IWDFT_PF_CASE(LQ, kNp, false, kTwo)                         \
+      else if (wide && !few) IWDFT_PF_CASE(LQ, kNp, false, false)                  \
+      else IWDFT_PF_CASE(LQ, 1, false, false)                                      \
+    } else if (wide && two) {                                                      \
+      IWDFT_PF_CASE(LQ, kNp, true, kTwo)                                           \
     } else if (wide && !few) {                                                     \
-      IWDFT_PF_CASE(LQ, kNp, true)                                          \
+      IWDFT_PF_CASE(LQ, kNp, true, false)                                          \
     } else {                                                                       \
-      IWDFT_PF_CASE(LQ, 1, true)                                            \
+      IWDFT_PF_CASE(LQ, 1, true, false)                                            \
     }                                                                              \
   }
   switch (logQ) {

@@ -101,13 +101,14 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(Params P, int layer, u
 // (as the FFT prefill does), so that a lane stores 16 bytes and NS lanes 16 NS adjacent bytes of an output row at a time: with
 // one pair per workgroup every 128-byte line was written in 32 pieces.  K and V of 64 slices, 8192 slots, 2048 bins, bf16:
 // 408 -> 232 us (0.54 GB, 2.3 TB/s); what is left is vector arithmetic, the coefficients are read once per pair.
-template <int LOGQ, bool BF16, bool MULTI, int NP>
-__global__ __launch_bounds__(512, 4) void reconstruct_fft_kernel(Params P, int layer, uint32_t a0, uint32_t n_slots,
+// TWO (8192 points): two transforms by 1024 threads, see prefill_fft.hip.
+template <int LOGQ, bool BF16, bool MULTI, int NP, bool TWO = false>
+__global__ __launch_bounds__(side_threads(LOGQ, TWO), 4) void reconstruct_fft_kernel(Params P, int layer, uint32_t a0, uint32_t n_slots,
                                                                 void* __restrict__ Kt, void* __restrict__ Vt,
                                                                 uint32_t tsh, int per_xcd, int n_st) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
-  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ), BS = side_bs(LOGQ);
-  static_assert(T * NS == 512 && NS * NP <= kRecPairs, "");
+  constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), NS = side_ns(LOGQ, TWO), BS = side_bs(LOGQ, TWO);
+  static_assert(T * NS == (TWO ? 1024 : 512) && NS * NP <= kRecPairs, "");
   constexpr int kElem = BF16 ? 2 : 4;
   constexpr int kRow = kHeadDim * kElem;
   constexpr int NW = NP * (BF16 ? 1 : 2);
@@ -212,22 +213,27 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
   // the pairs spread over more workgroups then
   const bool wide = (((uintptr_t)Kt | (uintptr_t)Vt) & 15u) == 0 &&
                     (uint64_t)n_st * (kRecPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
+  // longer ones gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310; 32, M = 16384, 2048 bins 266 / 252)
+  const bool two = logQ == 13 && P.M <= 16384 && two_transforms((int64_t)per_xcd * (kRecPairs / (BF16 ? 8 : 4)));
   hipError_t e = hipSuccess;
-#define IWDFT_RC_LAUNCH(LQ, MULTI, NP)                                                                  \
+#define IWDFT_RC_LAUNCH(LQ, MULTI, NP, TWO)                                                             \
   {                                                                                                     \
-    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ) * side_bs(LQ));                            \
-    const uint64_t blocks = (uint64_t)per_xcd * (kRecPairs / ((NP) * side_ns(LQ))) * 8;                 \
+    const size_t lds = sizeof(float2) * (size_t)(side_ns(LQ, TWO) * side_bs(LQ, TWO));                  \
+    const uint64_t blocks = (uint64_t)per_xcd * (kRecPairs / ((NP) * side_ns(LQ, TWO))) * 8;            \
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;                                    \
     static LdsLimit lim;                                                                                \
-    e = lim.ensure((const void*)reconstruct_fft_kernel<LQ, BF16, MULTI, NP>, (int)lds);                 \
+    e = lim.ensure((const void*)reconstruct_fft_kernel<LQ, BF16, MULTI, NP, TWO>, (int)lds);            \
     if (e != hipSuccess) return e;                                                                      \
-    reconstruct_fft_kernel<LQ, BF16, MULTI, NP><<<dim3((uint32_t)blocks), dim3(512), lds, st>>>(        \
-        P, layer, a0, n_slots, Kt, Vt, tsh, per_xcd, n_st);                                             \
+    reconstruct_fft_kernel<LQ, BF16, MULTI, NP, TWO>                                                    \
+        <<<dim3((uint32_t)blocks), dim3(side_threads(LQ, TWO)), lds, st>>>(                             \
+            P, layer, a0, n_slots, Kt, Vt, tsh, per_xcd, n_st);                                         \
   }
 #define IWDFT_RC_CASE(LQ, MULTI)                                                      \
   {                                                                                   \
     constexpr int kNp = side_pairs(LQ, BF16);                                   \
-    if (wide) IWDFT_RC_LAUNCH(LQ, MULTI, kNp) else IWDFT_RC_LAUNCH(LQ, MULTI, 1)      \
+    if (wide && two) IWDFT_RC_LAUNCH(LQ, MULTI, kNp, LQ == 13)                        \
+    else if (wide) IWDFT_RC_LAUNCH(LQ, MULTI, kNp, false)                             \
+    else IWDFT_RC_LAUNCH(LQ, MULTI, 1, false)                                         \
   }
   if (logM > logQ) IWDFT_RC_CASE(kFftMaxLogQ, true)
   else switch (logQ) {

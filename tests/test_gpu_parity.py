@@ -1049,6 +1049,35 @@ def test_fft_prefill_all_transform_lengths(dtype, L, S, R, n_bins):
     assert st["coef0"] < 2e-5
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_bins", [300, 2048])
+def test_two_transforms_of_8192_points_in_a_workgroup_give_the_same_bits(dtype, n_bins):
+    """Prefill, reconstruction and ablation of as many slices as fill whole rounds of workgroups of 1024 threads (two_transforms in
+    pair_io.h) against the same slices a few at a time, which run one transform per workgroup: the same arithmetic."""
+    cfg = small_cfg(L=8192, group=2, dtype=dtype, n_bins=n_bins, n_layers=1, batch=4, n_kv_heads=8)
+    bins = [np.sort(np.random.default_rng(n_bins).choice(8192, size=n_bins, replace=False)).astype(np.int32)]
+    K, V = wl.prefill_tensors(cfg, DEV)
+    a = make_cache(cfg, bins)
+    a.prefill(K, V)
+    ka, va = a.reconstruct(0, 0, 8192)
+    oa = torch.empty_like(K)
+    B.iwdft_ablate_chunk(K, oa, 22, 3)
+    few = small_cfg(L=8192, group=2, dtype=dtype, n_bins=n_bins, n_layers=1, batch=1, n_kv_heads=3)
+    b = make_cache(few, bins)
+    for row, h in ((0, 0), (1, 5), (3, 4)):
+        Kb, Vb = (x[:, row:row + 1, h:h + 3].contiguous() for x in (K, V))
+        b.prefill(Kb, Vb)
+        for x, y in zip(a.export_coeffs(0), b.export_coeffs(0)):
+            assert torch.equal(x[row:row + 1, h:h + 3], y)
+        kb, vb = b.reconstruct(0, 0, 8192)
+        assert torch.equal(ka[row:row + 1, h:h + 3], kb) and torch.equal(va[row:row + 1, h:h + 3], vb)
+        ob = torch.empty_like(Kb)
+        B.iwdft_ablate_chunk(Kb, ob, 22, 3)
+        assert torch.equal(oa[:, row:row + 1, h:h + 3], ob)
+    a.close()
+    b.close()
+
+
 def test_fft_and_dense_prefill_give_the_same_state():
     cfg = small_cfg(L=4096, dtype="bf16", n_bins=500, n_sink=2, n_recent=3)
     bins = random_bins(cfg, 41)
