@@ -8,6 +8,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <new>
 #include <vector>
 
@@ -51,6 +52,8 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int32_t G = 1, max_nb = 0, max_Bp = 0;
   bool use_fft = false;          // decode attention through power-of-two FFTs
   bool use_any_prefill = false;  // prefill through interpolated transforms
+  int pf_logN = 0;               // ... grid of so many points (log2)
+  int64_t pf_Pb = 1, pf_A = 0, pf_period = 0;  // blocks, samples of the longest one, frequencies with taps of their own
   bool use_chirp = false;        // ... through chirp-z transforms (any M up to kChirpMaxM when use_fft is false)
   int chirp_logN = 0;            // length of its circular convolutions
   int chirp_logS = 0;            // length of a table that the state buffer used to hold: its bytes stay, for copies of the buffer
@@ -86,6 +89,7 @@ constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kerne
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
 // grid points that take as long as one token of the contraction: bf16, fp32, grids of up to 4096 points and longer ones
 constexpr int64_t kAnyPrefillPoints[2][2] = {{180, 160}, {250, 185}};
+constexpr int64_t kAnyMaxPeriod = 65536;  // ... most frequencies with taps of their own (48 bytes each) where the blocks do not divide M
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
 constexpr int kLowMinLogN = 12, kLowMaxLogN = 14;  // grids of prefill and decode attention on low frequencies, M = 2^m
@@ -293,10 +297,22 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // M = 4036, 256 slices, 384 bins (173) 569 / 641; M = 8132, 64 slices, 512 bins (129) 462 / 348, 256 slices, 384 bins (172) 1111 / 1350;
   // fp32 M = 5000, 64 slices, 128 bins (210) 399 / 377; M = 6000, 256 slices, 384 bins (233) 1418 / 1619; M = 24573, 96 slices, 256 bins (197)
   // 1915 / 2300; M = 8132, 96 slices, 128 bins (193) 646 / 723.  Blocks of a few points only stay with the contraction.
+  // The number of blocks of a longer M need not divide it: the frequencies lie anywhere on the grid, and M is cut into the blocks of the fewest
+  // points in all (70 x 8 slices, M = 14473 = 41 x 353, 1978 bins: 41 blocks 27.0 ms, 2 7.1; 4 x 8, fp32, M = 25419 = 37 x 687, 4096 bins: 37 6.4, 7 1.4).
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
-    const int64_t Pb = d->M / pl->chirp_Q;
-    const int64_t points = Pb * (((int64_t)1 << pl->chirp_logN) + (Pb > 1 ? pl->max_nb * 3 / 2 : 0));
-    pl->use_any_prefill = S * points <= kAnyPrefillPoints[b16 ? 0 : 1][pl->chirp_logN > 12 ? 1 : 0] * d->M * rounds;
+    int64_t points = 0;
+    for (int64_t pb = (d->M + kChirpMaxM - 1) / kChirpMaxM; pb <= d->M / pl->chirp_Q; ++pb) {
+      const int64_t A = (d->M + pb - 1) / pb, g = std::gcd(d->M, pb);
+      if (A <= kFftMinM) break;
+      if (g != pb && d->M / g > kAnyMaxPeriod) continue;
+      int logN = 10;
+      while (((int64_t)1 << logN) < 2 * A) ++logN;
+      const int64_t n = pb * (((int64_t)1 << logN) + (pb > 1 ? pl->max_nb * 3 / 2 : 0));
+      if (points && n >= points) continue;
+      points = n;
+      pl->pf_logN = logN, pl->pf_Pb = pb, pl->pf_A = A, pl->pf_period = d->M / g;
+    }
+    pl->use_any_prefill = S * points <= kAnyPrefillPoints[b16 ? 0 : 1][pl->pf_logN > 12 ? 1 : 0] * d->M * rounds;
   }
 
   // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only
@@ -392,8 +408,8 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_pendV = o; o = align256(o + esz * n_sl * pend_rows * kHeadDim);
   pl->off_ps = o;    o = align256(o + (pl->write_every > 1 ? sizeof(float) * n_sl * (size_t)pl->G * kMaxPend : 0));
   pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
-  pl->off_dec = o;   o = align256(o + (pl->use_chirp ? sizeof(float) * ((size_t)1 << pl->chirp_logN) / 2 : 0));
-  pl->off_taps = o;  o = align256(o + (pl->use_chirp ? sizeof(float) * tap_floats(d->M > pl->chirp_Q ? kSumTaps : kTaps) * ((size_t)pl->chirp_Q / 2 + 1) : 0));
+  pl->off_dec = o;   o = align256(o + (pl->use_any_prefill ? sizeof(float) * ((size_t)1 << pl->pf_logN) / 2 : 0));
+  pl->off_taps = o;  o = align256(o + (pl->use_any_prefill ? sizeof(float) * tap_floats(pl->pf_Pb > 1 ? kSumTaps : kTaps) * ((size_t)pl->pf_period / 2 + 1) : 0));
   if (pl->parts > 1) {
     pl->off_parts = o; o = align256(o + sizeof(float2) * (size_t)ws * (size_t)pl->parts);
     pl->off_stats = o; o = align256(o + stats_bytes(*pl, (int64_t)n_sl));
@@ -656,9 +672,9 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
         e = hipMemcpy(c->ws + pl.off_chirpW, out.data(), sizeof(float2) * out.size(), hipMemcpyHostToDevice);
       }
       if (pl.use_any_prefill) {
-        const Window gw = grid_window(pl.chirp_logN, 0.5 * (double)pl.chirp_Q, desc->M > pl.chirp_Q ? kSumTaps : kTaps);
-        if (e == hipSuccess) e = make_samples((float*)(c->ws + pl.off_dec), pl.chirp_Q, pl.chirp_logN, gw);
-        if (e == hipSuccess) e = make_taps((float*)(c->ws + pl.off_taps), pl.chirp_Q, gw.N, 1.0, gw);
+        const Window gw = grid_window(pl.pf_logN, 0.5 * (double)pl.pf_A, pl.pf_Pb > 1 ? kSumTaps : kTaps);
+        if (e == hipSuccess) e = make_samples((float*)(c->ws + pl.off_dec), pl.pf_A, pl.pf_logN, gw);
+        if (e == hipSuccess) e = make_taps((float*)(c->ws + pl.off_taps), pl.pf_period, gw.N, 1.0, gw);
       }
     }
     if (e == hipSuccess && pl.tw_Q) {
@@ -717,6 +733,11 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.any_dec = pl.use_any_prefill ? (const float*)(c->ws + pl.off_dec) : nullptr;
     P.any_taps = pl.use_any_prefill ? (const float4*)(c->ws + pl.off_taps) : nullptr;
     P.any_logN = pl.chirp_logN;
+    P.pf_logN = pl.pf_logN;
+    P.pf_Pb = (uint32_t)pl.pf_Pb;
+    P.pf_A = (uint32_t)pl.pf_A;
+    P.pf_period = (uint32_t)pl.pf_period;
+    P.pf_step = pl.pf_period ? (uint32_t)(pl.pf_Pb / (desc->M / pl.pf_period)) : 0u;
     P.dec_logN = pl.dec_logN;
     P.dec_slices = (int32_t)pl.dec_slices;
     P.dec_weights = pl.dec_logN ? (const double*)(c->ws + pl.off_dec_w) : nullptr;

@@ -52,9 +52,12 @@ struct Params {
   // conjugate chirp divided by its length 2^any_logN, laid out as chirp.h reads it.
   const float2* chirp;
   const float4* chirpW;
-  // Interpolated transforms (interp.h) of any_Q points from a grid of 2^any_logN, for the same M; tables in the workspace.
   int32_t any_logN;
   uint32_t any_Q;
+  // Prefill of the same M through interpolated transforms (interp.h; prefill_any.hip): grid of 2^pf_logN points, pf_Pb blocks of up to pf_A samples,
+  // frequency k at entry (k pf_step) mod pf_period of pf_period; tables in the workspace.
+  int32_t pf_logN;
+  uint32_t pf_Pb, pf_A, pf_step, pf_period;
   const float* any_dec;    // 1 / W per sample
   const float4* any_taps;  // taps per frequency
   const float2* tab;  // twiddle tables of the in-LDS transforms (fft_tab.h)
