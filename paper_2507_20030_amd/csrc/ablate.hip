@@ -203,7 +203,7 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
   const bool aligned = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0;
   const bool wide = aligned && (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
   const bool two = aligned && (int64_t)per_xcd * (kAbPairs / 2) >= kCusPerXcd * side_ns(logQ);
-  const bool side = logQ == 13 && two_transforms((int64_t)per_xcd * (kAbPairs / (BF16 ? 8 : 4)));
+  const bool side = logQ == 13 && !BF16 && two_transforms((int64_t)per_xcd * (kAbPairs / (BF16 ? 8 : 4)));
   const float2* tab = nullptr;
   hipError_t e = fft_table(&tab);
   if (e != hipSuccess) return e;

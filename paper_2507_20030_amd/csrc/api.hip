@@ -72,7 +72,7 @@ struct Plan {  // byte offsets inside the two caller buffers, derived from a des
   int write_every = 1;           // fused decode step: coefficients written back every this many tokens
   size_t off_layers = 0, off_bins = 0, off_weights = 0, off_fold = 0, off_FK = 0, off_FV = 0, state_bytes = 0;
   size_t off_sinkK = 0, off_sinkV = 0, off_ringK = 0, off_ringV = 0;
-  int parts = 1;                 // workgroups per pair of query heads in the softmax (attn_parts.hip)
+  int parts = 1, part_room = 1;  // workgroups per pair of query heads in the softmax (attn_parts.hip), as many as the workspace has room for
   size_t off_parts = 0, off_stats = 0;
   size_t off_qc = 0, off_Pn = 0, off_pe = 0, off_pendK = 0, off_pendV = 0, off_ps = 0, off_direct = 0, ws_bytes = 0;
 };
@@ -110,7 +110,8 @@ constexpr int64_t tap_floats(int taps) { return taps > 8 ? 12 : 10; }  // of one
 // Low frequencies repeat the two transforms in every part: grids of 16384 points, M = 131072, 16 pairs 109 / 95, 64 134 / 120, two parts for 128
 // pairs 268 / 268; shorter grids slow down beside each other: 8192 points, M = 65536, 8 pairs 59 / 53, 504 workgroups for 72 pairs 106 / 111;
 // 4096 points, M = 65536, 8 pairs 49 / 39; four tokens per grid point gain on 16384 points only (M = 32768, 8 pairs 50 / 50, 32 64 / 64).
-int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws) {
+int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws, int* reserve) {
+  *reserve = 1;
   int64_t units, slots, least = 2;  // what can be shared out, workgroups at a time, fewest parts that pay
   if (pl.use_fft && M > kFftMaxQ) {
     const int per_thread = (pl.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
@@ -118,7 +119,7 @@ int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws) {
       units = M >> pl.low_logN;
       slots = pl.low_logN < kLowMaxLogN || units < 8 ? kCus / 2 : kCus;
       least = 3;
-      if (units < 8 && pl.low_logN < kLowMaxLogN) return 1;
+      if (units < 8 && pl.low_logN < kLowMaxLogN) units = 1;
     } else {
       units = M / kFftMaxQ;
       slots = units == 2 ? kCus / 2 : per_thread > 4 && per_thread <= 8 ? kCus : 2 * kCus;
@@ -129,13 +130,17 @@ int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws) {
   } else {
     return 1;
   }
-  const int64_t room = kPartBytes / (int64_t)(sizeof(float2) * (size_t)ws);
-  const int64_t n = std::min(std::min(units, room), std::min<int64_t>(slots / (slices * ((pl.G + 1) / 2)), kMaxParts));
+  const int64_t blocks = slices * ((pl.G + 1) / 2);
+  const int64_t room = std::min<int64_t>(kPartBytes / (int64_t)(sizeof(float2) * (size_t)ws), kMaxParts);
+  const int64_t n = std::min(std::min(units, room), slots / blocks);
+  // M = 2^m: the same room whichever bins are kept
+  const int64_t most = pl.use_fft ? std::min(std::min(M >> kLowMinLogN, room), 2 * kCus / blocks) : n;
+  *reserve = (int)std::max<int64_t>(most, 1);
   if (n < least) return 1;
   const int64_t share = (units + n - 1) / n;
   return (int)((units + share - 1) / share);  // no more than the longest share asks for
 }
-size_t stats_bytes(const Plan& pl, int64_t slices) { return sizeof(float4) * (size_t)(slices * ((pl.G + 1) / 2) * pl.parts); }
+size_t stats_bytes(const Plan& pl, int64_t slices, int parts) { return sizeof(float4) * (size_t)(slices * ((pl.G + 1) / 2) * parts); }
 // The parts' buffers at `rows` and `stats`.
 Parts parts_at(const Plan& pl, char* rows, char* stats) {
   Parts p;
@@ -366,7 +371,7 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
                 "divisor (e.g. move tokens to the sink / recent windows) or pass IWDFT_FLAG_DIRECT_SYNTHESIS to insist",
                 (long long)d->M, pl->max_nb, (int)kChirpMaxBlocks, (int)kChirpMaxM);
 
-  pl->parts = (d->flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : softmax_parts(*pl, d->M, S, ws);
+  if (!(d->flags & IWDFT_FLAG_SERIAL_PHASES)) pl->parts = softmax_parts(*pl, d->M, S, ws, &pl->part_room);
 
   size_t o = 0;
   pl->off_layers = o;  o = align256(o + sizeof(LayerInfo) * (size_t)d->n_layers);
@@ -410,10 +415,6 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   pl->off_chirpW = o; o = align256(o + (pl->use_chirp ? sizeof(float2) * ((size_t)1 << pl->chirp_logN) : 0));
   pl->off_dec = o;   o = align256(o + (pl->use_any_prefill ? sizeof(float) * ((size_t)1 << pl->pf_logN) / 2 : 0));
   pl->off_taps = o;  o = align256(o + (pl->use_any_prefill ? sizeof(float) * tap_floats(pl->pf_Pb > 1 ? kSumTaps : kTaps) * ((size_t)pl->pf_period / 2 + 1) : 0));
-  if (pl->parts > 1) {
-    pl->off_parts = o; o = align256(o + sizeof(float2) * (size_t)ws * (size_t)pl->parts);
-    pl->off_stats = o; o = align256(o + stats_bytes(*pl, (int64_t)n_sl));
-  }
   pl->off_direct = o;
   if (!pl->use_fft && !pl->use_chirp)
     o = align256(o + sizeof(float) * (size_t)d->n_layers * (size_t)slices_per_layer *
@@ -431,6 +432,10 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
     pl->off_low = o;
     o = align256(o + sizeof(float) * (pl->use_chirp ? 10 * ((size_t)d->M / 2 + 1) : (size_t)(d->M >> pl->low_logN) * kTaps));
     pl->off_grid = o;     o = align256(o + (pl->use_chirp ? 10 * sizeof(float) * (((size_t)1 << pl->low_logN) / 2 + 1) : 0));
+  }
+  if (pl->part_room > 1) {
+    pl->off_parts = o; o = align256(o + sizeof(float2) * (size_t)ws * (size_t)pl->part_room);
+    pl->off_stats = o; o = align256(o + stats_bytes(*pl, (int64_t)n_sl, pl->part_room));
   }
   pl->ws_bytes = o;
   return IWDFT_OK;
@@ -964,7 +969,7 @@ int compressed_decode_attn_static(iwdft_ctx* ctx, const void* d_q, void* d_out, 
   // ... and the parts of the softmax; where they do not fit, one workgroup per pair of heads does all of it (equal up to rounding).
   Parts parts;
   const size_t part_bytes = align256(sizeof(float2) * (size_t)pl.ws_total * (size_t)pl.parts);
-  const bool split = pl.parts > 1 && need + part_bytes + stats_bytes(pl, ctx->P.n_slices) <= kStaticScratchBytes;
+  const bool split = pl.parts > 1 && need + part_bytes + stats_bytes(pl, ctx->P.n_slices, pl.parts) <= kStaticScratchBytes;
   char* sc = nullptr;
   if ((rc = static_scratch(ctx->device, &sc)) != IWDFT_OK) return rc;
   if ((rc = flush_pending(ctx, (hipStream_t)hip_stream)) != IWDFT_OK) return rc;
