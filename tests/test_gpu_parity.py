@@ -461,6 +461,39 @@ def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
     b.close()
 
 
+@pytest.mark.parametrize("J", [0, 16])
+@pytest.mark.parametrize("L,n_bins,group", [(256, 64, 1), (512, 128, 2), (1024, 256, 1), (1024, 100, 4), (2048, 250, 2), (4096, 256, 1)])
+def test_short_contexts_write_back_as_exactly_as_the_three_kernels(L, n_bins, group, J):
+    """Token j is one in channel j and zero elsewhere, the state zero before: the coefficients of that channel are e^{j 2 pi k j / M} as the
+    step forms it.  Its distance from 64 bits, over all bins and tokens, is no larger than what the three kernels leave (5 % more for the other grouping
+    of the products where 16 tokens are written at once); one token at a time both parts of K are right to an ulp below one, 2^-24."""
+    cfg = small_cfg(L=L, group=group, dtype="f32", n_bins=n_bins, n_layers=1, batch=1, n_kv_heads=2)
+    bins = [np.sort(np.random.default_rng(L + n_bins).choice(L // 2 + 1, size=n_bins, replace=False)).astype(np.int32)]
+    zero = torch.zeros((1, 1, 2, L, 128), device=DEV)
+    row = torch.zeros((16, 1, 1, 2, 128), device=DEV)
+    for j in range(16):
+        row[j, ..., j] = 1.0
+    q = torch.zeros((1, 1, 2 * group, 128), device=DEV)
+    want = np.exp(2j * np.pi * np.outer(np.arange(16), bins[0]) / L)
+    errors = {}
+    for flags in (0, B.IWDFT_FLAG_SERIAL_PHASES):
+        c = make_cache(cfg, bins, flags=flags, write_every=J)
+        c.prefill(zero, zero)
+        for j in range(16):
+            c.step(row[j], row[j], q)
+        padded = -(-n_bins // 32) * 32
+        held = c.state[-2 * 2 * 128 * padded * 8:].view(torch.complex64).view(2, 2, 128, padded)  # K then V, slices, channels, bins
+        for name, F in zip("KV", held):
+            F = c128(F)
+            assert (F[:, :, n_bins:] == 0).all() and (F[:, 16:] == 0).all()
+            errors[name, flags] = np.abs(F[:, :16, :n_bins] - want)
+        c.close()
+    if J == 0:
+        assert errors["K", 0].max() <= 2.0 ** -24 * 2 ** 0.5
+    for name in "KV":
+        assert np.linalg.norm(errors[name, 0]) <= 1.05 * np.linalg.norm(errors[name, B.IWDFT_FLAG_SERIAL_PHASES]), name
+
+
 @pytest.mark.parametrize("L,n_bins,group,dims,S,R,J,dtype,low", [
     (16384, 900, 3, (2, 1, 2), 0, 0, 4, "bf16", False), (16384, 2500, 1, (1, 1, 5), 3, 40, 0, "f32", False),   # two blocks; 2 and 8 bins a thread
     (32768, 1500, 8, (1, 2, 3), 0, 0, 16, "bf16", False), (65536, 3100, 2, (1, 1, 9), 1, 2, 3, "bf16", False),  # fewer parts than blocks
