@@ -10,7 +10,6 @@ namespace {
 constexpr int kThreads = 512;
 constexpr int kRows = 8;  // coefficient rows in flight
 constexpr int kSliceMany = 96;
-constexpr int64_t kStreamBytes = (int64_t)160 << 20;  // larger states pass by the caches (256 MiB of them next to the memory)
 constexpr int slice_pairs(int GT) { return (GT + 1) / 2; }
 // Float2 of the transforms' buffers; the partial sums of the scores lie over them.
 constexpr int slice_buf(int GT, int logQ) {
@@ -55,7 +54,7 @@ __device__ __forceinline__ const void* exact_row_any(bool bf16, const Params& P,
 // through their shares (see attn.hip).  Needs one fold round per layer, rows of up to 2^LOGQ / 4 bins, all heads in one pass.
 template <int LOGQ, int GT, bool UPD>
 __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const void* __restrict__ q, void* __restrict__ out,
-                                                                float scale, int rlog, int stream, StepUpdate up) {
+                                                                float scale, int rlog, StepUpdate up) {
   constexpr int Q = 1 << LOGQ, T = fft_threads(LOGQ), TB = attn_threads(LOGQ), NWV = TB / 64, PAIRS = slice_pairs(GT);
   constexpr bool kAhead = GT < 8;  // two times kRows rows in flight, as far as the registers go
   constexpr int FB = fft_lds(LOGQ), BPT = Q / 4 / TB > 0 ? Q / 4 / TB : 1;  // kept bins of a thread at most
@@ -84,11 +83,6 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
   const int RL = 1 << rlog, groups = kThreads >> rlog, cpg = RL / 4;  // channels of a group of lanes
   const int i0 = (tid & (RL - 1)) * 2, grp = tid >> rlog;
   const bool cols = i0 < L.Bp, live = i0 < L.nb;
-  auto fetch = [&](const v4f* p) { return stream ? __builtin_nontemporal_load(p) : *p; };  // wave-uniform
-  auto put = [&](v4f* p, v4f v) {
-    if (stream) __builtin_nontemporal_store(v, p);
-    else *p = v;
-  };
   // bins i, i + 1 of a lane; any where there is none
   auto lane_bins = [&](int i, uint32_t (&k)[2]) {
     k[0] = (uint32_t)bins[i < L.nb ? i : L.nb - 1];
@@ -111,7 +105,7 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
   v4f* rowK = (v4f*)(P.FK + L.coef_off + ((int64_t)s * kHeadDim + grp * cpg) * L.Bp + i0);
   v4f f[kRows];
 #pragma unroll
-  for (int u = 0; u < kRows; ++u) f[u] = cols ? fetch(rowK + u * stride) : (v4f)(0.f);
+  for (int u = 0; u < kRows; ++u) f[u] = cols ? rowK[u * stride] : (v4f)(0.f);
 
   for (int e = tid; e < GT * kHeadDim; e += kThreads) {
     const int64_t at = ((int64_t)slice * P.G + e / kHeadDim) * kHeadDim + (e % kHeadDim);
@@ -189,13 +183,13 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
     v4f x[kRows];
     if (!kAhead && r > 0) {
 #pragma unroll
-      for (int u = 0; u < kRows; ++u) f[u] = cols ? fetch(rowK + (r + u) * stride) : (v4f)(0.f);
+      for (int u = 0; u < kRows; ++u) f[u] = cols ? rowK[(r + u) * stride] : (v4f)(0.f);
     }
 #pragma unroll
     for (int u = 0; u < kRows; ++u) x[u] = f[u];
     if (kAhead && r + kRows < cpg) {  // the next rows
 #pragma unroll
-      for (int u = 0; u < kRows; ++u) f[u] = cols ? fetch(rowK + (r + kRows + u) * stride) : (v4f)(0.f);
+      for (int u = 0; u < kRows; ++u) f[u] = cols ? rowK[(r + kRows + u) * stride] : (v4f)(0.f);
     }
     if constexpr (UPD) {
       v4f t = tw;
@@ -206,7 +200,7 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
       }
       if (live) {
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) put(rowK + (r + u) * stride, x[u]);
+        for (int u = 0; u < kRows; ++u) rowK[(r + u) * stride] = x[u];
       }
     }
 #pragma unroll
@@ -271,7 +265,7 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
   uint32_t kV[2];
   auto fetch_v = [&](int h, int ch) {
 #pragma unroll
-    for (int u = 0; u < R; ++u) fv[u] = ch * 128 + j0 < L.Bp ? fetch(rowV + (h * R + u) * stride + ch * 64) : (v4f)(0.f);
+    for (int u = 0; u < R; ++u) fv[u] = ch * 128 + j0 < L.Bp ? rowV[(h * R + u) * stride + ch * 64] : (v4f)(0.f);
     if constexpr (UPD) lane_bins(ch * 128 + j0, kV);
   };
 
@@ -422,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
             if (np > 1) t = cmul2(t, w);
           }
 #pragma unroll
-          for (int u = 0; u < R; ++u) put(rowV + (h * R + u) * stride + ch * 64, x[u]);
+          for (int u = 0; u < R; ++u) rowV[(h * R + u) * stride + ch * 64] = x[u];
         }
       }
       const int jc = j < L.Bp ? j : 0;
@@ -500,8 +494,6 @@ hipError_t launch_attn_slice(const Params& P, const void* q, void* out, float sc
   int logQ = 8, rlog = 5;
   while ((1u << logQ) < P.M) ++logQ;
   while ((2 << rlog) < P.max_Bp) ++rlog;
-  const int64_t coef = (int64_t)P.n_slices * kHeadDim * P.max_Bp * 2 * sizeof(float2);
-  const int stream = coef > kStreamBytes;
   const int lds = slice_lds(GT, logQ, up.np, P.S + P.R);
   hipError_t e = hipSuccess;
 #define IWDFT_SLICE1(LQ, GTV, UPD)                                                                       \
@@ -510,7 +502,7 @@ hipError_t launch_attn_slice(const Params& P, const void* q, void* out, float sc
     e = lim.ensure((const void*)attn_slice_kernel<LQ, GTV, UPD>, kSliceMaxLds);                          \
     if (e != hipSuccess) return e;                                                                       \
     attn_slice_kernel<LQ, GTV, UPD><<<dim3((uint32_t)P.n_slices), dim3(kThreads), (size_t)lds, st>>>(    \
-        P, q, out, scale, rlog, stream, up);                                                                     \
+        P, q, out, scale, rlog, up);                                                                         \
   }
 #define IWDFT_SLICE(LQ, GTV)             \
   {                                      \

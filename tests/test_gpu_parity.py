@@ -430,7 +430,7 @@ def test_score_kernel_of_few_and_of_many_blocks(group, batch, heads, n_bins, J):
     (1024, 4, 65, (2, 2, 3), 0, 0, 16, "bf16"), (1024, 7, 129, (2, 8, 8), 2, 3, 5, "f32"),    # 64 and 128 lanes a row
     (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16"), (2048, 8, 512, (2, 6, 8), 0, 2, 2, "bf16"),   # all lanes two rows of a head group
     (4096, 4, 1023, (1, 12, 8), 2, 5, 4, "bf16"), (4096, 3, 900, (2, 8, 8), 0, 0, 0, "f32"),  # one row over all lanes
-    (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16"),  # states beyond 160 MiB: streaming accesses
+    (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16"),  # states beyond 160 MiB
 ])
 def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
     """One workgroup per slice (attn_slice.hip) against the oracle and against the three kernels, which IWDFT_FLAG_SERIAL_PHASES
