@@ -149,6 +149,13 @@ typedef struct {
 /* Sizes of the two caller-provided device buffers for this descriptor. */
 int iwdft_query_bytes(const iwdft_desc* desc, size_t* state_bytes, size_t* workspace_bytes);
 
+/* How decode attention on such a context shares out its work, for tests and tuning (host only): with `pending` tokens (0 .. 16) that the
+ * coefficients do not hold yet and, for write_back != 0, written into them by the same call -- compressed_decode_attn: 0, 0;
+ * iwdft_append_attn: 1, 1, or with desc.write_every = J > 1 its call j = 1 .. J of a round: j, j == J.  workgroups = 0: the three phases in one launch,
+ * one workgroup per slice; n >= 1: kernels of their own, n workgroups for the softmax of a pair of query heads (1 also with the
+ * direct sums).  Not for contexts with IWDFT_FLAG_SHORTCUT or more than 8 query heads per KV head, whose steps run as append and attention. */
+int iwdft_query_attn(const iwdft_desc* desc, int32_t pending, int32_t write_back, int32_t* workgroups);
+
 /* Validates desc, copies the bin lists into d_state and zeroes the coefficients
  * (synchronous; not a hot call).  Both buffers must be 256-byte aligned and stay
  * alive and untouched by the caller until iwdft_destroy.  Neither may serve two

@@ -28,7 +28,7 @@ EXPORTED = [
     "iwdft_query_bytes", "iwdft_create", "iwdft_destroy", "iwdft_prefill", "iwdft_append",
     "iwdft_reconstruct", "iwdft_reconstruct_grid", "compressed_decode_attn", "iwdft_append_attn", "iwdft_export_coeffs", "iwdft_export_bins",
     "iwdft_num_tokens", "iwdft_set_num_tokens", "iwdft_last_error", "iwdft_phase_timing", "iwdft_phase_times", "iwdft_prefill_kind", "iwdft_attn_kind", "iwdft_attn_pipelined",
-    "iwdft_select_bins", "iwdft_ablate_chunk", "iwdft_flush", "compressed_decode_attn_static",
+    "iwdft_select_bins", "iwdft_ablate_chunk", "iwdft_flush", "compressed_decode_attn_static", "iwdft_query_attn",
 ]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libiwdft.so")
@@ -69,6 +69,7 @@ def load_library() -> ctypes.CDLL:
     dp = ctypes.POINTER(iwdft_desc)
     szp = ctypes.POINTER(ctypes.c_size_t)
     lib.iwdft_query_bytes.argtypes = [dp, szp, szp]
+    lib.iwdft_query_attn.argtypes = [dp, i32, i32, ctypes.POINTER(i32)]
     lib.iwdft_create.argtypes = [dp, vp, ctypes.c_size_t, vp, ctypes.c_size_t, ctypes.POINTER(vp)]
     lib.iwdft_destroy.argtypes = [vp]
     lib.iwdft_prefill.argtypes = [vp, vp, vp, vp]
@@ -150,6 +151,13 @@ def iwdft_query_bytes(desc: Descriptor):
     s, w = ctypes.c_size_t(0), ctypes.c_size_t(0)
     _check(load_library().iwdft_query_bytes(ctypes.byref(desc.c), ctypes.byref(s), ctypes.byref(w)))
     return s.value, w.value
+
+
+def iwdft_query_attn(desc: Descriptor, pending: int = 0, write_back: bool = False) -> int:
+    """0: decode attention in one launch; n >= 1: n workgroups per pair of query heads in the softmax."""
+    n = ctypes.c_int32(0)
+    _check(load_library().iwdft_query_attn(ctypes.byref(desc.c), pending, int(write_back), ctypes.byref(n)))
+    return n.value
 
 
 def iwdft_create(desc: Descriptor, state: torch.Tensor, workspace: torch.Tensor) -> ctypes.c_void_p:

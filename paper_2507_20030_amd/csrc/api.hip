@@ -151,6 +151,19 @@ Parts parts_at(const Plan& pl, char* rows, char* stats) {
   return p;
 }
 
+// What decides whether decode attention runs as one launch (attn_slice_fits).
+void set_attn_shape(const iwdft_desc& d, const Plan& pl, Params* P) {
+  P->n_slices = d.n_layers * d.batch * d.n_kv_heads;
+  P->G = pl.G;
+  P->M = (uint32_t)d.M;
+  P->max_Bp = pl.max_Bp;
+  P->S = d.n_sink;
+  P->R = d.n_recent;
+  P->serial_phases = (d.flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : 0;
+  P->one_fold = pl.use_fft && 4 * (int64_t)pl.max_Bp <= d.M ? 1 : 0;
+  for (const LayerInfo& L : pl.layers) P->one_fold &= L.fold_rounds == 1;
+}
+
 int make_plan(const iwdft_desc* d, Plan* pl) {
   if (!d) return fail(IWDFT_ERR_ARG, "desc is NULL");
   if (d->n_layers <= 0 || d->batch <= 0 || d->n_kv_heads <= 0 || d->n_q_heads <= 0)
@@ -618,6 +631,22 @@ int iwdft_query_bytes(const iwdft_desc* desc, size_t* state_bytes, size_t* works
   }
 }
 
+int iwdft_query_attn(const iwdft_desc* desc, int32_t pending, int32_t write_back, int32_t* workgroups) {
+  try {
+    if (!workgroups) return fail(IWDFT_ERR_ARG, "output pointer is NULL");
+    if (pending < 0 || pending > kMaxPend) return fail(IWDFT_ERR_ARG, "pending = %d outside [0, %d]", pending, kMaxPend);
+    Plan pl;
+    int rc = make_plan(desc, &pl);
+    if (rc != IWDFT_OK) return rc;
+    Params P{};
+    set_attn_shape(*desc, pl, &P);
+    *workgroups = attn_slice_fits(P, pending, write_back != 0) ? 0 : pl.parts;
+    return IWDFT_OK;
+  } catch (...) {  // std::bad_alloc from the host-side containers: nothing may cross the C ABI
+    return fail(IWDFT_ERR_ARG, "out of host memory");
+  }
+}
+
 int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void* d_workspace,
                  size_t workspace_bytes, iwdft_ctx** out) {
   try {
@@ -721,14 +750,11 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.n_layers = desc->n_layers;
     P.batch = desc->batch;
     P.n_kv = desc->n_kv_heads;
-    P.G = pl.G;
-    P.n_slices = desc->n_layers * desc->batch * desc->n_kv_heads;
+    set_attn_shape(*desc, pl, &P);
     P.kv_dtype = desc->kv_dtype;
-    P.M = (uint32_t)desc->M;
     P.Mmask = ((desc->M & (desc->M - 1)) == 0) ? (uint32_t)(desc->M - 1) : 0u;
     if (desc->M == 1) P.Mmask = 0;  // M = 1: "mod 1" through the generic path
     P.max_nb = pl.max_nb;
-    P.max_Bp = pl.max_Bp;
     P.layers = (const LayerInfo*)(c->state + pl.off_layers);
     P.bins = (const int32_t*)(c->state + pl.off_bins);
     P.weights = (const float*)(c->state + pl.off_weights);
@@ -760,12 +786,7 @@ int iwdft_create(const iwdft_desc* desc, void* d_state, size_t state_bytes, void
     P.FV = (float2*)(c->state + pl.off_FV);
     P.gain = 1.0f;
     P.x_scale = 1.0f;
-    P.one_fold = pl.use_fft && 4 * (int64_t)pl.max_Bp <= desc->M ? 1 : 0;
-    for (const LayerInfo& L : pl.layers) P.one_fold &= L.fold_rounds == 1;
     P.scale_pairs = pl.scale_pairs ? 1 : 0;
-    P.serial_phases = (desc->flags & IWDFT_FLAG_SERIAL_PHASES) ? 1 : 0;
-    P.S = desc->n_sink;
-    P.R = desc->n_recent;
     P.sinkK = c->state + pl.off_sinkK;
     P.sinkV = c->state + pl.off_sinkV;
     P.ringK = c->state + pl.off_ringK;

@@ -162,7 +162,6 @@ __device__ __forceinline__ float wave_reduce(float v, Op op) {
 
 // Decode attention of short contexts, all three phases of a slice in one workgroup (attn_slice.hip).
 constexpr int kSliceMaxLds = 152 << 10;
-bool attn_slice_fits(const Params& P, int np, bool update);
 hipError_t launch_attn_slice(const Params& P, const void* q, void* out, float scale, const StepUpdate& up, bool update,
                              hipStream_t st);
 

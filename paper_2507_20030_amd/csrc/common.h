@@ -224,6 +224,8 @@ struct Parts {
 constexpr int kMaxParts = 64;
 hipError_t launch_merge(const Params& P, const Parts& parts, float2* Pn, float* pe, float scale, int np, uint32_t ptsh, float* ps,
                         hipStream_t st);
+// Whether a decode step with np pending tokens, written back or only read, runs as one launch (attn_slice.hip).
+bool attn_slice_fits(const Params& P, int np, bool update);
 // pe: [slice][query head][S + R] normalised softmax weights of the exact tokens (workspace).
 // marks may be null.
 hipError_t launch_attn(const Params& P, const void* q, void* out, float scale, float2* qc,

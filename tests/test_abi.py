@@ -96,6 +96,19 @@ def test_prefill_of_long_contexts_takes_the_grid_by_rule(M, n_bins, heads, dtype
     assert ws - dense == max(grids, arrays) + tables - arrays
 
 
+def test_query_attn_checks_its_arguments():
+    d = desc(M=1024)
+    assert B.iwdft_query_attn(d) == B.iwdft_query_attn(d, 16, True) == 0 and B.iwdft_query_attn(desc()) == 1
+    for pending in (-1, 17):
+        with pytest.raises(B.IwdftError) as e:
+            B.iwdft_query_attn(d, pending)
+        assert e.value.code == B.IWDFT_ERR_ARG
+    lib = B.load_library()
+    assert lib.iwdft_query_attn(ctypes.byref(d.c), 0, 0, None) == B.IWDFT_ERR_ARG
+    n = ctypes.c_int32()
+    assert lib.iwdft_query_attn(None, 0, 0, ctypes.byref(n)) == B.IWDFT_ERR_ARG
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_layers=0, bins=[]), B.IWDFT_ERR_ARG),
     (dict(n_q_heads=3), B.IWDFT_ERR_ARG),

@@ -424,18 +424,19 @@ def test_score_kernel_of_few_and_of_many_blocks(group, batch, heads, n_bins, J):
                slices=wl.sample_slices(cfg, 5))
 
 
-@pytest.mark.parametrize("L,group,n_bins,dims,S,R,J,dtype", [
-    (256, 1, 1, (2, 1, 1), 0, 0, 0, "f32"), (256, 8, 64, (2, 1, 4), 1, 0, 4, "bf16"),       # one bin; a full quarter, 16 lanes a transform
-    (512, 5, 33, (3, 2, 2), 3, 70, 0, "bf16"), (512, 2, 128, (2, 1, 4), 0, 9, 16, "f32"),     # more exact tokens than lanes; a last head pair with one head
-    (1024, 4, 65, (2, 2, 3), 0, 0, 16, "bf16"), (1024, 7, 129, (2, 8, 8), 2, 3, 5, "f32"),    # 64 and 128 lanes a row
-    (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16"), (2048, 8, 512, (2, 6, 8), 0, 2, 2, "bf16"),   # all lanes two rows of a head group
-    (4096, 4, 1023, (1, 12, 8), 2, 5, 4, "bf16"), (4096, 3, 900, (2, 8, 8), 0, 0, 0, "f32"),  # one row over all lanes
-    (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16"),  # states beyond 160 MiB
+@pytest.mark.parametrize("L,group,n_bins,dims,S,R,J,dtype,one", [
+    (256, 1, 1, (2, 1, 1), 0, 0, 0, "f32", "aw"), (256, 8, 64, (2, 1, 4), 1, 0, 4, "bf16", "ar"),       # one bin; a full quarter, 16 lanes a transform
+    (512, 5, 33, (3, 8, 4), 3, 70, 0, "bf16", "aw"), (512, 2, 128, (2, 1, 4), 0, 9, 16, "f32", "arw"),     # more exact tokens than lanes; a last head pair with one head
+    (1024, 4, 65, (2, 2, 3), 0, 0, 16, "bf16", "arw"), (1024, 7, 129, (2, 8, 8), 2, 3, 5, "f32", "arw"),    # 64 and 128 lanes a row
+    (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16", "arw"), (2048, 8, 512, (2, 10, 8), 0, 2, 2, "bf16", "arw"),   # all lanes two rows of a head group
+    (4096, 4, 1023, (1, 20, 8), 2, 5, 4, "bf16", "ar"), (4096, 3, 790, (2, 10, 8), 0, 0, 0, "f32", "aw"),  # one row over all lanes
+    (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16", "aw"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16", "arw"),  # states beyond 160 MiB
 ])
-def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
+def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype, one):
     """One workgroup per slice (attn_slice.hip) against the oracle and against the three kernels, which IWDFT_FLAG_SERIAL_PHASES
-    keeps: masks up to M / 2 without shared slots, ragged rows, layers of different lengths, update and read-only steps.  Same sums in
-    another order: fp32 outputs agree to 1e-5 (scores of magnitude 50 times 2^-23), bf16 to one rounding (2^-8 of the largest)."""
+    keeps: masks up to M / 2 without shared slots, ragged rows, layers of different lengths.  `one`: what runs as one launch, attention alone, steps that
+    read only and steps that write back.  Same sums in another order: fp32 outputs agree to 1e-5 (scores of magnitude 50 times 2^-23), bf16 to one
+    rounding (2^-8 of the largest)."""
     cfg = small_cfg(L=L, group=group, dtype=dtype, n_bins=n_bins, n_layers=dims[0], batch=dims[1], n_kv_heads=dims[2], n_sink=S,
                     n_recent=R, steps=6)
     rng = np.random.default_rng(L + n_bins)
@@ -444,6 +445,9 @@ def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype):
     run_stream(cfg, bins, fused=True, write_every=J, rec=(0, 16), tag=f"slice-L{L}-G{group}-B{n_bins}")
     K, V = wl.prefill_tensors(cfg, DEV)
     a, b = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins, flags=B.IWDFT_FLAG_SERIAL_PHASES, write_every=J)
+    calls = dict(a=(0, False), r=(1, False), w=(max(J, 1), True))
+    assert "".join(c for c in calls if (c != "r" or J > 1) and B.iwdft_query_attn(a.desc, *calls[c]) == 0) == one
+    assert all(B.iwdft_query_attn(b.desc, *x) == 1 for x in calls.values())
     a.prefill(K, V)
     b.prefill(K, V)
     tol = 1e-5 if dtype == "f32" else 2.0 ** -8
@@ -478,6 +482,7 @@ def test_short_contexts_write_back_as_exactly_as_the_three_kernels(L, n_bins, gr
     errors = {}
     for flags in (0, B.IWDFT_FLAG_SERIAL_PHASES):
         c = make_cache(cfg, bins, flags=flags, write_every=J)
+        assert B.iwdft_query_attn(c.desc, J or 1, True) == (1 if flags else 0)
         c.prefill(zero, zero)
         for j in range(16):
             c.step(row[j], row[j], q)
@@ -494,16 +499,16 @@ def test_short_contexts_write_back_as_exactly_as_the_three_kernels(L, n_bins, gr
         assert np.linalg.norm(errors[name, 0]) <= 1.05 * np.linalg.norm(errors[name, B.IWDFT_FLAG_SERIAL_PHASES]), name
 
 
-@pytest.mark.parametrize("L,n_bins,group,dims,S,R,J,dtype,low", [
-    (16384, 900, 3, (2, 1, 2), 0, 0, 4, "bf16", False), (16384, 2500, 1, (1, 1, 5), 3, 40, 0, "f32", False),   # two blocks; 2 and 8 bins a thread
-    (32768, 1500, 8, (1, 2, 3), 0, 0, 16, "bf16", False), (65536, 3100, 2, (1, 1, 9), 1, 2, 3, "bf16", False),  # fewer parts than blocks
-    (16384, 4200, 5, (1, 1, 1), 0, 9, 2, "f32", False),                                                          # sums in the rows themselves
-    (65536, 4096, 2, (1, 1, 3), 2, 0, 16, "f32", True), (131072, 4000, 3, (1, 1, 5), 0, 5, 4, "bf16", True),     # low frequencies: grids of 16384,
-    (65536, 2048, 4, (1, 2, 2), 0, 0, 8, "bf16", True), (65536, 1000, 1, (2, 1, 3), 0, 0, 0, "bf16", True),      # 8192 and 4096 points
-    (2 * 8162, 2000, 3, (1, 1, 2), 10, 50, 16, "bf16", False), (37 * 353, 700, 4, (2, 1, 2), 0, 3, 0, "f32", False),  # chirp-z blocks
-    (11 * 33 * 32, 300, 2, (1, 1, 3), 0, 0, 4, "bf16", False),
+@pytest.mark.parametrize("L,n_bins,group,dims,S,R,J,dtype,low,parts", [
+    (16384, 900, 3, (2, 1, 2), 0, 0, 4, "bf16", False, 2), (16384, 2500, 1, (1, 1, 5), 3, 40, 0, "f32", False, 2),   # two blocks; 2 and 8 bins a thread
+    (32768, 1500, 8, (1, 2, 3), 0, 0, 16, "bf16", False, 4), (65536, 3100, 2, (1, 1, 9), 1, 2, 3, "bf16", False, 8),  # fewer parts than blocks
+    (16384, 4200, 5, (1, 1, 1), 0, 9, 2, "f32", False, 2),                                                          # sums in the rows themselves
+    (65536, 4096, 2, (1, 1, 3), 2, 0, 16, "f32", True, 4), (131072, 4000, 3, (1, 1, 5), 0, 5, 4, "bf16", True, 8),     # low frequencies: grids of 16384,
+    (65536, 2048, 4, (1, 2, 2), 0, 0, 8, "bf16", True, 8), (65536, 1000, 1, (2, 1, 3), 0, 0, 0, "bf16", True, 16),      # 8192 and 4096 points
+    (2 * 8162, 2000, 3, (1, 1, 2), 10, 50, 16, "bf16", False, 2), (37 * 353, 700, 4, (2, 1, 2), 0, 3, 0, "f32", False, 37),  # chirp-z blocks
+    (11 * 33 * 32, 300, 2, (1, 1, 3), 0, 0, 4, "bf16", False, 2),
 ])
-def test_softmax_of_few_slices_shared_between_workgroups(L, n_bins, group, dims, S, R, J, dtype, low):
+def test_softmax_of_few_slices_shared_between_workgroups(L, n_bins, group, dims, S, R, J, dtype, low, parts):
     """attn_parts.hip against the oracle and against one workgroup per pair of heads, which IWDFT_FLAG_SERIAL_PHASES keeps: the same sums in
     another order (tolerances as in test_short_contexts_in_one_launch)."""
     cfg = small_cfg(L=L, group=group, dtype=dtype, n_bins=n_bins, n_layers=dims[0], batch=dims[1], n_kv_heads=dims[2], n_sink=S,
@@ -517,7 +522,7 @@ def test_softmax_of_few_slices_shared_between_workgroups(L, n_bins, group, dims,
     run_stream(cfg, bins, fused=True, write_every=J, steps=3, slices=wl.sample_slices(cfg, 2), rec=(0, 4), tag=f"parts-L{L}-G{group}")
     K, V = wl.prefill_tensors(cfg, DEV)
     a, b = make_cache(cfg, bins, write_every=J), make_cache(cfg, bins, flags=B.IWDFT_FLAG_SERIAL_PHASES, write_every=J)
-    assert a.ws_bytes > b.ws_bytes  # room for the rows of the parts
+    assert B.iwdft_query_attn(a.desc) == parts and a.ws_bytes > b.ws_bytes and B.iwdft_query_attn(b.desc) == 1
     a.prefill(K, V)
     b.prefill(K, V)
     tol = 1e-5 if dtype == "f32" else 2.0 ** -8
