@@ -9,7 +9,7 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kRows = 8;  // coefficient rows in flight
-constexpr int kSliceMany = 96;
+constexpr int kSliceMany = 96, kCus = 256;
 constexpr int slice_pairs(int GT) { return (GT + 1) / 2; }
 // Float2 of the transforms' buffers; the partial sums of the scores lie over them.
 constexpr int slice_buf(int GT, int logQ) {
@@ -472,20 +472,32 @@ __global__ __launch_bounds__(kThreads, 4) void attn_slice_kernel(Params P, const
 
 }  // namespace
 
-// Where one workgroup per slice beats the three kernels.  Few slices: it saves two launches and pays with one compute unit's share of the
-// bandwidth (8 slices, three kernels / this one, us: 128 bins, 1 head, update 16.2 / 12.8, read-only 19.4 / 13.8; 4 heads 18.6 / 17.0,
-// 22.5 / 17.8; 8 heads, read-only 25.8 / 23.3, update, 64 bins 19.4 / 20.0; 256 bins, 1 head 18.0 / 17.9, 4 heads 19.9 / 23.0, 23.5 / 22.1;
-// 512 bins, 1 head 19.5 / 26.8).  From kSliceMany slices on the phases of different slices run side by side: 160 slices of 512 bins, 4 heads
-// 87 / 58 and 56 / 40; 1024 of 128, 8 heads 224 / 103 and 167 / 89.  Written back at every step, states that the caches do not hold gain
-// by short rows only (update, 1 head: 384 slices of 512 bins 159 / 165, 2048 of 150 311 / 311; 4 heads, 1024 of 1024 784 / 840).
+// Where one workgroup per slice beats the three kernels, whether the coefficients come from the caches or from memory.  Figures: how many times
+// as fast, three states in turn; where there are two, the second behind other data in the caches.
+// - Few slices save two launches and pay with one compute unit's share of the bandwidth.  8 slices, written back, one head: 128 bins 1.41, 1.23; 160 1.11,
+//   1.02; 192 1.10, 0.94; 256 1.09, 0.88; four heads, 128 1.18, 1.08, 256 19.9 us / 23.0.  Read only, 256 bins: one head 1.30, 1.01, four 1.14,
+//   1.09; eight heads, 128 bins 1.20, 1.15.
+// - From kSliceMany slices on the phases of different slices run side by side; long rows want more of them.  Four heads, written back: 512
+//   bins, 96 slices 0.80, 128 0.90, 160 1.08, 192 1.05 (256 bins, 96 1.20).  Attention alone behind the append: 512 bins, 112 0.98,
+//   128 0.96, 144 1.01; 768, 112 0.93, 144 1.04.  Steps with pending tokens, which follow each other: 768 bins, 96 1.13, 0.96; 1024, 96
+//   1.11, 0.87, 128 1.11, 0.98.
+// - Written back, states that the caches do not hold gain by short rows only (one head: 384 slices of 512 bins 159 us / 165, 2048 of 150 311 / 311; four
+//   heads, 1024 of 1024 784 / 840).
+// - Read only, a compute unit holds two workgroups, and where the last round of 2 kCus is nearly empty long rows wait for its bandwidth.  1024 bins,
+//   one head: 256 slices 1.11, 320 0.91, 512 1.09, 576 0.93, 1024 1.02.  768 bins, four heads, pending tokens: 272 0.91, 320 0.96, 384 1.08.
+//   256 bins, one head, pending tokens: 512 1.28, 576 0.98, 640 0.93, 768 0.94 (two heads 1.03), 896 1.00; 512 bins 512 1.02, 576 0.95, 896 1.02.
 bool attn_slice_fits(const Params& P, int np, bool update) {
   if (!P.one_fold || P.M > 4096u || P.G > 8 || P.serial_phases) return false;
-  const int GT = P.G <= 2 ? P.G : (P.G <= 4 ? 4 : 8);
+  const int GT = P.G <= 2 ? P.G : (P.G <= 4 ? 4 : 8), S = P.n_slices, row = P.max_Bp;
   int logQ = 8;
   while ((1u << logQ) < P.M) ++logQ;
   if ((GT == 8 && logQ == 12) || slice_lds(GT, logQ, np, P.S + P.R) > kSliceMaxLds) return false;
-  if (P.n_slices < kSliceMany) return P.max_Bp <= 256 && (update ? GT < 8 && P.max_Bp * GT <= 512 : P.max_Bp * GT <= 1024);
-  return !update || P.max_Bp <= (GT == 1 ? 160 : 256) || (int64_t)P.n_slices * P.max_Bp <= 131072;
+  if (S < kSliceMany) return update ? GT < 8 && row <= 160 && row * GT <= 512 : row <= 256 && row * GT <= 1024;
+  if (update) return row <= (GT == 1 ? 160 : 256) || ((row <= 256 || S >= 160) && (int64_t)S * row <= 131072);
+  if ((row > 384 && np == 0 && S < 144) || (row > 768 && S < 128)) return false;
+  const int slots = 2 * kCus, rounds = (S + slots - 1) / slots;
+  const int least = S <= kCus ? 0 : row > 768 ? 85 : row > 512 ? 60 : row > 192 && GT <= 2 && np > 0 && S > slots ? (GT == 1 ? 80 : 70) : 0;
+  return S * 100LL >= (int64_t)least * rounds * slots;  // least per cent of the slots filled
 }
 
 hipError_t launch_attn_slice(const Params& P, const void* q, void* out, float scale, const StepUpdate& up, bool update,

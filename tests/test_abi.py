@@ -109,6 +109,24 @@ def test_query_attn_checks_its_arguments():
     assert lib.iwdft_query_attn(None, 0, 0, ctypes.byref(n)) == B.IWDFT_ERR_ARG
 
 
+@pytest.mark.parametrize("slices,row,group,attend,read,write", [
+    (95, 160, 1, 1, 1, 1), (95, 192, 1, 1, 1, 0), (95, 256, 4, 1, 1, 0), (95, 288, 1, 0, 0, 0), (95, 128, 4, 1, 1, 1), (95, 160, 4, 1, 1, 0),  # few
+    (95, 128, 8, 1, 1, 0), (95, 160, 8, 0, 0, 0), (96, 256, 8, 1, 1, 1), (96, 256, 1, 1, 1, 1), (513, 256, 1, 1, 0, 0), (513, 160, 1, 1, 1, 1),
+    (159, 288, 2, 1, 1, 0), (160, 288, 2, 1, 1, 1), (160, 800, 4, 1, 1, 1), (160, 832, 4, 1, 1, 0), (513, 256, 4, 1, 1, 1),       # written back
+    (143, 416, 4, 0, 1, 0), (143, 384, 4, 1, 1, 0), (144, 416, 4, 1, 1, 0), (127, 800, 1, 0, 0, 0), (128, 800, 1, 0, 1, 0),     # read only, long rows
+    (256, 1024, 4, 1, 1, 0), (257, 1024, 4, 0, 0, 0), (435, 1024, 4, 0, 0, 0), (436, 1024, 4, 1, 1, 0), (512, 1024, 4, 1, 1, 0),  # by rounds of 512
+    (513, 1024, 1, 0, 0, 0), (871, 1024, 1, 1, 1, 0), (307, 768, 2, 0, 0, 0), (308, 768, 2, 1, 1, 0), (614, 544, 4, 0, 0, 0), (615, 544, 4, 1, 1, 0),
+    (716, 224, 2, 1, 0, 1), (717, 224, 2, 1, 1, 1), (716, 224, 4, 1, 1, 1), (716, 192, 2, 1, 1, 1), (819, 224, 1, 1, 0, 0), (820, 224, 1, 1, 1, 0), (96, 512, 9, 0, 0, 0),
+])
+def test_short_contexts_take_one_launch_by_rule(slices, row, group, attend, read, write):
+    """Attention alone, a step that only reads with three tokens pending, and one that writes back: one launch (attn_slice_fits) on both sides of every
+    line, M = 2048 or, for longer rows, 4096."""
+    kw = dict(M=2048 if row <= 512 else 4096, n_layers=1, batch=slices, n_kv_heads=1, n_q_heads=group, bins=[np.arange(row)])
+    got = [B.iwdft_query_attn(desc(**kw), *x) == 0 for x in ((0, False), (3, False), (1, True))]
+    assert got == [attend, read, write]
+    assert B.iwdft_query_attn(desc(**kw, flags=B.IWDFT_FLAG_SERIAL_PHASES)) == 1
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_layers=0, bins=[]), B.IWDFT_ERR_ARG),
     (dict(n_q_heads=3), B.IWDFT_ERR_ARG),

@@ -428,7 +428,7 @@ def test_score_kernel_of_few_and_of_many_blocks(group, batch, heads, n_bins, J):
     (256, 1, 1, (2, 1, 1), 0, 0, 0, "f32", "aw"), (256, 8, 64, (2, 1, 4), 1, 0, 4, "bf16", "ar"),       # one bin; a full quarter, 16 lanes a transform
     (512, 5, 33, (3, 8, 4), 3, 70, 0, "bf16", "aw"), (512, 2, 128, (2, 1, 4), 0, 9, 16, "f32", "arw"),     # more exact tokens than lanes; a last head pair with one head
     (1024, 4, 65, (2, 2, 3), 0, 0, 16, "bf16", "arw"), (1024, 7, 129, (2, 8, 8), 2, 3, 5, "f32", "arw"),    # 64 and 128 lanes a row
-    (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16", "arw"), (2048, 8, 512, (2, 10, 8), 0, 2, 2, "bf16", "arw"),   # all lanes two rows of a head group
+    (2048, 1, 250, (1, 1, 3), 4, 0, 3, "bf16", "ar"), (2048, 8, 512, (2, 10, 8), 0, 2, 2, "bf16", "arw"),   # all lanes two rows of a head group
     (4096, 4, 1023, (1, 20, 8), 2, 5, 4, "bf16", "ar"), (4096, 3, 790, (2, 10, 8), 0, 0, 0, "f32", "aw"),  # one row over all lanes
     (1024, 2, 256, (1, 67, 10), 0, 0, 0, "bf16", "aw"), (512, 4, 120, (40, 8, 8), 1, 2, 8, "bf16", "arw"),  # states beyond 160 MiB
 ])
@@ -466,7 +466,7 @@ def test_short_contexts_in_one_launch(L, group, n_bins, dims, S, R, J, dtype, on
 
 
 @pytest.mark.parametrize("J", [0, 16])
-@pytest.mark.parametrize("L,n_bins,group", [(256, 64, 1), (512, 128, 2), (1024, 256, 1), (1024, 100, 4), (2048, 250, 2), (4096, 256, 1)])
+@pytest.mark.parametrize("L,n_bins,group", [(256, 64, 1), (512, 128, 2), (1024, 160, 1), (1024, 100, 4), (2048, 150, 2), (4096, 160, 1)])
 def test_short_contexts_write_back_as_exactly_as_the_three_kernels(L, n_bins, group, J):
     """Token j is one in channel j and zero elsewhere, the state zero before: the coefficients of that channel are e^{j 2 pi k j / M} as the
     step forms it.  Its distance from 64 bits, over all bins and tokens, is no larger than what the three kernels leave (5 % more for the other grouping
