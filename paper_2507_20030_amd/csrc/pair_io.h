@@ -134,9 +134,9 @@ constexpr uint64_t side_pairs_min(int logQ) { return logQ == 10 ? 768 : 256; }
 // to themselves.  Us, one / two transforms, by rounds: prefill 1 42 / 36, 1.5 59 / 66, 2 78 / 71, 2.5 122 / 130, 3.5 165 / 171, 8.5 332 / 340, 16
 // 724 / 663; fp32 1 31 / 24, 3 77 / 71, 16 532 / 521; reconstruction 1.5 75 / 87, 2 90 / 84, 3 157 / 139, 4 230 / 223; ablation fp32 4 253 / 230
 // (bf16, 2: 161 / 157 and 169 / 174, so it stays with one).
+constexpr int64_t kTwoRound = 32;  // workgroups that an XCD runs at a time
 inline bool two_transforms(int64_t blocks) {
-  constexpr int64_t kCus = 32;  // of an XCD
-  return blocks >= kCus && (blocks + kCus - 1) / kCus * kCus * 20 <= blocks * 21;
+  return blocks >= kTwoRound && (blocks + kTwoRound - 1) / kTwoRound * kTwoRound * 20 <= blocks * 21;
 }
 
 // f32_to_bf16 of both (the hardware conversion rounds to nearest even and keeps NaN, bit for bit the same).

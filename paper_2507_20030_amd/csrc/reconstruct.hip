@@ -213,8 +213,11 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
   // the pairs spread over more workgroups then
   const bool wide = (((uintptr_t)Kt | (uintptr_t)Vt) & 15u) == 0 &&
                     (uint64_t)n_st * (kRecPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
-  // longer ones gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310; 32, M = 16384, 2048 bins 266 / 252)
-  const bool two = logQ == 13 && P.M <= 16384 && two_transforms((int64_t)per_xcd * (kRecPairs / (BF16 ? 8 : 4)));
+  // One / two transforms a workgroup, three outputs in turn: M = 16384, bf16, 16 slices, 1024 to 4096 bins 1.0 to 1.2 times as fast, 32 1.03 to 1.1, fp32 8 to 64
+  // 1.0 to 1.4; longer ones gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310).  One round of workgroups only (bf16, 16
+  // slices, M = 8192) has nothing to hide the gather behind: 1500 bins 1.12, 1900 1.01 (behind other data in the caches 0.91), 2000 0.95, 2048 53 / 60.
+  const int64_t blocks = (int64_t)per_xcd * (kRecPairs / (BF16 ? 8 : 4));
+  const bool two = logQ == 13 && P.M <= 16384 && two_transforms(blocks) && !(BF16 && P.M == 8192 && blocks <= kTwoRound && P.max_nb > 1792);
   hipError_t e = hipSuccess;
 #define IWDFT_RC_LAUNCH(LQ, MULTI, NP, TWO)                                                             \
   {                                                                                                     \
