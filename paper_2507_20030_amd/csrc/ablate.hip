@@ -27,7 +27,7 @@ constexpr int kCusPerXcd = 32;
 // starts and the inverse one ends in registers, so samples cross LDS only inside the transforms; results take the place of
 // the inputs in the loaded words.  Only the chunk's entries and their mirrors are weighed.  64 slices of 8192 tokens, bf16:
 // 310 -> 167 us (0.27 GB read and written: 1.6 TB/s); what is left is the vector arithmetic of the two transforms.
-// TWO (8192 points): two transforms by 1024 threads, see prefill_fft.hip.
+// TWO (8192 points, fp32): two transforms by 1024 threads, see prefill_fft.hip.
 template <int LOGQ, bool BF16, int NP, bool TWO = false>
 __global__ __launch_bounds__(side_threads(LOGQ, TWO), 4) void ablate_kernel(const char* __restrict__ x, char* __restrict__ out,
                                                        const float2* __restrict__ tabs, int n_slices, int per_xcd, int lo,
@@ -203,7 +203,7 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
   const bool aligned = (((uintptr_t)x | (uintptr_t)out) & 15u) == 0;
   const bool wide = aligned && (uint64_t)n_slices * (kAbPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
   const bool two = aligned && (int64_t)per_xcd * (kAbPairs / 2) >= kCusPerXcd * side_ns(logQ);
-  const bool side = logQ == 13 && !BF16 && two_transforms((int64_t)per_xcd * (kAbPairs / (BF16 ? 8 : 4)));
+  const bool side = logQ == 13 && !BF16 && two_transforms((int64_t)per_xcd * (kAbPairs / 4));
   const float2* tab = nullptr;
   hipError_t e = fft_table(&tab);
   if (e != hipSuccess) return e;
@@ -221,7 +221,7 @@ static hipError_t launch_ablate_t(const void* x, void* out, int n_slices, int lo
 #define IWDFT_AB_CASE(LQ)                                                             \
   {                                                                                   \
     constexpr int kNp = side_pairs(LQ, BF16), kTwo = LQ < 12 ? 1 : 2;                 \
-    if (wide && side) IWDFT_AB_LAUNCH(LQ, kNp, LQ == 13)                              \
+    if (wide && side) IWDFT_AB_LAUNCH(LQ, kNp, LQ == 13 && !BF16)                     \
     else if (wide) IWDFT_AB_LAUNCH(LQ, kNp, false)                                    \
     else if (two) IWDFT_AB_LAUNCH(LQ, kTwo, false)                                    \
     else IWDFT_AB_LAUNCH(LQ, 1, false)                                                \

@@ -1090,7 +1090,7 @@ def test_fft_prefill_all_transform_lengths(dtype, L, S, R, n_bins):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_bins", [300, 2048])
 def test_two_transforms_of_8192_points_in_a_workgroup_give_the_same_bits(dtype, n_bins):
-    """Prefill, reconstruction and ablation of as many slices as fill whole rounds of workgroups of 1024 threads (two_transforms in
+    """Prefill, reconstruction and, in fp32, ablation of as many slices as fill whole rounds of workgroups of 1024 threads (two_transforms in
     pair_io.h) against the same slices a few at a time, which run one transform per workgroup: the same arithmetic."""
     cfg = small_cfg(L=8192, group=2, dtype=dtype, n_bins=n_bins, n_layers=1, batch=4, n_kv_heads=8)
     bins = [np.sort(np.random.default_rng(n_bins).choice(8192, size=n_bins, replace=False)).astype(np.int32)]
