@@ -89,6 +89,7 @@ constexpr int64_t kFftMaxQ = 8192;  // longest transform the FFT attention kerne
 constexpr int64_t kChirpMinM = 32, kChirpMaxM = 8192;  // chirp-z transforms: 2 Q - 1 <= 16384 points fit in LDS
 // grid points that take as long as one token of the contraction: bf16, fp32, grids of up to 4096 points and longer ones
 constexpr int64_t kAnyPrefillPoints[2][2] = {{180, 160}, {250, 185}};
+constexpr int64_t kAnyUnevenPoints = 140;  // bf16, longer grids, blocks that do not divide M
 constexpr int64_t kAnyMaxPeriod = 65536;  // ... most frequencies with taps of their own (48 bytes each) where the blocks do not divide M
 constexpr int64_t kDeferMinRows = 49152;  // fewest coefficient rows (slices x padded bins) of a deferred write-back, chirp-z
 constexpr int64_t kChirpMaxBlocks = 256;  // most decimated blocks M / Q of the chirp-z attention
@@ -315,22 +316,35 @@ int make_plan(const iwdft_desc* d, Plan* pl) {
   // M = 4036, 256 slices, 384 bins (173) 569 / 641; M = 8132, 64 slices, 512 bins (129) 462 / 348, 256 slices, 384 bins (172) 1111 / 1350;
   // fp32 M = 5000, 64 slices, 128 bins (210) 399 / 377; M = 6000, 256 slices, 384 bins (233) 1418 / 1619; M = 24573, 96 slices, 256 bins (197)
   // 1915 / 2300; M = 8132, 96 slices, 128 bins (193) 646 / 723.  Blocks of a few points only stay with the contraction.
-  // The number of blocks of a longer M need not divide it: the frequencies lie anywhere on the grid, and M is cut into the blocks of the fewest
-  // points in all (70 x 8 slices, M = 14473 = 41 x 353, 1978 bins: 41 blocks 27.0 ms, 2 7.1; 4 x 8, fp32, M = 25419 = 37 x 687, 4096 bins: 37 6.4, 7 1.4).
+  // The number of blocks of a longer M need not divide it: the frequencies lie anywhere on the grid, and M is cut into the blocks that cost
+  // least (70 x 8 slices, M = 14473 = 41 x 353, 1978 bins: 41 blocks 27.0 ms, 2 7.1; 4 x 8, fp32, M = 25419 = 37 x 687, 4096 bins: 37 6.4, 7 1.4).  Costs in per cent of a
+  // point of the longest grid, fitted to 2300 sets of times (190 lengths from 8200 to 65500, 8 to 384 slices, 64 to 4096 bins): a point of a grid of 2^10 .. 2^14 (kPointCost: full device;
+  // fewer slices, bf16 and fp32), a bin per block (kBinCost: blocks that divide M; that do not, where the phase takes 64 bits and the taps are those of `period` frequencies, more by
+  // 1.2 period / 65536).  Next to the blocks that divide M three sets of a thousand lose 3 % or more, none 7 %; all in all 1.21 times as fast.
+  // M = 62811, bf16, 96 slices, 4096 bins 9 even blocks 6.57 ms, 8 uneven 9.64, 1024 bins 4.79, 5.03, 512 bins 4.50, 4.27; fp32, M = 14473, 64
+  // bins, 32 slices 2 blocks 384 us, 4 342, 8 265, 15 262, 8 slices 105, 94, 98, 102.
   if (pl->use_chirp && pl->chirp_Q > kFftMinM && !(d->flags & IWDFT_FLAG_DENSE_PREFILL)) {
-    int64_t points = 0;
+    static constexpr int kPointCost[3][5] = {{85, 78, 80, 88, 100}, {160, 140, 125, 140, 100}, {175, 120, 105, 90, 100}};
+    static constexpr int kBinCost[2][2] = {{300, 325}, {225, 225}};
+    const int *point = kPointCost[S >= 16 ? 0 : b16 ? 1 : 2], *bin = kBinCost[b16 ? 0 : 1];
+    int64_t least = 0, points = 0;
     for (int64_t pb = (d->M + kChirpMaxM - 1) / kChirpMaxM; pb <= d->M / pl->chirp_Q; ++pb) {
       const int64_t A = (d->M + pb - 1) / pb, g = std::gcd(d->M, pb);
       if (A <= kFftMinM) break;
-      if (g != pb && d->M / g > kAnyMaxPeriod) continue;
+      const int64_t bins = pb > 1 ? pl->max_nb : 0, period = d->M / g;
+      if (g != pb && period > kAnyMaxPeriod) continue;
       int logN = 10;
       while (((int64_t)1 << logN) < 2 * A) ++logN;
-      const int64_t n = pb * (((int64_t)1 << logN) + (pb > 1 ? pl->max_nb * 3 / 2 : 0));
-      if (points && n >= points) continue;
-      points = n;
-      pl->pf_logN = logN, pl->pf_Pb = pb, pl->pf_A = A, pl->pf_period = d->M / g;
+      const int64_t cost = pb * (((int64_t)point[logN - 10] << logN) + bins * (g == pb ? bin[0] : bin[1] + bin[1] * period * 6 / (5 * 65536)));
+      if (least && cost >= least) continue;
+      least = cost;
+      points = pb * (((int64_t)1 << logN) + bins * (g == pb ? 3 : 5) / 2);
+      pl->pf_logN = logN, pl->pf_Pb = pb, pl->pf_A = A, pl->pf_period = period;
     }
-    pl->use_any_prefill = S * points <= kAnyPrefillPoints[b16 ? 0 : 1][pl->pf_logN > 12 ? 1 : 0] * d->M * rounds;
+    // uneven blocks on long grids in bf16 lose earlier (points per token and round: M = 37492, 64 slices, 92 bins (142) 1610 / 1709; M = 13827, 87 bins (154) 604 / 643;
+    // M = 31870, 200 bins (136) 1.01 times as fast; fp32 M = 24582, 128 slices, 384 bins (181) 1.27)
+    const int64_t line = b16 && pl->pf_logN > 12 && d->M % pl->pf_Pb ? kAnyUnevenPoints : kAnyPrefillPoints[b16 ? 0 : 1][pl->pf_logN > 12 ? 1 : 0];
+    pl->use_any_prefill = S * points <= line * d->M * rounds;
   }
 
   // Decode attention of low frequencies (attn_low_kernel) on the smallest grid that carries them, from four tokens per point on (read-only

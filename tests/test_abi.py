@@ -127,6 +127,19 @@ def test_short_contexts_take_one_launch_by_rule(slices, row, group, attend, read
     assert B.iwdft_query_attn(desc(**kw, flags=B.IWDFT_FLAG_SERIAL_PHASES)) == 1
 
 
+@pytest.mark.parametrize("M,n_bins,heads,dtype,logn,period", [
+    (62811, 4096, 96, B.IWDFT_BF16, 14, 6979), (62811, 512, 96, B.IWDFT_BF16, 14, 62811),   # 9 even blocks; 8 uneven ones
+    (24582, 2048, 8, B.IWDFT_BF16, 14, 12291), (65541, 2048, 8, B.IWDFT_F32, 14, 21847),    # 4 and 9 blocks: two and three of them in common with M
+    (14473, 64, 32, B.IWDFT_F32, 11, 14473), (14473, 2000, 96, B.IWDFT_BF16, 14, 14473),    # more blocks on a shorter grid; two
+    (37492, 92, 64, B.IWDFT_BF16, 0, 0), (13827, 87, 64, B.IWDFT_BF16, 0, 0), (31870, 200, 64, B.IWDFT_BF16, 14, 15935),  # the contraction; four blocks
+])
+def test_prefill_of_other_lengths_takes_the_blocks_by_rule(M, n_bins, heads, dtype, logn, period):
+    """The workspace holds 1 / W of the grid and ten taps for every frequency up to half a period."""
+    kw = dict(M=M, n_layers=1, n_kv_heads=heads, n_q_heads=heads, kv_dtype=dtype, bins=[np.arange(n_bins)])
+    ws, dense = (B.iwdft_query_bytes(desc(**kw, flags=f))[1] for f in (0, B.IWDFT_FLAG_DENSE_PREFILL))
+    assert ws - dense == (padded(4 * 2 ** logn // 2, 48 * (period // 2 + 1)) if logn else 0)
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_layers=0, bins=[]), B.IWDFT_ERR_ARG),
     (dict(n_q_heads=3), B.IWDFT_ERR_ARG),
