@@ -1225,8 +1225,9 @@ def test_chirp_prefill_all_convolution_lengths(dtype, L, S, R, n_bins, n_layers)
     assert st["coef0"] < 2e-5
 
 
-@pytest.mark.parametrize("L", [259, 511, 513, 1000, 2047, 2049, 4095, 4097, 8191, 2 * 6144, 3 * 8192, 3 * 8191,
-                               9 * 931, 41 * 353, 37 * 687, 11 * 2971, 5 * 8191, 13 * 5039])  # blocks that do not divide L, last ones one sample shorter
+@pytest.mark.parametrize("L", [259, 511, 513, 1000, 2047, 2049, 4095, 4097, 8191, 2 * 6144, 3 * 8192, 3 * 8191, 9 * 931, 5 * 8191,
+                               41 * 353, 37 * 687, 11 * 2971, 13 * 5039,  # 2, 7, 4 and 8 blocks that do not divide L, last ones one sample shorter
+                               24582, 65541, 63012])  # ... 4, 9 and 8, which have 2, 3 and 4 in common with L: taps for a part of the frequencies
 def test_interpolated_prefill_against_64_bit_transforms(L):
     """Every grid length at both ends of its range (L / 2 up to a power of two: the widest and the closest spacing of the taps; 24576
     = 3 x 8192: taps on grid points), a layer of low bins and one of bins anywhere.  Bar: aliasing 2e-8 + fp32 rounding, which grows
