@@ -111,35 +111,38 @@ constexpr int64_t tap_floats(int taps) { return taps > 8 ? 12 : 10; }  // of one
 // Low frequencies repeat the two transforms in every part: grids of 16384 points, M = 131072, 16 pairs 109 / 95, 64 134 / 120, two parts for 128
 // pairs 268 / 268; shorter grids slow down beside each other: 8192 points, M = 65536, 8 pairs 59 / 53, 504 workgroups for 72 pairs 106 / 111;
 // 4096 points, M = 65536, 8 pairs 49 / 39; four tokens per grid point gain on 16384 points only (M = 32768, 8 pairs 50 / 50, 32 64 / 64).
-int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws, int* reserve) {
-  *reserve = 1;
-  int64_t units, slots, least = 2;  // what can be shared out, workgroups at a time, fewest parts that pay
-  if (pl.use_fft && M > kFftMaxQ) {
-    const int per_thread = (pl.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
-    if (pl.low_logN) {
-      units = M >> pl.low_logN;
-      slots = pl.low_logN < kLowMaxLogN || units < 8 ? kCus / 2 : kCus;
-      least = 3;
-      if (units < 8 && pl.low_logN < kLowMaxLogN) units = 1;
-    } else {
-      units = M / kFftMaxQ;
-      slots = units == 2 ? kCus / 2 : per_thread > 4 && per_thread <= 8 ? kCus : 2 * kCus;
-    }
-  } else if (pl.use_chirp && M > pl.chirp_Q) {
-    units = M / pl.chirp_Q;
-    slots = (int64_t)kCus << std::min(kTabMaxLogQ - pl.chirp_logN, 4);
-  } else {
-    return 1;
-  }
-  const int64_t blocks = slices * ((pl.G + 1) / 2);
-  const int64_t room = std::min<int64_t>(kPartBytes / (int64_t)(sizeof(float2) * (size_t)ws), kMaxParts);
+int64_t parts_of(int64_t units, int64_t slots, int64_t blocks, int64_t room, int64_t least) {
   const int64_t n = std::min(std::min(units, room), slots / blocks);
-  // M = 2^m: the same room whichever bins are kept
-  const int64_t most = pl.use_fft ? std::min(std::min(M >> kLowMinLogN, room), 2 * kCus / blocks) : n;
-  *reserve = (int)std::max<int64_t>(most, 1);
   if (n < least) return 1;
   const int64_t share = (units + n - 1) / n;
-  return (int)((units + share - 1) / share);  // no more than the longest share asks for
+  return (units + share - 1) / share;  // no more than the longest share asks for
+}
+// M = 2^m > kFftMaxQ, on a grid of 2^low_logN points or (0) in blocks of kFftMaxQ.
+int64_t fft_parts(const Plan& pl, int64_t M, int low_logN, int64_t blocks, int64_t room) {
+  if (!low_logN) {
+    const int per_thread = (pl.max_Bp + fft_threads(kFftMaxLogQ) - 1) / fft_threads(kFftMaxLogQ);
+    return parts_of(M / kFftMaxQ, M / kFftMaxQ == 2 ? kCus / 2 : per_thread > 4 && per_thread <= 8 ? kCus : 2 * kCus, blocks, room, 2);
+  }
+  const int64_t units = M >> low_logN;  // tokens behind a grid point
+  if (units < 8 && low_logN < kLowMaxLogN) return 1;
+  return parts_of(units, low_logN < kLowMaxLogN || units < 8 ? kCus / 2 : kCus, blocks, room, 3);
+}
+int softmax_parts(const Plan& pl, int64_t M, int64_t slices, int64_t ws, int* reserve) {
+  *reserve = 1;
+  const int64_t blocks = slices * ((pl.G + 1) / 2);
+  const int64_t room = std::min<int64_t>(kPartBytes / (int64_t)(sizeof(float2) * (size_t)ws), kMaxParts);
+  if (pl.use_fft && M > kFftMaxQ) {
+    // the same room whichever bins are kept, as long as the rows are: what the most parts of the grids that could carry rows this long take
+    int64_t most = fft_parts(pl, M, 0, blocks, room);
+    for (int logN = kLowMinLogN; logN <= kLowMaxLogN; ++logN)
+      if ((M >> logN) >= kLowMinD && (M >> logN) <= kLowMaxD && 4 * (int64_t)(pl.max_nb - 1) <= ((int64_t)1 << logN))
+        most = std::max(most, fft_parts(pl, M, logN, blocks, room));
+    *reserve = (int)most;
+    return (int)fft_parts(pl, M, pl.low_logN, blocks, room);
+  }
+  if (pl.use_chirp && M > pl.chirp_Q)
+    *reserve = (int)parts_of(M / pl.chirp_Q, (int64_t)kCus << std::min(kTabMaxLogQ - pl.chirp_logN, 4), blocks, room, 2);
+  return *reserve;
 }
 size_t stats_bytes(const Plan& pl, int64_t slices, int parts) { return sizeof(float4) * (size_t)(slices * ((pl.G + 1) / 2) * parts); }
 // The parts' buffers at `rows` and `stats`.

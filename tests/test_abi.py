@@ -140,6 +140,24 @@ def test_prefill_of_other_lengths_takes_the_blocks_by_rule(M, n_bins, heads, dty
     assert ws - dense == (padded(4 * 2 ** logn // 2, 48 * (period // 2 + 1)) if logn else 0)
 
 
+@pytest.mark.parametrize("M,n_bins,heads,group,low,mixed", [
+    (131072, 4096, 8, 4, 8, 16), (131072, 1000, 8, 4, 8, 16), (131072, 4096, 64, 4, 1, 2), (65536, 4096, 8, 4, 4, 8), (65536, 1024, 2, 1, 16, 8),
+    (32768, 2048, 8, 4, 1, 4), (32768, 1000, 2, 4, 8, 4), (16384, 1000, 8, 4, 1, 2), (16384, 1000, 128, 2, 1, 1), (262144, 4096, 4, 1, 16, 32),
+    (524288, 4096, 4, 1, 64, 64), (3 * 8191, 2000, 8, 4, 3, 3), (8192, 2000, 8, 4, 1, 1),
+])
+def test_workspace_holds_the_parts_of_a_softmax_and_no_more(M, n_bins, heads, group, low, mixed):
+    """Rows and statistics of as many parts as low bins or bins up to M / 2 take, whichever are more (the room does not depend on which bins a
+    row of that length holds); IWDFT_FLAG_SERIAL_PHASES, with one part, needs none."""
+    kw = dict(M=M, n_layers=1, n_kv_heads=heads, n_q_heads=heads * group)
+    for bins, parts in ((np.arange(n_bins), low), (np.r_[np.arange(n_bins - 1), M // 2], mixed)):
+        d, serial = desc(bins=[bins], **kw), desc(bins=[bins], **kw, flags=B.IWDFT_FLAG_SERIAL_PHASES)
+        assert B.iwdft_query_attn(d) == parts and B.iwdft_query_attn(serial) == 1
+        room = max(low, mixed)
+        rows = 8 * heads * group * (-(-n_bins // 32) * 32)
+        want = padded(rows * room, 16 * heads * ((group + 1) // 2) * room) if room > 1 else 0
+        assert B.iwdft_query_bytes(d)[1] - B.iwdft_query_bytes(serial)[1] == want
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_layers=0, bins=[]), B.IWDFT_ERR_ARG),
     (dict(n_q_heads=3), B.IWDFT_ERR_ARG),
