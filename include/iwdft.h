@@ -237,7 +237,8 @@ int compressed_decode_attn(iwdft_ctx* ctx, const void* d_q, void* d_out, float s
 
 /* compressed_decode_attn for callers that cannot allocate device memory or hand over a workspace at the time
  * of the call (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * kernels and the same result, but the intermediate arrays (the q.F_K rows, the softmax-weight rows, the scores
+ * kernels and the same result, bit for bit -- up to rounding where several workgroups share the softmax of a pair of heads (iwdft_query_attn) and the
+ * array below has room for fewer of them -- but the intermediate arrays (the q.F_K rows, the softmax-weight rows, the scores
  * of the exact tokens; the score rows of the direct synthesis) live in a scratch array that is part of the
  * library's code object -- IWDFT_STATIC_SCRATCH_BYTES per GPU, held until the process ends -- instead of the
  * context's workspace.  Calls no hipMalloc / hipFree or any other allocating routine.  Returns IWDFT_ERR_SIZE

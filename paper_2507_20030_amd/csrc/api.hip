@@ -1004,15 +1004,20 @@ int compressed_decode_attn_static(iwdft_ctx* ctx, const void* d_q, void* d_out, 
   if (need > kStaticScratchBytes)
     return fail(IWDFT_ERR_SIZE, "compressed_decode_attn_static needs %zu bytes of scratch, the library holds %zu", need,
                 kStaticScratchBytes);
-  // ... and the parts of the softmax; where they do not fit, one workgroup per pair of heads does all of it (equal up to rounding).
+  // ... and as many parts of the softmax as there is room for (two of low frequencies do not pay, see softmax_parts); equal up to rounding whatever their number.
   Parts parts;
-  const size_t part_bytes = align256(sizeof(float2) * (size_t)pl.ws_total * (size_t)pl.parts);
-  const bool split = pl.parts > 1 && need + part_bytes + stats_bytes(pl, ctx->P.n_slices, pl.parts) <= kStaticScratchBytes;
+  const auto end_of = [&](int n) { return need + align256(rows * (size_t)n) + stats_bytes(pl, ctx->P.n_slices, n); };
+  int n_parts = pl.parts;
+  while (n_parts > 1 && end_of(n_parts) > kStaticScratchBytes) --n_parts;
+  if (n_parts < (pl.use_fft && pl.low_logN ? 3 : 2)) n_parts = 1;
   char* sc = nullptr;
   if ((rc = static_scratch(ctx->device, &sc)) != IWDFT_OK) return rc;
   if ((rc = flush_pending(ctx, (hipStream_t)hip_stream)) != IWDFT_OK) return rc;
   set_read_gain(ctx);
-  if (split) parts = parts_at(pl, sc + need, sc + need + part_bytes);
+  if (n_parts > 1) {
+    parts = parts_at(pl, sc + need, sc + need + align256(rows * (size_t)n_parts));
+    parts.n = n_parts;
+  }
   // Every entry of the arrays is written by the kernels before it is read, so nothing needs clearing
   // although the scratch still holds the previous call's contents.
   return launched(launch_attn(ctx->P, d_q, d_out, scale, (float2*)sc, (float2*)(sc + rows), (float*)(sc + 2 * rows),

@@ -75,3 +75,33 @@ def test_static_scratch_direct_synthesis_and_size_limit():
         B.compressed_decode_attn_static(cache.ctx, q, torch.empty_like(q))
     assert ei.value.code == B.IWDFT_ERR_SIZE
     cache.close()
+
+
+@pytest.mark.parametrize("L,heads,group,n_bins,parts", [
+    (32768, 4, 4, 1500, 4), (131072, 8, 2, 4000, 8),  # blocks of 8192 tokens; low frequencies
+    (2 * 8162, 2, 3, 2000, 2),                          # chirp-z blocks
+])
+def test_static_scratch_shares_the_softmax_as_the_workspace_form_does(L, heads, group, n_bins, parts):
+    cfg = wl.Config("na_parts", 1, 1, heads, group, 128, L, n_bins, 4, "f32", "low" if parts == 8 else "mixed", n_sink=3, n_recent=2, seed=15)
+    c = _ready_cache(cfg)
+    assert B.iwdft_query_attn(c.desc) == parts
+    for step in (3, 4):
+        _both(c, cfg, step)
+    c.close()
+
+
+def test_static_scratch_takes_fewer_workgroups_where_it_holds_no_more():
+    """16 slices of 4 heads, 24576 bins: 12 MiB a row set, two of them taken, so three parts fit of the workspace form's four.  The same sums in
+    another order: 1e-5 (scores of magnitude 50 times 2^-23)."""
+    rng = np.random.default_rng(16)
+    bins = [np.sort(rng.choice(65536, 24576, replace=False)).astype(np.int32)]
+    c = B.Cache(1, 2, 8, 32, 128, torch.float32, 65536, bins, device=DEV)
+    assert B.iwdft_query_attn(c.desc) == 4
+    K, V = torch.randn((2, 1, 2, 8, 65536, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(17))
+    c.prefill(K, V)
+    q = torch.randn((1, 2, 32, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(18))
+    ref, got = c.attend(q), torch.full_like(q, float("nan"))
+    B.compressed_decode_attn_static(c.ctx, q, got)
+    assert torch.isfinite(got).all()
+    assert 0 < float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+    c.close()
