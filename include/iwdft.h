@@ -114,11 +114,12 @@ enum {
                                        of any layer above min(M / 16, 4096)).  Same
                                        arithmetic, same results bit for bit.  Short contexts (M = 2^m <= 4096,
                                        no layer with more than M / 4 bins, no bin kept beside
-                                       its mirror, up to 8 query heads per KV head) run as one
-                                       launch where that is faster, and several workgroups
-                                       share the softmax of few slices of a long context
-                                       (M > 8192), both equal up to rounding; the flag keeps
-                                       them to the three kernels.                          */
+                                       its mirror, up to 8 query heads per KV head, 4 at
+                                       M = 4096) run as one launch where that is faster, and
+                                       several workgroups share the softmax of few slices of a
+                                       long context (M > 8192), their sums joined by one more
+                                       launch, both equal up to rounding (iwdft_query_attn
+                                       tells); the flag keeps them to the three kernels.   */
 };
 
 typedef struct {
@@ -199,8 +200,8 @@ int iwdft_attn_kind(const iwdft_ctx* ctx);
 
 /* Whether decode attention on this context (Sec. 4.2.2 "Calculating Attention") walks the slices in groups, with
  * the transforms of one group in the same launches as the K-coefficient stream of the next (see
- * IWDFT_FLAG_SERIAL_PHASES for the conditions): 1 = yes, 0 = the three kernels run one after the other;
- * -1 if ctx is NULL.  Results are identical either way; with 1 the marks of iwdft_phase_timing cannot separate
+ * IWDFT_FLAG_SERIAL_PHASES for the conditions): 1 = yes, 0 = no: kernels that run one after the other, or all in one launch (iwdft_query_attn);
+ * -1 if ctx is NULL.  Results are identical with and without groups; with 1 the marks of iwdft_phase_timing cannot separate
  * the first two kernels (their time is reported as phase 0, phase 1 reads ~0); nor can they for short contexts that run as
  * one launch (all of it phase 0). */
 int iwdft_attn_pipelined(const iwdft_ctx* ctx);

@@ -106,7 +106,7 @@ constexpr int64_t tap_floats(int taps) { return taps > 8 ? 12 : 10; }  // of one
 // Workgroups per pair of query heads in the softmax: where one each leaves the chip idle they share the blocks of a long context (low
 // frequencies: the tokens behind every grid point), as many as the device holds at a time.  What they save in blocks they pay with the launch of
 // attn_merge_kernel and its trip over their rows.  Decode step, 16 deferred, one workgroup / shared, us: two blocks (M = 16384), 16 pairs of heads
-// 48.7 / 45.8, 64 63.8 / 62.1, 128 132.8 / 138.2; more blocks, M = 65536, 4096 bins, 32 pairs 146 / 89, 128 283 / 252; M = 131072, 1500 bins, 64 pairs
+// 48.7 / 45.8, 64 63.8 / 62.1, 128 132.8 / 138.2; more blocks, M = 65536, 4096 bins, 32 pairs (16 slices of 4 heads) 136 / 86, (32 of 2) 150 / 99, 128 283 / 252; M = 131072, 1500 bins, 64 pairs
 // 199 / 93, 256 242 / 215; chirp-z, M = 32708, 2040 bins, 32 pairs 160 / 83, 96 219 / 164; M = 25419 (37 blocks of 687), 20 pairs 3882 / 1183.
 // Low frequencies repeat the two transforms in every part: grids of 16384 points, M = 131072, 16 pairs 109 / 95, 64 134 / 120, two parts for 128
 // pairs 268 / 268; shorter grids slow down beside each other: 8192 points, M = 65536, 8 pairs 59 / 53, 504 workgroups for 72 pairs 106 / 111;
