@@ -213,11 +213,14 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
   // the pairs spread over more workgroups then
   const bool wide = (((uintptr_t)Kt | (uintptr_t)Vt) & 15u) == 0 &&
                     (uint64_t)n_st * (kRecPairs / 4) >= side_pairs_min(logQ) * (uint64_t)side_ns(logQ);
-  // One / two transforms a workgroup, three outputs in turn: M = 16384, bf16, 16 slices, 1024 to 4096 bins 1.0 to 1.2 times as fast, 32 1.03 to 1.1, fp32 8 to 64
-  // 1.0 to 1.4; longer ones gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310).  One round of workgroups only (bf16, 16
-  // slices, M = 8192) has nothing to hide the gather behind: 1500 bins 1.12, 1900 1.01 (behind other data in the caches 0.91), 2000 0.95, 2048 53 / 60.
+  // One / two transforms a workgroup.  Longer contexts than 16384 gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310 us).  One round of
+  // workgroups only (bf16: 16 slices) has nothing to hide the gather behind: M = 8192, 1500 bins 1.12 times as fast, 1900 1.01 (behind other data
+  // in the caches 0.91), 2000 0.95, 2048 53 / 60; M = 16384, 1024 bins 1.01, 1.05, 1500 121 / 130, 2402 135 / 146, 4096 151 / 159, low and mixed
+  // masks alike (the first outputs of a context 138 / 135, 160 / 154, 187 / 175; three outputs in turn 1.0 to 1.2 times as fast).  Two rounds and more gain: M = 16384, 32 slices, 1024 bins 248 / 234, 2402
+  // 282 / 275, 4096 323 / 298; so does fp32, 8 slices, 1024 bins 77 / 72, 1800 88 / 86, 2402 to 4096 0.99 to 1.00, 16 slices, 2481 bins 209 / 195.
   const int64_t blocks = (int64_t)per_xcd * (kRecPairs / (BF16 ? 8 : 4));
-  const bool two = logQ == 13 && P.M <= 16384 && two_transforms(blocks) && !(BF16 && P.M == 8192 && blocks <= kTwoRound && P.max_nb > 1792);
+  const bool one_round = BF16 && blocks <= kTwoRound && P.max_nb > (P.M == 8192 ? 1792 : 1024);
+  const bool two = logQ == 13 && P.M <= 16384 && two_transforms(blocks) && !one_round;
   hipError_t e = hipSuccess;
 #define IWDFT_RC_LAUNCH(LQ, MULTI, NP, TWO)                                                             \
   {                                                                                                     \

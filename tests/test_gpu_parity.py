@@ -1116,6 +1116,32 @@ def test_two_transforms_of_8192_points_in_a_workgroup_give_the_same_bits(dtype, 
     b.close()
 
 
+@pytest.mark.parametrize("dtype,batch", [("bf16", 2), ("f32", 1), ("bf16", 4)])
+@pytest.mark.parametrize("n_bins", [1024, 1025, 4000])
+def test_reconstruction_of_two_blocks_with_two_transforms_gives_the_same_bits(dtype, batch, n_bins):
+    """16384 slots, one round of workgroups at both sides of the row length up to which bf16 takes two transforms a workgroup, and two rounds:
+    K and V of all slices against two slices at a time, which run one transform per workgroup."""
+    cfg = small_cfg(L=16384, group=2, dtype=dtype, n_bins=n_bins, n_layers=1, batch=batch, n_kv_heads=8)
+    bins = [np.sort(np.random.default_rng(n_bins).choice(8193, size=n_bins, replace=False)).astype(np.int32)]
+    K, V = wl.prefill_tensors(cfg, DEV)
+    a = make_cache(cfg, bins)
+    a.prefill(K, V)
+    ka, va = a.reconstruct(0, 0, 16384)
+    b = make_cache(small_cfg(L=16384, group=2, dtype=dtype, n_bins=n_bins, n_layers=1, batch=1, n_kv_heads=2), bins)
+    rows = 2 * 2 * 128 * (-(-n_bins // 32) * 32)  # floats of one slice pair's coefficients, K or V
+    for row, h in ((0, 0), (batch - 1, 6)):
+        b.prefill(*(x[:, row:row + 1, h:h + 2].contiguous() for x in (K, V)))
+        for which in (0, 1):  # the same coefficients, so that the prefill's own rules do not matter
+            src, dst = (c.state[c.state_bytes - 8 * 128 * (-(-n_bins // 32) * 32) * 2 * n:].view(torch.float32)
+                        for c, n in ((a, batch * 8), (b, 2)))
+            at = which * src.numel() // 2 + (row * 8 + h) * (rows // 2)
+            dst[which * rows:(which + 1) * rows] = src[at:at + rows]
+        kb, vb = b.reconstruct(0, 0, 16384)
+        assert torch.equal(ka[row:row + 1, h:h + 2], kb) and torch.equal(va[row:row + 1, h:h + 2], vb)
+    a.close()
+    b.close()
+
+
 def test_fft_and_dense_prefill_give_the_same_state():
     cfg = small_cfg(L=4096, dtype="bf16", n_bins=500, n_sink=2, n_recent=3)
     bins = random_bins(cfg, 41)
