@@ -216,11 +216,14 @@ static hipError_t launch_reconstruct_fft_t(const Params& P, int layer, uint32_t 
   // One / two transforms a workgroup.  Longer contexts than 16384 gather more bins per transform (16 slices, M = 32768, 4096 bins 295 / 310 us).  One round of
   // workgroups only (bf16: 16 slices) has nothing to hide the gather behind: M = 8192, 1500 bins 1.12 times as fast, 1900 1.01 (behind other data
   // in the caches 0.91), 2000 0.95, 2048 53 / 60; M = 16384, 1024 bins 1.01, 1.05, 1500 121 / 130, 2402 135 / 146, 4096 151 / 159, low and mixed
-  // masks alike (the first outputs of a context 138 / 135, 160 / 154, 187 / 175; three outputs in turn 1.0 to 1.2 times as fast).  Two rounds and more gain: M = 16384, 32 slices, 1024 bins 248 / 234, 2402
-  // 282 / 275, 4096 323 / 298; so does fp32, 8 slices, 1024 bins 77 / 72, 1800 88 / 86, 2402 to 4096 0.99 to 1.00, 16 slices, 2481 bins 209 / 195.
+  // masks alike (the first outputs of a context 138 / 135, 160 / 154, 187 / 175; three outputs in turn 1.0 to 1.2 times as fast).
+  // Two rounds and more have: M = 16384, 32 slices, 1024 bins 248 / 234, 2402 282 / 275, 4096 323 / 298; at 8192 long rows only, 32 slices, 400 bins 0.99
+  // times as fast, 800 103 / 107, 1200 0.98, 1600 0.99, 1800 1.01, 2048 123 / 121, 48 slices, 800 159 / 165, 64, 2048 232 / 225.  fp32, 16384 slots, 8
+  // slices, 1024 bins 77 / 72, 1800 88 / 86, 2402 to 4096 0.99 to 1.00, 16 slices, 2481 bins 209 / 195.
   const int64_t blocks = (int64_t)per_xcd * (kRecPairs / (BF16 ? 8 : 4));
-  const bool one_round = BF16 && blocks <= kTwoRound && P.max_nb > (P.M == 8192 ? 1792 : 1024);
-  const bool two = logQ == 13 && P.M <= 16384 && two_transforms(blocks) && !one_round;
+  const bool once = blocks <= kTwoRound;
+  const bool pays = !BF16 || (P.M == 8192 ? once == (P.max_nb <= 1792) : !once || P.max_nb <= 1024);
+  const bool two = logQ == 13 && P.M <= 16384 && two_transforms(blocks) && pays;
   hipError_t e = hipSuccess;
 #define IWDFT_RC_LAUNCH(LQ, MULTI, NP, TWO)                                                             \
   {                                                                                                     \
